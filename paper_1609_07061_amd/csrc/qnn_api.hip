@@ -100,9 +100,13 @@ int resolve_engine(const GemmArgs &g, int engine, int &chosen) {
     return QNN_OK;
 }
 
-int launch_on(const GemmArgs &g, int chosen, hipStream_t s) {
+// `chosen` is the route; if the library made the choice itself (`free_choice`), a product that the sliced kernel does faster
+// goes there.
+int launch_on(const GemmArgs &g, int chosen, bool free_choice, hipStream_t s) {
     int rc;
-    if (chosen == QNN_ENGINE_VALU)
+    if (free_choice && slice_preferred(g, chosen))
+        rc = launch_gemm_slice(g, s);
+    else if (chosen == QNN_ENGINE_VALU)
         rc = launch_gemm_valu(g, s);
     else if (chosen == QNN_ENGINE_MFMA_LDS)
         rc = launch_gemm_stage(g, s);
@@ -119,7 +123,7 @@ int dispatch(const GemmArgs &g, int engine, hipStream_t s) {
     int chosen;
     g_engine_count = 0;
     if (int rc = resolve_engine(g, engine, chosen)) return rc;
-    return launch_on(g, chosen, s);
+    return launch_on(g, chosen, engine == QNN_ENGINE_AUTO, s);
 }
 
 // Shared validation of the matrix-shaped products; fills `g`.  `empty` = a successful no-op (M == 0 or N == 0).
@@ -342,6 +346,7 @@ struct MlpPlan {
     int n;
     GemmArgs g[QNN_MAX_LAYERS];
     int engine[QNN_MAX_LAYERS];
+    bool free_choice;  // the caller asked for no engine
 };
 
 int64_t mlp_ldw(int64_t d) { return (words_for(d) + 3) & ~(int64_t)3; }
@@ -378,6 +383,7 @@ int plan_mlp(const uint8_t *x, int64_t batch, int64_t ldx, int in_bits, int n_la
     plan.ld0 = mlp_ldw(dims[0]);
     plan.plane_stride = batch * plan.ld0;
     plan.n = n_layers;
+    plan.free_choice = engine == QNN_ENGINE_AUTO;
     const size_t off = round256((size_t)in_bits * (size_t)plan.plane_stride * 4);
     size_t act_bytes = 0;
     for (int l = 1; l < n_layers; ++l) {
@@ -468,7 +474,7 @@ int run_mlp(const MlpPlan &plan, hipStream_t s) {
                                                         plan.ld_w_bytes, plan.rw_scaled, s))
             return rc;
     for (int l = 0; l < plan.n; ++l)
-        if (int rc = launch_on(plan.g[l], plan.engine[l], s)) return rc;
+        if (int rc = launch_on(plan.g[l], plan.engine[l], plan.free_choice, s)) return rc;
     return QNN_OK;
 }
 
@@ -656,6 +662,7 @@ struct NetStep {
 };
 struct NetPlan {
     int n;
+    bool free_choice;   // the caller asked for no engine
     FlagJobs flags;     // kFlags: every layer's flip flags, one launch
     ConvPrepJobs prep;  // kConvPrep: border-class thresholds of every convolution on the panel-fed kernel, one launch
     NetStep step[6 * kMaxNetLayers + 4];
@@ -734,7 +741,7 @@ int run_net(const NetPlan &plan, hipStream_t s) {
                 rc = launch_ones_plane(static_cast<uint32_t *>(st.dst), st.rows, st.a, st.b, s);
                 break;
             case NetStep::kGemm:
-                rc = launch_on(st.g, st.engine, s);
+                rc = launch_on(st.g, st.engine, plan.free_choice, s);
                 break;
             case NetStep::kFirstConv:
                 // src = image, mask = weights, dst = output bits; rows = B, a / b / c = H / W / C0, n = filters;
@@ -806,6 +813,7 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
     auto words = [&](size_t off) { return reinterpret_cast<uint32_t *>(ws + off); };
     static thread_local NetPlan plan;  // large: kept out of the stack
     plan.n = 0;
+    plan.free_choice = engine == QNN_ENGINE_AUTO;
     auto push = [&]() -> NetStep & {
         NetStep &st = plan.step[plan.n++];
         std::memset(&st, 0, sizeof(st));

@@ -167,6 +167,20 @@ static int compute_units() {
     return cus;
 }
 
+// Layout conditions of the panel-fed kernel: single planes, rows of whole 128-byte groups on 16-byte boundaries (row offsets are
+// 32-bit and formed for up to one tile beyond the last row before they are clamped).
+static bool panel_layout(const GemmArgs &g, const Variant *v, bool vec) {
+    const bool spans32 = 4.0L * (long double)(g.M + 256) * g.A.ld < 4294967296.0L && 4.0L * (long double)(g.N + 256) * g.ldw < 4294967296.0L;
+    return vec && spans32 && !g.A.rows_are_pixels && !g.A.rows_are_bytes && v->WPL == 4 && g.Kw % panel::kGroupWords == 0;
+}
+
+bool panel_takes(const GemmArgs &g) {
+    const Variant *v;
+    MfmaConst mc;
+    bool vec;
+    return prepare(g, true, v, mc, vec) && panel_layout(g, v, vec);
+}
+
 int launch_gemm_mfma(const GemmArgs &g, hipStream_t s, bool fp4) {
     const Variant *v;
     MfmaConst mc;
@@ -179,10 +193,7 @@ int launch_gemm_mfma(const GemmArgs &g, hipStream_t s, bool fp4) {
     const int64_t total = tiles_m * tiles_n;
     const unsigned grid = (unsigned)(total < cus ? total : cus);
     // single-plane products on the FP4 path whose rows are made of whole, aligned 16-byte groups: the panel-fed kernel
-    // (row offsets are 32-bit and formed for up to one tile beyond the last row before they are clamped)
-    const bool spans32 = 4.0L * (long double)(g.M + 256) * g.A.ld < 4294967296.0L && 4.0L * (long double)(g.N + 256) * g.ldw < 4294967296.0L;
-    if (fp4 && vec && spans32 && !g.A.rows_are_pixels && !g.A.rows_are_bytes && v->WPL == 4 &&
-        g.Kw % panel::kGroupWords == 0) {
+    if (fp4 && panel_layout(g, v, vec)) {
         const int64_t ngroups = ceil_div(g.Kw, panel::kGroupWords);
         int64_t aA, bA, xA0, aW, bW, xW0;
         MfmaConst pc = mc;

@@ -1,0 +1,121 @@
+// Operand description shared by the two FP4 kernels for products of any size and layout (qnn_gemm_slice.hip,
+// qnn_gemm_tile.hip): digits of an operand, and how a 256-element chunk of a digit becomes E2M1 operands.
+#pragma once
+#include <cstring>
+#include <utility>
+
+#include "qnn_internal.h"
+
+namespace qnn {
+namespace slice {
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));  // a 16-byte load at any word
+
+constexpr int kMaxDigits = QNN_MAX_PLANES;
+
+// How an operand's planes enter the multiplication.
+enum SliceKind {
+    kPm1 = 0,   // every digit is one +-1 plane, multiplied as +-1
+    kPair = 1,  // every digit is one or two 0/1 planes, multiplied as a number 0 .. 3
+    kOne = 2    // every digit is one plane, multiplied as 0 / 1 (a +-1 plane too: 2 b - 1 = 2 (b - 1/2))
+};
+// The digit's value is 2^lg (u - offset2 / 2), u = the number made of its planes' bits (as inverted).
+struct SliceDigit {
+    uint32_t off0, off1;  // byte offsets of the planes from the operand's base (off1 = off0 where there is no second one)
+    uint32_t inv0, inv1;  // all ones if the plane's bits are inverted
+    uint32_t use1;        // kPair: all ones if the second plane exists, else 0
+    int offset2;
+    int lg;
+    int scale;            // E8M0 bytes of the instruction's block scale for the four phases of a chunk
+};
+struct SliceOperand {
+    int count;
+    SliceDigit d[kMaxDigits];
+};
+struct SliceArgs {
+    SliceOperand a, w;
+    uint32_t chunks;       // 256-element chunks of a row (pixels: of KH KW taps padded to whole pieces each)
+    uint32_t row_words;    // words of a row (pixels: of a tap) = Kw (Cw)
+    uint32_t ppt, taps;    // pixels: 16-byte pieces per tap, taps
+    uint32_t magic_ppt, magic_kw;  // ceil(2^32 / .)
+    uint32_t alpha, c0;  // C = alpha (S - row corrections) + c0
+    int corrected;       // some digit has an offset: row sums are taken
+    int modified;        // some digit has an inverted or an absent plane
+    int clear_w;         // +-1 activation planes: where activation words are cleared the weight words have to be cleared too
+};
+
+// Fields for the operands of a digit, from its planes' words: a single plane as it lies; a pair of planes as two-bit fields
+// (b1 b0), those of the even bits in z0, of the odd bits in z1.
+//   A 0/1 plane with a negative coefficient enters inverted, -b = (1 - b) - 1, so every field is a number 0 .. 3 and its operand
+//   one mask away; with x = ua - oa, y = uw - ow the product sum is  sum ua uw - ow sum ua - oa sum uw + K oa ow,  row sums that
+//   cost a few population counts per 128 elements instead of four to five instructions per eight elements for signs.
+template <int kKind>
+__device__ __forceinline__ void make_fields(const u32x4 &w0, const u32x4 &w1, u32x4 &z0, u32x4 &z1) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if constexpr (kKind == kPair) {
+            const uint32_t f0 = (w0[i] & 0x55555555u) | ((w1[i] << 1) & 0xAAAAAAAAu);
+            const uint32_t f1 = ((w0[i] >> 1) & 0x55555555u) | (w1[i] & 0xAAAAAAAAu);
+            z0[i] = f0, z1[i] = f1;
+        } else {
+            z0[i] = w0[i];
+        }
+    }
+}
+// The planes' bits as the digit counts them: inverted where the coefficient is negative, the second plane absent or not.
+template <int kKind>
+__device__ __forceinline__ void apply_inversion(const uint32_t inv0, const uint32_t inv1, const uint32_t use1, u32x4 &w0, u32x4 &w1) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        w0[i] ^= inv0;
+        if constexpr (kKind == kPair) w1[i] = (w1[i] ^ inv1) & use1;
+    }
+}
+// sum + the sum of u over the 128 elements
+template <int kKind>
+__device__ __forceinline__ int add_sum(const u32x4 &w0, const u32x4 &w1, int sum) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if constexpr (kKind == kPair)
+            sum += __builtin_popcount(w0[i]) + 2 * __builtin_popcount(w1[i]);
+        else if constexpr (kKind == kOne)
+            sum += __builtin_popcount(w0[i]);
+        else
+            sum += 2 * __builtin_popcount(w0[i]) - 32;
+    }
+    return sum;
+}
+// E2M1 operand of phase ph: bit ph of every nibble of the words.
+template <int kKind>
+__device__ __forceinline__ v4i make_operand(const u32x4 &z0, const u32x4 &z1, const int ph) {
+    v4i f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if constexpr (kKind == kPair) {
+            const uint32_t z = (ph & 1) ? z1[i] : z0[i];
+            f[i] = (int)(((ph & 2) ? (z >> 2) : z) & 0x33333333u);
+        } else if constexpr (kKind == kOne) {
+            // bit 0, 1 or 2 of a nibble alone is 0.5, 1 or 2 (the block scale of the phase makes it 1); bit 3 is the sign bit
+            // and goes to bit 1 first
+            f[i] = (int)(ph == 3 ? (z0[i] >> 2) & 0x22222222u : z0[i] & (0x11111111u << ph));
+        } else {
+            const uint32_t s = z0[i] << (3 - ph);
+            f[i] = (int)((~s & 0x88888888u) | 0x22222222u);
+        }
+    }
+    return f;
+}
+__device__ __forceinline__ v8i widen(const v4i &x) { return __builtin_shufflevector(x, x, 0, 1, 2, 3, -1, -1, -1, -1); }
+
+// The kernels' arguments for a product and the kinds of its operands; false if they cannot take it.  bits: +-1 planes as kOne (with
+// corrections from row sums) instead of kPm1, and single 0/1 planes as kOne instead of kPair.
+bool slice_args(const GemmArgs &g, bool bits, SliceArgs &sc, int &kind_a, int &kind_w);
+
+}  // namespace slice
+}  // namespace qnn

@@ -1,0 +1,438 @@
+// Matrix-core kernel for products that do not fill the chip with large tiles, or whose rows are not made of whole aligned
+// groups: small batches, single time steps, odd layer widths, convolutions of a few images.
+//
+// Bound: latency.  Such a product is a few microseconds of matrix-core work at most; what it costs elsewhere is a serial
+// chain (one workgroup walking the whole of k behind a barrier per step) on a fraction of the compute units.  So here
+//   * a workgroup owns a small tile of C (32 x 32 or 64 x 64) and its waves share k between them: wave w takes the 256-element
+//     chunks w, w + waves, ... of every plane pair, and the partial sums meet once, in LDS, at the end (one barrier in the
+//     whole kernel);
+//   * a wave loads the packed words of its operand rows straight into registers, four words per lane, one chunk ahead of the
+//     multiplication.  16-byte loads at any 4-byte alignment; the last piece of a row is read four words from the row's end
+//     and the words that an earlier piece has brought already are cleared, so nothing beyond a row is read and K, leading
+//     dimensions and channel counts can be anything (of at least four words);
+//   * words become E2M1 operands of v_mfma_scale_f32_32x32x64_f8f6f4 in registers.  A +-1 plane: the nibble 0b0010 (1.0) with
+//     the sign bit set where the bit is clear.  Two 0/1 planes whose coefficients are c and 2c up to signs: ONE nibble,
+//     0.5 (b0 + 2 b1), i.e. one product where the planes one by one would take two.  The planes' powers of two are the block
+//     scales of the instruction.  Everything is a multiple of the coefficients' common factor and the sums stay
+//     below 2^24 of it (the host checks), so the float accumulation is exact.
+//   Phase t of a chunk multiplies bit t of every nibble of a lane's four words (both operands use the same order of k).
+#include "qnn_gemm_slice.h"
+
+namespace qnn {
+
+using namespace slice;
+
+namespace {
+
+// BMb x BNb blocks of 32 x 32 per wave; up to kMaxWaves waves share k.
+template <int kA, int kW, bool kPixels, int BMb, int BNb, int kMaxWaves>
+__global__ __launch_bounds__(64 * kMaxWaves, kMaxWaves == 4 ? 2 : 4) void gemm_slice_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
+    constexpr int BM = 32 * BMb, BN = 32 * BNb, kPitch = BN + 4;
+    constexpr int NA = kA == kPair ? 2 : 1, NW = kW == kPair ? 2 : 1;  // planes of a digit
+    __shared__ __attribute__((aligned(16))) float part[kMaxWaves][BM][kPitch];
+    __shared__ int part_a[kMaxWaves][BM], part_w[kMaxWaves][BN];
+    const uint32_t t = threadIdx.x, lane = t & 63u, r = lane & 31u, kg = lane >> 5;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6), waves = blockDim.x >> 6;
+    uint32_t tm, tn;
+    tile_of_block(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
+    const uint32_t m0 = tm * BM, n0 = tn * BN;
+
+    // rows of this lane (rows beyond the last repeat it and are not stored)
+    uint32_t a_off[BMb], w_off[BNb];  // byte offsets from the digit's plane
+    int a_y[BMb], a_x[BMb];           // pixels: input coordinates of the window's first tap
+#pragma unroll
+    for (int b = 0; b < BMb; ++b) {
+        uint32_t m = m0 + 32 * b + r;
+        m = m < (uint32_t)g.M ? m : (uint32_t)g.M - 1u;
+        if constexpr (kPixels) {
+            const uint32_t per = (uint32_t)(g.A.Ho * g.A.Wo);
+            const uint32_t img = m / per, rem = m - img * per;
+            const uint32_t yo = rem / (uint32_t)g.A.Wo, xo = rem - yo * (uint32_t)g.A.Wo;
+            a_y[b] = (int)yo * g.A.stride - g.A.pad, a_x[b] = (int)xo * g.A.stride - g.A.pad;
+            a_off[b] = img * (uint32_t)(g.A.H * g.A.Wd);  // pixels, not bytes
+        } else {
+            a_y[b] = a_x[b] = 0;
+            a_off[b] = m * (uint32_t)(g.A.ld * 4);
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < BNb; ++b) {
+        uint32_t n = n0 + 32 * b + r;
+        n = n < (uint32_t)g.N ? n : (uint32_t)g.N - 1u;
+        w_off[b] = n * (uint32_t)(g.ldw * 4);
+    }
+
+    struct Chunk {
+        u32x4 a[NA][BMb], w[NW][BNb];
+        uint32_t skip_a[BMb], skip;  // leading words to clear
+    };
+    const uint8_t *const a_base = reinterpret_cast<const uint8_t *>(g.A.base), *const w_base = reinterpret_cast<const uint8_t *>(g.W);
+    // 16 bytes of a row; pixels of fewer than four words (128 channels) word by word, the rest zero
+    auto load16 = [&](const uint8_t *p) __attribute__((always_inline)) -> u32x4 {
+        if (kPixels && sc.row_words < 4u) {
+            const uint32_t *w = reinterpret_cast<const uint32_t *>(p);
+            u32x4 v = {w[0], 0u, 0u, 0u};
+            if (sc.row_words > 1u) v.y = w[1];
+            if (sc.row_words > 2u) v.z = w[2];
+            return v;
+        }
+        return *reinterpret_cast<const u32x4_any *>(p);
+    };
+    auto load = [&](Chunk &x, const SliceDigit &da, const SliceDigit &dw, const uint32_t c) __attribute__((always_inline)) {
+        const uint32_t piece = 2u * c + kg;
+        uint32_t j, jw;  // first word within the row (pixels: the tap), and within the weight row
+        int ky = 0, kx = 0;
+        if constexpr (kPixels) {
+            uint32_t tap = __umulhi(piece, sc.magic_ppt);
+            if (sc.ppt == 1u) tap = piece;  // (ceil(2^32 / 1) does not fit)
+            uint32_t sub = piece - tap * sc.ppt;
+            j = sc.ppt == 1u || 4u * sub < sc.row_words - 4u ? 4u * sub : sc.row_words - 4u;
+            x.skip = 4u * sub - j;
+            if (tap >= sc.taps) tap = sc.taps - 1u, x.skip = 4u;
+            uint32_t q = __umulhi(tap, sc.magic_kw);
+            if (g.A.KW == 1) q = tap;
+            ky = (int)q, kx = (int)(tap - q * (uint32_t)g.A.KW);
+            jw = tap * sc.row_words + j;
+        } else {
+            j = 4u * piece < sc.row_words - 4u ? 4u * piece : sc.row_words - 4u;
+            x.skip = 4u * piece - j;
+            jw = j;
+        }
+#pragma unroll
+        for (int b = 0; b < BMb; ++b) {
+            uint32_t off;
+            if constexpr (kPixels) {
+                const int iy = a_y[b] + ky, ix = a_x[b] + kx;
+                const bool in = (uint32_t)iy < (uint32_t)g.A.H && (uint32_t)ix < (uint32_t)g.A.Wd;
+                // outside the image: any valid address, its words are cleared
+                const uint32_t px = a_off[b] + (in ? (uint32_t)(iy * g.A.Wd + ix) : 0u);
+                off = (px * sc.row_words + j) * 4u;
+                x.skip_a[b] = in ? x.skip : 4u;
+            } else {
+                off = a_off[b] + j * 4u;
+                x.skip_a[b] = x.skip;
+            }
+            x.a[0][b] = load16(a_base + da.off0 + off);
+            if constexpr (kA == kPair) x.a[1][b] = load16(a_base + da.off1 + off);
+        }
+#pragma unroll
+        for (int b = 0; b < BNb; ++b) {
+            const uint32_t off = w_off[b] + jw * 4u;
+            x.w[0][b] = load16(w_base + dw.off0 + off);
+            if constexpr (kW == kPair) x.w[1][b] = load16(w_base + dw.off1 + off);
+        }
+    };
+
+    v16f acc[BNb][BMb];
+#pragma unroll
+    for (int i = 0; i < BNb; ++i)
+#pragma unroll
+        for (int j = 0; j < BMb; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+
+    // row corrections of this lane's words (see make_fields)
+    int corr_a[BMb], corr_w[BNb];
+#pragma unroll
+    for (int b = 0; b < BMb; ++b) corr_a[b] = 0;
+#pragma unroll
+    for (int b = 0; b < BNb; ++b) corr_w[b] = 0;
+    const bool corrected = (kA == kPair || kW == kPair) && sc.corrected != 0;
+    // one chunk of one digit pair
+    auto multiply = [&](const Chunk &x, const SliceDigit &da, const SliceDigit &dw, const bool clear) __attribute__((always_inline)) {
+        u32x4 za[NA][BMb], zw[NW][BNb];
+        auto prepare = [&](auto kind_tag, const u32x4 p0, const u32x4 p1, const SliceDigit &d, const uint32_t skip, const bool clr, u32x4 &z0, u32x4 &z1) __attribute__((always_inline)) {
+            u32x4 w0 = p0, w1 = p1;
+            if (clr) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t keep = (uint32_t)i >= skip ? 0xFFFFFFFFu : 0u;
+                    w0[i] &= keep;
+                    if constexpr (decltype(kind_tag)::value == kPair) w1[i] &= keep;
+                }
+            }
+            if (sc.modified) apply_inversion<decltype(kind_tag)::value>(d.inv0, d.inv1, d.use1, w0, w1);
+            make_fields<decltype(kind_tag)::value>(w0, w1, z0, z1);
+            return corrected ? add_sum<decltype(kind_tag)::value>(w0, w1, 0) : 0;
+        };
+        const int shift = da.lg + dw.lg;
+#pragma unroll
+        for (int b = 0; b < BMb; ++b) {
+            const int sum = prepare(std::integral_constant<int, kA>{}, x.a[0][b], x.a[NA - 1][b], da, x.skip_a[b], clear || kPixels, za[0][b], za[NA - 1][b]);
+            if (corrected) corr_a[b] += ((sum * dw.offset2) << shift) >> 1;
+        }
+#pragma unroll
+        for (int b = 0; b < BNb; ++b) {
+            const int sum = prepare(std::integral_constant<int, kW>{}, x.w[0][b], x.w[NW - 1][b], dw, x.skip, clear || kPixels, zw[0][b], zw[NW - 1][b]);
+            if (corrected) corr_w[b] += ((sum * da.offset2) << shift) >> 1;
+        }
+#pragma unroll
+        for (int ph = 0; ph < 4; ++ph) {
+            v4i fa[BMb], fw[BNb];
+#pragma unroll
+            for (int b = 0; b < BMb; ++b) fa[b] = make_operand<kA>(za[0][b], za[NA - 1][b], ph);
+#pragma unroll
+            for (int b = 0; b < BNb; ++b) fw[b] = make_operand<kW>(zw[0][b], zw[NW - 1][b], ph);
+#pragma unroll
+            for (int i = 0; i < BNb; ++i)
+#pragma unroll
+                for (int j = 0; j < BMb; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen(fw[i]), widen(fa[j]), acc[i][j], 4, 4, 0, dw.scale, 0, da.scale);
+        }
+    };
+
+    // this wave's items: (digit pair, chunk) number wave, wave + waves, ... with the chunks innermost
+    const uint32_t pairs = (uint32_t)(sc.a.count * sc.w.count);
+    uint32_t pair = 0, c = wave;
+    auto settle = [&]() __attribute__((always_inline)) {
+        while (c >= sc.chunks && pair < pairs) c -= sc.chunks, ++pair;
+    };
+    settle();
+    Chunk cur, nxt;
+    uint32_t ia = 0, iw = 0;
+    if (pair < pairs) {
+        ia = pair / (uint32_t)sc.w.count, iw = pair - ia * (uint32_t)sc.w.count;
+        load(cur, sc.a.d[ia], sc.w.d[iw], c);
+    }
+    while (pair < pairs) {
+        const uint32_t c_now = c, ia_now = ia, iw_now = iw;
+        c += waves;
+        settle();
+        if (pair < pairs) {
+            ia = pair / (uint32_t)sc.w.count, iw = pair - ia * (uint32_t)sc.w.count;
+            load(nxt, sc.a.d[ia], sc.w.d[iw], c);
+        }
+        const bool clear = !kPixels && 8u * c_now + 8u > sc.row_words;
+        multiply(cur, sc.a.d[ia_now], sc.w.d[iw_now], clear);
+        cur = nxt;
+    }
+
+    // partial sums to LDS: register v of block [i][j] is C[m][n], m = 32 j + lane mod 32, n = 32 i + 8 (v / 4) + 4 kg + v mod 4
+#pragma unroll
+    for (int i = 0; i < BNb; ++i)
+#pragma unroll
+        for (int j = 0; j < BMb; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                *reinterpret_cast<f32x4 *>(&part[wave][32 * j + r][32 * i + 8 * q + 4 * kg]) = v;
+            }
+    if (corrected) {
+#pragma unroll
+        for (int b = 0; b < BMb; ++b) {
+            const int v = corr_a[b] + __shfl_xor(corr_a[b], 32, 64);
+            if (kg == 0) part_a[wave][32 * b + r] = v;
+        }
+#pragma unroll
+        for (int b = 0; b < BNb; ++b) {
+            const int v = corr_w[b] + __shfl_xor(corr_w[b], 32, 64);
+            if (kg == 0) part_w[wave][32 * b + r] = v;
+        }
+    }
+    __syncthreads();
+    const uint32_t rows = (uint32_t)g.M - m0 < (uint32_t)BM ? (uint32_t)g.M - m0 : (uint32_t)BM;
+    if (!g.epi.T) {
+        const bool vec = (g.epi.ldc % 4 == 0) && (reinterpret_cast<uintptr_t>(g.epi.C) % 16 == 0);
+        for (uint32_t i = t; i < rows * (BN / 4); i += blockDim.x) {
+            const uint32_t row = i / (BN / 4), col = 4u * (i % (BN / 4));
+            f32x4 s = *reinterpret_cast<const f32x4 *>(&part[0][row][col]);
+            for (uint32_t w = 1; w < waves; ++w) s += *reinterpret_cast<const f32x4 *>(&part[w][row][col]);
+            int corr[4] = {0, 0, 0, 0};
+            if (corrected)
+                for (uint32_t w = 0; w < waves; ++w)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) corr[e] += part_a[w][row] + part_w[w][col + e];
+            i32x4 val;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) val[e] = (int32_t)((uint32_t)((int32_t)s[e] - corr[e]) * sc.alpha + sc.c0);
+            const int64_t n = (int64_t)n0 + col;
+            int32_t *dst = g.epi.C + (int64_t)(m0 + row) * g.epi.ldc + n;
+            if (vec && n + 4 <= g.N)
+                *reinterpret_cast<i32x4 *>(dst) = val;
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < g.N) dst[e] = val[e];
+        }
+    } else {
+        // a lane keeps its column; a ballot packs 64 columns of a row (or 32 of each of two rows)
+        constexpr uint32_t kRowsPerWave = 64 / BN;
+        const uint32_t col = lane % BN;
+        const int64_t n = (int64_t)n0 + col;
+        const bool live = n < g.N;
+        const int32_t T = live ? g.epi.T[n] : 0;
+        const bool flip = live && g.epi.flip && g.epi.flip[n] != 0;
+        for (uint32_t row0 = wave * kRowsPerWave; row0 < rows; row0 += waves * kRowsPerWave) {
+            const uint32_t row = row0 + lane / BN;  // (below BM: BM is a multiple of kRowsPerWave)
+            float s = part[0][row][col];
+            for (uint32_t w = 1; w < waves; ++w) s += part[w][row][col];
+            int corr = 0;
+            if (corrected)
+                for (uint32_t w = 0; w < waves; ++w) corr += part_a[w][row] + part_w[w][col];
+            const int32_t val = (int32_t)((uint32_t)((int32_t)s - corr) * sc.alpha + sc.c0);
+            const unsigned long long bits = __ballot(live && ((val >= T) != flip));
+            const int64_t n_word = (int64_t)n0 + (BN == 64 ? (lane & 32u) : 0u);
+            if ((lane & 31u) == 0u && row < rows && n_word < g.N)
+                g.epi.out_bits[(int64_t)(m0 + row) * g.epi.ldo + n_word / 32] = (uint32_t)(bits >> lane);
+        }
+    }
+}
+
+// The digits of an operand; false if a coefficient is not the common factor times a power of two, or offsets leave 32 bits.
+bool make_digits(const Planes &pl, int64_t plane_stride, bool bits, SliceOperand &op, int &kind, int64_t &gcd_out, int64_t &sum_abs_over_gcd) {
+    std::memset(&op, 0, sizeof(op));
+    int64_t gcd = 0;
+    for (int p = 0; p < pl.count; ++p) {
+        int64_t x = gcd, y = pl.coef[p] < 0 ? -(int64_t)pl.coef[p] : pl.coef[p];
+        if (y == 0) return false;
+        while (y) {
+            const int64_t r = x % y;
+            x = y, y = r;
+        }
+        gcd = x;
+    }
+    if (pl.count == 1 && pl.coef[0] < 0) gcd = -gcd;  // one plane: the sign goes into the factor
+    int order[QNN_MAX_PLANES], lg[QNN_MAX_PLANES];
+    int64_t d[QNN_MAX_PLANES], sum = 0;
+    for (int p = 0; p < pl.count; ++p) {
+        d[p] = pl.coef[p] / gcd;
+        const int64_t ad = d[p] < 0 ? -d[p] : d[p];
+        if (ad > (1 << 20) || (ad & (ad - 1))) return false;
+        lg[p] = 0;
+        while (((int64_t)1 << lg[p]) < ad) ++lg[p];
+        sum += ad;
+        if (4.0L * (long double)p * (long double)plane_stride >= 4294967296.0L) return false;
+        int i = p;
+        for (; i > 0 && lg[order[i - 1]] > lg[p]; --i) order[i] = order[i - 1];
+        order[i] = p;
+    }
+    const bool sign = pl.mode == QNN_PLANE_SIGN;
+    kind = sign ? (bits ? kOne : kPm1) : (bits && pl.count == 1 ? kOne : kPair);
+    for (int i = 0; i < pl.count; ++i) {
+        SliceDigit &e = op.d[op.count++];
+        const int p = order[i];
+        e.off0 = e.off1 = (uint32_t)((int64_t)p * plane_stride * 4);
+        e.lg = lg[p] + (sign && bits ? 1 : 0);
+        e.inv0 = d[p] < 0 ? 0xFFFFFFFFu : 0u;
+        if (kind == kPair && i + 1 < pl.count && lg[order[i + 1]] == lg[p] + 1) {
+            const int p1 = order[++i];
+            e.off1 = (uint32_t)((int64_t)p1 * plane_stride * 4);
+            e.use1 = 0xFFFFFFFFu;
+            e.inv1 = d[p1] < 0 ? 0xFFFFFFFFu : 0u;
+            e.offset2 = d[p1] < 0 ? 4 : 0;
+        }
+        if (sign)
+            e.offset2 = bits ? 1 : 0;
+        else
+            e.offset2 += d[p] < 0 ? 2 : 0;
+        // a set first bit is worth 1 (kPm1), 0.5 (kPair), 0.5 / 1 / 2 / 1 in phases 0 .. 3 (kOne) as an operand
+        const int one = 127 + e.lg;
+        e.scale = kind == kPm1 ? one * 0x01010101 : (kind == kPair ? (one + 1) * 0x01010101 : one * 0x01010101 + 1 - 0x10000);
+    }
+    gcd_out = gcd, sum_abs_over_gcd = sum;
+    return true;
+}
+
+uint32_t magic(int64_t d) { return (uint32_t)((4294967296LL + d - 1) / d); }  // d >= 2
+
+}  // namespace
+
+namespace slice {
+bool slice_args(const GemmArgs &g, bool bits, SliceArgs &sc, int &kind_a, int &kind_w) {
+    std::memset(&sc, 0, sizeof(sc));
+    if (g.A.rows_are_bytes) return false;
+    const bool pix = g.A.rows_are_pixels != 0;
+    int64_t ga, gw, sa, sw;
+    if (!make_digits(g.pa, g.A.plane_stride, bits, sc.a, kind_a, ga, sa) || !make_digits(g.pw, g.strideW, bits, sc.w, kind_w, gw, sw)) return false;
+    const int64_t row_words = pix ? g.A.Cw : g.Kw;
+    if (row_words < (pix ? 1 : 4)) return false;
+    const int64_t ppt = ceil_div(row_words, 4), taps = pix ? (int64_t)g.A.KH * g.A.KW : 1, pieces = ppt * taps;
+    if (pieces >= 32768 || taps >= 32768) return false;  // (the quotients by multiplication are exact below 2^32 / divisor)
+    sc.row_words = (uint32_t)row_words, sc.ppt = (uint32_t)ppt, sc.taps = (uint32_t)taps;
+    sc.magic_ppt = ppt > 1 ? magic(ppt) : 0u, sc.magic_kw = pix && g.A.KW > 1 ? magic(g.A.KW) : 0u;
+    sc.chunks = (uint32_t)ceil_div(pieces, 2);
+    // exact float sums: |S| in units of the common factors stays below 2^24 (2^23, as the common factor itself: 24-bit products)
+    if ((long double)sa * (long double)sw * 256.0L * sc.chunks >= 8388608.0L) return false;
+    if (ga * gw >= 8388608 || ga * gw <= -8388608) return false;
+    // 32-bit byte offsets
+    const long double a_words = pix ? (long double)g.M / ((long double)g.A.Ho * g.A.Wo) * g.A.H * g.A.Wd * g.A.Cw : (long double)g.M * g.A.ld;
+    if (4.0L * a_words >= 4294967296.0L || 4.0L * (long double)g.N * g.ldw >= 4294967296.0L) return false;
+    if (g.M > 0x7FFFFF00LL || g.N > 0x7FFFFF00LL) return false;
+    sc.alpha = (uint32_t)(ga * gw);
+    // offsets of the digits (see make_fields): the constant part, over every processed element
+    int64_t constant = 0;
+    for (int i = 0; i < sc.a.count; ++i)
+        for (int j = 0; j < sc.w.count; ++j) {
+            const SliceDigit &da = sc.a.d[i], &dw = sc.w.d[j];
+            constant += ((int64_t)da.offset2 * dw.offset2 * 64 * sc.chunks) << (da.lg + dw.lg);
+            if (da.offset2 || dw.offset2) sc.corrected = 1;
+            if (da.inv0 || da.inv1 || dw.inv0 || dw.inv1 || (kind_a == kPair && !da.use1) || (kind_w == kPair && !dw.use1)) sc.modified = 1;
+        }
+    sc.c0 = (uint32_t)constant * sc.alpha;
+    sc.clear_w = g.pa.mode == QNN_PLANE_SIGN;
+    // +-1 planes on both sides: a processed element beyond K is (-sum coefA)(-sum coefW) instead of 0
+    if (g.pa.mode == QNN_PLANE_SIGN && g.pw.mode == QNN_PLANE_SIGN) {
+        int64_t ca = 0, cw = 0;
+        for (int p = 0; p < g.pa.count; ++p) ca += g.pa.coef[p];
+        for (int p = 0; p < g.pw.count; ++p) cw += g.pw.coef[p];
+        const int64_t surplus = 256 * (int64_t)sc.chunks - g.K;
+        sc.c0 += (uint32_t)(-surplus * ca * cw);
+    }
+    return true;
+}
+}  // namespace slice
+
+namespace {
+
+typedef void (*SliceFn)(const GemmArgs, const SliceArgs, uint32_t, uint32_t);
+template <int BMb, int BNb, int kMaxWaves>
+SliceFn slice_kernel(int ka, int kw, bool pix) {
+    if (pix) {
+        if (ka == kPm1) return kw == kPm1 ? gemm_slice_kernel<kPm1, kPm1, true, BMb, BNb, kMaxWaves> : gemm_slice_kernel<kPm1, kPair, true, BMb, BNb, kMaxWaves>;
+        return kw == kPm1 ? gemm_slice_kernel<kPair, kPm1, true, BMb, BNb, kMaxWaves> : gemm_slice_kernel<kPair, kPair, true, BMb, BNb, kMaxWaves>;
+    }
+    if (ka == kPm1) return kw == kPm1 ? gemm_slice_kernel<kPm1, kPm1, false, BMb, BNb, kMaxWaves> : gemm_slice_kernel<kPm1, kPair, false, BMb, BNb, kMaxWaves>;
+    return kw == kPm1 ? gemm_slice_kernel<kPair, kPm1, false, BMb, BNb, kMaxWaves> : gemm_slice_kernel<kPair, kPair, false, BMb, BNb, kMaxWaves>;
+}
+
+}  // namespace
+
+// Where the library's own choice goes to these kernels.  Measured (us, GPU time; route of the shape -> best of these):
+//   vector-ALU route: everything (32 x 4096 x 4096 20 -> 4.5; 20 x 4096 x 2048 with 4 x 4 planes 134 -> 8; convolution of four
+//     13 x 13 maps, 384 -> 256 channels, 39 -> 5; 1000 x 1000 x 1000 8.7 -> 5.3);
+//   single planes that miss the panel-fed kernel's layout: everything (1999 x 3001 x 2500 82 -> 21; 8000^3 640 -> 234);
+//   single planes that fit it: while its 256 x 128 tiles leave compute units idle (256 x 1024 x 8192 24 -> 6; 8192 x 256 x 8192
+//     25 -> 14; 2048^3 12.9 -> 11.5), not beyond (4096^3 33 against 38);
+//   several planes merged in LDS: everything (256 maps, 2-bit activations, 64 -> 35; 1000 x 4096 x 2048 with 4 x 4 planes
+//     45 -> 32), but not large products of four digit pairs (2240 x 4096 x 2048 with 4 x 4 planes 57 against 68).
+bool slice_preferred(const GemmArgs &g, int route) {
+    SliceArgs sc;
+    int ka, kw;
+    if (!slice_args(g, false, sc, ka, kw)) return false;
+    if (route == QNN_ENGINE_MFMA_FP4 && panel_takes(g)) return ceil_div(g.M, 256) * ceil_div(g.N, 128) < 256;
+    if (route == QNN_ENGINE_MFMA_LDS && sc.a.count * sc.w.count >= 4)
+        return (long double)g.M * (long double)g.N * (long double)g.K * (sc.a.count * sc.w.count) < 5e10L;
+    return true;
+}
+
+int launch_gemm_slice(const GemmArgs &g, hipStream_t s) {
+    SliceArgs sc;
+    int ka, kw;
+    if (!slice_args(g, false, sc, ka, kw)) return fail(QNN_ERR_UNSUPPORTED, "sliced matrix-core kernel cannot take these arguments");
+    const bool pix = g.A.rows_are_pixels != 0;
+    // Tile by the number of tiles: 128 x 128 where there are enough of them for the chip (2048^3, 256 tiles, 11.5 us against 13.9
+    // with 64 x 64; 1024 x 1024 x 4096, 64 tiles, 13.3 against 7.7; convolutions pay more per group of k: from 384 tiles on),
+    // 32 x 32 with k shared by up to sixteen waves where 64 x 64 tiles are few (256 x 1024 x 8192, 64 tiles, 5.9 against 9.6 us;
+    // 1000 x 1000 x 1000, 256 tiles, 5.8 against 5.2) or mostly padding.
+    if (ceil_div(g.M, 128) * ceil_div(g.N, 128) >= (pix ? 384 : 192) && g.M >= 96 && g.N >= 96) return launch_gemm_tile(g, s);
+    const bool large = ceil_div(g.M, 64) * ceil_div(g.N, 64) >= 160 && g.M > 32 && g.N > 32;
+    const int64_t items = (int64_t)sc.chunks * sc.a.count * sc.w.count;
+    const int64_t edge = large ? 64 : 32, tiles_m = ceil_div(g.M, edge), tiles_n = ceil_div(g.N, edge);
+    if (tiles_m * tiles_n > 0x7FFFFFFFLL) return fail(QNN_ERR_SHAPE, "gemm: too many tiles");
+    const int most = large ? 4 : 16;
+    const int waves = items < most ? (int)items : most;
+    const SliceFn fn = large ? slice_kernel<2, 2, 4>(ka, kw, pix) : slice_kernel<1, 1, 16>(ka, kw, pix);
+    return QNN_LAUNCH("gemm_slice", fn, dim3((unsigned)(tiles_m * tiles_n)), dim3(64u * waves), 0, s, g, sc, (uint32_t)tiles_m, (uint32_t)tiles_n);
+}
+
+}  // namespace qnn

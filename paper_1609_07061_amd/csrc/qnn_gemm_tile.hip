@@ -1,0 +1,383 @@
+// Matrix-core kernel for products of ordinary size whose rows can be anything: odd widths, rows that start at any word,
+// several bit planes, convolutions (the larger sibling of qnn_gemm_slice.hip; same digits, same operands).
+//
+// Bound: matrix cores and the vector instructions that make their operands, about one for one.  A workgroup of four waves owns a
+// 128 x 128 tile of C, a wave 64 x 64 of it (2 x 2 blocks: 28 vector instructions per operand block and 256 elements against
+// 512 matrix-core cycles for the four products), two or three workgroups share a compute unit and fill each other's waits.
+//   * Loads: a wave reads eight rows x 128 contiguous bytes per instruction (an instruction whose 64 lanes read 64 rows costs
+//     the address path of the compute unit 64 cycles, this one 16 to 19), 16 bytes per lane at any 4-byte alignment, a group of
+//     1024 elements ahead of the multiplication, into registers.  The last piece of a row is read four words from its end and
+//     the words an earlier piece has brought are cleared, so nothing beyond a row is read.
+//   * The words go to LDS once per workgroup, already cleared and, for two planes of a digit, already interleaved; piece c of row
+//     r sits at piece c xor (r mod 8), so that writes (eight rows x eight pieces) and reads (32 rows, one piece) use all banks.
+//   * Epilogue through LDS: a 32 x 64 block per wave at a time, so that C leaves as 256-byte pieces of rows.
+#include "qnn_gemm_slice.h"
+
+namespace qnn {
+
+using namespace slice;
+
+namespace {
+
+constexpr int kTileThreads = 256;
+constexpr int kTile = 128;
+constexpr int kPlaneBytes = kTile * 128;  // a group of one plane of an operand
+constexpr int kStagePitch = 68;           // floats per row of the epilogue's block: 64 and a gap
+
+template <int kA, int kW, bool kPixels>
+__global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
+    constexpr int NA = kA == kPair ? 2 : 1, NW = kW == kPair ? 2 : 1;  // planes of a digit
+    constexpr int kOperandBytes = (NA + NW) * kPlaneBytes, kEpiBytes = 4 * 32 * kStagePitch * 4;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kOperandBytes > kEpiBytes ? kOperandBytes : kEpiBytes];
+    __shared__ __attribute__((aligned(16))) int corr_a[kTile], corr_w[kTile];  // row corrections (see make_fields)
+    const uint32_t t = threadIdx.x, lane = t & 63u, r = lane & 31u, kg = lane >> 5;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave >> 1, wn = wave & 1u;
+    uint32_t tm, tn;
+    tile_of_block(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
+    const uint32_t m0 = tm * kTile, n0 = tn * kTile;
+
+    // ------------------------------------------------------------------------------------------------ loads
+    // load i of a plane: rows 32 i + 8 wave + lane / 8, piece lane mod 8 of the group
+    const uint32_t prow = 8u * wave + (lane >> 3), piece0 = lane & 7u;
+    uint32_t a_off[4], w_off[4];  // byte offset of the row (pixels: first pixel of the image)
+    int a_y[4], a_x[4];           // pixels: input coordinates of the window's first tap
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t m = m0 + 32 * i + prow;
+        m = m < (uint32_t)g.M ? m : (uint32_t)g.M - 1u;  // (rows beyond the last repeat it and are not stored)
+        if constexpr (kPixels) {
+            const uint32_t per = (uint32_t)(g.A.Ho * g.A.Wo);
+            const uint32_t img = m / per, rem = m - img * per;
+            const uint32_t yo = rem / (uint32_t)g.A.Wo, xo = rem - yo * (uint32_t)g.A.Wo;
+            a_y[i] = (int)yo * g.A.stride - g.A.pad, a_x[i] = (int)xo * g.A.stride - g.A.pad;
+            a_off[i] = img * (uint32_t)(g.A.H * g.A.Wd);
+        } else {
+            a_y[i] = a_x[i] = 0;
+            a_off[i] = m * (uint32_t)(g.A.ld * 4);
+        }
+        uint32_t n = n0 + 32 * i + prow;
+        n = n < (uint32_t)g.N ? n : (uint32_t)g.N - 1u;
+        w_off[i] = n * (uint32_t)(g.ldw * 4);
+    }
+    struct Group {
+        u32x4 a[NA][4], w[NW][4];
+        uint32_t skip, inside;  // leading words to clear; pixels: bit i = the tap of row i lies inside the image
+    };
+    const uint8_t *const a_base = reinterpret_cast<const uint8_t *>(g.A.base), *const w_base = reinterpret_cast<const uint8_t *>(g.W);
+    // 16 bytes of a row; pixels of fewer than four words (128 channels) word by word, the rest zero
+    auto load16 = [&](const uint8_t *p) __attribute__((always_inline)) -> u32x4 {
+        if (kPixels && sc.row_words < 4u) {
+            const uint32_t *w = reinterpret_cast<const uint32_t *>(p);
+            u32x4 v = {w[0], 0u, 0u, 0u};
+            if (sc.row_words > 1u) v.y = w[1];
+            if (sc.row_words > 2u) v.z = w[2];
+            return v;
+        }
+        return *reinterpret_cast<const u32x4_any *>(p);
+    };
+    auto load = [&](Group &x, const SliceDigit &da, const SliceDigit &dw, const uint32_t G) __attribute__((always_inline)) {
+        const uint32_t piece = 8u * G + piece0;
+        uint32_t j, jw;  // first word within the row (pixels: the tap), and within the weight row
+        int ky = 0, kx = 0;
+        if constexpr (kPixels) {
+            uint32_t tap = __umulhi(piece, sc.magic_ppt);
+            if (sc.ppt == 1u) tap = piece;  // (ceil(2^32 / 1) does not fit)
+            const uint32_t sub = piece - tap * sc.ppt;
+            j = sc.ppt == 1u || 4u * sub < sc.row_words - 4u ? 4u * sub : sc.row_words - 4u;
+            x.skip = 4u * sub - j;
+            if (tap >= sc.taps) tap = sc.taps - 1u, x.skip = 4u;
+            uint32_t q = __umulhi(tap, sc.magic_kw);
+            if (g.A.KW == 1) q = tap;
+            ky = (int)q, kx = (int)(tap - q * (uint32_t)g.A.KW);
+            jw = tap * sc.row_words + j;
+        } else {
+            j = 4u * piece < sc.row_words - 4u ? 4u * piece : sc.row_words - 4u;
+            x.skip = 4u * piece - j;
+            jw = j;
+        }
+        x.inside = 0xFu;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            uint32_t off;
+            if constexpr (kPixels) {
+                const int iy = a_y[i] + ky, ix = a_x[i] + kx;
+                const bool in = (uint32_t)iy < (uint32_t)g.A.H && (uint32_t)ix < (uint32_t)g.A.Wd;
+                // outside the image: any valid address, its words are cleared
+                off = ((a_off[i] + (in ? (uint32_t)(iy * g.A.Wd + ix) : 0u)) * sc.row_words + j) * 4u;
+                if (!in) x.inside &= ~(1u << i);
+            } else {
+                off = a_off[i] + j * 4u;
+            }
+            x.a[0][i] = load16(a_base + da.off0 + off);
+            if constexpr (kA == kPair) x.a[1][i] = load16(a_base + da.off1 + off);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t off = w_off[i] + jw * 4u;
+            x.w[0][i] = load16(w_base + dw.off0 + off);
+            if constexpr (kW == kPair) x.w[1][i] = load16(w_base + dw.off1 + off);
+        }
+    };
+    int sum_a[4] = {0, 0, 0, 0}, sum_w[4] = {0, 0, 0, 0};  // row sums of this lane's pieces, current digit pair
+    // registers -> LDS: fields of digit planes, plane after plane.  tail: pieces end or start within the group
+    auto store = [&](Group &x, const SliceDigit &da, const SliceDigit &dw, const uint32_t G, const bool tail) __attribute__((always_inline)) {
+        const uint32_t at = prow * 128u + ((piece0 ^ (prow & 7u)) << 4);
+        if (kPixels || tail) {
+            uint32_t keep[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) keep[e] = (uint32_t)e >= x.skip ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t in = (x.inside >> i) & 1u ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t k = kPixels ? (keep[e] & in) : keep[e];
+                    x.a[0][i][e] &= k;
+                    if constexpr (kA == kPair) x.a[1][i][e] &= k;
+                }
+            }
+            if (sc.clear_w) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        x.w[0][i][e] &= keep[e];
+                        if constexpr (kW == kPair) x.w[1][i][e] &= keep[e];
+                    }
+            }
+        }
+        if (sc.modified) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                apply_inversion<kA>(da.inv0, da.inv1, da.use1, x.a[0][i], x.a[NA - 1][i]);
+                apply_inversion<kW>(dw.inv0, dw.inv1, dw.use1, x.w[0][i], x.w[NW - 1][i]);
+            }
+        }
+        if (sc.corrected && 8u * G + piece0 < 2u * sc.chunks) {  // (pieces beyond the last chunk are not multiplied)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                sum_a[i] = add_sum<kA>(x.a[0][i], x.a[NA - 1][i], sum_a[i]);
+                sum_w[i] = add_sum<kW>(x.w[0][i], x.w[NW - 1][i], sum_w[i]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            u32x4 z0, z1;
+            make_fields<kA>(x.a[0][i], x.a[NA - 1][i], z0, z1);
+            *reinterpret_cast<u32x4 *>(lds + at + i * 4096) = z0;
+            if constexpr (kA == kPair) *reinterpret_cast<u32x4 *>(lds + kPlaneBytes + at + i * 4096) = z1;
+            make_fields<kW>(x.w[0][i], x.w[NW - 1][i], z0, z1);
+            *reinterpret_cast<u32x4 *>(lds + NA * kPlaneBytes + at + i * 4096) = z0;
+            if constexpr (kW == kPair) *reinterpret_cast<u32x4 *>(lds + (NA + 1) * kPlaneBytes + at + i * 4096) = z1;
+        }
+    };
+
+    // ------------------------------------------------------------------------------------------------ products
+    v16f acc[2][2];  // [n block][m block]
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+    // lane (r, kg) of a block reads piece 2 q + kg of row r for chunk q of the group
+    const uint8_t *const pa = lds + (wm * 64u + r) * 128u, *const pw = lds + NA * kPlaneBytes + (wn * 64u + r) * 128u;
+    struct Words {
+        u32x4 a[NA][2], w[NW][2];
+    };
+    struct Operands {
+        v4i a[2], w[2];
+    };
+    auto fetch = [&](const uint32_t q, Words &z) __attribute__((always_inline)) {
+        const uint32_t piece = ((2u * q + kg) ^ (r & 7u)) << 4;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+#pragma unroll
+            for (int p = 0; p < NA; ++p) z.a[p][b] = *reinterpret_cast<const u32x4 *>(pa + p * kPlaneBytes + b * 4096 + piece);
+#pragma unroll
+            for (int p = 0; p < NW; ++p) z.w[p][b] = *reinterpret_cast<const u32x4 *>(pw + p * kPlaneBytes + b * 4096 + piece);
+        }
+    };
+    auto make = [&](const Words &z, const int ph, Operands &f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) f.a[b] = make_operand<kA>(z.a[0][b], z.a[NA - 1][b], ph), f.w[b] = make_operand<kW>(z.w[0][b], z.w[NW - 1][b], ph);
+    };
+    // Phase ph multiplies the operands made during the phase before and meanwhile makes the next one's (from z, or from the
+    // next chunk's words), the vector instructions spread between the matrix-core ones.
+    auto phase = [&](auto ph_tag, const int a_scale, const int w_scale, const Words &z, Operands &f) __attribute__((always_inline)) {
+        constexpr int ph = decltype(ph_tag)::value;
+        Operands next;
+        make(z, (ph + 1) & 3, next);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen(f.w[i]), widen(f.a[j]), acc[i][j], 4, 4, ph, w_scale, ph, a_scale);
+        f = next;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, kA == kPair || kW == kPair ? 7 : 5, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](const int a_scale, const int w_scale, const uint32_t chunks) __attribute__((always_inline)) {
+        Words z0, z1;
+        Operands f;
+        fetch(0, z0);
+        make(z0, 0, f);
+        auto chunk = [&](const Words &z, Words &zn, const uint32_t next) __attribute__((always_inline)) {
+            fetch(next, zn);
+            phase(std::integral_constant<int, 0>{}, a_scale, w_scale, z, f);
+            phase(std::integral_constant<int, 1>{}, a_scale, w_scale, z, f);
+            phase(std::integral_constant<int, 2>{}, a_scale, w_scale, z, f);
+            phase(std::integral_constant<int, 3>{}, a_scale, w_scale, zn, f);
+        };
+#pragma unroll 1
+        for (uint32_t q = 0; q < chunks; ++q) {
+            chunk(z0, z1, q + 1u < chunks ? q + 1u : q);
+            z0 = z1;
+        }
+    };
+
+    const uint32_t groups = (sc.chunks + 3u) / 4u, pairs = (uint32_t)(sc.a.count * sc.w.count);
+    Group x;
+    load(x, sc.a.d[0], sc.w.d[0], 0u);
+    uint32_t ia = 0, iw = 0, G = 0;
+    int corr_a4[4] = {0, 0, 0, 0}, corr_w4[4] = {0, 0, 0, 0};
+    int a_scale = sc.a.d[0].scale, w_scale = sc.w.d[0].scale;
+    for (uint32_t item = 0, items = pairs * groups; item < items; ++item) {
+        if (item > 0) __syncthreads();  // the group before has been read
+        store(x, sc.a.d[ia], sc.w.d[iw], G, 32u * G + 32u > sc.row_words);
+        __syncthreads();
+        const uint32_t left = sc.chunks - 4u * G;
+        const bool pair_ends = G + 1u == groups;
+        if (pair_ends && sc.corrected) {  // weigh the row sums of this pair
+            const int shift = sc.a.d[ia].lg + sc.w.d[iw].lg;
+            const int a_fac = (sc.w.d[iw].offset2 << shift) >> 1, w_fac = (sc.a.d[ia].offset2 << shift) >> 1;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                corr_a4[i] += sum_a[i] * a_fac, corr_w4[i] += sum_w[i] * w_fac;
+                sum_a[i] = 0, sum_w[i] = 0;
+            }
+        }
+        if (++G == groups) {
+            G = 0;
+            if (++iw == (uint32_t)sc.w.count) iw = 0, ++ia;
+        }
+        const bool more = item + 1 < items;
+        if (more) load(x, sc.a.d[ia], sc.w.d[iw], G);
+        multiply(a_scale, w_scale, left < 4u ? left : 4u);
+        if (more && pair_ends) a_scale = sc.a.d[ia].scale, w_scale = sc.w.d[iw].scale;
+    }
+
+    // ------------------------------------------------------------------------------------------------ epilogue
+    // register v of block [i][j] is C[m][n], m = 32 j + lane mod 32, n = 32 i + 8 (v / 4) + 4 kg + v mod 4 of the wave's tile
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (sc.corrected) {
+#pragma unroll
+            for (int d = 1; d < 8; d <<= 1) corr_a4[i] += __shfl_xor(corr_a4[i], d, 64), corr_w4[i] += __shfl_xor(corr_w4[i], d, 64);
+        }
+        // (as the epilogue subtracts them: times alpha, the constant with the weight rows' part)
+        if (piece0 == 0)
+            corr_a[32 * i + prow] = (int)((uint32_t)corr_a4[i] * sc.alpha), corr_w[32 * i + prow] = (int)((uint32_t)corr_w4[i] * sc.alpha - sc.c0);
+    }
+    __syncthreads();
+    float *const stage = reinterpret_cast<float *>(lds) + wave * (32 * kStagePitch);
+    const int alpha = (int)sc.alpha;  // (sums and alpha are below 2^23 in magnitude: a 24-bit product, full rate)
+    auto times_alpha = [alpha](const float s) __attribute__((always_inline)) { return __mul24((int)s, alpha); };
+    const int64_t n_wave = (int64_t)n0 + 64 * wn;
+    const bool vec = (g.epi.ldc % 4 == 0) && (reinterpret_cast<uintptr_t>(g.epi.C) % 16 == 0);
+    int32_t T = 0;
+    bool live = false, flip = false;
+    if (g.epi.T) {
+        live = n_wave + lane < g.N;
+        T = live ? g.epi.T[n_wave + lane] : 0;
+        flip = live && g.epi.flip && g.epi.flip[n_wave + lane] != 0;
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int64_t m_blk = (int64_t)m0 + 64 * wm + 32 * j;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                *reinterpret_cast<f32x4 *>(&stage[r * kStagePitch + 32 * i + 8 * q + 4 * kg]) = v;
+            }
+        // (a wave's LDS operations execute in order: only the compiler has to be kept from reordering them)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (!g.epi.T) {
+            if (vec && n_wave + 64 <= g.N) {
+                const i32x4 cw4 = *reinterpret_cast<const i32x4 *>(&corr_w[64 * wn + 4 * (lane & 15u)]);
+#pragma unroll
+                for (int s = 0; s < 8; ++s) {  // four rows x 256 bytes
+                    const uint32_t row = 4u * s + (lane >> 4), col = 4u * (lane & 15u);
+                    const f32x4 v = *reinterpret_cast<const f32x4 *>(&stage[row * kStagePitch + col]);
+                    const int ca = corr_a[64 * wm + 32 * j + row];
+                    i32x4 val;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t corr = (uint32_t)ca + (uint32_t)cw4[e];
+                        val[e] = (int32_t)((uint32_t)times_alpha(v[e]) - (uint32_t)corr);
+                    }
+                    const int64_t m = m_blk + row;
+                    if (m < g.M) *reinterpret_cast<i32x4 *>(g.epi.C + m * g.epi.ldc + n_wave + col) = val;
+                }
+            } else {
+                // rows that start anywhere, or the last columns: one row per store, lanes on consecutive columns
+                const int cw = corr_w[64 * wn + lane];
+                const bool in = n_wave + lane < g.N;
+                int32_t *dst = g.epi.C + m_blk * g.epi.ldc + n_wave + lane;
+#pragma unroll 8
+                for (uint32_t s = 0; s < 32; ++s) {
+                    const uint32_t corr = (uint32_t)corr_a[64 * wm + 32 * j + s] + (uint32_t)cw;
+                    const int32_t val = (int32_t)((uint32_t)times_alpha(stage[s * kStagePitch + lane]) - (uint32_t)corr);
+                    if (in && m_blk + s < g.M) *dst = val;
+                    dst += g.epi.ldc;
+                }
+            }
+        } else {
+            // a lane keeps its column; the ballot of row s is two words, kept by lanes 2 s and 2 s + 1
+            const int cw = corr_w[64 * wn + lane];
+            uint32_t mine = 0;
+#pragma unroll 8
+            for (uint32_t s = 0; s < 32; ++s) {
+                const uint32_t corr = (uint32_t)corr_a[64 * wm + 32 * j + s] + (uint32_t)cw;
+                const int32_t val = (int32_t)((uint32_t)times_alpha(stage[s * kStagePitch + lane]) - corr);
+                const unsigned long long bits = __ballot(live && ((val >= T) != flip));
+                mine = lane == 2u * s ? (uint32_t)bits : mine;
+                mine = lane == 2u * s + 1u ? (uint32_t)(bits >> 32) : mine;
+            }
+            const int64_t m = m_blk + (lane >> 1), n = n_wave + 32 * (lane & 1u);
+            if (m < g.M && n < g.N) g.epi.out_bits[m * g.epi.ldo + n / 32] = mine;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+}
+
+typedef void (*TileFn)(const GemmArgs, const SliceArgs, uint32_t, uint32_t);
+template <bool kPixels>
+TileFn tile_kernel(int ka, int kw) {
+    if (ka == kOne) return kw == kOne ? gemm_tile_kernel<kOne, kOne, kPixels> : gemm_tile_kernel<kOne, kPair, kPixels>;
+    return kw == kOne ? gemm_tile_kernel<kPair, kOne, kPixels> : gemm_tile_kernel<kPair, kPair, kPixels>;
+}
+
+}  // namespace
+
+int launch_gemm_tile(const GemmArgs &g, hipStream_t s) {
+    SliceArgs sc;
+    int ka, kw;
+    if (!slice_args(g, true, sc, ka, kw)) return fail(QNN_ERR_UNSUPPORTED, "tiled FP4 kernel cannot take these arguments");
+    const int64_t tiles_m = ceil_div(g.M, kTile), tiles_n = ceil_div(g.N, kTile);
+    if (tiles_m * tiles_n > 0x7FFFFFFFLL) return fail(QNN_ERR_SHAPE, "gemm: too many tiles");
+    const TileFn fn = g.A.rows_are_pixels ? tile_kernel<true>(ka, kw) : tile_kernel<false>(ka, kw);
+    return QNN_LAUNCH("gemm_tile", fn, dim3((unsigned)(tiles_m * tiles_n)), dim3(kTileThreads), 0, s, g, sc, (uint32_t)tiles_m, (uint32_t)tiles_n);
+}
+
+}  // namespace qnn

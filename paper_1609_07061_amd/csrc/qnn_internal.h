@@ -117,6 +117,13 @@ int launch_gemm_mfma(const GemmArgs &g, hipStream_t s, bool fp4 = false);
 // The same engine's kernel for operands of several bit planes, which expands them once per workgroup into LDS.
 bool stage_supports(const GemmArgs &g);
 int launch_gemm_stage(const GemmArgs &g, hipStream_t s);
+// FP4 matrix-core kernels for products of any size and layout (qnn_gemm_slice.hip: small tiles whose waves share k;
+// qnn_gemm_tile.hip: larger tiles).  slice_preferred: whether they take the product and beat the engine (`route`) that the shape
+// would go to otherwise; launch_gemm_slice chooses between the two.
+bool slice_preferred(const GemmArgs &g, int route);
+int launch_gemm_slice(const GemmArgs &g, hipStream_t s);
+int launch_gemm_tile(const GemmArgs &g, hipStream_t s);
+bool panel_takes(const GemmArgs &g);  // whether the FP4 route would use the panel-fed kernel
 
 // Expansion of packed +-1 weights (N rows of K elements) to one int8 per element (row pitch ld_out, a multiple of 128,
 // zeros beyond K) and rw_scaled[n] = 128 * (sum of the weights of row n): operands of the uint8-input kernel.

@@ -1,0 +1,92 @@
+"""The FP4 kernels for products of any size and layout (32 x 32 and 64 x 64 tiles with k shared between waves, 128 x 128 tiles),
+at the sizes where they can go wrong: one word more or less than a 16-byte piece, a 256-element chunk, a 1024-element group;
+one row or column more or less than a tile; rows that start at any word; every pairing of planes into digits.  All results are
+whole numbers: equality with the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import qnn_inputs as qi
+from qnn_testlib import dev, host, host_u32, np_pack_bits, np_pack_pm1
+
+pytestmark = pytest.mark.gpu
+
+# 32 x 32, 64 x 64 and 128 x 128 tiles (by the number of tiles), ragged on both edges
+SHAPES = [(1, 1), (31, 33), (65, 32), (640, 1025), (1601, 2049)]
+KS = [97, 128, 129, 255, 257, 1024, 1056, 2049]
+
+
+@pytest.mark.parametrize("M,N", SHAPES)
+@pytest.mark.parametrize("K", KS)
+def test_any_row_length_and_pitch(seed, M, N, K):
+    import paper_1609_07061_amd as q
+
+    a, w = qi.pm1(seed, 1200, (M, K)), qi.pm1(seed, 1201, (N, K))
+    Kw = (K + 31) // 32
+    A, W = dev(np_pack_pm1(a, Kw + 1))[:, :Kw], dev(np_pack_pm1(w, Kw + 3))[:, :Kw]
+    want = oracle.gemm_pm1(a, w)
+    for pad in (0, 3):
+        out = torch.full((M, N + pad), -7, dtype=torch.int32, device="cuda")
+        q.qnn_binary_gemm(A, W, K, out=out[:, :N])
+        got = host(out)
+        assert np.array_equal(got[:, :N], want) and (got[:, N:] == -7).all(), (M, N, K, pad)
+    T, flip = qi.uniform_int(seed, 1202, (N,), -9, 9), qi.bernoulli_bits(seed, 1203, (N,))
+    Nw = (N + 31) // 32
+    bits = torch.full((M, Nw + 1), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    q.qnn_binary_gemm_sign(A, W, K, dev(T), dev(flip), out=bits[:, :Nw])
+    got = host_u32(bits)
+    assert np.array_equal(got[:, :Nw], oracle.pack_bits(oracle.threshold(want, T, flip))), (M, N, K)
+    assert (got[:, Nw:] == 0x5A5A5A5A).all(), (M, N, K)
+
+
+# pairs of consecutive powers of two with every combination of signs, gaps between powers, common factors, both modes
+PLANES = [([1, 2], 0, [1], 1), ([1, -2], 0, [-1, 2], 0), ([-1, -2, 4], 0, [3], 0), ([1, 2, 4, -8], 0, [1, 2, 4, -8], 0),
+          ([4, 1], 0, [2, -16], 0), ([-3, 6, 12], 1, [5, 10], 0), ([1, -4], 1, [-2, 1], 1), ([-5], 0, [1], 1), ([1], 1, [-2, 4], 0),
+          ([1 << p for p in range(8)], 0, [1], 1)]
+
+
+@pytest.mark.parametrize("M,N,K", [(33, 65, 300), (700, 1100, 1100), (1700, 2000, 131)])
+@pytest.mark.parametrize("ca,ma,cw,mw", PLANES)
+def test_digits_of_every_plane_pairing(seed, M, N, K, ca, ma, cw, mw):
+    import paper_1609_07061_amd as q
+
+    pa, pw = qi.bernoulli_bits(seed, 1210, (len(ca), M, K)), qi.bernoulli_bits(seed, 1211, (len(cw), N, K))
+    want = oracle.gemm_planes(pa, ca, ma, pw, cw, mw)
+    got = q.qnn_bitplane_gemm(dev(np_pack_bits(pa)), ca, ma, dev(np_pack_bits(pw)), cw, mw, K)
+    assert np.array_equal(host(got), want), (M, N, K)
+
+
+# (images, height = width, channels, filters, kernel, pad, stride): channels of one, two, three words and of one word more or less
+# than a piece; maps whose windows reach outside on every side; enough tiles for the 128 x 128 kernel in the last two
+CONVS = [(1, 6, 20, 33, 3, 1, 1), (2, 7, 64, 40, 3, 1, 2), (3, 9, 96, 64, 5, 2, 1), (2, 8, 128, 65, 3, 1, 1), (2, 9, 150, 70, 3, 0, 1),
+         (3, 11, 230, 130, 1, 0, 1), (100, 23, 96, 100, 3, 1, 1), (64, 28, 160, 129, 3, 2, 1)]
+
+
+@pytest.mark.parametrize("B,S,cin,cout,k,pad,stride", CONVS)
+@pytest.mark.parametrize("coef", [[1], [1, 2], [1, 2, -4]])
+def test_convolutions_of_any_channel_count(seed, B, S, cin, cout, k, pad, stride, coef):
+    import paper_1609_07061_amd as q
+
+    planes = qi.bernoulli_bits(seed, 1220, (len(coef), B, S, S, cin))
+    u = sum(int(c) * planes[p].astype(np.int32) for p, c in enumerate(coef))
+    w = qi.pm1(seed, 1221, (cout, k, k, cin))
+    want = oracle.conv2d(u, w.astype(np.int32), pad, stride)
+    A, W = dev(np_pack_bits(planes)), dev(np_pack_pm1(w)[None])
+    got = q.qnn_bitplane_conv2d(A, coef, q.PLANE_BIT, cin, W, [1], q.PLANE_SIGN, pad, stride)
+    assert np.array_equal(host(got), want)
+    T, flip = qi.uniform_int(seed, 1222, (cout,), -9, 9), qi.bernoulli_bits(seed, 1223, (cout,))
+    got = q.qnn_bitplane_conv2d_sign(A, coef, q.PLANE_BIT, cin, W, [1], q.PLANE_SIGN, pad, stride, dev(T), dev(flip))
+    want_bits = oracle.pack_bits(oracle.threshold(want.reshape(-1, cout), T, flip))
+    assert np.array_equal(host_u32(got).reshape(want_bits.shape), want_bits)
+
+
+@pytest.mark.parametrize("cin", [20, 64, 130])
+def test_convolution_of_sign_maps_without_padding(seed, cin):
+    """+-1 activations: where a piece holds fewer words than four, or a chunk fewer taps than it has room for, the surplus counts
+    (-1)(-1) and is taken off."""
+    import paper_1609_07061_amd as q
+
+    a, w = qi.pm1(seed, 1230, (2, 9, 9, cin)), qi.pm1(seed, 1231, (37, 3, 3, cin))
+    got = q.qnn_bitplane_conv2d(dev(np_pack_pm1(a)[None]), [1], q.PLANE_SIGN, cin, dev(np_pack_pm1(w)[None]), [1], q.PLANE_SIGN, 0, 1)
+    assert np.array_equal(host(got), oracle.conv2d(a.astype(np.int32), w.astype(np.int32), 0, 1))
