@@ -207,7 +207,7 @@ bool merge_plan(const Planes &pl, MergeOperand &op, int64_t &scale) {
 
 }  // namespace
 
-KernelFn kernel_values(bool narrow) { return narrow ? gemm_bytes_panel_kernel<false, 2, false> : gemm_bytes_panel_kernel<false, 4, false>; }
+KernelFn kernel_values(bool tail) { return tail ? gemm_bytes_panel_kernel<false, true> : gemm_bytes_panel_kernel<false, false>; }
 
 bool merge_supports(const Planes &pa, const Planes &pw) {
     MergeOperand a, w;
@@ -228,7 +228,7 @@ int launch_merge_planes(const GemmArgs &g, int8_t *outA, int8_t *outW, int64_t l
                       g.K, ld_out);
 }
 
-KernelFn kernel(bool narrow) { return narrow ? gemm_bytes_panel_kernel<true, 2> : gemm_bytes_panel_kernel<true, 4>; }
+KernelFn kernel(bool tail) { return tail ? gemm_bytes_panel_kernel<true, true> : gemm_bytes_panel_kernel<true, false>; }
 
 int launch_expand_weights(const uint32_t *W, int64_t N, int64_t K, int64_t ldw, int8_t *out, int64_t ld_out, int32_t *rw_scaled,
                           hipStream_t s) {

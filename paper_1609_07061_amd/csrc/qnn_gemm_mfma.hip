@@ -167,6 +167,10 @@ static int compute_units() {
     return cus;
 }
 
+// Byte-operand kernel: the last round's tiles as halves on twice the workgroups, where they are at most half as many (10000 x 784 ->
+// 4096 has 2.5 rounds: 48.5 us against 53 with a third whole round).
+static bool halve_last_round(int64_t total, int cus) { return cus % 16 == 0 && total > cus && total % cus != 0 && 2 * (total % cus) <= cus; }
+
 // Layout conditions of the panel-fed kernel: single planes, rows of whole 128-byte groups on 16-byte boundaries (row offsets are
 // 32-bit and formed for up to one tile beyond the last row before they are clamped).
 static bool panel_layout(const GemmArgs &g, const Variant *v, bool vec) {
@@ -229,16 +233,9 @@ int launch_gemm_mfma(const GemmArgs &g, hipStream_t s, bool fp4) {
         MfmaConst pc = mc;
         pc.alpha = 1, pc.alpha_shift = 0, pc.cRA = 0, pc.cRW = 1, pc.c0 = 0, pc.needRW = 1;
         const int64_t ngroups = ceil_div(g.K, bytes_panel::kGroupK);
-        // 256 x 128 tiles where they fill the rounds of workgroups clearly better than 256 x 256 ones
-        auto fill = [&](int64_t tiles) { return (double)tiles / (double)(ceil_div(tiles, cus) * cus); };
-        const int64_t wide_n = ceil_div(g.N, 256), narrow_n = ceil_div(g.N, 128);
-        const bool narrow = fill(tiles_m * narrow_n) > 1.1 * fill(tiles_m * wide_n);
-        const int64_t tiles_nb = narrow ? narrow_n : wide_n, ptotal = tiles_m * tiles_nb;
-        if (ptotal <= 0x7FFFFFFFLL) {
-            const unsigned pgrid = (unsigned)(ptotal < cus ? ptotal : cus);
-            return QNN_LAUNCH("gemm_bytes_panel", bytes_panel::kernel(narrow), dim3(pgrid), dim3(bytes_panel::kThreads), 0, s, g, pc,
-                              (uint32_t)tiles_m, (uint32_t)tiles_nb, (uint32_t)ngroups);
-        }
+        const bool tail = halve_last_round(total, cus);
+        return QNN_LAUNCH("gemm_bytes_panel", bytes_panel::kernel(tail), dim3(grid), dim3(bytes_panel::kThreads), 0, s, g, pc, (uint32_t)tiles_m,
+                          (uint32_t)tiles_n, (uint32_t)ngroups);
     }
     const KernelFn fn = g.A.rows_are_bytes ? byte_kernels()[g.epi.T ? 1 : 0]
                         : fp4              ? (vec ? v->fp4_vec : v->fp4_any)
@@ -399,17 +396,9 @@ int launch_values(const GemmArgs &g, hipStream_t s) {
         for (int sh = 0; sh < 31; ++sh)
             if (scale == ((int64_t)1 << sh)) mc.alpha_shift = sh;
         const int cus = compute_units();
-        const int64_t tiles_m = ceil_div(g.M, 256);
-        const int64_t wide_n = ceil_div(g.N, 256), narrow_n = ceil_div(g.N, 128);
-        // The narrow tile has room for three group buffers and keeps more bytes on their way from memory, which is what
-        // bounds this kernel (a byte per element, eight times the traffic of packed bits): the wide tile only where its
-        // tiles come out cheaper by a count of rounds of whole tiles (a round of wide tiles = 1.9 rounds of narrow ones),
-        // which sees padded columns as well as thin last rounds.
-        const bool narrow = tiles_m * wide_n < cus ||
-                            (double)ceil_div(tiles_m * narrow_n, cus) <= 1.9 * (double)ceil_div(tiles_m * wide_n, cus);
-        const int64_t tiles_n = narrow ? narrow_n : wide_n, total = tiles_m * tiles_n;
+        const int64_t tiles_m = ceil_div(g.M, 256), tiles_n = ceil_div(g.N, 256), total = tiles_m * tiles_n;
         const unsigned grid = (unsigned)(total < cus ? total : cus);
-        rc = QNN_LAUNCH("gemm_values", bytes_panel::kernel_values(narrow), dim3(grid), dim3(bytes_panel::kThreads), 0, s, v, mc,
+        rc = QNN_LAUNCH("gemm_values", bytes_panel::kernel_values(halve_last_round(total, cus)), dim3(grid), dim3(bytes_panel::kThreads), 0, s, v, mc,
                         (uint32_t)tiles_m, (uint32_t)tiles_n, (uint32_t)ceil_div(g.K, bytes_panel::kGroupK));
     }
     if (hipFreeAsync(mem, s) != hipSuccess) {

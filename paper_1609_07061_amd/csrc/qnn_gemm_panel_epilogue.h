@@ -28,7 +28,7 @@ __device__ __forceinline__ void load_thresholds_to_lds(const GemmArgs &g, const 
     const uint32_t thr_lds = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) int32_t *)thr_tab);
     const uint32_t flip_lds = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint32_t *)flip_tab);
 #pragma unroll
-    for (int h = 0; h < WBN / 2; ++h) {
+    for (int h = 0; h < (WBN + 1) / 2; ++h) {
         int64_t n = n_wave + 64 * h + lane;
         if (n > g.N - 1) n = g.N - 1;
         const uint32_t off = (uint32_t)n;  // (N < 2^31)
@@ -85,7 +85,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &g, const MfmaConst
         // output word (n mod 32 = 8 q + 4 kg + i  ->  bit 8 q + i): the per-wave LDS tables are rewritten in place
         asm volatile("s_waitcnt vmcnt(%0)" : : "n"(kLoadsAfter) : "memory");
 #pragma unroll
-        for (int h = 0; h < WTN / 64; ++h) {
+        for (int h = 0; h < (WTN + 63) / 64; ++h) {
             const int nl = 64 * h + lane;
             const int32_t tv = thr_tab[nl];
             const uint32_t fv = flip_tab[nl];

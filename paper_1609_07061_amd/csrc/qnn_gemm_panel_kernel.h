@@ -13,7 +13,7 @@
 //     issued right after the barrier that frees a group buffer, i.e. at least three steps (about 6000 cycles)
 //     before the data is needed; two group buffers take turns (three for the 256 x 128 tile, whose steps are half as
 //     long), and the barrier lets the loads of the later groups stay in flight;
-//   * a 16-byte piece c of row r sits at piece c xor (r mod 8) of its LDS row (the lanes of a load pick their global
+//   * a 16-byte piece c of row r sits at piece c xor (r / 2 mod 8) of its LDS row (the lanes of a load pick their global
 //     piece accordingly; the order of pieces inside a line does not change the cost of the load), so that the reads
 //     (lanes = consecutive rows, same piece) use all banks;
 //   * every lane reads the 16 bytes of its row and k-group for the next step with one ds_read_b128 per 32-row block;
@@ -100,7 +100,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
 
     // ------------------------------------------------------------------------------------------------ producer
     // A load instruction of a wave covers 8 consecutive rows x 128 bytes and fills 1 KiB of LDS: lane i lands at
-    // 16 i behind the address in M0, i.e. in slot i mod 8 of row i / 8, so it fetches piece (i mod 8) xor (row mod 8).
+    // 16 i behind the address in M0, i.e. in slot i mod 8 of row i / 8, so it fetches piece (i mod 8) xor (row / 2 mod 8).
     // Per quarter (64 rows) of a panel wave w loads rows 8 w .. 8 w + 7 and 32 + 8 w .. 32 + 8 w + 7.  Rows are
     // addressed by 32-bit byte offsets from the operand's base.
     // The lane-dependent parts are re-derived behind an opaque copy wherever they are used: address arithmetic that the
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
     auto p_piece = [&]() __attribute__((always_inline)) {
         if constexpr (kConv) {
             const uint32_t tt = opaque(tid);
-            const uint32_t piece = (tt & 7u) ^ ((tt >> 3) & 7u);
+            const uint32_t piece = (tt & 7u) ^ ((tt >> 4) & 7u);
             const uint32_t q = p_G * 8u + piece;               // piece of the row
             const uint32_t tap = q >> g.cpt_shift, sub = q - (tap << g.cpt_shift);
             const uint32_t ky = (tap * 11u) >> 5, kx = tap - 3u * ky;  // tap / 3, tap mod 3 (tap < 32)
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
         tile_of_block(p_vb, total_tiles, tiles_m, tiles_n, tm, tn);
         const uint32_t tt = opaque(tid);
         const uint32_t pr = tt >> 3;                                  // row within a load's 32-row block
-        const uint32_t piece16 = ((tt & 7u) ^ ((tt >> 3) & 7u)) << 4;  // (slot xor (row mod 8)) * 16 bytes
+        const uint32_t piece16 = ((tt & 7u) ^ ((tt >> 4) & 7u)) << 4;  // (slot xor (row / 2 mod 8)) * 16 bytes
         if constexpr (kConv) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
     auto fetch = [&](const int q, const uint32_t buf, Step &d) __attribute__((always_inline)) {
         const uint32_t ln = opaque(tid) & 63u;
         const uint32_t r = ln & 31u, kg = ln >> 5;
-        const uint32_t piece = ((kg ^ (r & 7u)) << 4) ^ (uint32_t)(q << 5);
+        const uint32_t piece = ((kg ^ ((r >> 1) & 7u)) << 4) ^ (uint32_t)(q << 5);
         const uint8_t *pa = lds + (buf + (uint32_t)(wm * WTILE * kRowBytes) + r * (uint32_t)kRowBytes + piece);
         const uint8_t *pw = lds + (buf + (uint32_t)kPanelBytes + (first_col + (uint32_t)(wn * 32 * WI)) * (uint32_t)kRowBytes +
                                    r * (uint32_t)kRowBytes + piece);

@@ -9,7 +9,7 @@
 //     1024 elements ahead of the multiplication, into registers.  The last piece of a row is read four words from its end and
 //     the words an earlier piece has brought are cleared, so nothing beyond a row is read.
 //   * The words go to LDS once per workgroup, already cleared and, for two planes of a digit, already interleaved; piece c of row
-//     r sits at piece c xor (r mod 8), so that writes (eight rows x eight pieces) and reads (32 rows, one piece) use all banks.
+//     r sits at piece c xor (r / 2 mod 8), so that writes (eight rows x eight pieces) and reads (32 rows, one piece) use all banks.
 //   * Epilogue through LDS: a 32 x 64 block per wave at a time, so that C leaves as 256-byte pieces of rows.
 #include "qnn_gemm_slice.h"
 
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(const GemmAr
     int sum_a[4] = {0, 0, 0, 0}, sum_w[4] = {0, 0, 0, 0};  // row sums of this lane's pieces, current digit pair
     // registers -> LDS: fields of digit planes, plane after plane.  tail: pieces end or start within the group
     auto store = [&](Group &x, const SliceDigit &da, const SliceDigit &dw, const uint32_t G, const bool tail) __attribute__((always_inline)) {
-        const uint32_t at = prow * 128u + ((piece0 ^ (prow & 7u)) << 4);
+        const uint32_t at = prow * 128u + ((piece0 ^ ((prow >> 1) & 7u)) << 4);
         if (kPixels || tail) {
             uint32_t keep[4];
 #pragma unroll
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(const GemmAr
         v4i a[2], w[2];
     };
     auto fetch = [&](const uint32_t q, Words &z) __attribute__((always_inline)) {
-        const uint32_t piece = ((2u * q + kg) ^ (r & 7u)) << 4;
+        const uint32_t piece = ((2u * q + kg) ^ ((r >> 1) & 7u)) << 4;
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
 #pragma unroll
