@@ -110,8 +110,7 @@ int qnn_binary_gemm_sign(const uint32_t *A, int64_t lda_words, const uint32_t *W
  * Large products (M, N >= 256, K >= 512, M N K >= 2^31) of multi-plane operands whose values fit int8 are computed
  * from the values: both operands' planes are merged to one byte per element in temporary device memory of
  * (M + N) * roundup(K, 128) bytes that the call takes from, and returns to, the memory pool of `stream`
- * (hipMallocAsync / hipFreeAsync: stream-ordered, no synchronization); QNN_ERR_HIP if the pool cannot supply it.
- * qnn_binary_backward's two products are of this kind. */
+ * (hipMallocAsync / hipFreeAsync: stream-ordered, no synchronization); QNN_ERR_HIP if the pool cannot supply it. */
 int qnn_bitplane_gemm(const uint32_t *A, int Pa, const int32_t *coefA, int modeA, int64_t lda_words,
                       int64_t strideA_words, const uint32_t *W, int Pb, const int32_t *coefW, int modeW,
                       int64_t ldw_words, int64_t strideW_words, int32_t *C, int64_t ldc, int64_t M, int64_t N,
@@ -280,7 +279,10 @@ int qnn_transpose_bits(const uint32_t *in, int64_t rows, int64_t cols, int64_t l
  * W: DEVICE packed +-1 [N][ldw_words] (along k, as the forward pass holds it); A: DEVICE packed +-1 [M][lda_words].
  * gA: DEVICE int32 [M][ld_ga]; gW: DEVICE int32 [N][ld_gw].  coefG: HOST.  workspace: DEVICE, 256-byte aligned,
  * qnn_binary_backward_workspace_bytes(...) bytes (the transposed operands).  QNN_ERR_OVERFLOW if
- * (sum |coefG|) * max(M, N) >= 2^31. */
+ * (sum |coefG|) * max(M, N) >= 2^31.
+ * Large steps are computed from bytes like the large products of qnn_bitplane_gemm, with up to (M + N) * roundup(max(M, N), 128) +
+ * K * roundup(max(M, N), 128) bytes of temporary memory from the pool of `stream` (with eight planes the transposed gradient
+ * lies in the workspace); QNN_ERR_HIP if the pool cannot supply it. */
 int qnn_binary_backward(const uint32_t *G, int Pg, const int32_t *coefG, int modeG, int64_t ldg_words,
                         int64_t strideG_words, const uint32_t *W, int64_t ldw_words, const uint32_t *A,
                         int64_t lda_words, int32_t *gA, int64_t ld_ga, int32_t *gW, int64_t ld_gw, int64_t M, int64_t N,

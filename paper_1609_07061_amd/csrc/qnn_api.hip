@@ -31,6 +31,12 @@ int fail(int code, const char *fmt, ...) {
     return code;
 }
 
+void note_engine(int engine) {
+    g_last_engine = engine;
+    g_engines[0] = engine;
+    g_engine_count = 1;
+}
+
 int check_launch(const char *what) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(QNN_ERR_HIP, "%s: %s", what, hipGetErrorString(e));

@@ -167,8 +167,8 @@ static int compute_units() {
     return cus;
 }
 
-// Byte-operand kernel: the last round's tiles as halves on twice the workgroups, where they are at most half as many (10000 x 784 ->
-// 4096 has 2.5 rounds: 48.5 us against 53 with a third whole round).
+// Byte-operand kernel: the last round's tiles as halves on twice the workgroups, where they are at most half as many (10000 x 784 -> 4096 has 2.5 rounds).
+
 static bool halve_last_round(int64_t total, int cus) { return cus % 16 == 0 && total > cus && total % cus != 0 && 2 * (total % cus) <= cus; }
 
 // Layout conditions of the panel-fed kernel: single planes, rows of whole 128-byte groups on 16-byte boundaries (row offsets are
@@ -369,46 +369,113 @@ bool values_path(const GemmArgs &g) {
     return bytes_panel::merge_supports(g.pa, g.pw);
 }
 
+// C = alpha S + c_row (sum of the left row) of two operands of int8 values, rows of `pitch` bytes
+int launch_values_product(const GemmArgs &g, const int8_t *a8, const int8_t *w8, int64_t pitch, int64_t alpha, const int32_t *row_sums, int64_t c_row,
+                          hipStream_t s) {
+    GemmArgs v = g;
+    v.A.base = reinterpret_cast<const uint32_t *>(a8);
+    v.A.ld = pitch;
+    v.A.plane_stride = 0;
+    v.A.rows_are_bytes = 1;
+    v.w_bytes = w8;
+    v.ld_w_bytes = pitch;
+    v.rw_scaled = nullptr;
+    v.row_sums = row_sums;
+    MfmaConst mc;
+    std::memset(&mc, 0, sizeof(mc));
+    mc.alpha = (uint32_t)alpha, mc.cRA = (uint32_t)c_row;
+    mc.alpha_shift = -1;
+    for (int sh = 0; sh < 31; ++sh)
+        if (alpha == ((int64_t)1 << sh)) mc.alpha_shift = sh;
+    const int cus = compute_units();
+    const int64_t tiles_m = ceil_div(g.M, 256), tiles_n = ceil_div(g.N, 256), total = tiles_m * tiles_n;
+    const unsigned grid = (unsigned)(total < cus ? total : cus);
+    return QNN_LAUNCH("gemm_values", bytes_panel::kernel_values(halve_last_round(total, cus)), dim3(grid), dim3(bytes_panel::kThreads), 0, s, v, mc,
+                      (uint32_t)tiles_m, (uint32_t)tiles_n, (uint32_t)ceil_div(g.K, bytes_panel::kGroupK));
+}
+
+// Temporary device memory from the stream's pool, given back in stream order.
+struct PoolMemory {
+    void *ptr = nullptr;
+    hipStream_t s;
+    explicit PoolMemory(hipStream_t stream) : s(stream) {}
+    int take(size_t bytes) {
+        if (hipMallocAsync(&ptr, bytes, s) != hipSuccess || !ptr) {
+            (void)hipGetLastError();
+            ptr = nullptr;
+            return fail(QNN_ERR_HIP, "gemm: no memory for the merged operands (%zu bytes)", bytes);
+        }
+        return QNN_OK;
+    }
+    int give_back(int rc) {
+        if (ptr && hipFreeAsync(ptr, s) != hipSuccess) {
+            (void)hipGetLastError();
+            if (rc == QNN_OK) rc = fail(QNN_ERR_HIP, "gemm: returning the merged operands' memory failed");
+        }
+        return rc;
+    }
+};
+
 int launch_values(const GemmArgs &g, hipStream_t s) {
     const int64_t pitch = values_pitch(g.K);
     const size_t bytes_a = (size_t)g.M * (size_t)pitch, bytes_w = (size_t)g.N * (size_t)pitch;
-    void *mem = nullptr;
-    if (hipMallocAsync(&mem, bytes_a + bytes_w, s) != hipSuccess || !mem) {
-        (void)hipGetLastError();
-        return fail(QNN_ERR_HIP, "gemm: no memory for the merged operands (%zu bytes)", bytes_a + bytes_w);
-    }
-    int8_t *a8 = static_cast<int8_t *>(mem), *w8 = a8 + bytes_a;  // (bytes_a is a multiple of 128)
+    PoolMemory mem(s);
+    if (int rc = mem.take(bytes_a + bytes_w)) return rc;
+    int8_t *a8 = static_cast<int8_t *>(mem.ptr), *w8 = a8 + bytes_a;  // (bytes_a is a multiple of 128)
     int64_t scale = 0;
     int rc = bytes_panel::launch_merge_planes(g, a8, w8, pitch, scale, s);
-    if (rc == QNN_OK) {
-        GemmArgs v = g;
-        v.A.base = reinterpret_cast<const uint32_t *>(a8);
-        v.A.ld = pitch;
-        v.A.plane_stride = 0;
-        v.A.rows_are_bytes = 1;
-        v.w_bytes = w8;
-        v.ld_w_bytes = pitch;
-        v.rw_scaled = nullptr;
-        MfmaConst mc;
-        std::memset(&mc, 0, sizeof(mc));
-        mc.alpha = (uint32_t)scale;
-        mc.alpha_shift = -1;
-        for (int sh = 0; sh < 31; ++sh)
-            if (scale == ((int64_t)1 << sh)) mc.alpha_shift = sh;
-        const int cus = compute_units();
-        const int64_t tiles_m = ceil_div(g.M, 256), tiles_n = ceil_div(g.N, 256), total = tiles_m * tiles_n;
-        const unsigned grid = (unsigned)(total < cus ? total : cus);
-        rc = QNN_LAUNCH("gemm_values", bytes_panel::kernel_values(halve_last_round(total, cus)), dim3(grid), dim3(bytes_panel::kThreads), 0, s, v, mc,
-                        (uint32_t)tiles_m, (uint32_t)tiles_n, (uint32_t)ceil_div(g.K, bytes_panel::kGroupK));
-    }
-    if (hipFreeAsync(mem, s) != hipSuccess) {
-        (void)hipGetLastError();
-        if (rc == QNN_OK) rc = fail(QNN_ERR_HIP, "gemm: returning the merged operands' memory failed");
-    }
-    return rc;
+    if (rc == QNN_OK) rc = launch_values_product(g, a8, w8, pitch, scale, nullptr, 0, s);
+    return mem.give_back(rc);
+}
+
+// One product of the backward step as a bit-plane product (for the choice of the way it takes).
+GemmArgs backward_product(const BackwardArgs &b, int64_t M, int64_t N, int64_t K, int32_t *C, int64_t ldc) {
+    GemmArgs g;
+    std::memset(&g, 0, sizeof(g));
+    g.pa = b.pg;
+    g.pw.count = 1, g.pw.mode = QNN_PLANE_SIGN, g.pw.coef[0] = 1;
+    g.A.base = b.G, g.W = b.W;
+    g.M = M, g.N = N, g.K = K, g.Kw = words_for(K);
+    g.A.ld = g.ldw = g.Kw;
+    g.epi.C = C, g.epi.ldc = ldc;
+    return g;
 }
 
 }  // namespace
+
+// Where each of the two products would go to the byte kernel anyway, its operands are made in fewer passes: the gradient's planes
+// become bytes in both orders in one pass (instead of a transposition of all planes and a merge per product), the +-1 matrices
+// are transposed straight to bytes, as 0 / 1 (sum g w = 2 sum g b - sum g, the sums from the same pass: half of the products are
+// zero, and the card's power limit, which holds the clock of these kernels down, gives back 6 %: 159 -> 149 us at
+// 4096 x 4096 x 10000).  10000 x 4096 x 4096 with eight planes: operands 115 -> 64 us.
+bool backward_bytes_preferred(const BackwardArgs &b) {
+    if (!bytes_panel::merge_both_supports(b.pg)) return false;
+    const GemmArgs ga = backward_product(b, b.M, b.K, b.N, b.gA, b.ld_ga), gw = backward_product(b, b.N, b.K, b.M, b.gW, b.ld_gw);
+    for (const GemmArgs *g : {&ga, &gw})
+        if (!mfma_preferred(*g) || !values_path(*g) || slice_preferred(*g, QNN_ENGINE_MFMA_LDS)) return false;
+    return true;
+}
+
+int launch_backward_bytes(const BackwardArgs &b, int8_t *gt, hipStream_t s) {
+    const int64_t pn = values_pitch(b.N), pm = values_pitch(b.M);
+    const size_t size_g = (size_t)b.M * pn, size_gt = gt ? 0 : (size_t)b.N * pm, size_w = (size_t)b.K * (pn > pm ? pn : pm);
+    const size_t sums = ((size_t)(b.M + b.N) * 4 + 255) / 256 * 256;
+    PoolMemory mem(s);
+    if (int rc = mem.take(sums + size_g + size_gt + size_w)) return rc;
+    int32_t *row_sums = static_cast<int32_t *>(mem.ptr), *col_sums = row_sums + b.M;
+    int8_t *g8 = static_cast<int8_t *>(mem.ptr) + sums;  // (all sizes are multiples of 128)
+    if (!gt) gt = g8 + size_g;
+    int8_t *w8 = g8 + size_g + size_gt;  // the transposed weights, then the transposed activations
+    int64_t scale = 0;
+    const GemmArgs ga = backward_product(b, b.M, b.K, b.N, b.gA, b.ld_ga), gw = backward_product(b, b.N, b.K, b.M, b.gW, b.ld_gw);
+    int rc = bytes_panel::launch_transpose_to_bytes(b.W, b.N, b.K, b.ldw, reinterpret_cast<uint8_t *>(w8), pn, row_sums, b.M + b.N, s);
+    if (rc == QNN_OK)
+        rc = bytes_panel::launch_merge_transpose(b.pg, b.G, b.strideG, b.ldg, b.M, b.N, g8, pn, gt, pm, row_sums, col_sums, scale, s);
+    if (rc == QNN_OK) rc = launch_values_product(ga, g8, w8, pn, 2 * scale, row_sums, -scale, s);
+    if (rc == QNN_OK) rc = bytes_panel::launch_transpose_to_bytes(b.A, b.M, b.K, b.lda, reinterpret_cast<uint8_t *>(w8), pm, nullptr, 0, s);
+    if (rc == QNN_OK) rc = launch_values_product(gw, gt, w8, pm, 2 * scale, col_sums, -scale, s);
+    return mem.give_back(rc);
+}
 
 bool stage_supports(const GemmArgs &g) {
     if (values_path(g)) return true;

@@ -11,6 +11,8 @@ namespace qnn {
 
 // Records the message returned by qnn_last_error() for the calling thread and passes `code` through.
 int fail(int code, const char *fmt, ...);
+// Records the engine that a call used (qnn_last_engine, qnn_last_engines) where it does not go through the common dispatch.
+void note_engine(int engine);
 // Checks hipGetLastError() after a launch; QNN_OK or QNN_ERR_HIP.
 int check_launch(const char *what);
 // Launches a kernel and reports the outcome of THIS launch: an error that an earlier HIP call of the caller left behind
@@ -74,6 +76,8 @@ struct GemmArgs {
     const int8_t *w_bytes;
     int64_t ld_w_bytes;
     const int32_t *rw_scaled;
+    // Optional, with operands of int8 values only: sums of the left operand's rows (the epilogue's term cRA * sum)
+    const int32_t *row_sums;
     // Only for the convolution on the panel-fed FP4 kernel (panel::gemm_panel_kernel<true, 2, false, true>): A.base is
     // the lower of {the plane "value is -1" of a +-1 map, a 16-byte line of zeros}; a_delta / zero_off are the byte
     // offsets of the two from it; class_thr[cls * class_ld + n] is the threshold of filter n for a pixel of border class
@@ -123,6 +127,17 @@ int launch_gemm_stage(const GemmArgs &g, hipStream_t s);
 bool slice_preferred(const GemmArgs &g, int route);
 int launch_gemm_slice(const GemmArgs &g, hipStream_t s);
 int launch_gemm_tile(const GemmArgs &g, hipStream_t s);
+// Both products of the backward step from bytes (g_a = g W into gA, g_W = g^T a into gW): whether they take this way, and the
+// launches.  gt: where the transposed gradient goes if it holds N * roundup(M, 128) bytes, else null.
+struct BackwardArgs {
+    Planes pg;
+    const uint32_t *G, *W, *A;
+    int64_t ldg, strideG, ldw, lda;
+    int32_t *gA, *gW;
+    int64_t ld_ga, ld_gw, M, N, K;
+};
+bool backward_bytes_preferred(const BackwardArgs &b);
+int launch_backward_bytes(const BackwardArgs &b, int8_t *gt, hipStream_t s);
 bool panel_takes(const GemmArgs &g);  // whether the FP4 route would use the panel-fed kernel
 
 // Expansion of packed +-1 weights (N rows of K elements) to one int8 per element (row pitch ld_out, a multiple of 128,
@@ -133,6 +148,13 @@ namespace bytes_panel {
 // merge_supports: whether the values of both operands fit int8.
 bool merge_supports(const Planes &pa, const Planes &pw);
 int launch_merge_planes(const GemmArgs &g, int8_t *outA, int8_t *outW, int64_t ld_out, int64_t &scale, hipStream_t s);
+// The backward step's operands as bytes: a gradient (planes with multipliers +-2^q) in both orders with its row and column sums,
+// and a packed bit matrix transposed to bytes 0 / 1 (which also clears n_clear words).
+bool merge_both_supports(const Planes &pl);
+int launch_merge_transpose(const Planes &pl, const uint32_t *planes, int64_t plane_stride, int64_t ld, int64_t M, int64_t N, int8_t *out,
+                           int64_t ld_out, int8_t *out_t, int64_t ld_t, int32_t *row_sums, int32_t *col_sums, int64_t &scale, hipStream_t s);
+int launch_transpose_to_bytes(const uint32_t *in, int64_t rows, int64_t cols, int64_t ld, uint8_t *out, int64_t ld_out, int32_t *clear,
+                              int64_t n_clear, hipStream_t s);
 int launch_expand_weights(const uint32_t *W, int64_t N, int64_t K, int64_t ldw, int8_t *out, int64_t ld_out, int32_t *rw_scaled,
                           hipStream_t s);
 }

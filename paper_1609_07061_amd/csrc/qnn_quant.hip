@@ -470,6 +470,19 @@ extern "C" int qnn_binary_backward(const uint32_t *G, int Pg, const int32_t *coe
     // (the products' 16-byte load paths) whatever the other operand holds there; the transposes write that padding.
     const bool pad = modeG == QNN_PLANE_BIT;
     int rc;
+    BackwardArgs b;
+    b.pg.count = Pg, b.pg.mode = modeG;
+    for (int p = 0; p < Pg; ++p) b.pg.coef[p] = coefG[p];
+    b.G = G, b.W = W, b.A = A, b.ldg = ldg_words, b.strideG = Pg > 1 ? strideG_words : 0, b.ldw = ldw_words, b.lda = lda_words;
+    b.gA = gA, b.gW = gW, b.ld_ga = ld_ga, b.ld_gw = ld_gw, b.M = M, b.N = N, b.K = K;
+    // (what the products refuse is left to them)
+    const bool valid = (modeG == QNN_PLANE_BIT || modeG == QNN_PLANE_SIGN) && b.strideG >= 0 && aligned4(G) && aligned4(gA) && aligned4(gW);
+    if (valid && backward_bytes_preferred(b)) {
+        // (eight planes of the transposed gradient take as much of the workspace as its bytes)
+        if ((rc = launch_backward_bytes(b, Pg == 8 ? reinterpret_cast<int8_t *>(Gt) : nullptr, st))) return rc;
+        note_engine(QNN_ENGINE_MFMA_LDS);
+        return QNN_OK;
+    }
     // g_a = g W: the reduction runs over n, so W (N x K, packed along k) is needed packed along n
     if ((rc = launch_transpose(W, N, K, ldw_words, 0, 1, Wt, ldn, 0, pad ? ldn : words_for(N), st))) return rc;
     if ((rc = qnn_bitplane_gemm(G, Pg, coefG, modeG, ldg_words, strideG_words, Wt, 1, &one, QNN_PLANE_SIGN, ldn, 0, gA, ld_ga,

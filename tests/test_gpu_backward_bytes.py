@@ -1,0 +1,32 @@
+"""The backward step from bytes: sizes one off the tiles of its operand kernels (128 rows x 256 columns, four rows x 32 columns),
+of its products (256 x 256, halves in the last round) and of their groups of 128; planes that stand for every kind of value."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import qnn_inputs as qi
+from qnn_testlib import dev, host, np_pack_bits, np_pack_pm1
+
+pytestmark = pytest.mark.gpu
+
+VALUES = [1, 2, 4, 8, 16, 32, 64, -128]
+
+
+@pytest.mark.parametrize("M,N,K", [(2560, 2600, 2050), (2817, 2433, 2049), (2400, 2304, 2273)])
+@pytest.mark.parametrize("coef,mode", [(VALUES, 0), ([-3 * c for c in VALUES], 0), ([64, 1, 2, -4, 16, 8, 32], 0), ([1, -2, 4, 8, 16, -32], 1)])
+def test_large_backward_step(seed, M, N, K, coef, mode):
+    import paper_1609_07061_amd as q
+
+    planes = qi.bernoulli_bits(seed, 1300, (len(coef), M, N)).astype(np.int64)
+    g = sum(c * (planes[p] if mode == 0 else 2 * planes[p] - 1) for p, c in enumerate(coef))
+    w, a = qi.pm1(seed, 1301, (N, K)), qi.pm1(seed, 1302, (M, K))
+    Nw = (N + 31) // 32
+    G = dev(np_pack_bits(planes.astype(np.uint8), Nw + 1))[:, :, :Nw]  # rows and planes with a gap
+    ga, gw = q.qnn_binary_backward(G, coef, mode, N, dev(np_pack_pm1(w)), dev(np_pack_pm1(a)), K)
+    want_ga = torch.from_numpy(g).double().cuda() @ torch.from_numpy(w.astype(np.float64)).cuda()
+    want_gw = torch.from_numpy(np.ascontiguousarray(g.T)).double().cuda() @ torch.from_numpy(a.astype(np.float64)).cuda()
+    assert torch.equal(ga, want_ga.to(torch.int32)), (M, N, K, coef)
+    assert torch.equal(gw, want_gw.to(torch.int32)), (M, N, K, coef)
+    rows = np.array([0, M - 1])
+    assert np.array_equal(host(ga)[rows], oracle.gemm_int(g[rows].astype(np.int32), np.ascontiguousarray(w.T).astype(np.int32)))
