@@ -748,6 +748,7 @@ int run_net(const NetPlan &plan, hipStream_t s) {
                 break;
             case NetStep::kGemm:
                 rc = launch_on(st.g, st.engine, plan.free_choice, s);
+                if (rc == QNN_OK && st.a) g_last_engine = g_engines[g_engine_count - 1] = st.a;  // (a: the class to report, if not the engine)
                 break;
             case NetStep::kFirstConv:
                 // src = image, mask = weights, dst = output bits; rows = B, a / b / c = H / W / C0, n = filters;
@@ -840,15 +841,19 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
     }
     const int flags_step = plan.n;
     if (n_layers > 1) push().kind = NetStep::kFlags;
-    // convolutions that take the panel-fed FP4 kernel (every one but the first, if the shapes allow): their thresholds
-    // per border class, all in one launch
+    // whether a convolution (not the first) takes the panel-fed FP4 kernel; which addresses its input and the line of zeros,
+    // both in the workspace, with 32-bit offsets
+    auto on_panel_kernel = [&](int64_t hh, int64_t ww, int64_t cc, int64_t co) {
+        return (engine == QNN_ENGINE_AUTO || engine == QNN_ENGINE_MFMA_FP4) && L.total < 0xFFFF0000ull && conv_panel_supports(B, hh, ww, cc, co) &&
+               (engine != QNN_ENGINE_AUTO || conv_panel_preferred(B, hh, ww, co));
+    };
+    // convolutions that take the panel-fed FP4 kernel: their thresholds per border class, all in one launch
     plan.prep.count = 0;
     plan.prep.zero_line = words(L.zero_line);
     {
         int64_t hh = H, ww = Wd, cc = C0;
         for (int l = 0; l < n_conv; ++l) {
-            if (l > 0 && (engine == QNN_ENGINE_AUTO || engine == QNN_ENGINE_MFMA_FP4) && L.total < 0xFFFF0000ull &&
-                conv_panel_supports(B, hh, ww, cc, cout[l])) {
+            if (l > 0 && on_panel_kernel(hh, ww, cc, cout[l])) {
                 const int j = plan.prep.count++;
                 plan.prep.W[j] = W[l], plan.prep.T[j] = T[l];
                 plan.prep.out[j] = reinterpret_cast<int32_t *>(ws + L.class_thr[l]);
@@ -899,12 +904,10 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
         NetStep &st = push();
         st.kind = NetStep::kGemm;
         const Epilogue e{nullptr, 0, T[l], fl, conv_dst, Cwo};
-        // (the panel-fed convolution addresses its input and the line of zeros, both in the workspace, with 32-bit offsets)
-        const bool panel_engine = (engine == QNN_ENGINE_AUTO || engine == QNN_ENGINE_MFMA_FP4) && L.total < 0xFFFF0000ull;
-        const bool on_panel = l > 0 && panel_engine && conv_panel_supports(B, h, w, cin, co);
+        const bool on_panel = l > 0 && on_panel_kernel(h, w, cin, co);
         // the next convolution reads this layer's output: on the panel-fed kernel it takes the plane "value is -1" alone,
         // otherwise the 2-bit code, whose plane "inside the image" is then written too
-        const bool ones_needed = inverted && !(panel_engine && conv_panel_supports(B, ho, wo, co, cout[l + 1]));
+        const bool ones_needed = inverted && !on_panel_kernel(ho, wo, co, cout[l + 1]);
         if (on_panel) {
             // the map's plane "value is -1" alone; out = (conv >= T) xor fl, and the kernel takes the complement of fl:
             // the caller's flags where fl is their inversion, the inverted ones where fl is the caller's
@@ -925,6 +928,8 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
                                co, 3, 3, 1, 1, e, engine, st.g, empty))
             return rc;
         if (int rc = choose(st.g, st.engine)) return rc;
+        // (a small convolution that the panel-fed kernel could take belongs to the FP4 class wherever it runs)
+        if (l > 0 && engine == QNN_ENGINE_AUTO && conv_panel_supports(B, h, w, cin, co)) st.a = QNN_ENGINE_MFMA_FP4;
         }
         if (pool[l]) {
             NetStep &pl = push();

@@ -258,6 +258,10 @@ bool conv_panel_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N)
     return ceil_div(M, 256) * ceil_div(N, 128) <= 0x7FFFFFFFLL;
 }
 
+// From 32 of its 256 x 128 tiles on: the CIFAR-10 ConvNet on 4, 16, 64 images of 32 x 32 takes 59, 87, 103 us with the line at 32
+// tiles, 98, 100, 103 with every convolution on the panel-fed kernel, 59, 92, 144 with none there (other sizes alike).
+bool conv_panel_preferred(int64_t B, int64_t H, int64_t Wd, int64_t N) { return ceil_div(B * H * Wd, 256) * ceil_div(N, 128) >= 32; }
+
 int64_t conv_panel_class_ld(int64_t N) { return ceil_div(N, 128) * 128; }
 
 int launch_conv_panel(const uint32_t *plane, int64_t B, int H, int Wd, int C, const uint32_t *W, int64_t N, const int32_t *T,

@@ -171,6 +171,8 @@ int launch_threshold_sign(const int32_t *C, int64_t ldc, int64_t M, int64_t N, c
 // panel::launch_conv_class_thr (one launch for all convolutions of a network); zero_line and the plane must lie within
 // 4 GiB of each other.
 bool conv_panel_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N);
+// whether it is faster than the map's 2-bit code on the kernels for products of any size
+bool conv_panel_preferred(int64_t B, int64_t H, int64_t Wd, int64_t N);
 int64_t conv_panel_class_ld(int64_t N);
 int launch_conv_panel(const uint32_t *plane, int64_t B, int H, int Wd, int C, const uint32_t *W, int64_t N, const int32_t *T,
                       const uint8_t *flip_complement, uint32_t *out, int64_t ldo, const int32_t *class_thr,
