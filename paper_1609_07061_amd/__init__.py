@@ -100,8 +100,16 @@ def _check(status: int):
         raise QnnError(status, _lib.qnn_last_error().decode())
 
 
+# The current stream's handle without a torch.cuda.Stream object around it: 0.2 us instead of 2.8, of the 10 us that a small call
+# took on the host (of which the launch is 4).
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _current_device is None or _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _dev(t: Optional[torch.Tensor], dtype, name: str) -> Optional[int]:
@@ -116,19 +124,20 @@ def _dev(t: Optional[torch.Tensor], dtype, name: str) -> Optional[int]:
 
 def _rows_ld(t: torch.Tensor, name: str):
     """(rows, cols, leading dimension) of a 2-D tensor whose rows are contiguous."""
-    if t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
+    shape, stride = t.shape, t.stride()
+    if len(shape) != 2 or (shape[1] > 1 and stride[1] != 1):
         raise ValueError(f"{name} must be 2-D with contiguous rows")
-    ld = t.stride(0) if t.shape[0] > 1 else max(t.shape[1], 1)
-    return t.shape[0], t.shape[1], ld
+    rows, cols = shape
+    return rows, cols, stride[0] if rows > 1 else max(cols, 1)
 
 
 def _planes_ld(t: torch.Tensor, name: str):
     """(planes, rows, words, ld, plane stride) of a [P][rows][words] tensor."""
-    if t.dim() != 3 or (t.shape[2] > 1 and t.stride(2) != 1):
+    shape, stride = t.shape, t.stride()
+    if len(shape) != 3 or (shape[2] > 1 and stride[2] != 1):
         raise ValueError(f"{name} must be [planes][rows][words] with contiguous rows")
-    ld = t.stride(1) if t.shape[1] > 1 else max(t.shape[2], 1)
-    ps = t.stride(0) if t.shape[0] > 1 else 0
-    return t.shape[0], t.shape[1], t.shape[2], ld, ps
+    planes, rows, words = shape
+    return planes, rows, words, stride[1] if rows > 1 else max(words, 1), stride[0] if planes > 1 else 0
 
 
 def _coef(c: Sequence[int]):
