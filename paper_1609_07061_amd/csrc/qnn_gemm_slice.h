@@ -47,6 +47,8 @@ struct SliceArgs {
     uint32_t alpha, c0;  // C = alpha (S - row corrections) + c0
     int corrected;       // some digit has an offset: row sums are taken
     int modified;        // some digit has an inverted or an absent plane
+    int sum_a, sum_w;    // the left / right operand's row sums are wanted
+    int ragged;          // the rows (pixels: the taps) are not made of whole pieces
     int clear_w;         // +-1 activation planes: where activation words are cleared the weight words have to be cleared too
 };
 
@@ -112,6 +114,75 @@ __device__ __forceinline__ v4i make_operand(const u32x4 &z0, const u32x4 &z1, co
     return f;
 }
 __device__ __forceinline__ v8i widen(const v4i &x) { return __builtin_shufflevector(x, x, 0, 1, 2, 3, -1, -1, -1, -1); }
+
+// How the rows of the left operand are found (LeftAddr): a matrix, the patches of an image, or those of an image whose pixels have
+// fewer than four words.
+enum SliceRows { kMatrix = 0, kPatches = 1, kNarrowPatches = 2 };
+
+// 16 bytes of a row; narrow pixels word by word, the rest zero
+template <int kRows>
+__device__ __forceinline__ u32x4 load_piece(const uint8_t *p, const SliceArgs &sc) {
+    if constexpr (kRows == kNarrowPatches) {
+        const uint32_t *w = reinterpret_cast<const uint32_t *>(p);
+        u32x4 v = {w[0], 0u, 0u, 0u};
+        if (sc.row_words > 1u) v.y = w[1];
+        if (sc.row_words > 2u) v.z = w[2];
+        return v;
+    } else {
+        return *reinterpret_cast<const u32x4_any *>(p);
+    }
+}
+
+// The patch of output pixel m: byte offset of its first tap's pixel (modulo 2^32: the tap may lie outside the image) and which
+// of its tap rows (bits 0 .. 15) and tap columns (bits 16 .. 31) lie inside.
+struct Patch {
+    uint32_t off, in;
+};
+__device__ __forceinline__ Patch patch_of(const GemmArgs &g, const SliceArgs &sc, const uint32_t m) {
+    const uint32_t per = (uint32_t)(g.A.Ho * g.A.Wo);
+    const uint32_t img = m / per, rem = m - img * per;
+    const uint32_t yo = rem / (uint32_t)g.A.Wo, xo = rem - yo * (uint32_t)g.A.Wo;
+    const int y = (int)yo * g.A.stride - g.A.pad, x = (int)xo * g.A.stride - g.A.pad;
+    auto inside = [](const int first, const int taps, const int size) {  // taps t with 0 <= first + t < size
+        const int lo = first < 0 ? (-first < 16 ? -first : 16) : 0, end = size - first;
+        const int hi = end < taps ? (end > 0 ? end : 0) : taps;
+        return hi > lo ? ((1u << hi) - 1u) & ~((1u << lo) - 1u) : 0u;
+    };
+    Patch p;
+    p.off = (img * (uint32_t)(g.A.H * g.A.Wd) + (uint32_t)(y * g.A.Wd + x)) * sc.row_words * 4u;
+    p.in = inside(y, g.A.KH, g.A.H) | (inside(x, g.A.KW, g.A.Wd) << 16);
+    return p;
+}
+// A lane's piece of the rows: first word within the row (pixels: the tap) and within the weight row, leading words to clear;
+// pixels: the tap's row and column, the byte offset from the first tap's pixel.
+struct Piece {
+    uint32_t word, w_word, skip, ky, kx, off;
+};
+template <int kRows>
+__device__ __forceinline__ Piece piece_of(const GemmArgs &g, const SliceArgs &sc, const uint32_t piece) {
+    Piece p;
+    if constexpr (kRows == kMatrix) {
+        p.word = p.w_word = 4u * piece < sc.row_words - 4u ? 4u * piece : sc.row_words - 4u;
+        p.skip = 4u * piece - p.word;
+        p.ky = p.kx = 0u;
+        p.off = p.word * 4u;
+    } else {
+        uint32_t tap = __umulhi(piece, sc.magic_ppt);
+        if (sc.ppt == 1u) tap = piece;  // (ceil(2^32 / 1) does not fit)
+        const uint32_t sub = piece - tap * sc.ppt;
+        p.word = sc.ppt == 1u || 4u * sub < sc.row_words - 4u ? 4u * sub : sc.row_words - 4u;
+        p.skip = 4u * sub - p.word;
+        p.ky = 0u;
+        if (tap >= sc.taps) tap = 0u, p.skip = 4u, p.ky = 15u;  // beyond the patch: a tap row that no patch has
+        uint32_t q = __umulhi(tap, sc.magic_kw);
+        if (g.A.KW == 1) q = tap;
+        p.kx = tap - q * (uint32_t)g.A.KW;
+        p.off = ((q * (uint32_t)g.A.Wd + p.kx) * sc.row_words + p.word) * 4u;
+        p.ky |= q;
+        p.w_word = tap * sc.row_words + p.word;
+    }
+    return p;
+}
 
 // The kernels' arguments for a product and the kinds of its operands; false if they cannot take it.  bits: +-1 planes as kOne (with
 // corrections from row sums) instead of kPm1, and single 0/1 planes as kOne instead of kPair.

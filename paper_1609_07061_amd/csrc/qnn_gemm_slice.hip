@@ -25,8 +25,9 @@ using namespace slice;
 namespace {
 
 // BMb x BNb blocks of 32 x 32 per wave; up to kMaxWaves waves share k.
-template <int kA, int kW, bool kPixels, int BMb, int BNb, int kMaxWaves>
+template <int kA, int kW, int kRows, int BMb, int BNb, int kMaxWaves>
 __global__ __launch_bounds__(64 * kMaxWaves, kMaxWaves == 4 ? 2 : 4) void gemm_slice_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
+    constexpr bool kPixels = kRows != kMatrix;
     constexpr int BM = 32 * BMb, BN = 32 * BNb, kPitch = BN + 4;
     constexpr int NA = kA == kPair ? 2 : 1, NW = kW == kPair ? 2 : 1;  // planes of a digit
     __shared__ __attribute__((aligned(16))) float part[kMaxWaves][BM][kPitch];
@@ -38,21 +39,16 @@ __global__ __launch_bounds__(64 * kMaxWaves, kMaxWaves == 4 ? 2 : 4) void gemm_s
     const uint32_t m0 = tm * BM, n0 = tn * BN;
 
     // rows of this lane (rows beyond the last repeat it and are not stored)
-    uint32_t a_off[BMb], w_off[BNb];  // byte offsets from the digit's plane
-    int a_y[BMb], a_x[BMb];           // pixels: input coordinates of the window's first tap
+    uint32_t a_off[BMb], a_in[BMb], w_off[BNb];  // byte offsets from the digit's plane (pixels: of the patch, see patch_of)
 #pragma unroll
     for (int b = 0; b < BMb; ++b) {
         uint32_t m = m0 + 32 * b + r;
         m = m < (uint32_t)g.M ? m : (uint32_t)g.M - 1u;
         if constexpr (kPixels) {
-            const uint32_t per = (uint32_t)(g.A.Ho * g.A.Wo);
-            const uint32_t img = m / per, rem = m - img * per;
-            const uint32_t yo = rem / (uint32_t)g.A.Wo, xo = rem - yo * (uint32_t)g.A.Wo;
-            a_y[b] = (int)yo * g.A.stride - g.A.pad, a_x[b] = (int)xo * g.A.stride - g.A.pad;
-            a_off[b] = img * (uint32_t)(g.A.H * g.A.Wd);  // pixels, not bytes
+            const Patch p = patch_of(g, sc, m);
+            a_off[b] = p.off, a_in[b] = p.in;
         } else {
-            a_y[b] = a_x[b] = 0;
-            a_off[b] = m * (uint32_t)(g.A.ld * 4);
+            a_off[b] = m * (uint32_t)(g.A.ld * 4), a_in[b] = 0u;
         }
     }
 #pragma unroll
@@ -67,59 +63,27 @@ __global__ __launch_bounds__(64 * kMaxWaves, kMaxWaves == 4 ? 2 : 4) void gemm_s
         uint32_t skip_a[BMb], skip;  // leading words to clear
     };
     const uint8_t *const a_base = reinterpret_cast<const uint8_t *>(g.A.base), *const w_base = reinterpret_cast<const uint8_t *>(g.W);
-    // 16 bytes of a row; pixels of fewer than four words (128 channels) word by word, the rest zero
-    auto load16 = [&](const uint8_t *p) __attribute__((always_inline)) -> u32x4 {
-        if (kPixels && sc.row_words < 4u) {
-            const uint32_t *w = reinterpret_cast<const uint32_t *>(p);
-            u32x4 v = {w[0], 0u, 0u, 0u};
-            if (sc.row_words > 1u) v.y = w[1];
-            if (sc.row_words > 2u) v.z = w[2];
-            return v;
-        }
-        return *reinterpret_cast<const u32x4_any *>(p);
-    };
     auto load = [&](Chunk &x, const SliceDigit &da, const SliceDigit &dw, const uint32_t c) __attribute__((always_inline)) {
-        const uint32_t piece = 2u * c + kg;
-        uint32_t j, jw;  // first word within the row (pixels: the tap), and within the weight row
-        int ky = 0, kx = 0;
-        if constexpr (kPixels) {
-            uint32_t tap = __umulhi(piece, sc.magic_ppt);
-            if (sc.ppt == 1u) tap = piece;  // (ceil(2^32 / 1) does not fit)
-            uint32_t sub = piece - tap * sc.ppt;
-            j = sc.ppt == 1u || 4u * sub < sc.row_words - 4u ? 4u * sub : sc.row_words - 4u;
-            x.skip = 4u * sub - j;
-            if (tap >= sc.taps) tap = sc.taps - 1u, x.skip = 4u;
-            uint32_t q = __umulhi(tap, sc.magic_kw);
-            if (g.A.KW == 1) q = tap;
-            ky = (int)q, kx = (int)(tap - q * (uint32_t)g.A.KW);
-            jw = tap * sc.row_words + j;
-        } else {
-            j = 4u * piece < sc.row_words - 4u ? 4u * piece : sc.row_words - 4u;
-            x.skip = 4u * piece - j;
-            jw = j;
-        }
+        const Piece p = piece_of<kRows>(g, sc, 2u * c + kg);
+        x.skip = p.skip;
 #pragma unroll
         for (int b = 0; b < BMb; ++b) {
-            uint32_t off;
+            uint32_t off = a_off[b] + p.off;
+            x.skip_a[b] = p.skip;
             if constexpr (kPixels) {
-                const int iy = a_y[b] + ky, ix = a_x[b] + kx;
-                const bool in = (uint32_t)iy < (uint32_t)g.A.H && (uint32_t)ix < (uint32_t)g.A.Wd;
-                // outside the image: any valid address, its words are cleared
-                const uint32_t px = a_off[b] + (in ? (uint32_t)(iy * g.A.Wd + ix) : 0u);
-                off = (px * sc.row_words + j) * 4u;
-                x.skip_a[b] = in ? x.skip : 4u;
-            } else {
-                off = a_off[b] + j * 4u;
-                x.skip_a[b] = x.skip;
+                // outside the image: the plane's first words, cleared before use
+                const bool in = ((a_in[b] >> p.ky) & (a_in[b] >> (p.kx + 16u)) & 1u) != 0u;
+                off = in ? off : 0u;
+                x.skip_a[b] = in ? p.skip : 4u;
             }
-            x.a[0][b] = load16(a_base + da.off0 + off);
-            if constexpr (kA == kPair) x.a[1][b] = load16(a_base + da.off1 + off);
+            x.a[0][b] = load_piece<kRows>(a_base + da.off0 + off, sc);
+            if constexpr (kA == kPair) x.a[1][b] = load_piece<kRows>(a_base + da.off1 + off, sc);
         }
 #pragma unroll
         for (int b = 0; b < BNb; ++b) {
-            const uint32_t off = w_off[b] + jw * 4u;
-            x.w[0][b] = load16(w_base + dw.off0 + off);
-            if constexpr (kW == kPair) x.w[1][b] = load16(w_base + dw.off1 + off);
+            const uint32_t off = w_off[b] + p.w_word * 4u;
+            x.w[0][b] = load_piece<kRows>(w_base + dw.off0 + off, sc);
+            if constexpr (kW == kPair) x.w[1][b] = load_piece<kRows>(w_base + dw.off1 + off, sc);
         }
     };
 
@@ -346,6 +310,7 @@ bool slice_args(const GemmArgs &g, bool bits, SliceArgs &sc, int &kind_a, int &k
     if (!make_digits(g.pa, g.A.plane_stride, bits, sc.a, kind_a, ga, sa) || !make_digits(g.pw, g.strideW, bits, sc.w, kind_w, gw, sw)) return false;
     const int64_t row_words = pix ? g.A.Cw : g.Kw;
     if (row_words < (pix ? 1 : 4)) return false;
+    if (pix && (g.A.KH > 15 || g.A.KW > 15)) return false;  // (which taps lie inside the image: sixteen bits each way, one spare)
     const int64_t ppt = ceil_div(row_words, 4), taps = pix ? (int64_t)g.A.KH * g.A.KW : 1, pieces = ppt * taps;
     if (pieces >= 32768 || taps >= 32768) return false;  // (the quotients by multiplication are exact below 2^32 / divisor)
     sc.row_words = (uint32_t)row_words, sc.ppt = (uint32_t)ppt, sc.taps = (uint32_t)taps;
@@ -365,11 +330,13 @@ bool slice_args(const GemmArgs &g, bool bits, SliceArgs &sc, int &kind_a, int &k
         for (int j = 0; j < sc.w.count; ++j) {
             const SliceDigit &da = sc.a.d[i], &dw = sc.w.d[j];
             constant += ((int64_t)da.offset2 * dw.offset2 * 64 * sc.chunks) << (da.lg + dw.lg);
-            if (da.offset2 || dw.offset2) sc.corrected = 1;
+            if (dw.offset2) sc.sum_a = sc.corrected = 1;
+            if (da.offset2) sc.sum_w = sc.corrected = 1;
             if (da.inv0 || da.inv1 || dw.inv0 || dw.inv1 || (kind_a == kPair && !da.use1) || (kind_w == kPair && !dw.use1)) sc.modified = 1;
         }
     sc.c0 = (uint32_t)constant * sc.alpha;
     sc.clear_w = g.pa.mode == QNN_PLANE_SIGN;
+    sc.ragged = row_words % 4 != 0;
     // +-1 planes on both sides: a processed element beyond K is (-sum coefA)(-sum coefW) instead of 0
     if (g.pa.mode == QNN_PLANE_SIGN && g.pw.mode == QNN_PLANE_SIGN) {
         int64_t ca = 0, cw = 0;
@@ -385,15 +352,13 @@ bool slice_args(const GemmArgs &g, bool bits, SliceArgs &sc, int &kind_a, int &k
 namespace {
 
 typedef void (*SliceFn)(const GemmArgs, const SliceArgs, uint32_t, uint32_t);
-template <int BMb, int BNb, int kMaxWaves>
-SliceFn slice_kernel(int ka, int kw, bool pix) {
-    if (pix) {
-        if (ka == kPm1) return kw == kPm1 ? gemm_slice_kernel<kPm1, kPm1, true, BMb, BNb, kMaxWaves> : gemm_slice_kernel<kPm1, kPair, true, BMb, BNb, kMaxWaves>;
-        return kw == kPm1 ? gemm_slice_kernel<kPair, kPm1, true, BMb, BNb, kMaxWaves> : gemm_slice_kernel<kPair, kPair, true, BMb, BNb, kMaxWaves>;
-    }
-    if (ka == kPm1) return kw == kPm1 ? gemm_slice_kernel<kPm1, kPm1, false, BMb, BNb, kMaxWaves> : gemm_slice_kernel<kPm1, kPair, false, BMb, BNb, kMaxWaves>;
-    return kw == kPm1 ? gemm_slice_kernel<kPair, kPm1, false, BMb, BNb, kMaxWaves> : gemm_slice_kernel<kPair, kPair, false, BMb, BNb, kMaxWaves>;
+template <int kRows, int BMb, int BNb, int kMaxWaves>
+SliceFn slice_kernel(int ka, int kw) {
+    if (ka == kPm1) return kw == kPm1 ? gemm_slice_kernel<kPm1, kPm1, kRows, BMb, BNb, kMaxWaves> : gemm_slice_kernel<kPm1, kPair, kRows, BMb, BNb, kMaxWaves>;
+    return kw == kPm1 ? gemm_slice_kernel<kPair, kPm1, kRows, BMb, BNb, kMaxWaves> : gemm_slice_kernel<kPair, kPair, kRows, BMb, BNb, kMaxWaves>;
 }
+template <int kRows>
+SliceFn slice_kernel(int ka, int kw, bool large) { return large ? slice_kernel<kRows, 2, 2, 4>(ka, kw) : slice_kernel<kRows, 1, 1, 16>(ka, kw); }
 
 }  // namespace
 
@@ -431,7 +396,7 @@ int launch_gemm_slice(const GemmArgs &g, hipStream_t s) {
     if (tiles_m * tiles_n > 0x7FFFFFFFLL) return fail(QNN_ERR_SHAPE, "gemm: too many tiles");
     const int most = large ? 4 : 16;
     const int waves = items < most ? (int)items : most;
-    const SliceFn fn = large ? slice_kernel<2, 2, 4>(ka, kw, pix) : slice_kernel<1, 1, 16>(ka, kw, pix);
+    const SliceFn fn = !pix ? slice_kernel<kMatrix>(ka, kw, large) : (g.A.Cw < 4 ? slice_kernel<kNarrowPatches>(ka, kw, large) : slice_kernel<kPatches>(ka, kw, large));
     return QNN_LAUNCH("gemm_slice", fn, dim3((unsigned)(tiles_m * tiles_n)), dim3(64u * waves), 0, s, g, sc, (uint32_t)tiles_m, (uint32_t)tiles_n);
 }
 

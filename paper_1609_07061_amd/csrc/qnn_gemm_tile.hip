@@ -24,8 +24,9 @@ constexpr int kTile = 128;
 constexpr int kPlaneBytes = kTile * 128;  // a group of one plane of an operand
 constexpr int kStagePitch = 68;           // floats per row of the epilogue's block: 64 and a gap
 
-template <int kA, int kW, bool kPixels>
+template <int kA, int kW, int kRows>
 __global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
+    constexpr bool kPixels = kRows != kMatrix;
     constexpr int NA = kA == kPair ? 2 : 1, NW = kW == kPair ? 2 : 1;  // planes of a digit
     constexpr int kOperandBytes = (NA + NW) * kPlaneBytes, kEpiBytes = 4 * 32 * kStagePitch * 4;
     __shared__ __attribute__((aligned(16))) uint8_t lds[kOperandBytes > kEpiBytes ? kOperandBytes : kEpiBytes];
@@ -39,21 +40,16 @@ __global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(const GemmAr
     // ------------------------------------------------------------------------------------------------ loads
     // load i of a plane: rows 32 i + 8 wave + lane / 8, piece lane mod 8 of the group
     const uint32_t prow = 8u * wave + (lane >> 3), piece0 = lane & 7u;
-    uint32_t a_off[4], w_off[4];  // byte offset of the row (pixels: first pixel of the image)
-    int a_y[4], a_x[4];           // pixels: input coordinates of the window's first tap
+    uint32_t a_off[4], a_in[4], w_off[4];  // byte offset of the row (pixels: of the patch, see patch_of)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         uint32_t m = m0 + 32 * i + prow;
         m = m < (uint32_t)g.M ? m : (uint32_t)g.M - 1u;  // (rows beyond the last repeat it and are not stored)
         if constexpr (kPixels) {
-            const uint32_t per = (uint32_t)(g.A.Ho * g.A.Wo);
-            const uint32_t img = m / per, rem = m - img * per;
-            const uint32_t yo = rem / (uint32_t)g.A.Wo, xo = rem - yo * (uint32_t)g.A.Wo;
-            a_y[i] = (int)yo * g.A.stride - g.A.pad, a_x[i] = (int)xo * g.A.stride - g.A.pad;
-            a_off[i] = img * (uint32_t)(g.A.H * g.A.Wd);
+            const Patch p = patch_of(g, sc, m);
+            a_off[i] = p.off, a_in[i] = p.in;
         } else {
-            a_y[i] = a_x[i] = 0;
-            a_off[i] = m * (uint32_t)(g.A.ld * 4);
+            a_off[i] = m * (uint32_t)(g.A.ld * 4), a_in[i] = 0u;
         }
         uint32_t n = n0 + 32 * i + prow;
         n = n < (uint32_t)g.N ? n : (uint32_t)g.N - 1u;
@@ -61,89 +57,64 @@ __global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(const GemmAr
     }
     struct Group {
         u32x4 a[NA][4], w[NW][4];
-        uint32_t skip, inside;  // leading words to clear; pixels: bit i = the tap of row i lies inside the image
+        uint32_t skip, ky, kx;  // leading words to clear; pixels: the tap's row and column
     };
     const uint8_t *const a_base = reinterpret_cast<const uint8_t *>(g.A.base), *const w_base = reinterpret_cast<const uint8_t *>(g.W);
-    // 16 bytes of a row; pixels of fewer than four words (128 channels) word by word, the rest zero
-    auto load16 = [&](const uint8_t *p) __attribute__((always_inline)) -> u32x4 {
-        if (kPixels && sc.row_words < 4u) {
-            const uint32_t *w = reinterpret_cast<const uint32_t *>(p);
-            u32x4 v = {w[0], 0u, 0u, 0u};
-            if (sc.row_words > 1u) v.y = w[1];
-            if (sc.row_words > 2u) v.z = w[2];
-            return v;
-        }
-        return *reinterpret_cast<const u32x4_any *>(p);
-    };
+    auto inside = [&](const int i, const uint32_t ky, const uint32_t kx) __attribute__((always_inline)) { return (a_in[i] >> ky) & (a_in[i] >> (kx + 16u)) & 1u; };
     auto load = [&](Group &x, const SliceDigit &da, const SliceDigit &dw, const uint32_t G) __attribute__((always_inline)) {
-        const uint32_t piece = 8u * G + piece0;
-        uint32_t j, jw;  // first word within the row (pixels: the tap), and within the weight row
-        int ky = 0, kx = 0;
-        if constexpr (kPixels) {
-            uint32_t tap = __umulhi(piece, sc.magic_ppt);
-            if (sc.ppt == 1u) tap = piece;  // (ceil(2^32 / 1) does not fit)
-            const uint32_t sub = piece - tap * sc.ppt;
-            j = sc.ppt == 1u || 4u * sub < sc.row_words - 4u ? 4u * sub : sc.row_words - 4u;
-            x.skip = 4u * sub - j;
-            if (tap >= sc.taps) tap = sc.taps - 1u, x.skip = 4u;
-            uint32_t q = __umulhi(tap, sc.magic_kw);
-            if (g.A.KW == 1) q = tap;
-            ky = (int)q, kx = (int)(tap - q * (uint32_t)g.A.KW);
-            jw = tap * sc.row_words + j;
-        } else {
-            j = 4u * piece < sc.row_words - 4u ? 4u * piece : sc.row_words - 4u;
-            x.skip = 4u * piece - j;
-            jw = j;
-        }
-        x.inside = 0xFu;
+        const Piece p = piece_of<kRows>(g, sc, 8u * G + piece0);
+        x.skip = p.skip, x.ky = p.ky, x.kx = p.kx;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            uint32_t off;
-            if constexpr (kPixels) {
-                const int iy = a_y[i] + ky, ix = a_x[i] + kx;
-                const bool in = (uint32_t)iy < (uint32_t)g.A.H && (uint32_t)ix < (uint32_t)g.A.Wd;
-                // outside the image: any valid address, its words are cleared
-                off = ((a_off[i] + (in ? (uint32_t)(iy * g.A.Wd + ix) : 0u)) * sc.row_words + j) * 4u;
-                if (!in) x.inside &= ~(1u << i);
-            } else {
-                off = a_off[i] + j * 4u;
-            }
-            x.a[0][i] = load16(a_base + da.off0 + off);
-            if constexpr (kA == kPair) x.a[1][i] = load16(a_base + da.off1 + off);
+            uint32_t off = a_off[i] + p.off;
+            // outside the image: the plane's first words, cleared below
+            if constexpr (kPixels) off = inside(i, p.ky, p.kx) ? off : 0u;
+            x.a[0][i] = load_piece<kRows>(a_base + da.off0 + off, sc);
+            if constexpr (kA == kPair) x.a[1][i] = load_piece<kRows>(a_base + da.off1 + off, sc);
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const uint32_t off = w_off[i] + jw * 4u;
-            x.w[0][i] = load16(w_base + dw.off0 + off);
-            if constexpr (kW == kPair) x.w[1][i] = load16(w_base + dw.off1 + off);
+            const uint32_t off = w_off[i] + p.w_word * 4u;
+            x.w[0][i] = load_piece<kRows>(w_base + dw.off0 + off, sc);
+            if constexpr (kW == kPair) x.w[1][i] = load_piece<kRows>(w_base + dw.off1 + off, sc);
         }
     };
     int sum_a[4] = {0, 0, 0, 0}, sum_w[4] = {0, 0, 0, 0};  // row sums of this lane's pieces, current digit pair
     // registers -> LDS: fields of digit planes, plane after plane.  tail: pieces end or start within the group
     auto store = [&](Group &x, const SliceDigit &da, const SliceDigit &dw, const uint32_t G, const bool tail) __attribute__((always_inline)) {
         const uint32_t at = prow * 128u + ((piece0 ^ ((prow >> 1) & 7u)) << 4);
-        if (kPixels || tail) {
-            uint32_t keep[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) keep[e] = (uint32_t)e >= x.skip ? 0xFFFFFFFFu : 0u;
+        // words outside the image, beyond the row's end, or brought by the piece before
+        if constexpr (kPixels) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const uint32_t in = (x.inside >> i) & 1u ? 0xFFFFFFFFu : 0u;
+                const uint32_t in = 0u - inside(i, x.ky, x.kx);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const uint32_t k = kPixels ? (keep[e] & in) : keep[e];
-                    x.a[0][i][e] &= k;
-                    if constexpr (kA == kPair) x.a[1][i][e] &= k;
+                    x.a[0][i][e] &= in;
+                    if constexpr (kA == kPair) x.a[1][i][e] &= in;
                 }
             }
-            if (sc.clear_w) {
+        }
+        if (kPixels ? sc.ragged : tail) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t keep = (uint32_t)e >= x.skip ? 0xFFFFFFFFu : 0u;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        x.w[0][i][e] &= keep[e];
-                        if constexpr (kW == kPair) x.w[1][i][e] &= keep[e];
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    x.a[0][i][e] &= keep;
+                    if constexpr (kA == kPair) x.a[1][i][e] &= keep;
+                }
+            }
+        }
+        if (sc.clear_w && (kPixels || tail)) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t keep = (uint32_t)e >= x.skip ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    x.w[0][i][e] &= keep;
+                    if constexpr (kW == kPair) x.w[1][i][e] &= keep;
+                }
             }
         }
         if (sc.modified) {
@@ -153,11 +124,15 @@ __global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(const GemmAr
                 apply_inversion<kW>(dw.inv0, dw.inv1, dw.use1, x.w[0][i], x.w[NW - 1][i]);
             }
         }
-        if (sc.corrected && 8u * G + piece0 < 2u * sc.chunks) {  // (pieces beyond the last chunk are not multiplied)
+        // (pieces beyond the last chunk are not multiplied: they count only where they are zero)
+        if (!sc.modified || 8u * G + piece0 < 2u * sc.chunks) {
+            if (sc.sum_a) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                sum_a[i] = add_sum<kA>(x.a[0][i], x.a[NA - 1][i], sum_a[i]);
-                sum_w[i] = add_sum<kW>(x.w[0][i], x.w[NW - 1][i], sum_w[i]);
+                for (int i = 0; i < 4; ++i) sum_a[i] = add_sum<kA>(x.a[0][i], x.a[NA - 1][i], sum_a[i]);
+            }
+            if (sc.sum_w) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sum_w[i] = add_sum<kW>(x.w[0][i], x.w[NW - 1][i], sum_w[i]);
             }
         }
 #pragma unroll
@@ -362,10 +337,10 @@ __global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(const GemmAr
 }
 
 typedef void (*TileFn)(const GemmArgs, const SliceArgs, uint32_t, uint32_t);
-template <bool kPixels>
+template <int kRows>
 TileFn tile_kernel(int ka, int kw) {
-    if (ka == kOne) return kw == kOne ? gemm_tile_kernel<kOne, kOne, kPixels> : gemm_tile_kernel<kOne, kPair, kPixels>;
-    return kw == kOne ? gemm_tile_kernel<kPair, kOne, kPixels> : gemm_tile_kernel<kPair, kPair, kPixels>;
+    if (ka == kOne) return kw == kOne ? gemm_tile_kernel<kOne, kOne, kRows> : gemm_tile_kernel<kOne, kPair, kRows>;
+    return kw == kOne ? gemm_tile_kernel<kPair, kOne, kRows> : gemm_tile_kernel<kPair, kPair, kRows>;
 }
 
 }  // namespace
@@ -376,7 +351,7 @@ int launch_gemm_tile(const GemmArgs &g, hipStream_t s) {
     if (!slice_args(g, true, sc, ka, kw)) return fail(QNN_ERR_UNSUPPORTED, "tiled FP4 kernel cannot take these arguments");
     const int64_t tiles_m = ceil_div(g.M, kTile), tiles_n = ceil_div(g.N, kTile);
     if (tiles_m * tiles_n > 0x7FFFFFFFLL) return fail(QNN_ERR_SHAPE, "gemm: too many tiles");
-    const TileFn fn = g.A.rows_are_pixels ? tile_kernel<true>(ka, kw) : tile_kernel<false>(ka, kw);
+    const TileFn fn = !g.A.rows_are_pixels ? tile_kernel<kMatrix>(ka, kw) : (g.A.Cw < 4 ? tile_kernel<kNarrowPatches>(ka, kw) : tile_kernel<kPatches>(ka, kw));
     return QNN_LAUNCH("gemm_tile", fn, dim3((unsigned)(tiles_m * tiles_n)), dim3(kTileThreads), 0, s, g, sc, (uint32_t)tiles_m, (uint32_t)tiles_n);
 }
 
