@@ -212,7 +212,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, kMaxWaves == 4 ? 2 : 4) void gemm_s
             const int64_t n = (int64_t)n0 + col;
             int32_t *dst = g.epi.C + (int64_t)(m0 + row) * g.epi.ldc + n;
             if (vec && n + 4 <= g.N)
-                *reinterpret_cast<i32x4 *>(dst) = val;
+                __builtin_nontemporal_store(val, reinterpret_cast<i32x4 *>(dst));
             else
 #pragma unroll
                 for (int e = 0; e < 4; ++e)

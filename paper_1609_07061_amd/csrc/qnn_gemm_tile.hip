@@ -25,7 +25,7 @@ constexpr int kPlaneBytes = kTile * 128;  // a group of one plane of an operand
 constexpr int kStagePitch = 68;           // floats per row of the epilogue's block: 64 and a gap
 
 template <int kA, int kW, int kRows>
-__global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
+__global__ __launch_bounds__(kTileThreads, kA == kOne && kW == kOne ? 3 : 2) void gemm_tile_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
     constexpr bool kPixels = kRows != kMatrix;
     constexpr int NA = kA == kPair ? 2 : 1, NW = kW == kPair ? 2 : 1;  // planes of a digit
     constexpr int kOperandBytes = (NA + NW) * kPlaneBytes, kEpiBytes = 4 * 32 * kStagePitch * 4;
@@ -177,41 +177,25 @@ __global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(const GemmAr
 #pragma unroll
         for (int b = 0; b < 2; ++b) f.a[b] = make_operand<kA>(z.a[0][b], z.a[NA - 1][b], ph), f.w[b] = make_operand<kW>(z.w[0][b], z.w[NW - 1][b], ph);
     };
-    // Phase ph multiplies the operands made during the phase before and meanwhile makes the next one's (from z, or from the
-    // next chunk's words), the vector instructions spread between the matrix-core ones.
-    auto phase = [&](auto ph_tag, const int a_scale, const int w_scale, const Words &z, Operands &f) __attribute__((always_inline)) {
-        constexpr int ph = decltype(ph_tag)::value;
-        Operands next;
-        make(z, (ph + 1) & 3, next);
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen(f.w[i]), widen(f.a[j]), acc[i][j], 4, 4, ph, w_scale, ph, a_scale);
-        f = next;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, kA == kPair || kW == kPair ? 7 : 5, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    };
     auto multiply = [&](const int a_scale, const int w_scale, const uint32_t chunks) __attribute__((always_inline)) {
-        Words z0, z1;
-        Operands f;
-        fetch(0, z0);
-        make(z0, 0, f);
-        auto chunk = [&](const Words &z, Words &zn, const uint32_t next) __attribute__((always_inline)) {
-            fetch(next, zn);
-            phase(std::integral_constant<int, 0>{}, a_scale, w_scale, z, f);
-            phase(std::integral_constant<int, 1>{}, a_scale, w_scale, z, f);
-            phase(std::integral_constant<int, 2>{}, a_scale, w_scale, z, f);
-            phase(std::integral_constant<int, 3>{}, a_scale, w_scale, zn, f);
-        };
 #pragma unroll 1
         for (uint32_t q = 0; q < chunks; ++q) {
-            chunk(z0, z1, q + 1u < chunks ? q + 1u : q);
-            z0 = z1;
+            Words z;
+            fetch(q, z);
+            auto phase = [&](auto ph_tag) __attribute__((always_inline)) {
+                constexpr int ph = decltype(ph_tag)::value;
+                Operands f;
+                make(z, ph, f);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen(f.w[i]), widen(f.a[j]), acc[i][j], 4, 4, ph, w_scale, ph, a_scale);
+            };
+            phase(std::integral_constant<int, 0>{});
+            phase(std::integral_constant<int, 1>{});
+            phase(std::integral_constant<int, 2>{});
+            phase(std::integral_constant<int, 3>{});
         }
     };
 
@@ -300,7 +284,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(const GemmAr
                         val[e] = (int32_t)((uint32_t)times_alpha(v[e]) - (uint32_t)corr);
                     }
                     const int64_t m = m_blk + row;
-                    if (m < g.M) *reinterpret_cast<i32x4 *>(g.epi.C + m * g.epi.ldc + n_wave + col) = val;
+                    if (m < g.M) __builtin_nontemporal_store(val, reinterpret_cast<i32x4 *>(g.epi.C + m * g.epi.ldc + n_wave + col));
                 }
             } else {
                 // rows that start anywhere, or the last columns: one row per store, lanes on consecutive columns
