@@ -655,7 +655,7 @@ int qnn_bitplane_conv2d(const uint32_t *A, int Pa, const int32_t *coefA, int mod
 namespace {
 constexpr int kMaxNetLayers = 2 * QNN_MAX_LAYERS;
 struct NetStep {
-    enum Kind { kPack, kFlags, kOnes, kGemm, kPool, kFirstConv, kConvPrep, kConvPanel } kind;
+    enum Kind { kPack, kFlags, kOnes, kGemm, kPool, kFirstConv, kConvPrep, kConvMap } kind;
     GemmArgs g;      // kGemm (convolution or fully connected)
     int engine;      // kGemm
     // kPack / kFlags / kOnes / kPool operands
@@ -664,20 +664,21 @@ struct NetStep {
     int64_t rows, n;
     int a, b, c;
     const uint32_t *mask;
+    const uint32_t *w;  // kConvMap: filters
     bool invert;
 };
 struct NetPlan {
     int n;
     bool free_choice;   // the caller asked for no engine
     FlagJobs flags;     // kFlags: every layer's flip flags, one launch
-    ConvPrepJobs prep;  // kConvPrep: border-class thresholds of every convolution on the panel-fed kernel, one launch
+    ConvPrepJobs prep;  // kConvPrep: border-class thresholds of every convolution on a plane, one launch
     NetStep step[6 * kMaxNetLayers + 4];
 };
 
 struct NetLayout {
     size_t planes0, flags, act[2], tmp, fc[2], total;
     size_t flag_bits[kMaxNetLayers], flag_inv[kMaxNetLayers];
-    size_t class_thr[kMaxNetLayers], zero_line;  // scratch of the convolutions on the panel-fed kernel
+    size_t class_thr[kMaxNetLayers];  // thresholds per border class of the convolutions on planes
 };
 
 // Sizes of the workspace regions; false if the shapes are not valid.
@@ -723,10 +724,9 @@ bool net_layout(int64_t B, int64_t H, int64_t Wd, int64_t C0, int in_bits, int n
         const int64_t n = l < n_conv ? cout[l] : fc_out[l - n_conv];
         L.flag_bits[l] = take((size_t)words_for(n) * 4);
         L.flag_inv[l] = take((size_t)n);
-        L.class_thr[l] = l < n_conv ? take((size_t)16 * (size_t)conv_panel_class_ld(n) * 4) : 0;
+        L.class_thr[l] = l < n_conv ? take((size_t)16 * (size_t)conv_class_ld(n) * 4) : 0;
     }
-    L.zero_line = take(256);
-    L.total = off + 256;
+    L.total = off + 512;
     return true;
 }
 
@@ -765,13 +765,12 @@ int run_net(const NetPlan &plan, hipStream_t s) {
                 rc = panel::launch_conv_class_thr(jobs, plan.flags, s);
                 break;
             }
-            case NetStep::kConvPanel:
-                // src = plane "value is -1" of the input map, mask = weights, dst = output bits, dst2 = class thresholds;
-                // rows = B, a / b / c = H / W / C, n = filters; thresholds, complemented flips and the output pitch in
-                // g.epi; g.W = the line of zeros
-                rc = launch_conv_panel(static_cast<const uint32_t *>(st.src), st.rows, st.a, st.b, st.c, st.mask, st.n, st.g.epi.T,
-                                       st.g.epi.flip, static_cast<uint32_t *>(st.dst), st.g.epi.ldo, static_cast<const int32_t *>(st.dst2),
-                                       st.g.W, s);
+            case NetStep::kConvMap:
+                // src = plane "value is -1" of the input map, w = filters, dst = output bits, dst2 = class thresholds;
+                // rows = B, a / b / c = H / W / C, n = filters; complemented flips and the output pitch in g.epi; mask (may be
+                // null) / invert = the pooling done along
+                rc = launch_conv_map(static_cast<const uint32_t *>(st.src), st.rows, st.a, st.b, st.c, st.w, st.n, st.g.epi.flip,
+                                     static_cast<uint32_t *>(st.dst), st.g.epi.ldo, static_cast<const int32_t *>(st.dst2), st.mask, st.invert, s);
                 if (rc == QNN_OK) {
                     g_last_engine = QNN_ENGINE_MFMA_FP4;
                     if (g_engine_count < 2 * QNN_MAX_LAYERS) g_engines[g_engine_count++] = QNN_ENGINE_MFMA_FP4;
@@ -841,24 +840,22 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
     }
     const int flags_step = plan.n;
     if (n_layers > 1) push().kind = NetStep::kFlags;
-    // whether a convolution (not the first) takes the panel-fed FP4 kernel; which addresses its input and the line of zeros,
-    // both in the workspace, with 32-bit offsets
-    auto on_panel_kernel = [&](int64_t hh, int64_t ww, int64_t cc, int64_t co) {
-        return (engine == QNN_ENGINE_AUTO || engine == QNN_ENGINE_MFMA_FP4) && L.total < 0xFFFF0000ull && conv_panel_supports(B, hh, ww, cc, co) &&
-               (engine != QNN_ENGINE_AUTO || conv_panel_preferred(B, hh, ww, co));
+    // whether a convolution (not the first) reads its map as the plane "value is -1" (tiled FP4 kernel) or as the 2-bit code
+    auto on_plane = [&](int64_t hh, int64_t ww, int64_t cc, int64_t co) {
+        return (engine == QNN_ENGINE_AUTO || engine == QNN_ENGINE_MFMA_FP4) && conv_map_supports(B, hh, ww, cc, co) &&
+               (engine != QNN_ENGINE_AUTO || conv_map_preferred(B, hh, ww, co));
     };
-    // convolutions that take the panel-fed FP4 kernel: their thresholds per border class, all in one launch
+    // thresholds per border class of the convolutions on planes, all in one launch
     plan.prep.count = 0;
-    plan.prep.zero_line = words(L.zero_line);
     {
         int64_t hh = H, ww = Wd, cc = C0;
         for (int l = 0; l < n_conv; ++l) {
-            if (l > 0 && on_panel_kernel(hh, ww, cc, cout[l])) {
+            if (l > 0 && on_plane(hh, ww, cc, cout[l])) {
                 const int j = plan.prep.count++;
                 plan.prep.W[j] = W[l], plan.prep.T[j] = T[l];
                 plan.prep.out[j] = reinterpret_cast<int32_t *>(ws + L.class_thr[l]);
-                plan.prep.N[j] = cout[l], plan.prep.ld[j] = conv_panel_class_ld(cout[l]);
-                plan.prep.Cw[j] = (int)words_for(cc);
+                plan.prep.N[j] = cout[l], plan.prep.ld[j] = conv_class_ld(cout[l]);
+                plan.prep.Cw[j] = (int)words_for(cc), plan.prep.C[j] = cc;
             }
             if (pool[l]) hh /= 2, ww /= 2;
             cc = cout[l];
@@ -904,19 +901,18 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
         NetStep &st = push();
         st.kind = NetStep::kGemm;
         const Epilogue e{nullptr, 0, T[l], fl, conv_dst, Cwo};
-        const bool on_panel = l > 0 && on_panel_kernel(h, w, cin, co);
-        // the next convolution reads this layer's output: on the panel-fed kernel it takes the plane "value is -1" alone,
+        const bool on_map = l > 0 && on_plane(h, w, cin, co);
+        // the next convolution reads this layer's output: as a plane it takes "value is -1" alone,
         // otherwise the 2-bit code, whose plane "inside the image" is then written too
-        const bool ones_needed = inverted && !on_panel_kernel(ho, wo, co, cout[l + 1]);
-        if (on_panel) {
-            // the map's plane "value is -1" alone; out = (conv >= T) xor fl, and the kernel takes the complement of fl:
-            // the caller's flags where fl is their inversion, the inverted ones where fl is the caller's
-            st.kind = NetStep::kConvPanel;
-            st.src = a_planes + a_stride, st.mask = W[l], st.dst = conv_dst, st.dst2 = ws + L.class_thr[l];
+        const bool ones_needed = inverted && !on_plane(ho, wo, co, cout[l + 1]);
+        const bool pooled_along = on_map && pool[l] && !ones_needed && conv_map_pools(h, w);
+        if (on_map) {
+            st.kind = NetStep::kConvMap;
+            st.src = a_planes + a_stride, st.w = W[l], st.dst = pooled_along ? kept_bits : conv_dst, st.dst2 = ws + L.class_thr[l];
             st.rows = B, st.a = (int)h, st.b = (int)w, st.c = (int)cin, st.n = co;
             st.g.epi = e;
             st.g.epi.flip = inverted ? (flip ? flip[l] : nullptr) : reinterpret_cast<const uint8_t *>(ws + L.flag_inv[l]);
-            st.g.W = words(L.zero_line);
+            if (pooled_along) st.mask = words(L.flag_bits[l]), st.invert = inverted;
         } else if (l == 0 && first_direct) {
             st.kind = NetStep::kFirstConv;
             st.src = x, st.mask = W[0], st.dst = conv_dst;
@@ -928,10 +924,12 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
                                co, 3, 3, 1, 1, e, engine, st.g, empty))
             return rc;
         if (int rc = choose(st.g, st.engine)) return rc;
-        // (a small convolution that the panel-fed kernel could take belongs to the FP4 class wherever it runs)
-        if (l > 0 && engine == QNN_ENGINE_AUTO && conv_panel_supports(B, h, w, cin, co)) st.a = QNN_ENGINE_MFMA_FP4;
+        // (convolutions of at least 256 pixels and whole, power-of-two groups of 128 channels belong to the FP4 class wherever they
+        // run)
+        if (l > 0 && engine == QNN_ENGINE_AUTO && B * h * w >= 256 && h > 1 && w > 1 && cin % 128 == 0 && ((cin / 128) & (cin / 128 - 1)) == 0)
+            st.a = QNN_ENGINE_MFMA_FP4;
         }
-        if (pool[l]) {
+        if (pool[l] && !pooled_along) {
             NetStep &pl = push();
             pl.kind = NetStep::kPool;
             pl.src = conv_dst, pl.dst = kept_bits;

@@ -244,63 +244,6 @@ int launch_gemm_mfma(const GemmArgs &g, hipStream_t s, bool fp4) {
                        (uint32_t)tiles_n);
 }
 
-// ------------------------------------------------------------------------------------------------ convolution on the panel-fed kernel
-bool conv_panel_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N) {
-    // (at least two rows and columns: a pixel is then in one of three row classes and one of three column classes)
-    if (B < 1 || H < 2 || Wd < 2 || H > 32767 || Wd > 32767 || C < 128 || C % 128 || N < 1) return false;
-    if (16 * conv_panel_class_ld(N) >= (1 << 28)) return false;  // 32-bit byte offsets into the class table
-    const int64_t cpt = C / 128;
-    if (cpt & (cpt - 1)) return false;
-    const int64_t M = B * H * Wd, Cw = C / 32;
-    if (M < 256 || M > 0x7FFFFFFFLL) return false;
-    // 32-bit byte offsets: the plane (plus the distance to the line of zeros, checked at the launch) and the weights
-    if ((long double)(M + 256) * Cw * 4 >= 2147483648.0L || (long double)(N + 256) * 9 * Cw * 4 >= 4294967296.0L) return false;
-    return ceil_div(M, 256) * ceil_div(N, 128) <= 0x7FFFFFFFLL;
-}
-
-// From 32 of its 256 x 128 tiles on: the CIFAR-10 ConvNet on 4, 16, 64 images of 32 x 32 takes 59, 87, 103 us with the line at 32
-// tiles, 98, 100, 103 with every convolution on the panel-fed kernel, 59, 92, 144 with none there (other sizes alike).
-bool conv_panel_preferred(int64_t B, int64_t H, int64_t Wd, int64_t N) { return ceil_div(B * H * Wd, 256) * ceil_div(N, 128) >= 32; }
-
-int64_t conv_panel_class_ld(int64_t N) { return ceil_div(N, 128) * 128; }
-
-int launch_conv_panel(const uint32_t *plane, int64_t B, int H, int Wd, int C, const uint32_t *W, int64_t N, const int32_t *T,
-                      const uint8_t *flip_complement, uint32_t *out, int64_t ldo, const int32_t *class_thr,
-                      const uint32_t *zero_line, hipStream_t s) {
-    if (!conv_panel_supports(B, H, Wd, C, N)) return fail(QNN_ERR_UNSUPPORTED, "convolution on the panel-fed kernel: shape not supported");
-    const int Cw = C / 32;
-    const int64_t M = B * H * Wd, ld = conv_panel_class_ld(N);
-    const uint8_t *pa = reinterpret_cast<const uint8_t *>(plane), *pz = reinterpret_cast<const uint8_t *>(zero_line);
-    const uint8_t *base = pa < pz ? pa : pz;
-    const uint64_t a_delta = (uint64_t)(pa - base), z_off = (uint64_t)(pz - base);
-    if (a_delta + (uint64_t)(M + 256) * Cw * 4 >= 4294967296ULL || z_off + 256 >= 4294967296ULL)
-        return fail(QNN_ERR_UNSUPPORTED, "convolution on the panel-fed kernel: scratch too far from the feature map");
-    GemmArgs g;
-    std::memset(&g, 0, sizeof(g));
-    g.A.base = reinterpret_cast<const uint32_t *>(base);
-    g.A.ld = Cw, g.A.rows_are_pixels = 1;
-    g.A.H = H, g.A.Wd = Wd, g.A.Ho = H, g.A.Wo = Wd, g.A.Cw = Cw, g.A.KH = 3, g.A.KW = 3, g.A.pad = 1, g.A.stride = 1;
-    g.pa.count = 1, g.pa.mode = QNN_PLANE_BIT, g.pa.coef[0] = 1;
-    g.W = W, g.ldw = 9 * Cw, g.pw.count = 1, g.pw.mode = QNN_PLANE_BIT, g.pw.coef[0] = 1;
-    g.epi.T = T, g.epi.flip = flip_complement, g.epi.out_bits = out, g.epi.ldo = ldo;
-    g.M = M, g.N = N, g.K = 9 * (int64_t)C, g.Kw = 9 * Cw;
-    g.class_thr = class_thr, g.class_ld = ld;
-    g.a_delta = (uint32_t)a_delta, g.zero_off = (uint32_t)z_off;
-    g.inv_w = 1.0 / (double)Wd, g.inv_hw = 1.0 / ((double)H * (double)Wd);
-    int sh = 0;
-    while ((1 << sh) < C / 128) ++sh;
-    g.cpt_shift = sh;
-    g.last_steps = (int)ceil_div(g.Kw - (ceil_div(g.Kw, panel::kGroupWords) - 1) * panel::kGroupWords, 8);
-    MfmaConst mc;
-    std::memset(&mc, 0, sizeof(mc));
-    mc.alpha = 1u;  // (the convolution's epilogue compares the sums as they are)
-    const int64_t tiles_m = ceil_div(M, 256), tiles_n = ceil_div(N, 128), total = tiles_m * tiles_n;
-    const int cus = compute_units();
-    const unsigned grid = (unsigned)(total < cus ? total : cus);
-    return QNN_LAUNCH("conv_panel", panel::conv_kernel(), dim3(grid), dim3(panel::kThreads), 0, s, g, mc, (uint32_t)tiles_m,
-                      (uint32_t)tiles_n, (uint32_t)ceil_div(g.Kw, panel::kGroupWords));
-}
-
 // ------------------------------------------------------------------------------------------------ staged kernels
 namespace {
 

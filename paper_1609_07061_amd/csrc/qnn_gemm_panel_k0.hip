@@ -10,15 +10,12 @@ KernelFn find_kernel(bool sign, bool narrow, bool tail) {
     return sign ? gemm_panel_kernel<true, 4> : gemm_panel_kernel<false, 4>;
 }
 
-KernelFn conv_kernel() { return gemm_panel_kernel<true, 2, false, true>; }
-
 namespace {
 // class_thr[cls][n] = floor(e / 2) as a float, clamped to +-2^23 (the sums it is compared with are far smaller), where
 // e = 2 sum_{taps inside for cls} sum_c b[n][tap][c] - (taps inside) C - T[n] = (sum of the filter's weights on the taps
 // inside) - T[n]: the convolution is that sum minus 2 S, S = sum_k p w, so it reaches T[n] iff S <= e / 2; cls bit 0: the pixel is in the first row (the upper taps lie outside), 1: last
 // row, 2: first column, 3: last column.  Entries of filters beyond N are zero.  All layers of a network in one launch:
 // sixteen lanes per filter, lane t < 9 counts the set bits of tap t, then lane c sums the taps that class c keeps.
-// Also clears the line of zeros that the convolutions read for taps outside the image.
 // The first flag_blocks workgroups do another small job of the same moment instead, so that a network's forward pass
 // starts with one launch: the flip flags of its layers as packed words and as inverted bytes (bits[w] bit t =
 // (flip[32 w + t] != 0) for channels below n, flip == nullptr reading as all zero; inv[c] = !flip[c]); workgroup b takes
@@ -41,7 +38,6 @@ __global__ __launch_bounds__(256) void conv_class_thr_kernel(const ConvPrepJobs 
         return;
     }
     const int64_t block = (int64_t)blockIdx.x - flag_blocks;
-    if (block == 0 && threadIdx.x < 64) jobs.zero_line[threadIdx.x] = 0u;
     int j = 0;
     while (j + 1 < jobs.count && block >= jobs.first_block[j + 1]) ++j;
     const int64_t n = (block - jobs.first_block[j]) * 16 + (threadIdx.x >> 4);
@@ -62,7 +58,7 @@ __global__ __launch_bounds__(256) void conv_class_thr_kernel(const ConvPrepJobs 
         if (!outside) sum += pc, ++taps;
     }
     if (n < ld) {
-        int64_t e = n < N ? 2 * sum - taps * (int64_t)Cw * 32 - (int64_t)jobs.T[j][n] : 0;
+        int64_t e = n < N ? 2 * sum - taps * jobs.C[j] - (int64_t)jobs.T[j][n] : 0;
         e >>= 1;  // floor
         e = e < -(1 << 23) ? -(1 << 23) : (e > (1 << 23) ? (1 << 23) : e);
         jobs.out[j][sub * ld + n] = (int32_t)__float_as_uint((float)(int32_t)e);

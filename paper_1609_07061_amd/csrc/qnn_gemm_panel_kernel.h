@@ -65,15 +65,7 @@ __device__ __forceinline__ void phase_groups(std::integer_sequence<int, I...>) {
 // 256 x 256 tiles would leave a large part of the last round of workgroups idle).
 // kTail (WBN = 4; grid = a multiple of 16 workgroups, fewer than there are tiles, and at most half a grid of tiles in the
 // last round): that round's tiles are taken as halves of 128 columns by two workgroups each.
-// kConv (kSign, WBN = 2): the activation rows are the patch rows of a 3 x 3 "same" convolution (pad 1, stride 1) over
-// the plane "value is -1" of a +-1 feature map, channels-last, whole 16-byte pieces of channels per tap (App. A's
-// ConvNet under Alg. 4).  With a = 1 - 2 p inside the image (0 outside) and w = 2 b - 1,
-//   conv = sum_{taps inside} sum_c w  -  2 S,   S = sum_k p w,
-// so the kernel multiplies the bits p as they are (taps outside the image read a line of zeros) with the filters as +-1,
-// and the part that depends on which taps lie inside, a function of the pixel's border class and the filter, sits in
-// the threshold: the epilogue compares S with class_thr[class][n] (see wave_epilogue_conv).  The steps of a tile's
-// last group of k that lie wholly beyond the patch's 9 C bits are not multiplied (g.last_steps).
-template <bool kSign, int WBN, bool kTail = false, bool kConv = false>
+template <bool kSign, int WBN, bool kTail = false>
 __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs g, const MfmaConst mc, uint32_t tiles_m,
                                                                   uint32_t tiles_n, uint32_t ngroups) {
     // Group buffers: activation panel (256 rows) + weight panel (BN rows).  Two take turns; the narrow tile with the
@@ -82,9 +74,8 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
     constexpr int kGroupBytesT = kPanelBytes + 2 * 32 * WBN * kRowBytes;
     constexpr int kBuffers = (kSign && WBN == 2) ? 3 : 2;
     __shared__ __attribute__((aligned(16))) uint8_t lds[kBuffers * kGroupBytesT];
-    __shared__ __attribute__((aligned(16))) uint32_t rw_table[kConv ? 1 : kThreads / 64][kConv ? 4 : WTILE];
-    // (kConv: per wave the thresholds of nine border classes x the wave's 64 filters, three 1 KiB loads' worth)
-    __shared__ __attribute__((aligned(16))) int32_t thr_table[kSign ? kThreads / 64 : 1][kSign ? (kConv ? 12 * 64 : WTILE) : 4];
+    __shared__ __attribute__((aligned(16))) uint32_t rw_table[kThreads / 64][WTILE];
+    __shared__ __attribute__((aligned(16))) int32_t thr_table[kSign ? kThreads / 64 : 1][kSign ? WTILE : 4];
     __shared__ __attribute__((aligned(16))) uint32_t flip_table[kSign ? kThreads / 64 : 1][kSign ? WTILE : 4];
     // int32 epilogue: per wave one 32 x 32 staging block, through which a block is turned from the accumulator layout
     // (a lane = one row) into whole 128-byte lines per row
@@ -132,74 +123,21 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
     const bool has_half = kTail && tail_vb < total_tiles;
     const uint32_t half_col = ((vb0 >> 3) & 1u) * (uint32_t)(32 * WBN);
     static_assert(!kTail || WBN == 4, "halved tiles in the last round: the wide tile only");
-    static_assert(!kConv || (kSign && WBN == 2 && !kTail), "convolution: threshold output, 256 x 128 tiles");
     uint32_t p_vb = vb0, p_G = 0, p_item = 0;
     // kRowRegs (the narrow tile, whose accumulators leave registers free): one offset register per load, and a copy is
     // all a load needs.  Otherwise one register per panel holds the offset of the lane's row in the first 32-row
     // block, a second one the offset in the operand's last row, and a load adds its block's distance and clamps.
     constexpr bool kRowRegs = WBN == 2;
     uint32_t a_off[kRowRegs ? 8 : 1], w_off[kRowRegs ? BNt / 32 : 1], a_max = 0, w_max = 0;
-    // kConv: a_off = byte offset of the pixel's channels, a_yx = its coordinates (y | x << 16); per group: the byte
-    // offset from the pixel to this lane's piece of the group (tap, part of the tap), the tap's ky | kx << 2 (-1 beyond
-    // the ninth tap), and what to add to w_off (the group's offset; for pieces beyond the end of a weight row, minus
-    // the lane's piece offset: the row's first bytes, which meet zeros on the other side)
-    uint32_t a_yx[kConv ? 8 : 1];
-    uint32_t p_tap_off = 0, p_w_add = 0;
-    int p_tap = -1;
     const uint32_t lda_bytes = (uint32_t)g.A.ld * 4u, ldw_bytes = (uint32_t)g.ldw * 4u;
     const uint32_t last_m = (uint32_t)(g.M - 1), last_n = (uint32_t)(g.N - 1);
-    // (y, x) of output pixel m = (b H + y) Wd + x: quotients through double-precision reciprocals (exact to within one,
-    // then corrected), a dozen instructions instead of two integer divisions
-    auto pixel_of = [&](uint32_t m, uint32_t &y, uint32_t &x) __attribute__((always_inline)) {
-        auto div = [](uint32_t a, uint32_t d, double inv, uint32_t &q, uint32_t &r) __attribute__((always_inline)) {
-            q = (uint32_t)((double)a * inv);
-            int32_t rem = (int32_t)(a - q * d);
-            if (rem < 0) --q, rem += (int32_t)d;
-            if (rem >= (int32_t)d) ++q, rem -= (int32_t)d;
-            r = (uint32_t)rem;
-        };
-        const uint32_t hw = (uint32_t)(g.A.H * g.A.Wd);
-        uint32_t b, rem;
-        div(m, hw, g.inv_hw, b, rem);
-        div(rem, (uint32_t)g.A.Wd, g.inv_w, y, x);
-    };
-    // kConv, per group: this lane's piece of the group at the cursor
-    auto p_piece = [&]() __attribute__((always_inline)) {
-        if constexpr (kConv) {
-            const uint32_t tt = opaque(tid);
-            const uint32_t piece = (tt & 7u) ^ ((tt >> 4) & 7u);
-            const uint32_t q = p_G * 8u + piece;               // piece of the row
-            const uint32_t tap = q >> g.cpt_shift, sub = q - (tap << g.cpt_shift);
-            const uint32_t ky = (tap * 11u) >> 5, kx = tap - 3u * ky;  // tap / 3, tap mod 3 (tap < 32)
-            p_tap = tap < 9u ? (int)(ky | (kx << 2)) : -1;
-            p_tap_off = (uint32_t)(((int)ky - 1) * g.A.Wd + ((int)kx - 1)) * lda_bytes + sub * 16u;
-            const bool in_row = q * 16u < (uint32_t)g.Kw * 4u;
-            p_w_add = in_row ? p_G * (uint32_t)kRowBytes : 0u - piece * 16u;
-        }
-    };
     auto p_locate = [&]() __attribute__((always_inline)) {
         uint32_t tm, tn;
         tile_of_block(p_vb, total_tiles, tiles_m, tiles_n, tm, tn);
         const uint32_t tt = opaque(tid);
         const uint32_t pr = tt >> 3;                                  // row within a load's 32-row block
         const uint32_t piece16 = ((tt & 7u) ^ ((tt >> 4) & 7u)) << 4;  // (slot xor (row / 2 mod 8)) * 16 bytes
-        if constexpr (kConv) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                uint32_t m = tm * (uint32_t)BM + (uint32_t)(32 * i) + pr;
-                m = m > last_m ? last_m : m;
-                uint32_t y, x;
-                pixel_of(m, y, x);
-                a_off[i] = m * lda_bytes + g.a_delta;
-                a_yx[i] = y | (x << 16);
-            }
-#pragma unroll
-            for (int i = 0; i < BNt / 32; ++i) {
-                uint32_t n = tn * (uint32_t)BNt + (uint32_t)(32 * i) + pr;
-                n = n > last_n ? last_n : n;
-                w_off[i] = n * ldw_bytes + piece16;
-            }
-        } else if constexpr (kRowRegs) {
+        if constexpr (kRowRegs) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 uint32_t m = tm * (uint32_t)BM + (uint32_t)(32 * i) + pr;
@@ -233,7 +171,6 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
             // (after the last tile the loads are repeated and never used)
             p_locate();
         }
-        p_piece();
     };
     // 16 bytes per lane from base + voff (or base + min(voff + sadd, vmax)) to LDS address lds_addr + 16 * lane.  The
     // address travels in M0; between the write of M0 and the load there has to be an instruction, here the one that
@@ -261,16 +198,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
         for (int h = 0; h < 2; ++h) {
             const int i = 2 * q + h;
             const bool has_w = 32 * i < BNt;
-            if constexpr (kConv) {
-                // the tap's pixel lies inside the image: its channels; otherwise the line of zeros
-                const uint32_t y = a_yx[i] & 0xFFFFu, x = a_yx[i] >> 16;
-                const uint32_t yy = y + ((uint32_t)p_tap & 3u) - 1u, xx = x + (((uint32_t)p_tap >> 2) & 3u) - 1u;
-                // (bitwise: a short-circuit here becomes branches, which cut the phase into pieces)
-                const uint32_t in = (uint32_t)(p_tap >= 0) & (uint32_t)(yy < (uint32_t)g.A.H) & (uint32_t)(xx < (uint32_t)g.A.Wd);
-                const uint32_t there = a_off[i] + p_tap_off;
-                load_to_lds(g.A.base, g.zero_off ^ ((g.zero_off ^ there) & (0u - in)), dst + (uint32_t)(h * 32 * kRowBytes));
-                if (has_w) load_to_lds(g.W, w_off[i % (BNt / 32)] + p_w_add, dst + (uint32_t)(kPanelBytes + h * 32 * kRowBytes));
-            } else if constexpr (kRowRegs) {
+            if constexpr (kRowRegs) {
                 load_to_lds(a_base, a_off[i], dst + (uint32_t)(h * 32 * kRowBytes));
                 if (has_w) load_to_lds(w_base, w_off[i % (BNt / 32)], dst + (uint32_t)(kPanelBytes + h * 32 * kRowBytes));
             } else {
@@ -301,7 +229,6 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
     // ------------------------------------------------------------------------------------------------ prologue
     // the first groups into the buffers; the cursor stays at the last of them
     p_locate();
-    p_piece();
 #pragma unroll 1
     for (int b = 0; b < kBuffers; ++b) {
         if (b > 0) p_advance();
@@ -368,10 +295,6 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
     // so for t = 0, 1, 2 one AND per word makes the operand and the block scale of the instruction (2, 1, 1/2 on
     // both sides: exact powers of two) turns every product of two set bits into 1; bit 3 is the sign and is moved to
     // bit 1 first.  20 vector-ALU instructions per 128 elements instead of 28 with shift-and-mask throughout.
-    // kConv: the filters enter as +-1 instead of 0 / 1 (a set bit is +1), so that the sum over k of p w is the whole
-    // data-dependent part of the convolution and no row sums are needed: with bit t of a nibble moved to bit 3, every
-    // nibble becomes 0b0010 (1.0) with the sign bit set where the filter bit is clear; block scale 1 in all phases.
-    auto plus_minus_one = [](uint32_t x) __attribute__((always_inline)) { return (x & 0x22222222u) | (~x & 0xAAAAAAAAu); };
     auto expand = [&](const Step &c, const int tt, Frags &f) __attribute__((always_inline)) {
         const uint32_t mask = tt == 0 ? 0x11111111u : (tt == 2 ? 0x44444444u : 0x22222222u);
 #pragma unroll
@@ -383,10 +306,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
         for (int b = 0; b < WI; ++b) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if constexpr (kConv)
-                    f.w[b][j] = (int)plus_minus_one(word_of(c.W[b], j) << (3 - tt));
-                else
-                    f.w[b][j] = (int)(word_of(c.W[b], j) & mask);
+                f.w[b][j] = (int)(word_of(c.W[b], j) & mask);
             }
         }
     };
@@ -403,13 +323,11 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if ((b * 4 + j) % 3 == part) sh.a[b][j] = word_of(c.A[b], j) >> 2;
-        if constexpr (!kConv) {
 #pragma unroll
-            for (int b = 0; b < WI; ++b)
+        for (int b = 0; b < WI; ++b)
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if ((WB * 4 + b * 4 + j) % 3 == part) sh.w[b][j] = word_of(c.W[b], j) >> 2;
-        }
+            for (int j = 0; j < 4; ++j)
+                if ((WB * 4 + b * 4 + j) % 3 == part) sh.w[b][j] = word_of(c.W[b], j) >> 2;
     };
     auto expand_shifted = [&](const Step &c, const Shifted &sh, Frags &f) __attribute__((always_inline)) {
 #pragma unroll
@@ -421,10 +339,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
         for (int b = 0; b < WI; ++b) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if constexpr (kConv)
-                    f.w[b][j] = (int)plus_minus_one(word_of(c.W[b], j));
-                else
-                    f.w[b][j] = (int)(sh.w[b][j] & 0x22222222u);
+                f.w[b][j] = (int)(sh.w[b][j] & 0x22222222u);
             }
         }
     };
@@ -432,7 +347,6 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
     // alone, the compiler keeps the counts of a whole loop trip in registers of their own and adds them up at the end
     // (three-operand adds), which costs over a hundred registers and spills the sums themselves.
     auto count = [&](const Step &c, const int tt) __attribute__((always_inline)) {
-        if constexpr (kConv) return;  // (the convolution's epilogue needs no row sums)
 #pragma unroll
         for (int b = 0; b < WB; ++b) {
             ra[b] += (int32_t)__builtin_popcount(word_of(c.A[b], tt));
@@ -446,14 +360,13 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
     };
     // block scales of the four phases as E8M0 bytes (2^(e - 127)): 2, 1, 1/2, 1
     const int scales = 0x7F7E7F80;
-    const int scales_w = kConv ? 0x7F7F7F7F : scales;
     auto multiply = [&](const Frags &f, auto t_tag) __attribute__((always_inline)) {
         constexpr int tt = decltype(t_tag)::value;
 #pragma unroll
         for (int i = 0; i < WI; ++i)
 #pragma unroll
             for (int j = 0; j < WB; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen(f.w[i]), widen(f.a[j]), acc[i][j], 4, 4, tt, scales_w, tt, scales);
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen(f.w[i]), widen(f.a[j]), acc[i][j], 4, 4, tt, scales, tt, scales);
     };
     // One step = four phases; each phase multiplies the operands made during the previous one and meanwhile counts
     // one word per row and makes the next phase's operands.  `issue_fetch` (the LDS reads of the following step) runs
@@ -498,18 +411,13 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
 
     // thresholds / flip flags of the tile being finished, straight into this wave's LDS tables
     auto load_thresholds = [&](const int64_t n_wave) __attribute__((always_inline)) {
-        if constexpr (kConv)
-            load_class_thresholds_to_lds(g, n_wave, thr_table[wave], flip_table[wave]);
-        else if constexpr (kSign)
+        if constexpr (kSign)
             load_thresholds_to_lds<WI>(g, n_wave, thr_table[wave], flip_table[wave]);
     };
 
     auto finish = [&](const int64_t m_wave, const int64_t n_wave) __attribute__((always_inline)) {
-        if constexpr (kConv)
-            wave_epilogue_conv<WI, kLoadsPerGroup>(g, acc, thr_table[wave], flip_table[wave], m_wave, n_wave, pixel_of);
-        else
-            wave_finish<kSign, WI, kLoadsPerGroup>(g, mc, acc, ra, rw, rw_table[kConv ? 0 : wave], thr_table[wave], flip_table[wave],
-                                                   stage[wave], m_wave, n_wave);
+        wave_finish<kSign, WI, kLoadsPerGroup>(g, mc, acc, ra, rw, rw_table[wave], thr_table[wave], flip_table[wave], stage[wave], m_wave,
+                                               n_wave);
     };
 
     Step buf0, buf1;
@@ -543,52 +451,8 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
             compute(buf1, buf0, frags, [&]() __attribute__((always_inline)) { fetch(0, other, buf0); }, produce, last_tag);
             rd = other;
         };
-        // kConv: the patch's 9 C bits end inside the tile's last group; its steps that hold padding alone are left
-        // out (the loads stay as they are).  A step consumes buf0 and fetches into buf1 or the other way round, and
-        // the next tile expects its first step in buf0.
-        auto short_group = [&](auto steps_tag) __attribute__((always_inline)) {
-            constexpr int kSteps = decltype(steps_tag)::value;
-            const uint32_t other = rd + kGroupBytesT == kBuffers * kGroupBytesT ? 0u : rd + (uint32_t)kGroupBytesT;
-            p_advance();
-            if constexpr (kSteps == 1) {
-                panel_barrier();
-                compute(buf0, buf1, frags, [&]() __attribute__((always_inline)) { fetch(0, other, buf1); }, produce, std::true_type{});
-                buf0 = buf1;
-            } else if constexpr (kSteps == 2) {
-                compute(buf0, buf1, frags, [&]() __attribute__((always_inline)) { fetch(1, rd, buf1); }, no_produce, std::false_type{});
-                panel_barrier();
-                compute(buf1, buf0, frags, [&]() __attribute__((always_inline)) { fetch(0, other, buf0); }, produce, std::true_type{});
-            } else {
-                compute(buf0, buf1, frags, [&]() __attribute__((always_inline)) { fetch(1, rd, buf1); }, no_produce, std::false_type{});
-                compute(buf1, buf0, frags, [&]() __attribute__((always_inline)) { fetch(2, rd, buf0); }, no_produce, std::false_type{});
-                panel_barrier();
-                compute(buf0, buf1, frags, [&]() __attribute__((always_inline)) { fetch(0, other, buf1); }, produce, std::true_type{});
-                buf0 = buf1;
-            }
-            rd = other;
-        };
         for (uint32_t G = 0; G + 1 < ngroups; ++G) group(std::false_type{});
-        if constexpr (kConv) {
-            if (g.last_steps == 1)
-                short_group(std::integral_constant<int, 1>{});
-            else if (g.last_steps == 2)
-                short_group(std::integral_constant<int, 2>{});
-            else if (g.last_steps == 3)
-                short_group(std::integral_constant<int, 3>{});
-            else
-                group(std::true_type{});
-        } else {
-            group(std::true_type{});
-        }
-        // The sums are pinned here: otherwise the compiler moves the last group's matrix-core instructions down into the
-        // epilogue's blocks (their only users), one dependent chain per accumulator block behind that block's store,
-        // and keeps the whole group's operands in registers until then.
-        if constexpr (kConv) {
-#pragma unroll
-            for (int i = 0; i < WI; ++i)
-#pragma unroll
-                for (int j = 0; j < WB; ++j) asm volatile("" : "+a"(acc[i][j]));
-        }
+        group(std::true_type{});
         finish(m_wave, n_wave);
         expand(buf0, 0, frags);
     }
@@ -603,7 +467,6 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_kernel(const GemmArgs 
 typedef void (*KernelFn)(const GemmArgs, const MfmaConst, uint32_t, uint32_t, uint32_t);
 // narrow: the 256 x 128 workgroup tile; tail: the wide tile with the last round's tiles taken as halves by two workgroups each
 KernelFn find_kernel(bool sign, bool narrow, bool tail);
-KernelFn conv_kernel();  // the convolution variant (threshold output, 256 x 128 tiles)
 
 }  // namespace panel
 }  // namespace qnn

@@ -44,6 +44,7 @@ struct SliceArgs {
     uint32_t row_words;    // words of a row (pixels: of a tap) = Kw (Cw)
     uint32_t ppt, taps;    // pixels: 16-byte pieces per tap, taps
     uint32_t magic_ppt, magic_kw;  // ceil(2^32 / .)
+    uint32_t inv_hw, inv_w;        // pixels: floor(2^32 / .) of the output map's pixels and width (2^32 - 1 for 1)
     uint32_t alpha, c0;  // C = alpha (S - row corrections) + c0
     int corrected;       // some digit has an offset: row sums are taken
     int modified;        // some digit has an inverted or an absent plane
@@ -138,10 +139,17 @@ __device__ __forceinline__ u32x4 load_piece(const uint8_t *p, const SliceArgs &s
 struct Patch {
     uint32_t off, in;
 };
+// a / d and the remainder for a < 2^31 (the product with floor(2^32 / d) falls short by less than one)
+__device__ __forceinline__ uint32_t quotient(const uint32_t a, const uint32_t d, const uint32_t inv, uint32_t &rem) {
+    uint32_t q = __umulhi(a, inv);
+    rem = a - q * d;
+    if (rem >= d) ++q, rem -= d;
+    return q;
+}
 __device__ __forceinline__ Patch patch_of(const GemmArgs &g, const SliceArgs &sc, const uint32_t m) {
     const uint32_t per = (uint32_t)(g.A.Ho * g.A.Wo);
-    const uint32_t img = m / per, rem = m - img * per;
-    const uint32_t yo = rem / (uint32_t)g.A.Wo, xo = rem - yo * (uint32_t)g.A.Wo;
+    uint32_t rem, xo;
+    const uint32_t img = quotient(m, per, sc.inv_hw, rem), yo = quotient(rem, (uint32_t)g.A.Wo, sc.inv_w, xo);
     const int y = (int)yo * g.A.stride - g.A.pad, x = (int)xo * g.A.stride - g.A.pad;
     auto inside = [](const int first, const int taps, const int size) {  // taps t with 0 <= first + t < size
         const int lo = first < 0 ? (-first < 16 ? -first : 16) : 0, end = size - first;

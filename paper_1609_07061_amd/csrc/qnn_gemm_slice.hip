@@ -316,6 +316,11 @@ bool slice_args(const GemmArgs &g, bool bits, SliceArgs &sc, int &kind_a, int &k
     sc.row_words = (uint32_t)row_words, sc.ppt = (uint32_t)ppt, sc.taps = (uint32_t)taps;
     sc.magic_ppt = ppt > 1 ? magic(ppt) : 0u, sc.magic_kw = pix && g.A.KW > 1 ? magic(g.A.KW) : 0u;
     sc.chunks = (uint32_t)ceil_div(pieces, 2);
+    if (pix) {
+        auto inverse = [](int64_t v) { return v > 1 ? (uint32_t)(4294967296LL / v) : 0xFFFFFFFFu; };
+        if ((int64_t)g.A.Ho * g.A.Wo > 0x7FFFFFFFLL) return false;
+        sc.inv_hw = inverse((int64_t)g.A.Ho * g.A.Wo), sc.inv_w = inverse(g.A.Wo);
+    }
     // exact float sums: |S| in units of the common factors stays below 2^24 (2^23, as the common factor itself: 24-bit products)
     if ((long double)sa * (long double)sw * 256.0L * sc.chunks >= 8388608.0L) return false;
     if (ga * gw >= 8388608 || ga * gw <= -8388608) return false;

@@ -24,8 +24,20 @@ constexpr int kTile = 128;
 constexpr int kPlaneBytes = kTile * 128;  // a group of one plane of an operand
 constexpr int kStagePitch = 68;           // floats per row of the epilogue's block: 64 and a gap
 
-template <int kA, int kW, int kRows>
-__global__ __launch_bounds__(kTileThreads, kA == kOne && kW == kOne ? 3 : 2) void gemm_tile_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
+// (a wave's LDS operations execute in order: only the compiler has to be kept from reordering them)
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// kMap (3 x 3 "same" convolutions of +-1 maps, pad 1, stride 1, threshold output): the left operand is the map's plane "value is -1"
+// (0 outside the image), the filters enter as +-1.  With a = 1 - 2 p inside the image, conv = sum_{taps inside} sum_c w - 2 S,
+// S = sum_k p w, so a pixel's bit is (S > class_thr[class][n]) xor flip[n], class = which of the image's borders the pixel lies on
+// (see conv_class_thr_kernel).  A lane keeps a filter, so the class is one for the whole wave and row, and the 2 x 2 max-pooling
+// that may follow (OR of the four bits where the threshold does not flip, AND where it does) is three exchanges of packed words.
+template <int kA, int kW, int kRows, bool kMap = false>
+__global__ __launch_bounds__(kTileThreads, kA == kOne && kW != kPair ? 3 : 2) void gemm_tile_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
     constexpr bool kPixels = kRows != kMatrix;
     constexpr int NA = kA == kPair ? 2 : 1, NW = kW == kPair ? 2 : 1;  // planes of a digit
     constexpr int kOperandBytes = (NA + NW) * kPlaneBytes, kEpiBytes = 4 * 32 * kStagePitch * 4;
@@ -36,6 +48,17 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW == kOne ? 3 : 2) voi
     uint32_t tm, tn;
     tile_of_block(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
     const uint32_t m0 = tm * kTile, n0 = tn * kTile;
+    // kMap: thresholds of nine border classes (row class 0 = interior, 1 = first row, 2 = last row; column class likewise; 3 row +
+    // column) for the wave's 64 filters.  The table in memory is indexed by four bits (first row, last row, first column, last).
+    __shared__ float thr_tab[kMap ? 4 : 1][kMap ? 9 * 64 : 1];
+    if constexpr (kMap) {
+#pragma unroll
+        for (uint32_t c9 = 0; c9 < 9; ++c9) {
+            const uint32_t rc = c9 / 3, cc = c9 % 3;
+            const uint32_t c16 = (rc == 1 ? 1u : 0u) | (rc == 2 ? 2u : 0u) | (cc == 1 ? 4u : 0u) | (cc == 2 ? 8u : 0u);
+            thr_tab[wave][64 * c9 + lane] = __int_as_float(g.class_thr[c16 * (uint32_t)g.class_ld + n0 + 64u * wn + lane]);
+        }
+    }
 
     // ------------------------------------------------------------------------------------------------ loads
     // load i of a plane: rows 32 i + 8 wave + lane / 8, piece lane mod 8 of the group
@@ -95,7 +118,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW == kOne ? 3 : 2) voi
                 }
             }
         }
-        if (kPixels ? sc.ragged : tail) {
+        if (kPixels ? (kRows == kPatches && sc.ragged) : tail) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const uint32_t keep = (uint32_t)e >= x.skip ? 0xFFFFFFFFu : 0u;
@@ -106,7 +129,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW == kOne ? 3 : 2) voi
                 }
             }
         }
-        if (sc.clear_w && (kPixels || tail)) {
+        if (!kMap && sc.clear_w && (kPixels || tail)) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const uint32_t keep = (uint32_t)e >= x.skip ? 0xFFFFFFFFu : 0u;
@@ -117,7 +140,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW == kOne ? 3 : 2) voi
                 }
             }
         }
-        if (sc.modified) {
+        if (!kMap && sc.modified) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 apply_inversion<kA>(da.inv0, da.inv1, da.use1, x.a[0][i], x.a[NA - 1][i]);
@@ -125,7 +148,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW == kOne ? 3 : 2) voi
             }
         }
         // (pieces beyond the last chunk are not multiplied: they count only where they are zero)
-        if (!sc.modified || 8u * G + piece0 < 2u * sc.chunks) {
+        if (!kMap && (!sc.modified || 8u * G + piece0 < 2u * sc.chunks)) {
             if (sc.sum_a) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) sum_a[i] = add_sum<kA>(x.a[0][i], x.a[NA - 1][i], sum_a[i]);
@@ -211,7 +234,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW == kOne ? 3 : 2) voi
         __syncthreads();
         const uint32_t left = sc.chunks - 4u * G;
         const bool pair_ends = G + 1u == groups;
-        if (pair_ends && sc.corrected) {  // weigh the row sums of this pair
+        if (!kMap && pair_ends && sc.corrected) {  // weigh the row sums of this pair
             const int shift = sc.a.d[ia].lg + sc.w.d[iw].lg;
             const int a_fac = (sc.w.d[iw].offset2 << shift) >> 1, w_fac = (sc.a.d[ia].offset2 << shift) >> 1;
 #pragma unroll
@@ -232,6 +255,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW == kOne ? 3 : 2) voi
 
     // ------------------------------------------------------------------------------------------------ epilogue
     // register v of block [i][j] is C[m][n], m = 32 j + lane mod 32, n = 32 i + 8 (v / 4) + 4 kg + v mod 4 of the wave's tile
+    if constexpr (!kMap) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         if (sc.corrected) {
@@ -242,12 +266,79 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW == kOne ? 3 : 2) voi
         if (piece0 == 0)
             corr_a[32 * i + prow] = (int)((uint32_t)corr_a4[i] * sc.alpha), corr_w[32 * i + prow] = (int)((uint32_t)corr_w4[i] * sc.alpha - sc.c0);
     }
+    }
     __syncthreads();
     float *const stage = reinterpret_cast<float *>(lds) + wave * (32 * kStagePitch);
     const int alpha = (int)sc.alpha;  // (sums and alpha are below 2^23 in magnitude: a 24-bit product, full rate)
     auto times_alpha = [alpha](const float s) __attribute__((always_inline)) { return __mul24((int)s, alpha); };
     const int64_t n_wave = (int64_t)n0 + 64 * wn;
     const bool vec = (g.epi.ldc % 4 == 0) && (reinterpret_cast<uintptr_t>(g.epi.C) % 16 == 0);
+    if constexpr (kMap) {
+        const int64_t n = n_wave + lane;
+        const unsigned long long live = __ballot(n < g.N), flips = __ballot(n < g.N && g.epi.flip && g.epi.flip[n] != 0);
+        const uint32_t m_wave = __builtin_amdgcn_readfirstlane(m0 + 64u * wm);
+        // where the thresholds of the pixel m_wave + lane begin in the table
+        uint32_t row0, x, y, img_rem;
+        const uint32_t m_lane = m_wave + lane;
+        (void)quotient(m_lane, (uint32_t)(g.A.H * g.A.Wd), sc.inv_hw, img_rem);
+        y = quotient(img_rem, (uint32_t)g.A.Wd, sc.inv_w, x);
+        const uint32_t c9 = 3u * (y == 0u ? 1u : (y + 1u == (uint32_t)g.A.H ? 2u : 0u)) + (x == 0u ? 1u : (x + 1u == (uint32_t)g.A.Wd ? 2u : 0u));
+        const int row_thr = (int)(64u * c9);
+        row0 = quotient(m_wave, (uint32_t)g.A.Wd, sc.inv_w, x);  // row of the first pixel, over all images
+        uint32_t word[2];  // lane 2 s + h: word h of pixel 32 j + s
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                    *reinterpret_cast<f32x4 *>(&stage[r * kStagePitch + 32 * i + 8 * q + 4 * kg]) = v;
+                }
+            wave_lds_fence();
+            uint32_t mine = 0;
+#pragma unroll
+            for (int s = 0; s < 32; ++s) {
+                const uint32_t first = (uint32_t)__builtin_amdgcn_readlane(row_thr, 32 * j + s);
+                const unsigned long long bits = (__ballot(stage[s * kStagePitch + lane] > thr_tab[wave][first + lane]) ^ flips) & live;
+                asm("v_writelane_b32 %0, %1, %2" : "+v"(mine) : "s"((uint32_t)bits), "n"(2 * s));
+                asm("v_writelane_b32 %0, %1, %2" : "+v"(mine) : "s"((uint32_t)(bits >> 32)), "n"(2 * s + 1));
+            }
+            word[j] = mine;
+            wave_lds_fence();
+        }
+        const int64_t n_word = n_wave + 32 * (lane & 1u);
+        if (n_word >= g.N) return;
+        if (!g.pool_and) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int64_t m = (int64_t)m_wave + 32 * j + (lane >> 1);
+                if (m < g.M) g.epi.out_bits[m * g.epi.ldo + n_word / 32] = word[j];
+            }
+            return;
+        }
+        // 2 x 2 max-pooling of whole row pairs (maps 8, 16 or 32 pixels wide with an even height: the 64 pixels are 8, 4 or 2
+        // rows, the first of them even)
+        const uint32_t mask = g.pool_and[n_word / 32] ^ g.pool_invert;
+        auto merge = [mask](const uint32_t a, const uint32_t b) { return ((a | b) & ~mask) | (a & b & mask); };
+        const uint32_t below = g.A.Wd == 16 ? 32u : 16u;  // lanes between a pixel and the one below it (8 or 16 wide)
+        uint32_t pooled[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            uint32_t v = g.A.Wd == 32 ? merge(word[0], word[1]) : merge(word[j], (uint32_t)__shfl_xor((int)word[j], (int)below, 64));
+            pooled[j] = merge(v, (uint32_t)__shfl_xor((int)v, 2, 64));
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const uint32_t s = 32u * j + (lane >> 1), sy = s / (uint32_t)g.A.Wd, sx = s - sy * (uint32_t)g.A.Wd;
+            const int64_t m = (int64_t)m_wave + s;
+            if (m < g.M && ((sy | sx) & 1u) == 0u) {
+                const int64_t row = (int64_t)row0 + sy;  // (over all images: their heights are even)
+                g.epi.out_bits[(row / 2 * (g.A.Wd / 2) + sx / 2) * g.epi.ldo + n_word / 32] = pooled[j];
+            }
+        }
+        return;
+    }
     int32_t T = 0;
     bool live = false, flip = false;
     if (g.epi.T) {
@@ -265,10 +356,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW == kOne ? 3 : 2) voi
                 f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
                 *reinterpret_cast<f32x4 *>(&stage[r * kStagePitch + 32 * i + 8 * q + 4 * kg]) = v;
             }
-        // (a wave's LDS operations execute in order: only the compiler has to be kept from reordering them)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_fence();
         if (!g.epi.T) {
             if (vec && n_wave + 64 <= g.N) {
                 const i32x4 cw4 = *reinterpret_cast<const i32x4 *>(&corr_w[64 * wn + 4 * (lane & 15u)]);
@@ -314,9 +402,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW == kOne ? 3 : 2) voi
             const int64_t m = m_blk + (lane >> 1), n = n_wave + 32 * (lane & 1u);
             if (m < g.M && n < g.N) g.epi.out_bits[m * g.epi.ldo + n / 32] = mine;
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_fence();
     }
 }
 
@@ -337,6 +423,49 @@ int launch_gemm_tile(const GemmArgs &g, hipStream_t s) {
     if (tiles_m * tiles_n > 0x7FFFFFFFLL) return fail(QNN_ERR_SHAPE, "gemm: too many tiles");
     const TileFn fn = !g.A.rows_are_pixels ? tile_kernel<kMatrix>(ka, kw) : (g.A.Cw < 4 ? tile_kernel<kNarrowPatches>(ka, kw) : tile_kernel<kPatches>(ka, kw));
     return QNN_LAUNCH("gemm_tile", fn, dim3((unsigned)(tiles_m * tiles_n)), dim3(kTileThreads), 0, s, g, sc, (uint32_t)tiles_m, (uint32_t)tiles_n);
+}
+
+// ---------------------------------------------------------------------------------------------------- convolution of a +-1 map
+bool conv_map_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N) {
+    // (at least two rows and columns: a pixel is then in one of three row classes and one of three column classes)
+    if (B < 1 || H < 2 || Wd < 2 || H > 32767 || Wd > 32767 || C < 1 || N < 1) return false;
+    const int64_t M = B * H * Wd, Cw = words_for(C);
+    if (M > 0x7FFFFF00LL || N > 0x7FFFFF00LL || 9 * ceil_div(Cw, 4) >= 32768) return false;
+    if (16 * conv_class_ld(N) >= (1 << 28)) return false;  // 32-bit offsets into the class table
+    if ((long double)M * Cw * 4 >= 4294967296.0L || (long double)N * 9 * Cw * 4 >= 4294967296.0L) return false;
+    return 9 * Cw * 32 < 8388608 && ceil_div(M, kTile) * ceil_div(N, kTile) <= 0x7FFFFFFFLL;
+}
+
+// From 48 tiles on: the App. A ConvNet of width 128 on 4, 16, 64, 256 images of 32 x 32 takes 57, 74, 83, 140 us with the line at 48
+// tiles, 77, 78, 84, 143 with every convolution on its map's plane, 58, 86, 137, 209 with none (other widths and sizes alike).
+bool conv_map_preferred(int64_t B, int64_t H, int64_t Wd, int64_t N) { return ceil_div(B * H * Wd, kTile) * ceil_div(N, kTile) >= 48; }
+
+int64_t conv_class_ld(int64_t N) { return ceil_div(N, kTile) * kTile; }
+
+bool conv_map_pools(int64_t H, int64_t Wd) { return H % 2 == 0 && (Wd == 8 || Wd == 16 || Wd == 32); }
+
+int launch_conv_map(const uint32_t *plane, int64_t B, int H, int Wd, int64_t C, const uint32_t *W, int64_t N, const uint8_t *flip_complement,
+                    uint32_t *out, int64_t ldo, const int32_t *class_thr, const uint32_t *pool_and, bool pool_invert, hipStream_t s) {
+    if (!conv_map_supports(B, H, Wd, C, N)) return fail(QNN_ERR_UNSUPPORTED, "convolution of a +-1 map: shape not supported");
+    GemmArgs g;
+    std::memset(&g, 0, sizeof(g));
+    const int64_t Cw = words_for(C);
+    g.A.base = plane, g.A.rows_are_pixels = 1;
+    g.A.H = H, g.A.Wd = Wd, g.A.Ho = H, g.A.Wo = Wd, g.A.Cw = (int)Cw, g.A.KH = 3, g.A.KW = 3, g.A.pad = 1, g.A.stride = 1;
+    g.pa.count = 1, g.pa.mode = QNN_PLANE_BIT, g.pa.coef[0] = 1;
+    g.pw.count = 1, g.pw.mode = QNN_PLANE_BIT, g.pw.coef[0] = 1;
+    g.W = W, g.ldw = g.Kw = 9 * Cw;
+    g.epi.flip = flip_complement, g.epi.out_bits = out, g.epi.ldo = ldo;
+    g.M = B * H * Wd, g.N = N, g.K = 9 * C;
+    g.class_thr = class_thr, g.class_ld = conv_class_ld(N);
+    g.pool_and = pool_and, g.pool_invert = pool_invert ? 0xFFFFFFFFu : 0u;
+    SliceArgs sc;
+    int ka, kw;
+    if (!slice_args(g, true, sc, ka, kw)) return fail(QNN_ERR_UNSUPPORTED, "convolution of a +-1 map: shape not supported");
+    sc.w.d[0].scale = 127 * 0x01010101;  // the filters' words as +-1 operands (kPm1)
+    const int64_t tiles_m = ceil_div(g.M, kTile), tiles_n = ceil_div(g.N, kTile);
+    const TileFn fn = Cw < 4 ? gemm_tile_kernel<kOne, kPm1, kNarrowPatches, true> : gemm_tile_kernel<kOne, kPm1, kPatches, true>;
+    return QNN_LAUNCH("conv_map", fn, dim3((unsigned)(tiles_m * tiles_n)), dim3(kTileThreads), 0, s, g, sc, (uint32_t)tiles_m, (uint32_t)tiles_n);
 }
 
 }  // namespace qnn

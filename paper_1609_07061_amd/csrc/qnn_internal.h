@@ -78,18 +78,12 @@ struct GemmArgs {
     const int32_t *rw_scaled;
     // Optional, with operands of int8 values only: sums of the left operand's rows (the epilogue's term cRA * sum)
     const int32_t *row_sums;
-    // Only for the convolution on the panel-fed FP4 kernel (panel::gemm_panel_kernel<true, 2, false, true>): A.base is
-    // the lower of {the plane "value is -1" of a +-1 map, a 16-byte line of zeros}; a_delta / zero_off are the byte
-    // offsets of the two from it; class_thr[cls * class_ld + n] is the threshold of filter n for a pixel of border class
-    // cls (bit 0: first row, 1: last row, 2: first column, 3: last column); inv_w = 1 / Wd and inv_hw = 1 / (H Wd) for
-    // the pixel coordinates; cpt_shift = log2(16-byte pieces per tap); last_steps = how many of the four 256-bit steps of
-    // a tile's last group of k hold bits of the patch (the others are padding and are not multiplied).
+    // Only for convolutions of +-1 maps on the tiled FP4 kernel: class_thr[cls * class_ld + n] is the threshold of filter n for a pixel
+    // of border class cls (bit 0: first row, 1: last row, 2: first column, 3: last column).
     const int32_t *class_thr;
     int64_t class_ld;
-    uint32_t a_delta, zero_off;
-    double inv_w, inv_hw;
-    int cpt_shift;
-    int last_steps;
+    const uint32_t *pool_and;  // tiled kernel on a +-1 map: 2 x 2 max-pooling follows; packed flags of the filters whose bits are AND-ed
+    uint32_t pool_invert;      // ... inverted with this
 };
 
 // Tile index with consecutive ids of one XCD (ids congruent mod 8 share an L2) laid on neighbouring tiles, and tiles
@@ -164,19 +158,17 @@ int launch_pack_bitplanes(const uint8_t *v, int64_t rows, int64_t K, int64_t ldv
 int launch_threshold_sign(const int32_t *C, int64_t ldc, int64_t M, int64_t N, const int32_t *T, const uint8_t *flip,
                           uint32_t *out, int64_t ldo, hipStream_t s);
 
-// 3 x 3 "same" convolution of a +-1 feature map (held as its plane "value is -1", [B][H][Wd][C / 32] words, C a
-// multiple of 128 with C / 128 a power of two) with +-1 filters and threshold output, on the panel-fed FP4 kernel.
-// bit = (conv >= T[n]) xor !flip_complement[n]: the caller passes the COMPLEMENT of its flip flags.  class_thr
-// (16 x conv_panel_class_ld(N) int32) and zero_line (256 bytes) are written beforehand, on the same stream, by
-// panel::launch_conv_class_thr (one launch for all convolutions of a network); zero_line and the plane must lie within
-// 4 GiB of each other.
-bool conv_panel_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N);
-// whether it is faster than the map's 2-bit code on the kernels for products of any size
-bool conv_panel_preferred(int64_t B, int64_t H, int64_t Wd, int64_t N);
-int64_t conv_panel_class_ld(int64_t N);
-int launch_conv_panel(const uint32_t *plane, int64_t B, int H, int Wd, int C, const uint32_t *W, int64_t N, const int32_t *T,
-                      const uint8_t *flip_complement, uint32_t *out, int64_t ldo, const int32_t *class_thr,
-                      const uint32_t *zero_line, hipStream_t s);
+// 3 x 3 "same" convolution of a +-1 feature map (held as its plane "value is -1", [B][H][Wd][ceil(C / 32)] words) with +-1 filters
+// and threshold output, on the tiled FP4 kernel.  bit = (conv >= T[n]) xor !flip_complement[n]: the caller passes the COMPLEMENT of
+// its flip flags.  class_thr (16 x conv_class_ld(N) words) is written beforehand, on the same stream, by
+// panel::launch_conv_class_thr (one launch for all convolutions of a network).  The 2 x 2 max-pooling that follows is done along if
+// conv_map_pools (pool_and = packed flip flags of the filters, pool_invert = the map holds inverted bits; null: no pooling).
+bool conv_map_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N);
+bool conv_map_preferred(int64_t B, int64_t H, int64_t Wd, int64_t N);  // against the map's 2-bit code
+bool conv_map_pools(int64_t H, int64_t Wd);
+int64_t conv_class_ld(int64_t N);
+int launch_conv_map(const uint32_t *plane, int64_t B, int H, int Wd, int64_t C, const uint32_t *W, int64_t N, const uint8_t *flip_complement,
+                    uint32_t *out, int64_t ldo, const int32_t *class_thr, const uint32_t *pool_and, bool pool_invert, hipStream_t s);
 struct ConvPrepJobs {
     int count;
     const uint32_t *W[2 * QNN_MAX_LAYERS];  // [N][9][Cw] filter bits
@@ -184,8 +176,8 @@ struct ConvPrepJobs {
     int32_t *out[2 * QNN_MAX_LAYERS];       // [16][ld]
     int64_t N[2 * QNN_MAX_LAYERS], ld[2 * QNN_MAX_LAYERS];
     int Cw[2 * QNN_MAX_LAYERS];
+    int64_t C[2 * QNN_MAX_LAYERS];          // channels
     int64_t first_block[2 * QNN_MAX_LAYERS + 1];  // filled by the launch
-    uint32_t *zero_line;
 };
 struct FlagJobs;
 namespace panel {
