@@ -3,13 +3,20 @@
 //
 // Bound: matrix cores and the vector instructions that make their operands, about one for one.  A workgroup of four waves owns a
 // 128 x 128 tile of C, a wave 64 x 64 of it (2 x 2 blocks: 28 vector instructions per operand block and 256 elements against
-// 512 matrix-core cycles for the four products), two or three workgroups share a compute unit and fill each other's waits.
-//   * Loads: a wave reads eight rows x 128 contiguous bytes per instruction (an instruction whose 64 lanes read 64 rows costs
-//     the address path of the compute unit 64 cycles, this one 16 to 19), 16 bytes per lane at any 4-byte alignment, a group of
-//     1024 elements ahead of the multiplication, into registers.  The last piece of a row is read four words from its end and
-//     the words an earlier piece has brought are cleared, so nothing beyond a row is read.
+// 512 matrix-core cycles for the four products), three workgroups share a compute unit (two where both operands have two planes)
+// and fill each other's waits.
+//   * Loads: a wave reads sixteen rows x 64 contiguous bytes, or eight x 128, per instruction (an instruction whose 64 lanes read
+//     64 rows costs the address path of the compute unit 64 cycles, eight rows 16 to 19), 16 bytes per lane at any 4-byte
+//     alignment, a group ahead of the multiplication, into registers.  A group is four pieces of a row: of eight, the loads in
+//     flight take the registers of the third workgroup, and that costs more than half as many barriers give (GPU time, eight ->
+//     four pieces: 2-bit convolution 256 x 13 x 13, 384 -> 256 channels, 34.1 -> 27.8 us, 4-bit 54.3 -> 46.3; products
+//     3000 x 4096 x 3000 23.8 -> 21.9).  It is eight where that brings no third workgroup or takes none away: matrices of
+//     two planes a digit on both sides (1000 x 4096 x 2048 of 4 bits: 30.4 us against 32.8 with four) and convolutions of +-1 maps.
+//     The last piece of a row is read four words from its end and the words an earlier piece has brought are cleared, so nothing
+//     beyond a row is read.
 //   * The words go to LDS once per workgroup, already cleared and, for two planes of a digit, already interleaved; piece c of row
-//     r sits at piece c xor (r / 2 mod 8), so that writes (eight rows x eight pieces) and reads (32 rows, one piece) use all banks.
+//     r sits at piece c xor (r / 2 mod 8), r / 4 mod 4 in groups of four, so that writes (whole rows of a group) and reads (32
+//     rows, one piece) use all banks.
 //   * Epilogue through LDS: a 32 x 64 block per wave at a time, so that C leaves as 256-byte pieces of rows.
 #include "qnn_gemm_slice.h"
 
@@ -21,8 +28,7 @@ namespace {
 
 constexpr int kTileThreads = 256;
 constexpr int kTile = 128;
-constexpr int kPlaneBytes = kTile * 128;  // a group of one plane of an operand
-constexpr int kStagePitch = 68;           // floats per row of the epilogue's block: 64 and a gap
+constexpr int kStagePitch = 68;  // floats per row of the epilogue's block: 64 and a gap
 
 // (a wave's LDS operations execute in order: only the compiler has to be kept from reordering them)
 __device__ __forceinline__ void wave_lds_fence() {
@@ -37,9 +43,14 @@ __device__ __forceinline__ void wave_lds_fence() {
 // (see conv_class_thr_kernel).  A lane keeps a filter, so the class is one for the whole wave and row, and the 2 x 2 max-pooling
 // that may follow (OR of the four bits where the threshold does not flip, AND where it does) is three exchanges of packed words.
 template <int kA, int kW, int kRows, bool kMap = false>
-__global__ __launch_bounds__(kTileThreads, kA == kOne && kW != kPair ? 3 : 2) void gemm_tile_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
+__global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) void gemm_tile_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
     constexpr bool kPixels = kRows != kMatrix;
     constexpr int NA = kA == kPair ? 2 : 1, NW = kW == kPair ? 2 : 1;  // planes of a digit
+    // 16-byte pieces of a row per group (two of them make a chunk of 256 elements)
+    constexpr int kPieces = kMap || (kA == kPair && kW == kPair && !kPixels) ? 8 : 4;
+    constexpr int kRowBytes = 16 * kPieces, kPlaneBytes = kTile * kRowBytes;    // a group of one plane of an operand
+    constexpr int kLoads = kPieces / 2, kLoadRows = kTile / kLoads;            // per plane: loads of a wave, rows of a load of the workgroup
+    constexpr uint32_t kSwizzle = kPieces == 8 ? 1 : 2;                        // rows of this power of two share an order of pieces
     constexpr int kOperandBytes = (NA + NW) * kPlaneBytes, kEpiBytes = 4 * 32 * kStagePitch * 4;
     __shared__ __attribute__((aligned(16))) uint8_t lds[kOperandBytes > kEpiBytes ? kOperandBytes : kEpiBytes];
     __shared__ __attribute__((aligned(16))) int corr_a[kTile], corr_w[kTile];  // row corrections (see make_fields)
@@ -61,12 +72,12 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW != kPair ? 3 : 2) vo
     }
 
     // ------------------------------------------------------------------------------------------------ loads
-    // load i of a plane: rows 32 i + 8 wave + lane / 8, piece lane mod 8 of the group
-    const uint32_t prow = 8u * wave + (lane >> 3), piece0 = lane & 7u;
-    uint32_t a_off[4], a_in[4], w_off[4];  // byte offset of the row (pixels: of the patch, see patch_of)
+    // load i of a plane: piece lane mod kPieces of rows kLoadRows i + prow
+    const uint32_t prow = (uint32_t)(64 / kPieces) * wave + lane / kPieces, piece0 = lane % kPieces;
+    uint32_t a_off[kLoads], a_in[kLoads], w_off[kLoads];  // byte offset of the row (pixels: of the patch, see patch_of)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        uint32_t m = m0 + 32 * i + prow;
+    for (int i = 0; i < kLoads; ++i) {
+        uint32_t m = m0 + kLoadRows * i + prow;
         m = m < (uint32_t)g.M ? m : (uint32_t)g.M - 1u;  // (rows beyond the last repeat it and are not stored)
         if constexpr (kPixels) {
             const Patch p = patch_of(g, sc, m);
@@ -74,21 +85,21 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW != kPair ? 3 : 2) vo
         } else {
             a_off[i] = m * (uint32_t)(g.A.ld * 4), a_in[i] = 0u;
         }
-        uint32_t n = n0 + 32 * i + prow;
+        uint32_t n = n0 + kLoadRows * i + prow;
         n = n < (uint32_t)g.N ? n : (uint32_t)g.N - 1u;
         w_off[i] = n * (uint32_t)(g.ldw * 4);
     }
     struct Group {
-        u32x4 a[NA][4], w[NW][4];
+        u32x4 a[NA][kLoads], w[NW][kLoads];
         uint32_t skip, ky, kx;  // leading words to clear; pixels: the tap's row and column
     };
     const uint8_t *const a_base = reinterpret_cast<const uint8_t *>(g.A.base), *const w_base = reinterpret_cast<const uint8_t *>(g.W);
     auto inside = [&](const int i, const uint32_t ky, const uint32_t kx) __attribute__((always_inline)) { return (a_in[i] >> ky) & (a_in[i] >> (kx + 16u)) & 1u; };
     auto load = [&](Group &x, const SliceDigit &da, const SliceDigit &dw, const uint32_t G) __attribute__((always_inline)) {
-        const Piece p = piece_of<kRows>(g, sc, 8u * G + piece0);
+        const Piece p = piece_of<kRows>(g, sc, (uint32_t)kPieces * G + piece0);
         x.skip = p.skip, x.ky = p.ky, x.kx = p.kx;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < kLoads; ++i) {
             uint32_t off = a_off[i] + p.off;
             // outside the image: the plane's first words, cleared below
             if constexpr (kPixels) off = inside(i, p.ky, p.kx) ? off : 0u;
@@ -96,20 +107,20 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW != kPair ? 3 : 2) vo
             if constexpr (kA == kPair) x.a[1][i] = load_piece<kRows>(a_base + da.off1 + off, sc);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < kLoads; ++i) {
             const uint32_t off = w_off[i] + p.w_word * 4u;
             x.w[0][i] = load_piece<kRows>(w_base + dw.off0 + off, sc);
             if constexpr (kW == kPair) x.w[1][i] = load_piece<kRows>(w_base + dw.off1 + off, sc);
         }
     };
-    int sum_a[4] = {0, 0, 0, 0}, sum_w[4] = {0, 0, 0, 0};  // row sums of this lane's pieces, current digit pair
+    int sum_a[kLoads] = {}, sum_w[kLoads] = {};  // row sums of this lane's pieces, current digit pair
     // registers -> LDS: fields of digit planes, plane after plane.  tail: pieces end or start within the group
     auto store = [&](Group &x, const SliceDigit &da, const SliceDigit &dw, const uint32_t G, const bool tail) __attribute__((always_inline)) {
-        const uint32_t at = prow * 128u + ((piece0 ^ ((prow >> 1) & 7u)) << 4);
+        const uint32_t at = prow * (uint32_t)kRowBytes + ((piece0 ^ ((prow >> kSwizzle) & (kPieces - 1u))) << 4);
         // words outside the image, beyond the row's end, or brought by the piece before
         if constexpr (kPixels) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < kLoads; ++i) {
                 const uint32_t in = 0u - inside(i, x.ky, x.kx);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -123,7 +134,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW != kPair ? 3 : 2) vo
             for (int e = 0; e < 4; ++e) {
                 const uint32_t keep = (uint32_t)e >= x.skip ? 0xFFFFFFFFu : 0u;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < kLoads; ++i) {
                     x.a[0][i][e] &= keep;
                     if constexpr (kA == kPair) x.a[1][i][e] &= keep;
                 }
@@ -134,7 +145,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW != kPair ? 3 : 2) vo
             for (int e = 0; e < 4; ++e) {
                 const uint32_t keep = (uint32_t)e >= x.skip ? 0xFFFFFFFFu : 0u;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < kLoads; ++i) {
                     x.w[0][i][e] &= keep;
                     if constexpr (kW == kPair) x.w[1][i][e] &= keep;
                 }
@@ -142,31 +153,31 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW != kPair ? 3 : 2) vo
         }
         if (!kMap && sc.modified) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < kLoads; ++i) {
                 apply_inversion<kA>(da.inv0, da.inv1, da.use1, x.a[0][i], x.a[NA - 1][i]);
                 apply_inversion<kW>(dw.inv0, dw.inv1, dw.use1, x.w[0][i], x.w[NW - 1][i]);
             }
         }
         // (pieces beyond the last chunk are not multiplied: they count only where they are zero)
-        if (!kMap && (!sc.modified || 8u * G + piece0 < 2u * sc.chunks)) {
+        if (!kMap && (!sc.modified || (uint32_t)kPieces * G + piece0 < 2u * sc.chunks)) {
             if (sc.sum_a) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) sum_a[i] = add_sum<kA>(x.a[0][i], x.a[NA - 1][i], sum_a[i]);
+                for (int i = 0; i < kLoads; ++i) sum_a[i] = add_sum<kA>(x.a[0][i], x.a[NA - 1][i], sum_a[i]);
             }
             if (sc.sum_w) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) sum_w[i] = add_sum<kW>(x.w[0][i], x.w[NW - 1][i], sum_w[i]);
+                for (int i = 0; i < kLoads; ++i) sum_w[i] = add_sum<kW>(x.w[0][i], x.w[NW - 1][i], sum_w[i]);
             }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < kLoads; ++i) {
             u32x4 z0, z1;
             make_fields<kA>(x.a[0][i], x.a[NA - 1][i], z0, z1);
-            *reinterpret_cast<u32x4 *>(lds + at + i * 4096) = z0;
-            if constexpr (kA == kPair) *reinterpret_cast<u32x4 *>(lds + kPlaneBytes + at + i * 4096) = z1;
+            *reinterpret_cast<u32x4 *>(lds + at + i * kLoadRows * kRowBytes) = z0;
+            if constexpr (kA == kPair) *reinterpret_cast<u32x4 *>(lds + kPlaneBytes + at + i * kLoadRows * kRowBytes) = z1;
             make_fields<kW>(x.w[0][i], x.w[NW - 1][i], z0, z1);
-            *reinterpret_cast<u32x4 *>(lds + NA * kPlaneBytes + at + i * 4096) = z0;
-            if constexpr (kW == kPair) *reinterpret_cast<u32x4 *>(lds + (NA + 1) * kPlaneBytes + at + i * 4096) = z1;
+            *reinterpret_cast<u32x4 *>(lds + NA * kPlaneBytes + at + i * kLoadRows * kRowBytes) = z0;
+            if constexpr (kW == kPair) *reinterpret_cast<u32x4 *>(lds + (NA + 1) * kPlaneBytes + at + i * kLoadRows * kRowBytes) = z1;
         }
     };
 
@@ -179,7 +190,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW != kPair ? 3 : 2) vo
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
     // lane (r, kg) of a block reads piece 2 q + kg of row r for chunk q of the group
-    const uint8_t *const pa = lds + (wm * 64u + r) * 128u, *const pw = lds + NA * kPlaneBytes + (wn * 64u + r) * 128u;
+    const uint8_t *const pa = lds + (wm * 64u + r) * (uint32_t)kRowBytes, *const pw = lds + NA * kPlaneBytes + (wn * 64u + r) * (uint32_t)kRowBytes;
     struct Words {
         u32x4 a[NA][2], w[NW][2];
     };
@@ -187,13 +198,13 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW != kPair ? 3 : 2) vo
         v4i a[2], w[2];
     };
     auto fetch = [&](const uint32_t q, Words &z) __attribute__((always_inline)) {
-        const uint32_t piece = ((2u * q + kg) ^ ((r >> 1) & 7u)) << 4;
+        const uint32_t piece = ((2u * q + kg) ^ ((r >> kSwizzle) & (kPieces - 1u))) << 4;
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
 #pragma unroll
-            for (int p = 0; p < NA; ++p) z.a[p][b] = *reinterpret_cast<const u32x4 *>(pa + p * kPlaneBytes + b * 4096 + piece);
+            for (int p = 0; p < NA; ++p) z.a[p][b] = *reinterpret_cast<const u32x4 *>(pa + p * kPlaneBytes + b * 32 * kRowBytes + piece);
 #pragma unroll
-            for (int p = 0; p < NW; ++p) z.w[p][b] = *reinterpret_cast<const u32x4 *>(pw + p * kPlaneBytes + b * 4096 + piece);
+            for (int p = 0; p < NW; ++p) z.w[p][b] = *reinterpret_cast<const u32x4 *>(pw + p * kPlaneBytes + b * 32 * kRowBytes + piece);
         }
     };
     auto make = [&](const Words &z, const int ph, Operands &f) __attribute__((always_inline)) {
@@ -222,23 +233,23 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW != kPair ? 3 : 2) vo
         }
     };
 
-    const uint32_t groups = (sc.chunks + 3u) / 4u, pairs = (uint32_t)(sc.a.count * sc.w.count);
+    const uint32_t groups = (2u * sc.chunks + kPieces - 1u) / kPieces, pairs = (uint32_t)(sc.a.count * sc.w.count);
     Group x;
     load(x, sc.a.d[0], sc.w.d[0], 0u);
     uint32_t ia = 0, iw = 0, G = 0;
-    int corr_a4[4] = {0, 0, 0, 0}, corr_w4[4] = {0, 0, 0, 0};
+    int corr_a4[kLoads] = {}, corr_w4[kLoads] = {};
     int a_scale = sc.a.d[0].scale, w_scale = sc.w.d[0].scale;
     for (uint32_t item = 0, items = pairs * groups; item < items; ++item) {
         if (item > 0) __syncthreads();  // the group before has been read
-        store(x, sc.a.d[ia], sc.w.d[iw], G, 32u * G + 32u > sc.row_words);
+        store(x, sc.a.d[ia], sc.w.d[iw], G, 4u * kPieces * (G + 1u) > sc.row_words);
         __syncthreads();
-        const uint32_t left = sc.chunks - 4u * G;
+        const uint32_t left = sc.chunks - kPieces / 2u * G;
         const bool pair_ends = G + 1u == groups;
         if (!kMap && pair_ends && sc.corrected) {  // weigh the row sums of this pair
             const int shift = sc.a.d[ia].lg + sc.w.d[iw].lg;
             const int a_fac = (sc.w.d[iw].offset2 << shift) >> 1, w_fac = (sc.a.d[ia].offset2 << shift) >> 1;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < kLoads; ++i) {
                 corr_a4[i] += sum_a[i] * a_fac, corr_w4[i] += sum_w[i] * w_fac;
                 sum_a[i] = 0, sum_w[i] = 0;
             }
@@ -249,7 +260,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW != kPair ? 3 : 2) vo
         }
         const bool more = item + 1 < items;
         if (more) load(x, sc.a.d[ia], sc.w.d[iw], G);
-        multiply(a_scale, w_scale, left < 4u ? left : 4u);
+        multiply(a_scale, w_scale, left < kPieces / 2u ? left : kPieces / 2u);
         if (more && pair_ends) a_scale = sc.a.d[ia].scale, w_scale = sc.w.d[iw].scale;
     }
 
@@ -257,14 +268,14 @@ __global__ __launch_bounds__(kTileThreads, kA == kOne && kW != kPair ? 3 : 2) vo
     // register v of block [i][j] is C[m][n], m = 32 j + lane mod 32, n = 32 i + 8 (v / 4) + 4 kg + v mod 4 of the wave's tile
     if constexpr (!kMap) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < kLoads; ++i) {
         if (sc.corrected) {
 #pragma unroll
-            for (int d = 1; d < 8; d <<= 1) corr_a4[i] += __shfl_xor(corr_a4[i], d, 64), corr_w4[i] += __shfl_xor(corr_w4[i], d, 64);
+            for (int d = 1; d < kPieces; d <<= 1) corr_a4[i] += __shfl_xor(corr_a4[i], d, 64), corr_w4[i] += __shfl_xor(corr_w4[i], d, 64);
         }
         // (as the epilogue subtracts them: times alpha, the constant with the weight rows' part)
         if (piece0 == 0)
-            corr_a[32 * i + prow] = (int)((uint32_t)corr_a4[i] * sc.alpha), corr_w[32 * i + prow] = (int)((uint32_t)corr_w4[i] * sc.alpha - sc.c0);
+            corr_a[kLoadRows * i + prow] = (int)((uint32_t)corr_a4[i] * sc.alpha), corr_w[kLoadRows * i + prow] = (int)((uint32_t)corr_w4[i] * sc.alpha - sc.c0);
     }
     }
     __syncthreads();
