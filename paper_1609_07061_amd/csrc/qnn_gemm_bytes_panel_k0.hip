@@ -52,20 +52,22 @@ __global__ __launch_bounds__(256) void expand_weights_kernel(const uint32_t *__r
 //   General multipliers: a nibble of a plane word becomes four bytes of 0 / 1 with one multiplication, the planes'
 //   contributions are summed as four bytes per register (positive and negative multipliers apart, no carries between
 //   bytes), and positive - negative + bias is formed byte-wise.
-//   Multipliers +-2^q with distinct q (`pow2`): plane p's word, inverted where its multiplier is negative, is row
-//   pos[p] of an 8 x 32 bit matrix whose transpose holds, per element, the byte sum_p 2^pos[p] (b_p xor inv_p), which
-//   is the value plus the sum of the negative multipliers' magnitudes (`neg_sum`, subtracted byte-wise); `twice`
-//   doubles that first (sign-mode planes: 2 b - 1).
+//   Multipliers +-2^q with distinct q (`pow2`): the word of the plane with 2^q, inverted where its multiplier is negative, is
+//   row q of an 8 x 32 bit matrix whose transpose holds, per element, the byte sum_q 2^q (b_q xor inv_q), which is the value
+//   plus the sum of the negative multipliers' magnitudes (`neg_sum`, subtracted byte-wise); `twice` doubles that first
+//   (sign-mode planes: 2 b - 1).  Half of the transposition falls away where no plane is above 2^3 (`low`).
+// Bound: vector instructions and the latency of one load (a wave has one word per lane).  Planes come from the host in the order
+// of their powers, which leaves out 64 selects a thread: 2240 and 4096 rows x 2048 of 4 planes 11 -> 8 us.
+// Slot i of src, inv: the plane with 2^i (pow2) or plane i; -1: none.
 struct MergeOperand {
     const uint32_t *planes;
     int64_t plane_stride, ld;  // words
     int64_t rows;
     int8_t *out;
-    int count;
     int32_t mult[QNN_MAX_PLANES];
     int32_t bias;
-    int pow2, twice;
-    int pos[QNN_MAX_PLANES];
+    int pow2, twice, low;
+    int src[QNN_MAX_PLANES];
     uint32_t inv[QNN_MAX_PLANES];
     int32_t neg_sum;
 };
@@ -95,19 +97,15 @@ __global__ __launch_bounds__(256) void merge_planes_kernel(const MergeOperand a,
     uint32_t words[QNN_MAX_PLANES];
 #pragma unroll
     for (int p = 0; p < QNN_MAX_PLANES; ++p)
-        words[p] = (p < op.count && j < Kw) ? op.planes[(int64_t)p * op.plane_stride + r * op.ld + j] : 0u;
+        words[p] = ((op.src[p] >= 0 && j < Kw) ? op.planes[op.src[p] * op.plane_stride + r * op.ld + j] : 0u) ^ op.inv[p];
     uint32_t o[8];
     if (op.pow2) {
-        uint32_t rows8[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int p = 0; p < QNN_MAX_PLANES; ++p) {
-            if (p >= op.count) break;
-            const uint32_t v = words[p] ^ op.inv[p];
-            const int q = op.pos[p];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) rows8[i] = q == i ? v : rows8[i];
+        if (op.low) {
+            const uint32_t rows4[8] = {words[0], words[1], words[2], words[3], 0u, 0u, 0u, 0u};
+            join_32_codes(rows4, o);
+        } else {
+            join_32_codes(words, o);
         }
-        join_32_codes(rows8, o);
         const uint32_t minus = (uint32_t)((-op.neg_sum) & 0xFF) * 0x01010101u;
         const uint32_t bias = (uint32_t)(op.bias & 0xFF) * 0x01010101u;
 #pragma unroll
@@ -122,7 +120,7 @@ __global__ __launch_bounds__(256) void merge_planes_kernel(const MergeOperand a,
         for (int q = 0; q < 8; ++q) pos[q] = 0u, neg[q] = 0u;
 #pragma unroll
         for (int p = 0; p < QNN_MAX_PLANES; ++p) {
-            if (p >= op.count) break;
+            if (op.src[p] < 0) break;
             const int32_t m = op.mult[p];
             const uint32_t am = (uint32_t)(m < 0 ? -m : m);
 #pragma unroll
@@ -299,7 +297,6 @@ bool merge_plan(const Planes &pl, MergeOperand &op, int64_t &scale) {
         op.mult[p] = (int32_t)(pl.mode == QNN_PLANE_BIT ? d : 2 * d);
     }
     for (int p = pl.count; p < QNN_MAX_PLANES; ++p) op.mult[p] = 0;
-    op.count = pl.count;
     if (pl.mode == QNN_PLANE_BIT) {
         op.bias = 0;
         if (hi > 127 || lo < -128) return false;
@@ -309,28 +306,35 @@ bool merge_plan(const Planes &pl, MergeOperand &op, int64_t &scale) {
         if (hi - lo > 127) return false;  // largest magnitude: every plane at the sign of its coefficient
     }
     // multipliers +-2^q with distinct q: the transposing merge
-    op.pow2 = 1, op.twice = pl.mode != QNN_PLANE_BIT, op.neg_sum = (int32_t)-lo;
-    uint32_t used = 0;
-    for (int p = 0; p < QNN_MAX_PLANES; ++p) op.pos[p] = 0, op.inv[p] = 0u;
-    for (int p = 0; p < pl.count; ++p) {
+    op.pow2 = 1, op.low = 1, op.twice = pl.mode != QNN_PLANE_BIT, op.neg_sum = (int32_t)-lo;
+    for (int q = 0; q < QNN_MAX_PLANES; ++q) op.src[q] = -1, op.inv[q] = 0u;
+    for (int p = 0; p < pl.count && op.pow2; ++p) {
         const int64_t d = pl.coef[p] / gcd, ad = d < 0 ? -d : d;
         int q = 0;
         while (((int64_t)1 << q) < ad) ++q;
-        if (((int64_t)1 << q) != ad || q > 7 || (used & (1u << q))) {
+        if (((int64_t)1 << q) != ad || q > 7 || op.src[q] >= 0) {
             op.pow2 = 0;
-            break;
+        } else {
+            op.src[q] = p;
+            op.inv[q] = d < 0 ? 0xFFFFFFFFu : 0u;
+            if (q > 3) op.low = 0;
         }
-        used |= 1u << q;
-        op.pos[p] = q;
-        op.inv[p] = d < 0 ? 0xFFFFFFFFu : 0u;
     }
+    if (!op.pow2)
+        for (int p = 0; p < QNN_MAX_PLANES; ++p) op.src[p] = p < pl.count ? p : -1, op.inv[p] = 0u;
     scale = gcd;
     return true;
 }
 
+template <bool kCodes>
+KernelFn kernel_of(bool tail, int blocks) {
+    if (tail) return gemm_bytes_panel_kernel<kCodes, true, 4>;
+    if (blocks == 4) return gemm_bytes_panel_kernel<kCodes, false, 4>;
+    return blocks == 3 ? gemm_bytes_panel_kernel<kCodes, false, 3> : gemm_bytes_panel_kernel<kCodes, false, 2>;
+}
 }  // namespace
 
-KernelFn kernel_values(bool tail) { return tail ? gemm_bytes_panel_kernel<false, true> : gemm_bytes_panel_kernel<false, false>; }
+KernelFn kernel_values(bool tail, int blocks) { return kernel_of<false>(tail, blocks); }
 
 bool merge_supports(const Planes &pa, const Planes &pw) {
     MergeOperand a, w;
@@ -363,8 +367,7 @@ int launch_merge_transpose(const Planes &pl, const uint32_t *planes, int64_t pla
     if (!merge_plan(pl, op, scale) || !op.pow2) return fail(QNN_ERR_UNSUPPORTED, "merged values do not fit int8");
     MergeBoth a;
     a.planes = planes, a.plane_stride = plane_stride, a.ld = ld, a.M = M, a.N = N;
-    for (int q = 0; q < 8; ++q) a.src[q] = -1, a.inv[q] = 0u;
-    for (int p = 0; p < op.count; ++p) a.src[op.pos[p]] = p, a.inv[op.pos[p]] = op.inv[p];
+    for (int q = 0; q < 8; ++q) a.src[q] = op.src[q], a.inv[q] = op.inv[q];
     a.neg_sum = op.neg_sum, a.bias = op.bias, a.twice = op.twice;
     a.out = out, a.ld_out = ld_out, a.out_t = out_t, a.ld_t = ld_t, a.row_sums = row_sums, a.col_sums = col_sums;
     const int64_t bx = ceil_div(ld_out, 256), by = ceil_div(ld_t, 128);
@@ -380,7 +383,7 @@ int launch_transpose_to_bytes(const uint32_t *in, int64_t rows, int64_t cols, in
                       ld_out, clear, n_clear);
 }
 
-KernelFn kernel(bool tail) { return tail ? gemm_bytes_panel_kernel<true, true> : gemm_bytes_panel_kernel<true, false>; }
+KernelFn kernel(bool tail, int blocks) { return kernel_of<true>(tail, blocks); }
 
 int launch_expand_weights(const uint32_t *W, int64_t N, int64_t K, int64_t ldw, int8_t *out, int64_t ld_out, int32_t *rw_scaled,
                           hipStream_t s) {

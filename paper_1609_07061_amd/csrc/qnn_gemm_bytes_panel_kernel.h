@@ -17,7 +17,7 @@
 // Workgroup tile 256 x 256 on eight waves of 128 x 64, two per SIMD: a load to LDS holds the issuing wave for tens of cycles and
 // every group ends in a barrier; with one wave of 128 x 128 per SIMD (the earlier shape of this kernel) the matrix cores waited
 // with it.  A group takes 2875 cycles of which 2048 are matrix-core time; at that rate the card's power limit holds the clock at
-// 1.9 GHz (random int8 operands).  4096 x 4096 x 10000: 168 -> 141 us; first layer 10000 x 784 -> 4096: 59 -> 48.5 us.
+// 1.9 GHz (random int8 operands).  Where rounds of such tiles leave much of the chip idle, tiles have 192 or 128 rows (see bytes_tiles).  4096 x 4096 x 10000: 168 -> 141 us; first layer 10000 x 784 -> 4096: 59 -> 48.5 us.
 // The same kernel, with kCodes = false, multiplies two operands that are int8 values already (bit planes merged to one
 // byte per element by merge_planes_kernel, Sec. 2.6 / Sec. 3: the weighted sum of the plane products is the product of
 // the values the planes stand for), with int32 sums as output and no correction terms.
@@ -33,21 +33,23 @@ using mfma::v16i;
 using mfma::v4i;
 
 constexpr int kThreads = 512;
-constexpr int WB = 4, WTILE = 128, BM = 256, BN = 256;  // a wave's tile: 128 rows x 64 columns
+constexpr int BM = 256, BN = 256;  // the largest tile: a wave's part of it is 128 rows x 64 columns
 constexpr int kRowBytes = 128;                         // codes of a row per group
 constexpr int kPanelBytes = BM * kRowBytes;            // one operand's rows of a group
 constexpr int kGroupBytes = 2 * kPanelBytes;
 constexpr int kGroupK = 128;
-constexpr int kLoadsPerGroup = 8;                      // loads to LDS that a wave issues per group
 
 // kCodes: the left operand holds uint8 codes (the kernel subtracts 128 and adds the weight rows' term g.rw_scaled), threshold
 // output; otherwise int8 values with int32 output.
 // kTail (grid = a multiple of 16 workgroups, fewer than there are tiles, and at most half a grid of tiles in the last round): that
 // round's tiles are taken as halves of 128 columns by two workgroups each.
-template <bool kCodes, bool kTail>
+// WB: blocks of 32 rows per wave, so the tile has 64 WB rows: 256, 192 or 128 (see bytes_tiles).
+template <bool kCodes, bool kTail, int WB>
 __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const GemmArgs g, const MfmaConst mc, uint32_t tiles_m,
                                                                        uint32_t tiles_n, uint32_t ngroups) {
     constexpr bool kSign = kCodes;
+    constexpr int kLoadsPerGroup = WB + 4;  // loads to LDS that a wave issues per group
+    static_assert(!kTail || WB == 4, "halves of whole tiles");
     // One LDS array: two group buffers, then either the per-wave tables of the threshold epilogue (thresholds, flip flags,
     // weight rows' terms: 64 entries each) or the per-wave 32 x 32 staging blocks of the int32 epilogue (all 160 KiB).
     constexpr int kRingBytes = 2 * kGroupBytes;
@@ -89,7 +91,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const Gem
     const bool has_half = kTail && tail_vb < total_tiles;
     const uint32_t half_col = ((vb0 >> 3) & 1u) * (uint32_t)(BN / 2);
     uint32_t p_vb = vb0, p_G = 0, p_item = 0;
-    uint32_t a_off[4], w_off[4];  // byte offsets of the rows this lane loads (weights: plus its piece of the line)
+    uint32_t a_off[WB], w_off[4];  // byte offsets of the rows this lane loads (weights: plus its piece of the line)
     uint32_t p_jb = 0;            // byte offset within an activation row of this lane's piece of the group at the cursor
     const uint32_t lda_bytes = (uint32_t)g.A.ld, ldw_bytes = (uint32_t)g.ld_w_bytes;
     const uint32_t last_m = (uint32_t)(g.M - 1), last_n = (uint32_t)(g.N - 1);
@@ -102,9 +104,11 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const Gem
         const uint32_t pr = tt >> 3, piece = (tt & 7u) ^ ((tt >> 4) & 7u);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            uint32_t m = tm * (uint32_t)BM + (uint32_t)(64 * i) + pr;
-            m = m > last_m ? last_m : m;
-            a_off[i] = m * lda_bytes;
+            if (i < WB) {
+                uint32_t m = tm * (uint32_t)(64 * WB) + (uint32_t)(64 * i) + pr;
+                m = m > last_m ? last_m : m;
+                a_off[i] = m * lda_bytes;
+            }
             uint32_t n = tn * (uint32_t)BN + (uint32_t)(64 * i) + pr;
             n = n > last_n ? last_n : n;
             w_off[i] = n * ldw_bytes + piece * 16u;
@@ -142,7 +146,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const Gem
     // load i of both panels of the group at the cursor (rows of the expanded weights hold whole groups: nothing to clamp)
     auto load_pair = [&](const int i, const uint32_t buf) __attribute__((always_inline)) {
         const uint32_t dst = lds_base + buf + (uint32_t)(i * 64 * kRowBytes) + (uint32_t)wave * (8u * kRowBytes);
-        load16_to_lds(g.A.base, a_off[i], p_jb, dst);
+        if (i < WB) load16_to_lds(g.A.base, a_off[i], p_jb, dst);
         load16_to_lds(g.w_bytes, w_off[i], opaque(p_G * (uint32_t)kGroupK), dst + (uint32_t)kPanelBytes);
     };
     // Workgroup barrier: the next group has landed (its loads were issued a whole group ago) and this wave's LDS reads have
@@ -178,7 +182,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const Gem
             const uint32_t ln = opaque(tid) & 63u;
             const uint32_t r = ln & 31u, kg = ln >> 5;
             const uint32_t piece = ((kg ^ ((r >> 1) & 7u)) << 4) ^ (uint32_t)(32 * s);
-            const uint8_t *pa = lds + (buf + (uint32_t)(wm * WTILE * kRowBytes) + r * (uint32_t)kRowBytes + piece);
+            const uint8_t *pa = lds + (buf + (uint32_t)(wm * 32 * WB * kRowBytes) + r * (uint32_t)kRowBytes + piece);
             const uint8_t *pw = lds + (buf + (uint32_t)kPanelBytes + (first_col + (uint32_t)(wn * 32 * WI) + r) * (uint32_t)kRowBytes + piece);
 #pragma unroll
             for (int b = 0; b < WB; ++b) f.a[b] = *reinterpret_cast<const v4i *>(pa + b * 32 * kRowBytes);
@@ -216,7 +220,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const Gem
         for (uint32_t done = 0; done < n_tiles; ++done, vb += gridDim.x) {
             uint32_t tile_m, tile_n;
             tile_of_block(vb, total_tiles, tiles_m, tiles_n, tile_m, tile_n);
-            const int64_t m_wave = (int64_t)tile_m * BM + wm * WTILE, n_wave = (int64_t)tile_n * BN + (int64_t)first_col + wn * 32 * WI;
+            const int64_t m_wave = (int64_t)tile_m * (64 * WB) + wm * 32 * WB, n_wave = (int64_t)tile_n * BN + (int64_t)first_col + wn * 32 * WI;
 #pragma unroll
             for (int j = 0; j < WB; ++j) ra[j] = 0;
 #pragma unroll
@@ -274,8 +278,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const Gem
 }
 
 typedef void (*KernelFn)(const GemmArgs, const MfmaConst, uint32_t, uint32_t, uint32_t);
-KernelFn kernel(bool tail);         // uint8 codes, threshold output
-KernelFn kernel_values(bool tail);  // int8 values, int32 output
+// blocks: rows of a tile / 64 (four with tail)
+KernelFn kernel(bool tail, int blocks);         // uint8 codes, threshold output
+KernelFn kernel_values(bool tail, int blocks);  // int8 values, int32 output
 
 }  // namespace bytes_panel
 }  // namespace qnn

@@ -167,9 +167,30 @@ static int compute_units() {
     return cus;
 }
 
-// Byte-operand kernel: the last round's tiles as halves on twice the workgroups, where they are at most half as many (10000 x 784 -> 4096 has 2.5 rounds).
-
-static bool halve_last_round(int64_t total, int cus) { return cus % 16 == 0 && total > cus && total % cus != 0 && 2 * (total % cus) <= cus; }
+// Tiles of the byte-operand kernel: 64 `blocks` rows x 256 columns, taken in rounds of one tile per compute unit.  A round costs
+// 1.41, 1.22 and 1.0 us per group of k with 256, 192 and 128 rows (reads of LDS and matrix cores overlap worse the fewer products
+// an operand feeds), and one of halved 256-row tiles, possible where the last round has tiles for at most half of the compute
+// units, 1.03; the fewest rounds by that cost are taken.  With 256 rows -> as chosen, merge of the planes included: 2240 x 4096 x
+// 2048 (144 -> 192 tiles) 50.7 -> 48.4 us, x 4096 69.5 -> 62.8; 2000 x 3000 x 1500 (96 -> 192) 43.0 -> 35.0; 10000 x 4096 x 4096
+// stays (2.5 rounds: 193 us against 208 with 192 rows), 10000 x 784 -> 4096 likewise.
+struct BytesTiles {
+    int blocks;
+    bool tail;
+    int64_t tiles_m, tiles_n;
+    unsigned grid;
+};
+static BytesTiles bytes_tiles(int64_t M, int64_t N, int cus) {
+    constexpr double kRound[5] = {0.0, 0.0, 1.0, 1.22, 1.41}, kHalves = 1.03;
+    BytesTiles t = {4, false, 0, ceil_div(N, 256), 0};
+    double best = 0.0;
+    for (int blocks = 4; blocks >= 2; --blocks) {
+        const int64_t tiles_m = ceil_div(M, 64 * blocks), total = tiles_m * t.tiles_n, whole = total / cus, rest = total % cus;
+        const bool tail = blocks == 4 && cus % 16 == 0 && whole > 0 && rest != 0 && 2 * rest <= cus;
+        const double cost = kRound[blocks] * (double)whole + (tail ? kHalves : (rest ? kRound[blocks] : 0.0));
+        if (blocks == 4 || cost < best) t.blocks = blocks, t.tail = tail, t.tiles_m = tiles_m, t.grid = (unsigned)(total < cus ? total : cus), best = cost;
+    }
+    return t;
+}
 
 // Layout conditions of the panel-fed kernel: single planes, rows of whole 128-byte groups on 16-byte boundaries (row offsets are
 // 32-bit and formed for up to one tile beyond the last row before they are clamped).
@@ -233,9 +254,9 @@ int launch_gemm_mfma(const GemmArgs &g, hipStream_t s, bool fp4) {
         MfmaConst pc = mc;
         pc.alpha = 1, pc.alpha_shift = 0, pc.cRA = 0, pc.cRW = 1, pc.c0 = 0, pc.needRW = 1;
         const int64_t ngroups = ceil_div(g.K, bytes_panel::kGroupK);
-        const bool tail = halve_last_round(total, cus);
-        return QNN_LAUNCH("gemm_bytes_panel", bytes_panel::kernel(tail), dim3(grid), dim3(bytes_panel::kThreads), 0, s, g, pc, (uint32_t)tiles_m,
-                          (uint32_t)tiles_n, (uint32_t)ngroups);
+        const BytesTiles bt = bytes_tiles(g.M, g.N, cus);
+        return QNN_LAUNCH("gemm_bytes_panel", bytes_panel::kernel(bt.tail, bt.blocks), dim3(bt.grid), dim3(bytes_panel::kThreads), 0, s, g, pc,
+                          (uint32_t)bt.tiles_m, (uint32_t)bt.tiles_n, (uint32_t)ngroups);
     }
     const KernelFn fn = g.A.rows_are_bytes ? byte_kernels()[g.epi.T ? 1 : 0]
                         : fp4              ? (vec ? v->fp4_vec : v->fp4_any)
@@ -334,11 +355,9 @@ int launch_values_product(const GemmArgs &g, const int8_t *a8, const int8_t *w8,
     mc.alpha_shift = -1;
     for (int sh = 0; sh < 31; ++sh)
         if (alpha == ((int64_t)1 << sh)) mc.alpha_shift = sh;
-    const int cus = compute_units();
-    const int64_t tiles_m = ceil_div(g.M, 256), tiles_n = ceil_div(g.N, 256), total = tiles_m * tiles_n;
-    const unsigned grid = (unsigned)(total < cus ? total : cus);
-    return QNN_LAUNCH("gemm_values", bytes_panel::kernel_values(halve_last_round(total, cus)), dim3(grid), dim3(bytes_panel::kThreads), 0, s, v, mc,
-                      (uint32_t)tiles_m, (uint32_t)tiles_n, (uint32_t)ceil_div(g.K, bytes_panel::kGroupK));
+    const BytesTiles bt = bytes_tiles(g.M, g.N, compute_units());
+    return QNN_LAUNCH("gemm_values", bytes_panel::kernel_values(bt.tail, bt.blocks), dim3(bt.grid), dim3(bytes_panel::kThreads), 0, s, v, mc,
+                      (uint32_t)bt.tiles_m, (uint32_t)bt.tiles_n, (uint32_t)ceil_div(g.K, bytes_panel::kGroupK));
 }
 
 // Temporary device memory from the stream's pool, given back in stream order.

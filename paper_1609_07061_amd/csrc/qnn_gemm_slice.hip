@@ -373,15 +373,19 @@ SliceFn slice_kernel(int ka, int kw, bool large) { return large ? slice_kernel<k
 //   single planes that miss the panel-fed kernel's layout: everything (1999 x 3001 x 2500 82 -> 21; 8000^3 640 -> 234);
 //   single planes that fit it: while its 256 x 128 tiles leave compute units idle (256 x 1024 x 8192 24 -> 6; 8192 x 256 x 8192
 //     25 -> 14; 2048^3 12.9 -> 11.5), not beyond (4096^3 33 against 38);
-//   several planes merged in LDS: everything (256 maps, 2-bit activations, 64 -> 35; 1000 x 4096 x 2048 with 4 x 4 planes
-//     45 -> 32), but not large products of four digit pairs (2240 x 4096 x 2048 with 4 x 4 planes 57 against 68).
+//   several planes merged in LDS: everything (256 maps, 2-bit activations, 64 -> 28; 1000 x 4096 x 2048 with 4 x 4 planes
+//     45 -> 30), but not large products of four digit pairs, which are faster as bytes: from 5e10 element products on (2240 x 4096 x
+//     2048 with 4 x 4 planes 45 against 57), or 3e10 where compute units hold two 128 x 128 tiles (2000 x 3000 x 1500 34 against 42,
+//     2240 x 2048 x 2048 37 against 42; below, 1500 x 4096 x 1000 30 against 26; 256 tiles: 1000 x 4096 x 2048 38 against 31).
 bool slice_preferred(const GemmArgs &g, int route) {
     SliceArgs sc;
     int ka, kw;
     if (!slice_args(g, false, sc, ka, kw)) return false;
     if (route == QNN_ENGINE_MFMA_FP4 && panel_takes(g)) return ceil_div(g.M, 256) * ceil_div(g.N, 128) < 256;
-    if (route == QNN_ENGINE_MFMA_LDS && sc.a.count * sc.w.count >= 4)
-        return (long double)g.M * (long double)g.N * (long double)g.K * (sc.a.count * sc.w.count) < 5e10L;
+    if (route == QNN_ENGINE_MFMA_LDS && sc.a.count * sc.w.count >= 4) {
+        const long double work = (long double)g.M * (long double)g.N * (long double)g.K * (sc.a.count * sc.w.count);
+        return work < (ceil_div(g.M, 128) * ceil_div(g.N, 128) > 256 ? 3e10L : 5e10L);
+    }
     return true;
 }
 

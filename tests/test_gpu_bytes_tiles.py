@@ -1,0 +1,38 @@
+"""Products of operands merged to bytes at every tile height (256, 192, 128 rows, halves in the last round), with rows and columns
+that end inside a tile, rows of C at any alignment, and planes at every position of a byte or none."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import qnn_inputs as qi
+from qnn_testlib import dev, host, np_pack_bits
+
+pytestmark = pytest.mark.gpu
+
+# tiles of 256 rows on 256 compute units: half a round (taken as 128 rows), 0.56 and 0.75 rounds (192), 1.25 rounds (halves), one
+SHAPES = [(1793, 4081, 600), (2230, 4096, 513), (3071, 4090, 640), (5000, 4100, 513), (4096, 4096, 512)]
+PLANES = [([1, 2, 4, -8], 0, [1, 2, 4, -8], 0), ([1, 4, 16, -64], 0, [2, 1, -4], 1), ([3, 5, -7], 0, [1, 3], 1)]
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+@pytest.mark.parametrize("ca,ma,cw,mw", PLANES)
+def test_merged_products(seed, M, N, K, ca, ma, cw, mw):
+    import paper_1609_07061_amd as q
+
+    def operand(stream, coef, mode, rows):
+        planes = qi.bernoulli_bits(seed, stream, (len(coef), rows, K)).astype(np.uint8)
+        values = sum(c * (planes[p].astype(np.int32) if mode == 0 else 2 * planes[p].astype(np.int32) - 1) for p, c in enumerate(coef))
+        return dev(np_pack_bits(planes, (K + 31) // 32)), values
+
+    A, va = operand(1400, ca, ma, M)
+    W, vw = operand(1401, cw, mw, N)
+    wide = torch.full((M, N + 3), 7, dtype=torch.int32, device="cuda")
+    for C in (torch.empty((M, N), dtype=torch.int32, device="cuda"), wide[:, 1:1 + N]):
+        q.qnn_bitplane_gemm(A, ca, ma, W, cw, mw, K, out=C, engine=q.ENGINE_MFMA_LDS)
+        # (sums below 2^24: exact in float64)
+        want = torch.from_numpy(va).cuda().double() @ torch.from_numpy(vw).cuda().double().t().contiguous()
+        assert torch.equal(C, want.to(torch.int32)), (M, N, K, ca)
+    assert bool((wide[:, 0] == 7).all()) and bool((wide[:, 1 + N:] == 7).all())
+    rows = np.array([0, M - 1])
+    assert np.array_equal(host(C)[rows], oracle.gemm_int(va[rows].astype(np.int32), vw.astype(np.int32)))
