@@ -655,10 +655,10 @@ int qnn_bitplane_conv2d(const uint32_t *A, int Pa, const int32_t *coefA, int mod
 namespace {
 constexpr int kMaxNetLayers = 2 * QNN_MAX_LAYERS;
 struct NetStep {
-    enum Kind { kPack, kFlags, kOnes, kGemm, kPool, kFirstConv, kConvPrep, kConvMap } kind;
+    enum Kind { kPack, kOnes, kGemm, kPool, kFirstConv, kConvPrep, kConvMap } kind;
     GemmArgs g;      // kGemm (convolution or fully connected)
     int engine;      // kGemm
-    // kPack / kFlags / kOnes / kPool operands
+    // kPack / kOnes / kPool operands
     const void *src;
     void *dst, *dst2;
     int64_t rows, n;
@@ -670,8 +670,10 @@ struct NetStep {
 struct NetPlan {
     int n;
     bool free_choice;   // the caller asked for no engine
-    FlagJobs flags;     // kFlags: every layer's flip flags, one launch
-    ConvPrepJobs prep;  // kConvPrep: border-class thresholds of every convolution on a plane, one launch
+    // what the layers read besides weights and thresholds, made by the first launch (kFirstConv or kConvPrep): every layer's flip
+    // flags and the border-class thresholds of every convolution on a plane
+    FlagJobs flags;
+    ConvPrepJobs prep;
     NetStep step[6 * kMaxNetLayers + 4];
 };
 
@@ -740,9 +742,6 @@ int run_net(const NetPlan &plan, hipStream_t s) {
                 rc = launch_pack_bitplanes(static_cast<const uint8_t *>(st.src), st.rows, st.n, st.n, st.a,
                                            static_cast<uint32_t *>(st.dst), st.b, st.rows * st.b, s);
                 break;
-            case NetStep::kFlags:
-                rc = launch_flags(plan.flags, s);
-                break;
             case NetStep::kOnes:
                 rc = launch_ones_plane(static_cast<uint32_t *>(st.dst), st.rows, st.a, st.b, s);
                 break;
@@ -752,19 +751,18 @@ int run_net(const NetPlan &plan, hipStream_t s) {
                 break;
             case NetStep::kFirstConv:
                 // src = image, mask = weights, dst = output bits; rows = B, a / b / c = H / W / C0, n = filters;
-                // the thresholds and flips travel in g.epi
+                // the thresholds and flips (complemented if `invert`) travel in g.epi
                 rc = launch_conv_first(static_cast<const uint8_t *>(st.src), st.rows, st.a, st.b, st.c, st.mask, st.n, st.g.epi.T,
-                                       st.g.epi.flip, static_cast<uint32_t *>(st.dst), static_cast<uint32_t *>(st.dst2), st.g.epi.ldo, s);
+                                       st.g.epi.flip, st.invert, static_cast<uint32_t *>(st.dst), static_cast<uint32_t *>(st.dst2), st.g.epi.ldo,
+                                       plan.prep, plan.flags, s);
                 if (rc == QNN_OK) {
                     g_last_engine = QNN_ENGINE_MFMA;
                     if (g_engine_count < 2 * QNN_MAX_LAYERS) g_engines[g_engine_count++] = QNN_ENGINE_MFMA;
                 }
                 break;
-            case NetStep::kConvPrep: {  // with the layers' flip flags
-                ConvPrepJobs jobs = plan.prep;
-                rc = panel::launch_conv_class_thr(jobs, plan.flags, s);
+            case NetStep::kConvPrep:
+                rc = launch_conv_class_thr(plan.prep, plan.flags, s);
                 break;
-            }
             case NetStep::kConvMap:
                 // src = plane "value is -1" of the input map, w = filters, dst = output bits, dst2 = class thresholds;
                 // rows = B, a / b / c = H / W / C, n = filters; complemented flips and the output pitch in g.epi; mask (may be
@@ -838,14 +836,12 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
         plan.flags.bits[l] = words(L.flag_bits[l]);
         plan.flags.inv[l] = ws + L.flag_inv[l];
     }
-    const int flags_step = plan.n;
-    if (n_layers > 1) push().kind = NetStep::kFlags;
     // whether a convolution (not the first) reads its map as the plane "value is -1" (tiled FP4 kernel) or as the 2-bit code
     auto on_plane = [&](int64_t hh, int64_t ww, int64_t cc, int64_t co) {
         return (engine == QNN_ENGINE_AUTO || engine == QNN_ENGINE_MFMA_FP4) && conv_map_supports(B, hh, ww, cc, co) &&
                (engine != QNN_ENGINE_AUTO || conv_map_preferred(B, hh, ww, co));
     };
-    // thresholds per border class of the convolutions on planes, all in one launch
+    // thresholds per border class of the convolutions on planes
     plan.prep.count = 0;
     {
         int64_t hh = H, ww = Wd, cc = C0;
@@ -861,19 +857,13 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
             cc = cout[l];
         }
     }
-    // (one launch prepares both the thresholds and the flags)
-    if (plan.prep.count > 0) {
-        if (n_layers > 1)
-            plan.step[flags_step].kind = NetStep::kConvPrep;
-        else
-            push().kind = NetStep::kConvPrep;
-    }
     // The first convolution multiplies the 8-bit codes themselves when a pixel's patch fits one matrix-core operand
     // row (three channels or fewer); otherwise, and when another engine is asked for, it goes through the input's
     // bit planes (Sec. 2.6): [in_bits][pixels][words per pixel]
     const bool first_direct = (engine == QNN_ENGINE_AUTO || engine == QNN_ENGINE_MFMA) && conv_first_supports(C0, cout[0], 3, 3, 1, 1);
     const int64_t Cw0 = words_for(C0);
     if (!first_direct) {
+        push().kind = NetStep::kConvPrep;
         NetStep &st = push();
         st.kind = NetStep::kPack;
         st.src = x, st.dst = ws + L.planes0;
@@ -919,6 +909,7 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
             st.dst2 = (ones_needed && !pool[l]) ? kept : nullptr;  // the ones plane of an unpooled output, written alongside
             st.rows = B, st.a = (int)H, st.b = (int)Wd, st.c = (int)C0, st.n = co;
             st.g.epi = e;
+            st.g.epi.flip = flip ? flip[l] : nullptr, st.invert = inverted;  // (the complemented flags are made in this launch)
         } else {
         if (int rc = conv_args(a_planes, a_count, a_coef, QNN_PLANE_BIT, a_stride, B, h, w, cin, W[l], 1, kOne, QNN_PLANE_SIGN, 0,
                                co, 3, 3, 1, 1, e, engine, st.g, empty))

@@ -26,11 +26,73 @@ using mfma::v4i;
 constexpr int kFirstThreads = 256;
 constexpr int kFirstMaxN = 1024;  // filters: 32 bytes of LDS each, plus three table entries
 
+// class_thr[cls][n] = floor(e / 2) as a float, clamped to +-2^23 (the sums it is compared with are far smaller), where
+// e = 2 sum_{taps inside for cls} sum_c b[n][tap][c] - (taps inside) C - T[n] = (sum of the filter's weights on the taps
+// inside) - T[n]: the convolution is that sum minus 2 S, S = sum_k p w, so it reaches T[n] iff S <= e / 2; cls bit 0: the pixel is in the first row (the upper taps lie outside), 1: last
+// row, 2: first column, 3: last column.  Entries of filters beyond N are zero.  All layers of a network in one launch:
+// sixteen lanes per filter, lane t < 9 counts the set bits of tap t, then lane c sums the taps that class c keeps.
+// The first flag_blocks workgroups prepare the flip flags of the layers instead, as packed words and as inverted bytes (bits[w]
+// bit t = (flip[32 w + t] != 0) for channels below n, flip == nullptr reading as all zero; inv[c] = !flip[c]); workgroup b takes
+// channels 256 (b mod per_job) .. + 255 of layer b / per_job.
+struct NetPrep {
+    ConvPrepJobs jobs;
+    FlagJobs flags;
+    uint32_t flag_blocks, per_job, blocks;  // blocks: with those of the thresholds
+};
+static_assert(sizeof(NetPrep) <= 3840, "kernel arguments");
+__device__ __forceinline__ void prepare_block(const NetPrep &p) {
+    const ConvPrepJobs &jobs = p.jobs;
+    const FlagJobs &flags = p.flags;
+    if (blockIdx.x < p.flag_blocks) {
+        const uint32_t fj = blockIdx.x / p.per_job;
+        const uint8_t *flip = flags.flip[fj];
+        const int64_t fn = flags.n[fj];
+        const int lane = threadIdx.x & 63;
+        const int64_t c = (int64_t)(blockIdx.x - fj * p.per_job) * 256 + threadIdx.x;
+        if (c - lane >= fn) return;  // (whole waves leave: the ballot below sees complete waves only)
+        const bool f = (c < fn && flip) ? (flip[c] != 0) : false;
+        const unsigned long long m = __ballot(f);
+        if (c < fn) flags.inv[fj][c] = f ? 0 : 1;
+        const int64_t w = (c - lane) / 32;
+        if (lane == 0) flags.bits[fj][w] = (uint32_t)m;
+        if (lane == 32 && c < fn) flags.bits[fj][w + 1] = (uint32_t)(m >> 32);
+        return;
+    }
+    const int64_t block = (int64_t)blockIdx.x - p.flag_blocks;
+    int j = 0;
+    while (j + 1 < jobs.count && block >= jobs.first_block[j + 1]) ++j;
+    const int64_t n = (block - jobs.first_block[j]) * 16 + (threadIdx.x >> 4);
+    const int sub = threadIdx.x & 15;
+    const int64_t N = jobs.N[j], ld = jobs.ld[j];
+    const int Cw = jobs.Cw[j];
+    int32_t count = 0;
+    if (n < N && sub < 9) {
+        const uint32_t *w = jobs.W[j] + (n * 9 + sub) * Cw;
+        for (int c = 0; c < Cw; ++c) count += __builtin_popcount(w[c]);
+    }
+    int64_t sum = 0, taps = 0;
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+        const int32_t pc = __shfl(count, (threadIdx.x & 48) + tap, 64);  // (every lane takes part in the exchange)
+        const int ky = tap / 3, kx = tap % 3;
+        const bool outside = (ky == 0 && (sub & 1)) || (ky == 2 && (sub & 2)) || (kx == 0 && (sub & 4)) || (kx == 2 && (sub & 8));
+        if (!outside) sum += pc, ++taps;
+    }
+    if (n < ld) {
+        int64_t e = n < N ? 2 * sum - taps * jobs.C[j] - (int64_t)jobs.T[j][n] : 0;
+        e >>= 1;  // floor
+        e = e < -(1 << 23) ? -(1 << 23) : (e > (1 << 23) ? (1 << 23) : e);
+        jobs.out[j][sub * ld + n] = (int32_t)__float_as_uint((float)(int32_t)e);
+    }
+}
+__global__ __launch_bounds__(kFirstThreads) void conv_class_thr_kernel(const NetPrep p) { prepare_block(p); }
+
 struct FirstConvArgs {
     const uint8_t *x;     // [B][H][W][C0]
     const uint32_t *W;    // [N][9] words, bit c of word t = weight of tap t, channel c (set = +1)
     const int32_t *T;     // [N]
     const uint8_t *flip;  // [N] or null
+    bool flip_all;        // every flip flag counts as its complement
     uint32_t *out;        // [B H W][ldo]
     uint32_t *ones;       // null, or [B H W][ldo]: receives the first N bits of every pixel set
     int64_t ldo;
@@ -38,7 +100,14 @@ struct FirstConvArgs {
     int H, Wd, C0, N;
 };
 
-__global__ __launch_bounds__(kFirstThreads) void conv_first_kernel(const FirstConvArgs a) {
+// The first workgroups of the launch prepare what the later layers read: a launch of their own for it held up the first layer
+// (App. A network, batch 4: 64.8 -> 62.2 us, batch 256: 144 -> 141.4 us).
+__global__ __launch_bounds__(kFirstThreads) void conv_first_kernel(const FirstConvArgs a, const NetPrep prep) {
+    if (blockIdx.x < prep.blocks) {
+        prepare_block(prep);
+        return;
+    }
+    const uint32_t block = blockIdx.x - prep.blocks, blocks = gridDim.x - prep.blocks;
     __shared__ __attribute__((aligned(16))) uint8_t sW[kFirstMaxN * 32];
     // per filter: threshold - 1 - 128 sum_k w (the matrix-core sum S meets the threshold iff S > that), and the filter's
     // flip flag and "exists" flag at the bit its n has in a lane's partial output word (n mod 32 = 8 q + 4 kg + i ->
@@ -64,7 +133,7 @@ __global__ __launch_bounds__(kFirstThreads) void conv_first_kernel(const FirstCo
         off[j] = ((ty - 1) * a.Wd + (tx - 1)) * C0 + c;
     }
     const int64_t tiles = (a.pixels + 31) / 32;
-    const int64_t tile_step = (int64_t)gridDim.x * (kFirstThreads / 64);
+    const int64_t tile_step = (int64_t)blocks * (kFirstThreads / 64);
     // The patch bytes of a tile of 32 pixels: lane (r, kg) asks for its 16 bytes of pixel r, branch-free (an element
     // outside the image or beyond the patch reads the pixel's own first byte and is dropped when the operand is put
     // together), so that the sixteen loads are issued back to back.  The loads of a wave's next tile are issued before
@@ -87,7 +156,7 @@ __global__ __launch_bounds__(kFirstThreads) void conv_first_kernel(const FirstCo
             in_mask |= (in ? 1u : 0u) << j;
         }
     };
-    const int64_t first_tile = (int64_t)blockIdx.x * (kFirstThreads / 64) + wave;
+    const int64_t first_tile = (int64_t)block * (kFirstThreads / 64) + wave;
     uint32_t got[16], in_mask = 0;
     if (first_tile < tiles) gather(first_tile, got, in_mask);
     // Per filter, by one thread: its nine words, threshold and flip flag are asked for together; then the filter as
@@ -101,7 +170,7 @@ __global__ __launch_bounds__(kFirstThreads) void conv_first_kernel(const FirstCo
 #pragma unroll
             for (int i = 0; i < 9; ++i) w9[i] = there ? a.W[(int64_t)n * 9 + i] & ((1u << kC0) - 1u) : 0u;
             const int32_t tv = there ? a.T[n] : 0;
-            const bool flipped = there && a.flip && a.flip[n];
+            const bool flipped = there && ((a.flip && a.flip[n]) != a.flip_all);
             uint32_t piece[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
             int32_t set = 0;
 #pragma unroll
@@ -209,17 +278,42 @@ bool conv_first_supports(int64_t C0, int64_t N, int KH, int KW, int pad, int str
     return KH == 3 && KW == 3 && pad == 1 && stride == 1 && C0 >= 1 && C0 <= 3 && N >= 1 && N <= kFirstMaxN;
 }
 
+static int net_prep(const ConvPrepJobs &jobs, const FlagJobs &flags, NetPrep &p) {
+    p.jobs = jobs, p.flags = flags;
+    int64_t most = 0;
+    for (int j = 0; j < flags.count; ++j) most = flags.n[j] > most ? flags.n[j] : most;
+    const int64_t per_job = ceil_div(most, 256), flag_blocks = per_job * flags.count;
+    int64_t blocks = 0;
+    for (int j = 0; j < jobs.count; ++j) {
+        p.jobs.first_block[j] = blocks;
+        blocks += ceil_div(jobs.ld[j], 16);
+    }
+    p.jobs.first_block[jobs.count] = blocks;
+    if (blocks + flag_blocks > 0x7FFF0000LL) return fail(QNN_ERR_SHAPE, "convnet: too many filters");
+    p.flag_blocks = (uint32_t)flag_blocks, p.per_job = (uint32_t)(per_job > 0 ? per_job : 1), p.blocks = (uint32_t)(blocks + flag_blocks);
+    return QNN_OK;
+}
+
+int launch_conv_class_thr(const ConvPrepJobs &jobs, const FlagJobs &flags, hipStream_t s) {
+    NetPrep p;
+    if (int rc = net_prep(jobs, flags, p)) return rc;
+    if (p.blocks == 0) return QNN_OK;
+    return QNN_LAUNCH("conv_class_thr", conv_class_thr_kernel, dim3(p.blocks), dim3(kFirstThreads), 0, s, p);
+}
+
 int launch_conv_first(const uint8_t *x, int64_t B, int H, int Wd, int C0, const uint32_t *W, int64_t N, const int32_t *T,
-                      const uint8_t *flip, uint32_t *out, uint32_t *ones, int64_t ldo, hipStream_t s) {
+                      const uint8_t *flip, bool flip_all, uint32_t *out, uint32_t *ones, int64_t ldo, const ConvPrepJobs &jobs,
+                      const FlagJobs &flags, hipStream_t s) {
+    NetPrep p;
+    if (int rc = net_prep(jobs, flags, p)) return rc;
     FirstConvArgs a;
-    a.x = x, a.W = W, a.T = T, a.flip = flip, a.out = out, a.ones = ones, a.ldo = ldo;
+    a.x = x, a.W = W, a.T = T, a.flip = flip, a.flip_all = flip_all, a.out = out, a.ones = ones, a.ldo = ldo;
     a.pixels = B * H * Wd, a.H = H, a.Wd = Wd, a.C0 = C0, a.N = (int)N;
-    if (a.pixels == 0) return QNN_OK;
     const int64_t tiles = ceil_div(a.pixels, 32);
     // a workgroup prepares the filter bytes once and then walks over pixel tiles: a few workgroups per compute unit
     const int64_t blocks = ceil_div(tiles, 4);
     const unsigned grid = (unsigned)(blocks < 768 ? blocks : 768);  // three workgroups fit a compute unit (LDS, registers)
-    return QNN_LAUNCH("conv_first", conv_first_kernel, dim3(grid), dim3(kFirstThreads), 0, s, a);
+    return QNN_LAUNCH("conv_first", conv_first_kernel, dim3(p.blocks + grid), dim3(kFirstThreads), 0, s, a, p);
 }
 
 }  // namespace qnn

@@ -40,7 +40,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 // kMap (3 x 3 "same" convolutions of +-1 maps, pad 1, stride 1, threshold output): the left operand is the map's plane "value is -1"
 // (0 outside the image), the filters enter as +-1.  With a = 1 - 2 p inside the image, conv = sum_{taps inside} sum_c w - 2 S,
 // S = sum_k p w, so a pixel's bit is (S > class_thr[class][n]) xor flip[n], class = which of the image's borders the pixel lies on
-// (see conv_class_thr_kernel).  A lane keeps a filter, so the class is one for the whole wave and row, and the 2 x 2 max-pooling
+// (see prepare_block).  A lane keeps a filter, so the class is one for the whole wave and row, and the 2 x 2 max-pooling
 // that may follow (OR of the four bits where the threshold does not flip, AND where it does) is three exchanges of packed words.
 template <int kA, int kW, int kRows, bool kMap = false>
 __global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) void gemm_tile_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {

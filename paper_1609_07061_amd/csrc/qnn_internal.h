@@ -161,7 +161,7 @@ int launch_threshold_sign(const int32_t *C, int64_t ldc, int64_t M, int64_t N, c
 // 3 x 3 "same" convolution of a +-1 feature map (held as its plane "value is -1", [B][H][Wd][ceil(C / 32)] words) with +-1 filters
 // and threshold output, on the tiled FP4 kernel.  bit = (conv >= T[n]) xor !flip_complement[n]: the caller passes the COMPLEMENT of
 // its flip flags.  class_thr (16 x conv_class_ld(N) words) is written beforehand, on the same stream, by
-// panel::launch_conv_class_thr (one launch for all convolutions of a network).  The 2 x 2 max-pooling that follows is done along if
+// launch_conv_first or launch_conv_class_thr (for all convolutions of a network at once).  The 2 x 2 max-pooling that follows is done along if
 // conv_map_pools (pool_and = packed flip flags of the filters, pool_invert = the map holds inverted bits; null: no pooling).
 bool conv_map_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N);
 bool conv_map_preferred(int64_t B, int64_t H, int64_t Wd, int64_t N);  // against the map's 2-bit code
@@ -179,23 +179,7 @@ struct ConvPrepJobs {
     int64_t C[2 * QNN_MAX_LAYERS];          // channels
     int64_t first_block[2 * QNN_MAX_LAYERS + 1];  // filled by the launch
 };
-struct FlagJobs;
-namespace panel {
-// (also prepares the layers' flip flags, see launch_flags, in the same launch; flags.count may be 0)
-int launch_conv_class_thr(ConvPrepJobs &jobs, const FlagJobs &flags, hipStream_t s);
-}
-
-// First convolution of a ConvNet straight from a uint8 image with at most three channels (3 x 3, pad 1, stride 1,
-// threshold output packed along the filters): whether the kernel takes the shape, and its launch.
-bool conv_first_supports(int64_t C0, int64_t N, int KH, int KW, int pad, int stride);
-// ones (may be null): also writes the "inside the image" plane of the output map, [pixels][ldo] like `out`.
-int launch_conv_first(const uint8_t *x, int64_t B, int H, int Wd, int C0, const uint32_t *W, int64_t N, const int32_t *T,
-                      const uint8_t *flip, uint32_t *out, uint32_t *ones, int64_t ldo, hipStream_t s);
-
-// ones (may be null) receives the "inside the image" plane of the pooled map (first C bits of every pixel set)
-int launch_pool_bits(const uint32_t *in, int64_t B, int H, int Wd, int Cw, const uint32_t *use_and, bool invert_all,
-                     uint32_t *out, uint32_t *ones, int C, hipStream_t s);
-// Flip flags of the layers of a network, turned into packed words and inverted bytes by one launch
+// Flip flags of the layers of a network, turned into packed words and inverted bytes
 struct FlagJobs {
     int count;
     const uint8_t *flip[2 * QNN_MAX_LAYERS];  // may be null: no channel flipped
@@ -203,7 +187,21 @@ struct FlagJobs {
     uint32_t *bits[2 * QNN_MAX_LAYERS];
     uint8_t *inv[2 * QNN_MAX_LAYERS];
 };
-int launch_flags(const FlagJobs &jobs, hipStream_t s);
+// (the layers' flip flags in the same launch; either count may be 0)
+int launch_conv_class_thr(const ConvPrepJobs &jobs, const FlagJobs &flags, hipStream_t s);
+
+// First convolution of a ConvNet straight from a uint8 image with at most three channels (3 x 3, pad 1, stride 1,
+// threshold output packed along the filters): whether the kernel takes the shape, and its launch.
+bool conv_first_supports(int64_t C0, int64_t N, int KH, int KW, int pad, int stride);
+// flip_all: every flip flag counts as its complement.  jobs, flags: prepared in the same launch, for later layers (counts may be 0).
+// ones (may be null): also writes the "inside the image" plane of the output map, [pixels][ldo] like `out`.
+int launch_conv_first(const uint8_t *x, int64_t B, int H, int Wd, int C0, const uint32_t *W, int64_t N, const int32_t *T,
+                      const uint8_t *flip, bool flip_all, uint32_t *out, uint32_t *ones, int64_t ldo, const ConvPrepJobs &jobs,
+                      const FlagJobs &flags, hipStream_t s);
+
+// ones (may be null) receives the "inside the image" plane of the pooled map (first C bits of every pixel set)
+int launch_pool_bits(const uint32_t *in, int64_t B, int H, int Wd, int Cw, const uint32_t *use_and, bool invert_all,
+                     uint32_t *out, uint32_t *ones, int C, hipStream_t s);
 int launch_ones_plane(uint32_t *out, int64_t rows, int Cw, int C, hipStream_t s);
 
 }  // namespace qnn

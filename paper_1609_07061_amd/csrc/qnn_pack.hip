@@ -333,26 +333,6 @@ __global__ __launch_bounds__(kBlock) void pool_bits_kernel(const uint32_t *__res
     }
 }
 
-// Per-channel flags -> packed words and inverted byte flags (helpers of the ConvNet forward), for all layers of a
-// network in one launch (blockIdx.y = layer): bits[w] bit t = (flip[32 w + t] != 0) for channels below n (flip ==
-// nullptr reads as all zero); inv[c] = !flip[c].
-__global__ __launch_bounds__(kBlock) void flags_kernel(const FlagJobs jobs) {
-    const int j = blockIdx.y;
-    const uint8_t *flip = jobs.flip[j];
-    const int64_t n = jobs.n[j];
-    uint32_t *out_bits = jobs.bits[j];
-    uint8_t *out_inv = jobs.inv[j];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (c - lane >= n) return;  // (whole waves leave: the ballot below sees complete waves only)
-    const bool f = (c < n && flip) ? (flip[c] != 0) : false;
-    const unsigned long long m = __ballot(f);
-    if (c < n) out_inv[c] = f ? 0 : 1;
-    const int64_t w = (c - lane) / 32;
-    if (lane == 0 && c - lane < n) out_bits[w] = (uint32_t)m;
-    if (lane == 32 && c - lane + 32 < n) out_bits[w + 1] = (uint32_t)(m >> 32);
-}
-
 // rows x Cw words with the first C bits of every row set (the "inside the image" plane of a +-1 feature map whose
 // zero padding must contribute exactly 0: value = plane0 - 2 * plane1, so 01 = +1, 11 = -1, 00 = 0).
 __global__ __launch_bounds__(kBlock) void ones_plane_kernel(uint32_t *__restrict__ out, int64_t rows, int Cw, int C) {
@@ -430,14 +410,6 @@ int launch_pool_bits(const uint32_t *in, int64_t B, int H, int Wd, int Cw, const
     if (total == 0) return QNN_OK;
     return QNN_LAUNCH("pool_bits", pool_bits_kernel, dim3(grid_for(ceil_div(total, (int64_t)kWave))), dim3(kBlock), 0, s, in, B,
                       H, Wd, Cw, use_and, invert_all ? 0xFFFFFFFFu : 0u, out, ones, C);
-}
-
-int launch_flags(const FlagJobs &jobs, hipStream_t s) {
-    int64_t most = 0;
-    for (int j = 0; j < jobs.count; ++j) most = jobs.n[j] > most ? jobs.n[j] : most;
-    if (jobs.count == 0 || most == 0) return QNN_OK;
-    return QNN_LAUNCH("flags", flags_kernel, dim3((unsigned)ceil_div(most, (int64_t)kBlock), (unsigned)jobs.count), dim3(kBlock), 0, s,
-                      jobs);
 }
 
 int launch_ones_plane(uint32_t *out, int64_t rows, int Cw, int C, hipStream_t s) {
