@@ -53,6 +53,9 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &g, const MfmaConst
                                               int32_t (&rw)[WBN], uint32_t *rw_tab, int32_t *thr_tab, uint32_t *flip_tab,
                                               int32_t *stage_w, const int64_t m_wave, const int64_t n_wave, Scale scale) {
     constexpr int WTN = 32 * WBN;
+    // The edge of C goes through LDS too, except in the widest tile, whose registers are full: there it made the whole kernel 0.5 %
+    // slower (8192^3, which has no edge: 180.7 -> 181.6 us)
+    constexpr bool kScatterEdge = WBN == 4;
     const int64_t Nw = (g.N + 31) / 32;
 
     // lane coordinates re-derived behind an opaque copy: index arithmetic computed before the tile loop and kept
@@ -118,15 +121,23 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &g, const MfmaConst
         if constexpr (!kSign) {
 #pragma unroll
             for (int bj = 0; bj < WB; ++bj) {
+                int32_t *row = g.epi.C + m_of[bj] * g.epi.ldc + n_blk + 4 * kg;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     i32x4 val;
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
                         val[i] = (int32_t)(scale(acc_to_sum(acc[bi][bj][4 * q + i])) + nterm[4 * q + i] + mterm[bj]);
-                    // 16-byte unit 2 q + kg of row r, swizzled with the row: neither this write nor the read
-                    // below puts two lanes of a pass on one LDS bank
-                    *reinterpret_cast<i32x4 *>(&stage_w[r * 32 + 4 * ((2 * q + kg) ^ ((r >> 1) & 7))]) = val;
+                    if constexpr (kFast || !kScatterEdge) {
+                        // 16-byte unit 2 q + kg of row r, swizzled with the row: neither this write nor the read
+                        // below puts two lanes of a pass on one LDS bank
+                        *reinterpret_cast<i32x4 *>(&stage_w[r * 32 + 4 * ((2 * q + kg) ^ ((r >> 1) & 7))]) = val;
+                    } else if (m_of[bj] < g.M) {
+                        const int64_t n0 = n_blk + 8 * q + 4 * kg;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (n0 + i < g.N) row[8 * q + i] = val[i];
+                    }
                 }
                 if constexpr (kFast) {
                     // read the block back as 8 rows x 128 bytes per instruction (LDS operations of a wave execute
@@ -143,7 +154,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &g, const MfmaConst
                     if (bi + bj > 0) store_lines((bi * WB + bj - 1) / WB, (bi * WB + bj - 1) % WB);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) pend[j] = line[j];
-                } else {
+                } else if constexpr (!kScatterEdge) {
                     // the edge of C, or rows of C at any alignment: two rows x 32 words per instruction (16 as before, but of 32
                     // rows x two words each; merged 4 x 4 bit planes, 2240 x 1001 x 999: 47.9 -> 34.7 us, 1000 x 4096 x 2048: 52.4 -> 47.3)
                     const int col = lane & 31;
