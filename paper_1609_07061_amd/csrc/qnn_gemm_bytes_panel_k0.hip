@@ -56,8 +56,9 @@ __global__ __launch_bounds__(256) void expand_weights_kernel(const uint32_t *__r
 //   row q of an 8 x 32 bit matrix whose transpose holds, per element, the byte sum_q 2^q (b_q xor inv_q), which is the value
 //   plus the sum of the negative multipliers' magnitudes (`neg_sum`, subtracted byte-wise); `twice` doubles that first
 //   (sign-mode planes: 2 b - 1).  Half of the transposition falls away where no plane is above 2^3 (`low`).
-// Bound: vector instructions and the latency of one load (a wave has one word per lane).  Planes come from the host in the order
-// of their powers, which leaves out 64 selects a thread: 2240 and 4096 rows x 2048 of 4 planes 11 -> 8 us.
+// Bound: the latency of one load and one store per thread and, behind a product, the drain of its stores (2240 and 4096 rows x 2048
+// of 4 planes: 7.8 us behind a quantizer, 13 us behind a product of 37 MB).  Planes come from the host in the order of their powers, so
+// that nothing is sorted here.
 // Slot i of src, inv: the plane with 2^i (pow2) or plane i; -1: none.
 struct MergeOperand {
     const uint32_t *planes;

@@ -1,10 +1,11 @@
 // Matrix-core kernel for products of ordinary size whose rows can be anything: odd widths, rows that start at any word,
 // several bit planes, convolutions (the larger sibling of qnn_gemm_slice.hip; same digits, same operands).
 //
-// Bound: matrix cores and the vector instructions that make their operands, about one for one.  A workgroup of four waves owns a
-// 128 x 128 tile of C, a wave 64 x 64 of it (2 x 2 blocks: 28 vector instructions per operand block and 256 elements against
-// 512 matrix-core cycles for the four products), three workgroups share a compute unit (two where both operands have two planes)
-// and fill each other's waits.
+// Bound: the vector instructions that make the operands, 13 to 19 per matrix-core instruction by the counters (about twice the
+// matrix cores' time), and the waits between them.  A workgroup of four waves owns a 128 x 128 tile of C, a wave 64 x 64 of it (2 x 2
+// blocks, so that an operand feeds two products); three workgroups share a compute unit (two where both operands have two planes) and
+// fill each other's waits.  1999 x 3001 x 2500: 84.5 -> 19.8 us against one operand row per lane; 2-bit convolution 256 x 13 x 13, 384 ->
+// 256 channels: 62.6 -> 26.9 us against planes merged to bytes in LDS.
 //   * Loads: a wave reads sixteen rows x 64 contiguous bytes, or eight x 128, per instruction (an instruction whose 64 lanes read
 //     64 rows costs the address path of the compute unit 64 cycles, eight rows 16 to 19), 16 bytes per lane at any 4-byte
 //     alignment, a group ahead of the multiplication, into registers.  A group is four pieces of a row: of eight, the loads in
