@@ -45,7 +45,9 @@ struct SliceArgs {
     uint32_t ppt, taps;    // pixels: 16-byte pieces per tap, taps
     uint32_t magic_ppt, magic_kw;  // ceil(2^32 / .)
     uint32_t inv_hw, inv_w;        // pixels: floor(2^32 / .) of the output map's pixels and width (2^32 - 1 for 1)
-    uint32_t alpha, c0;  // C = alpha (S - row corrections) + c0
+    // C = alpha_sum S - alpha (row corrections) + c0; S counts a +-1 plane that is multiplied as 0 / 1 with its bit, not with twice its
+    // bit, and alpha_sum is alpha times two for every operand of such planes
+    uint32_t alpha, alpha_sum, c0;
     int corrected;       // some digit has an offset: row sums are taken
     int modified;        // some digit has an inverted or an absent plane
     int sum_a, sum_w;    // the left / right operand's row sums are wanted

@@ -14,7 +14,7 @@
 //     the sign bit set where the bit is clear.  Two 0/1 planes whose coefficients are c and 2c up to signs: ONE nibble,
 //     0.5 (b0 + 2 b1), i.e. one product where the planes one by one would take two.  The planes' powers of two are the block
 //     scales of the instruction.  Everything is a multiple of the coefficients' common factor and the sums stay
-//     below 2^24 of it (the host checks), so the float accumulation is exact.
+//     below 2^23 of it (the host checks), so the float accumulation is exact.
 //   Phase t of a chunk multiplies bit t of every nibble of a lane's four words (both operands use the same order of k).
 #include "qnn_gemm_slice.h"
 
@@ -289,8 +289,9 @@ bool make_digits(const Planes &pl, int64_t plane_stride, bool bits, SliceOperand
             e.offset2 = bits ? 1 : 0;
         else
             e.offset2 += d[p] < 0 ? 2 : 0;
-        // a set first bit is worth 1 (kPm1), 0.5 (kPair), 0.5 / 1 / 2 / 1 in phases 0 .. 3 (kOne) as an operand
-        const int one = 127 + e.lg;
+        // a set first bit is worth 1 (kPm1), 0.5 (kPair), 0.5 / 1 / 2 / 1 in phases 0 .. 3 (kOne) as an operand; the factor 2 of a +-1
+        // plane multiplied as 0 / 1 is left to the epilogue (alpha_sum), so that |S| has the bound of the values' sums
+        const int one = 127 + lg[p];
         e.scale = kind == kPm1 ? one * 0x01010101 : (kind == kPair ? (one + 1) * 0x01010101 : one * 0x01010101 + 1 - 0x10000);
     }
     gcd_out = gcd, sum_abs_over_gcd = sum;
@@ -321,14 +322,17 @@ bool slice_args(const GemmArgs &g, bool bits, SliceArgs &sc, int &kind_a, int &k
         if ((int64_t)g.A.Ho * g.A.Wo > 0x7FFFFFFFLL) return false;
         sc.inv_hw = inverse((int64_t)g.A.Ho * g.A.Wo), sc.inv_w = inverse(g.A.Wo);
     }
-    // exact float sums: |S| in units of the common factors stays below 2^24 (2^23, as the common factor itself: 24-bit products)
+    // |S| in units of the common factors stays below 2^23: exact float sums, and with |alpha_sum| below 2^23 a 24-bit product in the
+    // tiled kernel's epilogue.  (The same conditions whether or not +-1 planes enter as 0 / 1: what one kernel takes the other takes.)
     if ((long double)sa * (long double)sw * 256.0L * sc.chunks >= 8388608.0L) return false;
-    if (ga * gw >= 8388608 || ga * gw <= -8388608) return false;
+    const int64_t twice = (g.pa.mode == QNN_PLANE_SIGN ? 2 : 1) * (g.pw.mode == QNN_PLANE_SIGN ? 2 : 1);
+    if (ga * gw * twice >= 8388608 || ga * gw * twice <= -8388608) return false;
     // 32-bit byte offsets
     const long double a_words = pix ? (long double)g.M / ((long double)g.A.Ho * g.A.Wo) * g.A.H * g.A.Wd * g.A.Cw : (long double)g.M * g.A.ld;
     if (4.0L * a_words >= 4294967296.0L || 4.0L * (long double)g.N * g.ldw >= 4294967296.0L) return false;
     if (g.M > 0x7FFFFF00LL || g.N > 0x7FFFFF00LL) return false;
     sc.alpha = (uint32_t)(ga * gw);
+    sc.alpha_sum = (uint32_t)(ga * gw * (bits ? twice : 1));
     // offsets of the digits (see make_fields): the constant part, over every processed element
     int64_t constant = 0;
     for (int i = 0; i < sc.a.count; ++i)

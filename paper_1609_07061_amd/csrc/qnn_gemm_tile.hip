@@ -281,8 +281,9 @@ __global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) v
     }
     __syncthreads();
     float *const stage = reinterpret_cast<float *>(lds) + wave * (32 * kStagePitch);
-    const int alpha = (int)sc.alpha;  // (sums and alpha are below 2^23 in magnitude: a 24-bit product, full rate)
-    auto times_alpha = [alpha](const float s) __attribute__((always_inline)) { return __mul24((int)s, alpha); };
+    // (the host has checked that the sums and alpha_sum are below 2^23 in magnitude: a 24-bit product, full rate)
+    const int alpha_sum = (int)sc.alpha_sum;
+    auto times_alpha = [alpha_sum](const float s) __attribute__((always_inline)) { return __mul24((int)s, alpha_sum); };
     const int64_t n_wave = (int64_t)n0 + 64 * wn;
     const bool vec = (g.epi.ldc % 4 == 0) && (reinterpret_cast<uintptr_t>(g.epi.C) % 16 == 0);
     if constexpr (kMap) {

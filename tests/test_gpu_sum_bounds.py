@@ -1,0 +1,91 @@
+"""The FP4 kernels for products of any size at the largest sums that their float accumulation takes: every bit set, every weight of one
+sign, row lengths just inside the bound that the host checks (sum |coefA| sum |coefW| 256 ceil(K / 256) < 2^23) and at the first lengths
+where the sum of the bits' products, which is two or four times that of the values if an operand's bits stand for +-1, needs more than 23 bits."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from qnn_testlib import host, host_u32
+
+pytestmark = pytest.mark.gpu
+
+U = [1 << p for p in range(8)]
+# planes and modes of both operands, row length
+CASES = [(U, 0, [1], 1, 16449), (U, 0, [1], 1, 20001), (U, 0, [1], 1, 32700), (U[:7], 0, [1], 1, 65500), (U[:6], 0, [1], 1, 66600),
+         (U[:7], 1, U[:7], 0, 261), (U[:7], 1, U[:7], 0, 511), (U, 0, U[:4], 1, 1097), (U[:4], 1, U, 0, 2047), (U[:4], 1, U[:4], 1, 18690),
+         ([3, -6], 0, [-5], 1, 20001)]
+
+
+def _rows(count, planes, K, seed):
+    """Packed planes of `count` rows and their bits as fp64 [planes][rows][K]: all set, all clear, one in two, random."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    bits = torch.zeros((planes, count, K), dtype=torch.uint8, device="cuda")
+    bits[:, 0::4] = 1
+    bits[:, 2::4, ::2] = 1
+    bits[:, 3::4] = torch.randint(0, 2, bits[:, 3::4].shape, generator=g, device="cuda", dtype=torch.uint8)
+    Kw = (K + 31) // 32
+    full = torch.nn.functional.pad(bits, (0, 32 * Kw - K)).reshape(planes, count, Kw, 32)
+    words = torch.zeros((planes, count, Kw), dtype=torch.int64, device="cuda")
+    for i in range(32):
+        words |= full[..., i].to(torch.int64) << i
+    return torch.where(words >= 1 << 31, words - (1 << 32), words).to(torch.int32), bits
+
+
+def _values(bits, coef, mode):
+    out = torch.zeros(bits.shape[1:], dtype=torch.float64, device="cuda")
+    for p, c in enumerate(coef):
+        out += float(c) * (bits[p].double() if mode == 0 else 2.0 * bits[p].double() - 1.0)
+    return out
+
+
+# tiles of 128 x 128 (196 of them), 64 x 64, 32 x 32
+@pytest.mark.parametrize("M,N", [(1700, 1700), (700, 1000), (33, 40)])
+@pytest.mark.parametrize("ca,ma,cw,mw,K", CASES)
+def test_saturated_operands(M, N, ca, ma, cw, mw, K):
+    import paper_1609_07061_amd as q
+
+    A, bits_a = _rows(M, len(ca), K, 1)
+    W, bits_w = _rows(N, len(cw), K, 2)
+    va, vw = _values(bits_a, ca, ma), _values(bits_w, cw, mw)
+    want = (va @ vw.t().contiguous()).to(torch.int32)  # (below 2^31: exact in fp64)
+    got = q.qnn_bitplane_gemm(A, ca, ma, W, cw, mw, K)
+    assert torch.equal(got, want), (M, N, K, int((got != want).sum()))
+    rows = [0, 1, 2, 3, M - 1]
+    assert np.array_equal(host(got)[rows], oracle.gemm_int(host(va[rows].to(torch.int32)), host(vw.to(torch.int32))))
+    # thresholds that the sums of row 0 meet exactly, miss by one, and exceed by one
+    T = want[0] + torch.arange(N, device="cuda", dtype=torch.int32) % 3 - 1
+    bit = host((want >= T[None]).to(torch.uint8))
+    got = q.qnn_bitplane_gemm_sign(A, ca, ma, W, cw, mw, K, T)
+    assert np.array_equal(host_u32(got), oracle.pack_bits(np.where(bit != 0, 1, -1).astype(np.int8))), (M, N, K)
+
+
+@pytest.mark.parametrize("M,N", [(1700, 1700), (40, 33)])
+@pytest.mark.parametrize("K", [(1 << 21) - 31, (1 << 21) + 33, (1 << 22) - 161])
+def test_long_rows_of_signs(M, N, K):
+    """+-1 x +-1 up to the longest rows that the kernels take."""
+    import paper_1609_07061_amd as q
+
+    Kw = (K + 31) // 32
+    last = (1 << (K % 32)) - 1 if K % 32 else -1
+    patterns = torch.tensor([-1, 0, 0x55555555, 0x0F0F0F0F], dtype=torch.int32, device="cuda")
+    tail = patterns & last
+
+    def rows(count):
+        which = torch.arange(count, device="cuda") % 4
+        r = patterns[which][:, None].repeat(1, Kw)
+        r[:, -1] = tail[which]
+        return r, which
+
+    def ones(x):
+        return sum((x >> i) & 1 for i in range(32)).to(torch.int64)
+
+    (A, ia), (W, iw) = rows(M), rows(N)
+    differ = ones(patterns[:, None] ^ patterns[None]) * (Kw - 1) + ones(tail[:, None] ^ tail[None])
+    want = (K - 2 * differ).to(torch.int32)[ia][:, iw]
+    got = q.qnn_binary_gemm(A, W, K)
+    assert torch.equal(got, want), (M, N, K, int((got != want).sum()))
+    T = want[0] + torch.arange(N, device="cuda", dtype=torch.int32) % 3 - 1
+    got = q.qnn_binary_gemm_sign(A, W, K, T)
+    bit = host((want >= T[None]).to(torch.uint8))
+    assert np.array_equal(host_u32(got), oracle.pack_bits(np.where(bit != 0, 1, -1).astype(np.int8))), (M, N, K)
