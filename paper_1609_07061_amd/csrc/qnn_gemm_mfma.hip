@@ -422,12 +422,14 @@ bool backward_bytes_preferred(const BackwardArgs &b) {
     return true;
 }
 
-int launch_backward_bytes(const BackwardArgs &b, int8_t *gt, hipStream_t s) {
+int launch_backward_bytes(const BackwardArgs &b, int8_t *gt, bool &no_memory, hipStream_t s) {
     const int64_t pn = values_pitch(b.N), pm = values_pitch(b.M);
     const size_t size_g = (size_t)b.M * pn, size_gt = gt ? 0 : (size_t)b.N * pm, size_w = (size_t)b.K * (pn > pm ? pn : pm);
     const size_t sums = ((size_t)(b.M + b.N) * 4 + 255) / 256 * 256;
     PoolMemory mem(s);
-    if (int rc = mem.take(sums + size_g + size_gt + size_w)) return rc;
+    const int taken = mem.take(sums + size_g + size_gt + size_w);
+    no_memory = taken != QNN_OK;
+    if (no_memory) return taken;
     int32_t *row_sums = static_cast<int32_t *>(mem.ptr), *col_sums = row_sums + b.M;
     int8_t *g8 = static_cast<int8_t *>(mem.ptr) + sums;  // (all sizes are multiples of 128)
     if (!gt) gt = g8 + size_g;

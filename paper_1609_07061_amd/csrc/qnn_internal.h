@@ -122,7 +122,8 @@ bool slice_preferred(const GemmArgs &g, int route);
 int launch_gemm_slice(const GemmArgs &g, hipStream_t s);
 int launch_gemm_tile(const GemmArgs &g, hipStream_t s);
 // Both products of the backward step from bytes (g_a = g W into gA, g_W = g^T a into gW): whether they take this way, and the
-// launches.  gt: where the transposed gradient goes if it holds N * roundup(M, 128) bytes, else null.
+// launches.  gt: where the transposed gradient goes if it holds N * roundup(M, 128) bytes, else null.  no_memory: the stream's pool could
+// not supply the operands; nothing has been launched then.
 struct BackwardArgs {
     Planes pg;
     const uint32_t *G, *W, *A;
@@ -131,7 +132,7 @@ struct BackwardArgs {
     int64_t ld_ga, ld_gw, M, N, K;
 };
 bool backward_bytes_preferred(const BackwardArgs &b);
-int launch_backward_bytes(const BackwardArgs &b, int8_t *gt, hipStream_t s);
+int launch_backward_bytes(const BackwardArgs &b, int8_t *gt, bool &no_memory, hipStream_t s);
 bool panel_takes(const GemmArgs &g);  // whether the FP4 route would use the panel-fed kernel
 
 // Expansion of packed +-1 weights (N rows of K elements) to one int8 per element (row pitch ld_out, a multiple of 128,

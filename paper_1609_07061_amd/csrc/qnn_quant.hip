@@ -479,9 +479,11 @@ extern "C" int qnn_binary_backward(const uint32_t *G, int Pg, const int32_t *coe
     const bool valid = (modeG == QNN_PLANE_BIT || modeG == QNN_PLANE_SIGN) && b.strideG >= 0 && aligned4(G) && aligned4(gA) && aligned4(gW);
     if (valid && backward_bytes_preferred(b)) {
         // (eight planes of the transposed gradient take as much of the workspace as its bytes)
-        if ((rc = launch_backward_bytes(b, Pg == 8 ? reinterpret_cast<int8_t *>(Gt) : nullptr, st))) return rc;
-        note_engine(QNN_ENGINE_MFMA_LDS);
-        return QNN_OK;
+        bool no_memory;
+        rc = launch_backward_bytes(b, Pg == 8 ? reinterpret_cast<int8_t *>(Gt) : nullptr, no_memory, st);
+        if (rc == QNN_OK) note_engine(QNN_ENGINE_MFMA_LDS);
+        // a pool that cannot hold the operands of both products may hold those of one, which the way below asks for
+        if (!no_memory) return rc;
     }
     // g_a = g W: the reduction runs over n, so W (N x K, packed along k) is needed packed along n
     if ((rc = launch_transpose(W, N, K, ldw_words, 0, 1, Wt, ldn, 0, pad ? ldn : words_for(N), st))) return rc;
