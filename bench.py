@@ -265,7 +265,7 @@ def main():
             extra["backward_hidden_layer_8bit_gradients"] = {
                 "parity_sample_ok": bool(ok), "ms": msb if ok else None,
                 "effective_integer_tmacs": imac / (msb * 1e-3) / 1e12 if ok else None,
-                "note": "LogQuant of the fp32 gradient to 8 planes, three bit transposes, two 8-plane x 1-plane products"}
+                "note": "LogQuant of the fp32 gradient to 8 planes, gradient to bytes in both orders, weights and activations transposed to bytes, two int8 products"}
 
         jobs.append((2, job_bwd))
 
@@ -507,7 +507,7 @@ def main():
     peak = ENGINE_PEAK[used]
     roof = {"bound": "alu" if used == 1 else "mfma", "achieved": tops3, "peak": peak, "unit": "TOP/s", "frac": tops3 / peak,
             "traffic": None,
-            "kernel": {1: "gemm_valu_kernel", 2: "gemm_mfma_kernel", 3: "gemm_panel_kernel<false, 4, false, false>"}[used],
+            "kernel": {1: "gemm_valu_kernel", 2: "gemm_mfma_kernel", 3: "gemm_panel_kernel<false, 4, false>"}[used],
             "peak_dtype": {1: "integer vector ALU: one xor and one popcount-accumulate per 32 MACs",
                            2: "int8 dense MFMA, int32 accumulate",
                            3: "fp4 (E2M1) dense MFMA, fp32 accumulate"}[used],

@@ -304,9 +304,10 @@ int qnn_conv2d_dedup(const uint32_t *A, int Pa, const int32_t *coefA, int64_t st
                      uint32_t *unique_count, void *workspace, size_t workspace_bytes, void *stream);
 size_t qnn_conv2d_dedup_workspace_bytes(int64_t B, int64_t H, int64_t Wd, int64_t Cin, int64_t Cout, int pad);
 
-/* Engine (QNN_ENGINE_VALU, QNN_ENGINE_MFMA or QNN_ENGINE_MFMA_FP4) that the calling thread's last successful multiply call used; 0 before
- * any.  With QNN_ENGINE_AUTO it names the class of the product (QNN_ENGINE_VALU: small or irregular, ...); the library may run a
- * product of any class on its FP4 matrix-core kernels for arbitrary sizes.  For reports: results never depend on it. */
+/* Engine (QNN_ENGINE_VALU, QNN_ENGINE_MFMA, QNN_ENGINE_MFMA_FP4 or QNN_ENGINE_MFMA_LDS) that ran the calling thread's last successful
+ * multiply call; 0 before any.  QNN_ENGINE_MFMA_FP4 covers every kernel on the FP4 matrix cores: with QNN_ENGINE_AUTO also those for
+ * products of several planes and of any size, which the engine asked for by name does not take.  For reports: results never depend on
+ * it. */
 int qnn_last_engine(void);
 
 /* Engines of the multiply launches made by the calling thread's last successful multiply / forward call, in launch

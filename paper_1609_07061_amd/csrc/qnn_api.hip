@@ -106,18 +106,20 @@ int resolve_engine(const GemmArgs &g, int engine, int &chosen) {
     return QNN_OK;
 }
 
-// `chosen` is the route; if the library made the choice itself (`free_choice`), a product that the sliced kernel does faster
-// goes there.
+// `chosen` is the route; if the library made the choice itself (`free_choice`), a product that the FP4 kernels for any size do faster
+// goes there, and that is the engine on record.
 int launch_on(const GemmArgs &g, int chosen, bool free_choice, hipStream_t s) {
     int rc;
-    if (free_choice && slice_preferred(g, chosen))
+    if (free_choice && slice_preferred(g, chosen)) {
         rc = launch_gemm_slice(g, s);
-    else if (chosen == QNN_ENGINE_VALU)
+        chosen = QNN_ENGINE_MFMA_FP4;
+    } else if (chosen == QNN_ENGINE_VALU) {
         rc = launch_gemm_valu(g, s);
-    else if (chosen == QNN_ENGINE_MFMA_LDS)
+    } else if (chosen == QNN_ENGINE_MFMA_LDS) {
         rc = launch_gemm_stage(g, s);
-    else
+    } else {
         rc = launch_gemm_mfma(g, s, chosen == QNN_ENGINE_MFMA_FP4);
+    }
     if (rc == QNN_OK) {
         g_last_engine = chosen;
         if (g_engine_count < 2 * QNN_MAX_LAYERS) g_engines[g_engine_count++] = chosen;
@@ -747,7 +749,6 @@ int run_net(const NetPlan &plan, hipStream_t s) {
                 break;
             case NetStep::kGemm:
                 rc = launch_on(st.g, st.engine, plan.free_choice, s);
-                if (rc == QNN_OK && st.a) g_last_engine = g_engines[g_engine_count - 1] = st.a;  // (a: the class to report, if not the engine)
                 break;
             case NetStep::kFirstConv:
                 // src = image, mask = weights, dst = output bits; rows = B, a / b / c = H / W / C0, n = filters;
@@ -915,10 +916,6 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
                                co, 3, 3, 1, 1, e, engine, st.g, empty))
             return rc;
         if (int rc = choose(st.g, st.engine)) return rc;
-        // (convolutions of at least 256 pixels and whole, power-of-two groups of 128 channels belong to the FP4 class wherever they
-        // run)
-        if (l > 0 && engine == QNN_ENGINE_AUTO && B * h * w >= 256 && h > 1 && w > 1 && cin % 128 == 0 && ((cin / 128) & (cin / 128 - 1)) == 0)
-            st.a = QNN_ENGINE_MFMA_FP4;
         }
         if (pool[l] && !pooled_along) {
             NetStep &pl = push();

@@ -33,6 +33,23 @@ def dev(a: np.ndarray) -> torch.Tensor:
     return torch.from_numpy(a).cuda()
 
 
+def kernels_of(call) -> list:
+    """The library's kernels that `call` launches, in order, by name and template arguments ("gemm_tile_kernel<0, 0, 0, false>")."""
+    import re
+
+    from torch.profiler import ProfilerActivity, profile
+
+    call()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    events = sorted((e.time_range.start, e.name) for e in p.events() if "qnn::" in e.name)
+    found = [re.search(r"(\w+_kernel(?:<[^>]*>)?)\(", name) for _, name in events]
+    assert events and all(found), events
+    return [f.group(1) for f in found]
+
+
 def host_u32(t: torch.Tensor) -> np.ndarray:
     return t.cpu().numpy().view(np.uint32)
 

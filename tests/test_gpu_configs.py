@@ -17,9 +17,9 @@ pytestmark = pytest.mark.gpu
 
 q = None
 VALU, MFMA, FP4, MFMA_LDS = 1, 2, 3, 4
-# engine AUTO picks per configuration; bench.py reports the same ones
-AUTO_ENGINE = {"c1": VALU, "c3": FP4, "c4": MFMA_LDS, "c5": MFMA_LDS}
-AUTO_ENGINES_C2 = [MFMA, FP4, FP4, VALU]  # first layer from the 8-bit codes, two hidden layers, 10-neuron output layer
+# engine that runs per configuration with AUTO; bench.py reports the same ones
+AUTO_ENGINE = {"c1": FP4, "c3": FP4, "c4": FP4, "c5": MFMA_LDS}
+AUTO_ENGINES_C2 = [MFMA, FP4, FP4, FP4]  # first layer from the 8-bit codes, two hidden layers, 10-neuron output layer
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -209,12 +209,12 @@ def test_many_tiles_short_k_threshold_output(seed, M, N, K, engine):
     assert_same(got[:, :ldo - 3], oracle.pack_bits(oracle.threshold(oracle.gemm_pm1(a, w), T, flip)))
 
 
-# K a multiple of 1024 and 16-byte aligned rows: the kernel that is fed from LDS panels.  (4000, 8100): 16 x 32 tiles of
-# 256 x 256, two per workgroup, ragged on both edges; (4200, 4360): 17 x 35 tiles of 256 x 128 (chosen because 17 x 18
-# large tiles would leave 40 % of the second round idle); (1000, 700): fewer tiles than workgroups, three groups of K;
-# (6000, 8500): 24 x 34 tiles, three or four per workgroup; (5000, 7000) with K = 4096: 20 x 28 = 560 tiles of
-# 256 x 256, two whole rounds of 256 workgroups and 48 tiles that are halved and shared out among 96 workgroups.
-# (9000, 128, 2048): 128 columns, which 256-column tiles would pad to twice the work: 36 tiles of 256 x 128.
+# K a multiple of 1024 and 16-byte aligned rows: the kernel that is fed from LDS panels (AUTO takes the tiled kernels for the smaller
+# ones; engine FP4 always the panels).  (4000, 8100): 16 x 32 tiles of 256 x 256, two per workgroup, ragged on both edges; (4200, 4360):
+# 17 x 35 tiles of 256 x 128 (chosen because 17 x 18 large tiles would leave 40 % of the second round idle); (1000, 700): fewer tiles than
+# workgroups, three groups of K; (6000, 8500): 24 x 34 tiles, three or four per workgroup; (5000, 7000) with K = 4096: 20 x 28 = 560 tiles
+# of 256 x 256, two whole rounds of 256 workgroups and 48 tiles that are halved and shared out among 96 workgroups.  (9000, 128, 2048):
+# 128 columns, which 256-column tiles would pad to twice the work: 36 tiles of 256 x 128.
 PANEL_TILES = [(4000, 8100, 1024), (4200, 4360, 2048), (1000, 700, 3072), (6000, 8500, 1024), (5000, 7000, 4096),
                (9000, 128, 2048)]
 
@@ -227,7 +227,7 @@ def test_panel_fed_kernel_int32_output(seed, M, N, K, engine):
     ldc = N + 4 * (K // 1024 - 1)
     out = torch.full((M, ldc), -7, dtype=torch.int32, device="cuda")
     q.qnn_binary_gemm(dev(np_pack_pm1(a)), dev(np_pack_pm1(w)), K, out=out[:, :N], engine=engine)
-    check_engine(engine, FP4 if M >= 4000 else 1)
+    check_engine(engine, FP4)
     got = host(out)
     assert (got[:, N:] == -7).all()
     assert_same(got[:, :N], oracle.gemm_pm1(a, w))
@@ -244,7 +244,7 @@ def test_panel_fed_kernel_threshold_output(seed, M, N, K, engine):
     out = torch.full((M, ldo), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
     q.qnn_binary_gemm_sign(dev(np_pack_pm1(a)), dev(np_pack_pm1(w)), K, dev(T), dev(flip), out=out[:, :ldo - 2],
                            engine=engine)
-    check_engine(engine, FP4 if M >= 4000 else 1)
+    check_engine(engine, FP4)
     got = host_u32(out)
     assert (got[:, ldo - 2:] == 0x5A5A5A5A).all()
     assert_same(got[:, :ldo - 2], oracle.pack_bits(oracle.threshold(oracle.gemm_pm1(a, w), T, flip)))
@@ -275,7 +275,7 @@ def test_many_tiles_first_layer_planes_threshold_output(seed, engine):
     kw = {} if engine is None else {"engine": engine}
     got = q.qnn_bitplane_gemm_sign(dev(xp), [1 << p for p in range(8)], q.PLANE_BIT, dev(np_pack_pm1(w)[None]), [1],
                                    q.PLANE_SIGN, K, dev(T), None, **kw)
-    check_engine(engine or 0, MFMA_LDS)
+    check_engine(engine or 0, FP4)
     assert_same(host_u32(got), oracle.pack_bits(oracle.threshold(oracle.gemm_int(x, w.astype(np.int32)), T)))
 
 
@@ -287,7 +287,7 @@ def test_many_tiles_int4_times_int4(seed, engine):
     coef = [1, 2, 4, -8]
     got = q.qnn_bitplane_gemm(dev(np_pack_bits(oracle.split_planes(a, 4))), coef, q.PLANE_BIT,
                               dev(np_pack_bits(oracle.split_planes(w, 4))), coef, q.PLANE_BIT, K, engine=engine)
-    check_engine(engine or 0, MFMA_LDS)
+    check_engine(engine or 0, FP4)
     assert_same(host(got), oracle.gemm_int(a, w))
 
 
@@ -334,15 +334,14 @@ def test_large_multi_plane_product_whose_values_exceed_a_byte(seed):
         q.qnn_bitplane_gemm(dev(np_pack_bits(pa)), ca, 0, dev(np_pack_bits(pw)), cw, 1, K, engine=MFMA_LDS)
 
 
-@pytest.mark.parametrize("Cin,auto", [(64, MFMA), (128, MFMA_LDS)])
-@pytest.mark.parametrize("engine", [None, MFMA])
-def test_many_tiles_conv(seed, engine, Cin, auto):
+@pytest.mark.parametrize("Cin,engine", [(64, None), (64, MFMA), (128, None), (128, MFMA), (128, MFMA_LDS)])
+def test_many_tiles_conv(seed, engine, Cin):
     """26 images of 13 x 13 pixels, 64 or 128 -> 4200 channels: 18 x 17 tiles of the implicit-im2col kernels (128
-    channels are four words per pixel, which AUTO gives to the kernel that merges the planes in LDS)."""
+    channels are four words per pixel, which the kernel that merges the planes in LDS needs)."""
     B, H, Wd, Cout = 26, 13, 13, 4200
     u = qi.uniform_int(seed, 80, (B, H, Wd, Cin), 0, 3)
     w = qi.pm1(seed, 81, (Cout, 3, 3, Cin))
     got = q.qnn_bitplane_conv2d(dev(np_pack_bits(oracle.split_planes(u, 2))), [1, 2], q.PLANE_BIT, Cin,
                                 dev(np_pack_pm1(w)[None]), [1], q.PLANE_SIGN, 1, 1, engine=engine)
-    check_engine(engine or 0, auto)
+    check_engine(engine or 0, FP4)
     assert_same(host(got), oracle.conv2d(u, w.astype(np.int32), 1, 1))

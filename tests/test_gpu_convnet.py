@@ -1,13 +1,15 @@
 """Binarized ConvNet forward (Alg. 4 on the network shape of App. A) against the oracle, logits element by element:
 small networks that exercise odd sizes, channel tails, pooling with flipped channels and every engine preference,
 and the CIFAR-10 ConvNet of the paper's table at a batch the oracle finishes in seconds."""
+import re
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
 import qnn_inputs as qi
-from qnn_testlib import dev, host, np_pack_pm1
+from qnn_testlib import dev, host, kernels_of, np_pack_pm1
 
 pytestmark = pytest.mark.gpu
 
@@ -67,32 +69,45 @@ def test_convnet_small(seed, B, H, Wd, C0, couts, pools, fcs, engine):
     assert np.array_equal(_run(q, case, couts, fcs, engine), want)
 
 
+# the kernels of a convolution behind the first layer: on the map's plane "value is -1", or as a product of any size on its 2-bit code
+MAP, SLICE = r"gemm_tile_kernel<\d, \d, \d, true>", r"gemm_slice_kernel<.*"
+
+
+def _products(q, case, couts, fcs, engine=0):
+    """The multiply kernels of a forward pass, one a layer."""
+    return [k for k in kernels_of(lambda: _run(q, case, couts, fcs, engine)) if k.startswith(("conv_first", "gemm"))]
+
+
 @pytest.mark.parametrize("with_flip", [True, False])
-def test_convnet_ragged_shapes_on_the_panel_fed_convolution(seed, with_flip):
-    """Non-square maps of 10 x 14 pixels, 420 pixels per batch (one whole tile of 256 rows and a ragged one), 256 channels
-    into 200 filters (a ragged tile of filters) and 200 channels into 64 (not a multiple of 128: another kernel)."""
+def test_convnet_ragged_shapes(seed, with_flip):
+    """Non-square maps of 10 x 14 pixels, 420 pixels per batch (three tiles of 128 rows and a ragged one), 256 channels into 200 filters
+    (a ragged tile of filters) and 200 channels into 64: fewer than 48 tiles per layer, so both on the small tiles; on the map's plane
+    if the FP4 engine is asked for."""
     import paper_1609_07061_amd as q
 
     couts, pools, fcs = [256, 200, 64], [0, 0, 1], [10]
-    x, conv_w, pools, fc_w, T, flip = _case(seed, 3, 10, 14, 3, couts, pools, fcs, 1800)
+    case = _case(seed, 3, 10, 14, 3, couts, pools, fcs, 1800)
+    x, conv_w, pools, fc_w, T, flip = case
     want = oracle.convnet(x, conv_w, pools, fc_w, T, flip if with_flip else None)
-    got = _run(q, (x, conv_w, pools, fc_w, T, flip), couts, fcs, with_flip=with_flip)
-    assert np.array_equal(got, want)
-    engines = q.qnn_last_engines()
-    assert engines[0] == 2 and engines[1] == 3 and engines[2] != 3, engines
+    for engine, kernel in ((q.ENGINE_AUTO, SLICE), (q.ENGINE_MFMA_FP4, MAP)):
+        got = _run(q, case, couts, fcs, engine=engine, with_flip=with_flip)
+        assert np.array_equal(got, want)
+        engines, kernels = q.qnn_last_engines(), _products(q, case, couts, fcs, engine)
+        assert engines[1:3] == [3, 3] and len(kernels) == 4, (engines, kernels)
+        assert all(re.fullmatch(kernel, k) for k in kernels[1:3]), kernels
+    assert q.qnn_last_engines()[0] != 2  # (asked for FP4: the first layer goes through the image's planes)
 
 
-def test_convnet_panel_fed_convolution_with_1024_channels(seed):
-    """1024 channels into 40 filters: the patch's 9216 bits are nine whole groups of 1024, so every step of a tile's last
-    group is multiplied (with 128, 256 or 512 channels some are padding and are left out)."""
+def test_convnet_convolution_with_1024_channels(seed):
+    """1024 channels into 40 filters: patches of 9216 bits, every chunk of 256 full."""
     import paper_1609_07061_amd as q
 
     couts, pools, fcs = [1024, 40, 32], [0, 0, 1], [6]
     case = _case(seed, 2, 8, 16, 3, couts, pools, fcs, 1900)
     want = oracle.convnet(*case)
-    assert np.array_equal(_run(q, case, couts, fcs), want)
-    engines = q.qnn_last_engines()
-    assert engines[0] == 2 and engines[1] == 3, engines
+    for engine in (q.ENGINE_AUTO, q.ENGINE_MFMA_FP4):
+        assert np.array_equal(_run(q, case, couts, fcs, engine), want)
+        assert q.qnn_last_engines()[1] == 3
 
 
 def test_convnet_first_convolution_over_several_turns_per_wave(seed):
@@ -108,9 +123,8 @@ def test_convnet_first_convolution_over_several_turns_per_wave(seed):
     assert q.qnn_last_engines()[0] == 2
 
 
-def test_convnet_panel_fed_convolution_over_several_tiles_per_workgroup(seed):
-    """75 images of 31 x 31 pixels and 128 channels: 72 075 pixels are 282 tiles of 256 rows (the last one ragged) for the
-    256 persistent workgroups, so some of them take a second tile."""
+def test_convnet_convolution_of_more_tiles_than_the_chip_holds(seed):
+    """75 images of 31 x 31 pixels and 128 channels: 72 075 pixels are 564 tiles of 128 rows, the last one ragged."""
     import paper_1609_07061_amd as q
 
     couts, pools, fcs = [128, 128], [0, 1], [10]
@@ -118,6 +132,7 @@ def test_convnet_panel_fed_convolution_over_several_tiles_per_workgroup(seed):
     want = oracle.convnet(*case)
     assert np.array_equal(_run(q, case, couts, fcs), want)
     assert q.qnn_last_engines()[:2] == [2, 3]
+    assert re.fullmatch(MAP, _products(q, case, couts, fcs)[1])
 
 
 def test_convnet_without_flips(seed):
@@ -141,5 +156,8 @@ def test_convnet_cifar10_architecture(seed):
     assert np.array_equal(got, want)
     engines = q.qnn_last_engines()
     # first layer: the byte kernel for images of up to three channels, reported as the matrix-core engine; the other
-    # convolutions (128, 256, 512 channels in): the panel-fed FP4 kernel on the maps' sign planes
-    assert len(engines) == 9 and engines[0] == 2 and all(e == 3 for e in engines[1:6]), engines
+    # convolutions: the tiled FP4 kernel on the maps' sign planes; fully connected layers of 64 rows: FP4 on small tiles
+    assert engines == [2] + [3] * 8, engines
+    kernels = _products(q, case, couts, fcs)
+    assert kernels[0] == "conv_first_kernel" and all(re.fullmatch(MAP, k) for k in kernels[1:6]), kernels
+    assert all(re.fullmatch(SLICE, k) for k in kernels[6:]), kernels
