@@ -40,7 +40,8 @@ __device__ __forceinline__ void load_thresholds_to_lds(const GemmArgs &g, const 
 
 // Accumulator register v of block [bi][bj] is C[m][n] with
 //   m = m_wave + 32 bj + (lane mod 32),   n = n_wave + 32 bi + 8 (v / 4) + 4 (lane / 32) + v mod 4.
-// kFast: the wave tile lies completely inside C and C allows 16-byte stores, so nothing needs a bounds check.
+// kTile: kInside, the wave tile lies completely inside C and C allows 16-byte stores, so nothing needs a bounds check; kLower (int32
+// sums), the same but for rows beyond the last; kAny, anything else.
 // ra, rw: this lane's partial row sums of the raw codes (activation rows / weight rows of the wave tile); rw_tab,
 // thr_tab, flip_tab (128 entries each) and stage_w (32 x 32 int32) are this wave's LDS areas.  thr_tab / flip_tab
 // arrive holding the thresholds and flip flags (0 / non-zero) of columns n_wave .. n_wave + 32 WBN - 1, brought in by
@@ -48,11 +49,13 @@ __device__ __forceinline__ void load_thresholds_to_lds(const GemmArgs &g, const 
 // of the same kind: waiting until at most that many loads are outstanding means the tables have landed, while the
 // operand loads for the next tile stay in flight.
 // kRwInLds: rw_tab already holds the weight rows' terms (brought in like the thresholds); rw is not used.
-template <bool kSign, int WBN, bool kFast, int kLoadsAfter, bool kRwInLds, int WB, typename Acc, typename Scale>
+enum TileKind { kInside, kLower, kAny };
+template <bool kSign, int WBN, TileKind kTile, int kLoadsAfter, bool kRwInLds, int WB, typename Acc, typename Scale>
 __device__ __forceinline__ void wave_epilogue(const GemmArgs &g, const MfmaConst &mc, Acc (&acc)[WBN][WB], int32_t (&ra)[WB],
                                               int32_t (&rw)[WBN], uint32_t *rw_tab, int32_t *thr_tab, uint32_t *flip_tab,
                                               int32_t *stage_w, const int64_t m_wave, const int64_t n_wave, Scale scale) {
     constexpr int WTN = 32 * WBN;
+    constexpr bool kFast = kTile != kAny;
     // The edge of C goes through LDS too, except in the widest tile, whose registers are full: there it made the whole kernel 0.5 %
     // slower (8192^3, which has no edge: 180.7 -> 181.6 us)
     constexpr bool kScatterEdge = WBN == 4;
@@ -99,14 +102,15 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &g, const MfmaConst
         __builtin_amdgcn_s_waitcnt(0xc07f);
         __builtin_amdgcn_wave_barrier();
     }
-    // kFast int32 output: lines of the block before the current one, read from LDS and not stored yet; lane
+    // kInside, kLower int32 output: lines of the block before the current one, read from LDS and not stored yet; lane
     // (row = lane / 8, 16-byte unit = lane mod 8) of store j writes row 8 j + lane / 8 of the block
     i32x4 pend[4];
     int32_t *const line_base = kSign ? nullptr : g.epi.C + (m_wave + (lane >> 3)) * g.epi.ldc + n_wave + 4 * (lane & 7);
     auto store_lines = [&](const int pbi, const int pbj) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            *reinterpret_cast<i32x4 *>(line_base + (int64_t)(pbj * 32 + 8 * j) * g.epi.ldc + pbi * 32) = pend[j];
+            if (kTile == kInside || m_wave + pbj * 32 + 8 * j + (lane >> 3) < g.M)
+                *reinterpret_cast<i32x4 *>(line_base + (int64_t)(pbj * 32 + 8 * j) * g.epi.ldc + pbi * 32) = pend[j];
     };
 #pragma unroll
     for (int bi = 0; bi < WBN; ++bi) {
@@ -155,7 +159,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &g, const MfmaConst
 #pragma unroll
                     for (int j = 0; j < 4; ++j) pend[j] = line[j];
                 } else if constexpr (!kScatterEdge) {
-                    // the edge of C, or rows of C at any alignment: two rows x 32 words per instruction (16 as before, but of 32
+                    // the right edge of C, or rows of C at any alignment: two rows x 32 words per instruction (16 as before, but of 32
                     // rows x two words each; merged 4 x 4 bit planes, 2240 x 1001 x 999: 47.9 -> 34.7 us, 1000 x 4096 x 2048: 52.4 -> 47.3)
                     const int col = lane & 31;
                     const int32_t *const unit = stage_w + (lane & 3);
@@ -228,28 +232,35 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &g, const MfmaConst
     if constexpr (kFast && !kSign) store_lines(WBN - 1, WB - 1);
 }
 
-// Chooses the epilogue variant for a finished wave tile (interior or edge, scale by shift or by multiplication).
+// Chooses the epilogue variant for a finished wave tile (interior or edge, scale by shift or by multiplication).  Tiles at the lower edge
+// alone keep the whole-line stores: with the word stores of kAny they were the last to finish (256 x 128 tiles, 10000 x 512 x 2048:
+// 16.4 -> 13.4 us, 1000 x 4096 x 2048 17.7 -> 14.1; merged 4 x 4 bit planes, 2240 x 4096 x 2048: 46.8 -> 43.8).  Not in the widest
+// tile, whose registers are full.
 template <bool kSign, int WBN, int kLoadsAfter, bool kRwInLds = false, int WB, typename Acc>
 __device__ __forceinline__ void wave_finish(const GemmArgs &g, const MfmaConst &mc, Acc (&acc)[WBN][WB], int32_t (&ra)[WB],
                                             int32_t (&rw)[WBN], uint32_t *rw_tab, int32_t *thr_tab, uint32_t *flip_tab,
                                             int32_t *stage_w, const int64_t m_wave, const int64_t n_wave) {
-    const bool interior = m_wave + 32 * WB <= g.M && n_wave + 32 * WBN <= g.N;
+    const bool rows_inside = m_wave + 32 * WB <= g.M, columns_inside = n_wave + 32 * WBN <= g.N;
     const bool wide = kSign || ((g.epi.ldc % 4 == 0) && (reinterpret_cast<uintptr_t>(g.epi.C) % 16 == 0));
-    const bool fast = interior && wide;
+    auto finish = [&](auto scale) __attribute__((always_inline)) {
+        if (wide && columns_inside && rows_inside) {
+            wave_epilogue<kSign, WBN, kInside, kLoadsAfter, kRwInLds>(g, mc, acc, ra, rw, rw_tab, thr_tab, flip_tab, stage_w, m_wave, n_wave, scale);
+            return;
+        }
+        if constexpr (!kSign && WBN < 4) {
+            if (wide && columns_inside) {
+                wave_epilogue<kSign, WBN, kLower, kLoadsAfter, kRwInLds>(g, mc, acc, ra, rw, rw_tab, thr_tab, flip_tab, stage_w, m_wave, n_wave, scale);
+                return;
+            }
+        }
+        wave_epilogue<kSign, WBN, kAny, kLoadsAfter, kRwInLds>(g, mc, acc, ra, rw, rw_tab, thr_tab, flip_tab, stage_w, m_wave, n_wave, scale);
+    };
     if (mc.alpha_shift >= 0) {
         const int sh = mc.alpha_shift;
-        auto scale = [sh](uint32_t x) { return x << sh; };
-        if (fast)
-            wave_epilogue<kSign, WBN, true, kLoadsAfter, kRwInLds>(g, mc, acc, ra, rw, rw_tab, thr_tab, flip_tab, stage_w, m_wave, n_wave, scale);
-        else
-            wave_epilogue<kSign, WBN, false, kLoadsAfter, kRwInLds>(g, mc, acc, ra, rw, rw_tab, thr_tab, flip_tab, stage_w, m_wave, n_wave, scale);
+        finish([sh](uint32_t x) { return x << sh; });
     } else {
         const uint32_t al = mc.alpha;
-        auto scale = [al](uint32_t x) { return x * al; };
-        if (fast)
-            wave_epilogue<kSign, WBN, true, kLoadsAfter, kRwInLds>(g, mc, acc, ra, rw, rw_tab, thr_tab, flip_tab, stage_w, m_wave, n_wave, scale);
-        else
-            wave_epilogue<kSign, WBN, false, kLoadsAfter, kRwInLds>(g, mc, acc, ra, rw, rw_tab, thr_tab, flip_tab, stage_w, m_wave, n_wave, scale);
+        finish([al](uint32_t x) { return x * al; });
     }
 }
 

@@ -36,3 +36,20 @@ def test_merged_products(seed, M, N, K, ca, ma, cw, mw):
     assert bool((wide[:, 0] == 7).all()) and bool((wide[:, 1 + N:] == 7).all())
     rows = np.array([0, M - 1])
     assert np.array_equal(host(C)[rows], oracle.gemm_int(va[rows].astype(np.int32), vw.astype(np.int32)))
+
+
+@pytest.mark.parametrize("rows", [1, 31, 33, 127, 200])
+def test_rows_below_the_last_one_are_not_written(seed, rows):
+    """Tiles cut by the last row of C alone, with 16-byte stores: 256 x 128 tiles of single planes, 256- and 128-row tiles of bytes."""
+    import paper_1609_07061_amd as q
+
+    M, N, K = 768 + rows, 1024, 1024
+    a, w = qi.bernoulli_bits(seed, 1410, (2, M, K)), qi.bernoulli_bits(seed, 1411, (N, K))
+    A, W = dev(np_pack_bits(a)), dev(np_pack_bits(w[None]))
+    vw = 2 * w.astype(np.int32) - 1
+    for planes, coef, mode, engine in ((A[:1], [1], 1, q.ENGINE_MFMA_FP4), (A, [1, 2], 0, q.ENGINE_MFMA_LDS)):
+        out = torch.full((M + 40, N), -7, dtype=torch.int32, device="cuda")
+        q.qnn_bitplane_gemm(planes, coef, mode, W, [1], 1, K, out=out[:M], engine=engine)
+        va = 2 * a[0].astype(np.int32) - 1 if mode == 1 else a[0].astype(np.int32) + 2 * a[1]
+        got = host(out)
+        assert np.array_equal(got[:M], oracle.gemm_int(va, vw)) and (got[M:] == -7).all(), (rows, engine)
