@@ -43,7 +43,7 @@ def test_rows_below_the_last_one_are_not_written(seed, rows):
     """Tiles cut by the last row of C alone, with 16-byte stores: 256 x 128 tiles of single planes, 256- and 128-row tiles of bytes."""
     import paper_1609_07061_amd as q
 
-    M, N, K = 768 + rows, 1024, 1024
+    M, N, K = 768 + rows, 1024, 3072  # (products of fewer than 2^31 elements are not merged to bytes)
     a, w = qi.bernoulli_bits(seed, 1410, (2, M, K)), qi.bernoulli_bits(seed, 1411, (N, K))
     A, W = dev(np_pack_bits(a)), dev(np_pack_bits(w[None]))
     vw = 2 * w.astype(np.int32) - 1
