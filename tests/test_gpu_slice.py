@@ -12,8 +12,8 @@ from qnn_testlib import dev, host, host_u32, np_pack_bits, np_pack_pm1
 
 pytestmark = pytest.mark.gpu
 
-# 32 x 32, 64 x 64 and 128 x 128 tiles (by the number of tiles), ragged on both edges
-SHAPES = [(1, 1), (31, 33), (65, 32), (640, 1025), (1601, 2049)]
+# 32 x 32 tiles on up to sixteen waves and, where there are many, on four; 64 x 64 (two shapes); 128 x 128; ragged on both edges
+SHAPES = [(1, 1), (31, 33), (65, 32), (16500, 20), (640, 1025), (1601, 2049), (1601, 3300)]
 KS = [97, 128, 129, 255, 257, 1024, 1056, 2049]
 
 
@@ -43,7 +43,7 @@ def test_any_row_length_and_pitch(seed, M, N, K):
 # pairs of consecutive powers of two with every combination of signs, gaps between powers, common factors, both modes
 PLANES = [([1, 2], 0, [1], 1), ([1, -2], 0, [-1, 2], 0), ([-1, -2, 4], 0, [3], 0), ([1, 2, 4, -8], 0, [1, 2, 4, -8], 0),
           ([4, 1], 0, [2, -16], 0), ([-3, 6, 12], 1, [5, 10], 0), ([1, -4], 1, [-2, 1], 1), ([-5], 0, [1], 1), ([1], 1, [-2, 4], 0),
-          ([1 << p for p in range(8)], 0, [1], 1)]
+          ([3], 0, [1, -2], 0), ([1], 0, [-4], 0), ([1 << p for p in range(8)], 0, [1], 1)]
 
 
 @pytest.mark.parametrize("M,N,K", [(33, 65, 300), (700, 1100, 1100), (1700, 2000, 131)])

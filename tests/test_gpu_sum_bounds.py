@@ -60,7 +60,7 @@ def test_saturated_operands(M, N, ca, ma, cw, mw, K):
     assert np.array_equal(host_u32(got), oracle.pack_bits(np.where(bit != 0, 1, -1).astype(np.int8))), (M, N, K)
 
 
-@pytest.mark.parametrize("M,N", [(1700, 1700), (40, 33)])
+@pytest.mark.parametrize("M,N", [(1700, 3400), (700, 1000), (40, 33)])
 @pytest.mark.parametrize("K", [(1 << 21) - 31, (1 << 21) + 33, (1 << 22) - 161])
 def test_long_rows_of_signs(M, N, K):
     """+-1 x +-1 up to the longest rows that the kernels take."""
