@@ -195,7 +195,7 @@ __device__ __forceinline__ Piece piece_of(const GemmArgs &g, const SliceArgs &sc
 }
 
 // The kernels' arguments for a product and the kinds of its operands; false if they cannot take it.  bits: +-1 planes as kOne (with
-// corrections from row sums) instead of kPm1, and single 0/1 planes as kOne instead of kPair.
+// corrections from row sums) instead of kPm1, and a lone 0/1 plane on the right as kOne instead of kPair (on the left it always is).
 bool slice_args(const GemmArgs &g, bool bits, SliceArgs &sc, int &kind_a, int &kind_w);
 
 }  // namespace slice

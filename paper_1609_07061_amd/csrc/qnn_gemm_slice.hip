@@ -5,7 +5,7 @@
 // chain (one workgroup walking the whole of k behind a barrier per step) on a fraction of the compute units.  So here
 //   * a workgroup owns a small tile of C (32 x 32 or 64 x 64) and its waves share k between them: wave w takes the 256-element
 //     chunks w, w + waves, ... of every plane pair, and the partial sums meet once, in LDS, at the end (one barrier in the
-//     whole kernel);
+//     whole kernel, two with 64 x 64 tiles);
 //   * a wave loads the packed words of its operand rows straight into registers, four words per lane, one chunk ahead of the
 //     multiplication.  16-byte loads at any 4-byte alignment; the last piece of a row is read four words from the row's end
 //     and the words that an earlier piece has brought already are cleared, so nothing beyond a row is read and K, leading
@@ -25,12 +25,18 @@ using namespace slice;
 namespace {
 
 // BMb x BNb blocks of 32 x 32 per wave; up to kMaxWaves waves share k.
+// Waves per SIMD that the registers have to allow: four workgroups with 64 x 64 tiles of single planes, two with pairs of planes (180 to
+// 220 registers; held to three they spill: convolutions of 2-bit maps with few tiles are 3 to 8 % slower).
+constexpr int waves_per_simd(int ka, int kw, int blocks) { return blocks == 2 && (ka == kPair || kw == kPair) ? 2 : 4; }
 template <int kA, int kW, int kRows, int BMb, int BNb, int kMaxWaves>
-__global__ __launch_bounds__(64 * kMaxWaves, kMaxWaves == 4 ? 2 : 4) void gemm_slice_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
+__global__ __launch_bounds__(64 * kMaxWaves, waves_per_simd(kA, kW, BMb)) void gemm_slice_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
     constexpr bool kPixels = kRows != kMatrix;
     constexpr int BM = 32 * BMb, BN = 32 * BNb, kPitch = BN + 4;
     constexpr int NA = kA == kPair ? 2 : 1, NW = kW == kPair ? 2 : 1;  // planes of a digit
-    __shared__ __attribute__((aligned(16))) float part[kMaxWaves][BM][kPitch];
+    // partial sums: a slot per wave; with 64 x 64 tiles half as many (see below), so that four workgroups fit on a compute unit and not two
+    // (convolution of a 0/1 map 64 x 56 x 56, 16 -> 32 channels of 5 x 5: 79.3 -> 37.3 us, with the lone plane by itself)
+    constexpr uint32_t kSlots = BMb == 2 ? kMaxWaves / 2 : kMaxWaves;
+    __shared__ __attribute__((aligned(16))) float part[kSlots][BM][kPitch];
     __shared__ int part_a[kMaxWaves][BM], part_w[kMaxWaves][BN];
     const uint32_t t = threadIdx.x, lane = t & 63u, r = lane & 31u, kg = lane >> 5;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6), waves = blockDim.x >> 6;
@@ -130,8 +136,8 @@ __global__ __launch_bounds__(64 * kMaxWaves, kMaxWaves == 4 ? 2 : 4) void gemm_s
             const int sum = prepare(std::integral_constant<int, kW>{}, x.w[0][b], x.w[NW - 1][b], dw, x.skip, clear || kPixels, zw[0][b], zw[NW - 1][b]);
             if (corrected) corr_w[b] += ((sum * da.offset2) << shift) >> 1;
         }
-#pragma unroll
-        for (int ph = 0; ph < 4; ++ph) {
+        auto phase = [&](auto ph_tag) __attribute__((always_inline)) {
+            constexpr int ph = decltype(ph_tag)::value;
             v4i fa[BMb], fw[BNb];
 #pragma unroll
             for (int b = 0; b < BMb; ++b) fa[b] = make_operand<kA>(za[0][b], za[NA - 1][b], ph);
@@ -141,14 +147,18 @@ __global__ __launch_bounds__(64 * kMaxWaves, kMaxWaves == 4 ? 2 : 4) void gemm_s
             for (int i = 0; i < BNb; ++i)
 #pragma unroll
                 for (int j = 0; j < BMb; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen(fw[i]), widen(fa[j]), acc[i][j], 4, 4, 0, dw.scale, 0, da.scale);
-        }
+                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen(fw[i]), widen(fa[j]), acc[i][j], 4, 4, ph, dw.scale, ph, da.scale);
+        };
+        phase(std::integral_constant<int, 0>{});
+        phase(std::integral_constant<int, 1>{});
+        phase(std::integral_constant<int, 2>{});
+        phase(std::integral_constant<int, 3>{});
     };
 
     // this wave's items: (digit pair, chunk) number wave, wave + waves, ... with the chunks innermost
     const uint32_t pairs = (uint32_t)(sc.a.count * sc.w.count);
     // waves that have an item (workgroups of more than four waves are made no larger)
-    const uint32_t parts = pairs * sc.chunks > waves ? waves : pairs * sc.chunks;
+    const uint32_t parts = kMaxWaves > 4 || pairs * sc.chunks > waves ? waves : pairs * sc.chunks;
     uint32_t pair = 0, c = wave;
     auto settle = [&]() __attribute__((always_inline)) {
         while (c >= sc.chunks && pair < pairs) c -= sc.chunks, ++pair;
@@ -174,27 +184,46 @@ __global__ __launch_bounds__(64 * kMaxWaves, kMaxWaves == 4 ? 2 : 4) void gemm_s
     }
 
     // partial sums to LDS: register v of block [i][j] is C[m][n], m = 32 j + lane mod 32, n = 32 i + 8 (v / 4) + 4 kg + v mod 4
-    if (wave < parts) {
+    auto slot_of = [&](const uint32_t slot, const int i, const int j, const int q) __attribute__((always_inline)) {
+        return reinterpret_cast<f32x4 *>(&part[slot][32 * j + r][32 * i + 8 * q + 4 * kg]);
+    };
+    auto put = [&](const uint32_t slot) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < BNb; ++i)
 #pragma unroll
             for (int j = 0; j < BMb; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                    *reinterpret_cast<f32x4 *>(&part[wave][32 * j + r][32 * i + 8 * q + 4 * kg]) = v;
-                }
-        if (corrected) {
+                for (int q = 0; q < 4; ++q) *slot_of(slot, i, j, q) = f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+    };
+    if (kSlots < kMaxWaves && parts > kSlots) {
+        // the upper half of the waves leaves its sums to the lower half, each wave of which adds those of one slot to its own
+        if (wave >= kSlots && wave < parts) put(wave - kSlots);
+        __syncthreads();
+        if (wave + kSlots < parts) {
 #pragma unroll
-            for (int b = 0; b < BMb; ++b) {
-                const int v = corr_a[b] + __shfl_xor(corr_a[b], 32, 64);
-                if (kg == 0) part_a[wave][32 * b + r] = v;
-            }
+            for (int i = 0; i < BNb; ++i)
 #pragma unroll
-            for (int b = 0; b < BNb; ++b) {
-                const int v = corr_w[b] + __shfl_xor(corr_w[b], 32, 64);
-                if (kg == 0) part_w[wave][32 * b + r] = v;
-            }
+                for (int j = 0; j < BMb; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 v = *slot_of(wave, i, j, q);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += v[e];
+                    }
+        }
+    }
+    const uint32_t slots = parts < kSlots ? parts : kSlots;
+    if (wave < slots) put(wave);
+    if (corrected && wave < parts) {
+#pragma unroll
+        for (int b = 0; b < BMb; ++b) {
+            const int v = corr_a[b] + __shfl_xor(corr_a[b], 32, 64);
+            if (kg == 0) part_a[wave][32 * b + r] = v;
+        }
+#pragma unroll
+        for (int b = 0; b < BNb; ++b) {
+            const int v = corr_w[b] + __shfl_xor(corr_w[b], 32, 64);
+            if (kg == 0) part_w[wave][32 * b + r] = v;
         }
     }
     __syncthreads();
@@ -204,7 +233,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, kMaxWaves == 4 ? 2 : 4) void gemm_s
         for (uint32_t i = t; i < rows * (BN / 4); i += blockDim.x) {
             const uint32_t row = i / (BN / 4), col = 4u * (i % (BN / 4));
             f32x4 s = *reinterpret_cast<const f32x4 *>(&part[0][row][col]);
-            for (uint32_t w = 1; w < parts; ++w) s += *reinterpret_cast<const f32x4 *>(&part[w][row][col]);
+            for (uint32_t w = 1; w < slots; ++w) s += *reinterpret_cast<const f32x4 *>(&part[w][row][col]);
             int corr[4] = {0, 0, 0, 0};
             if (corrected)
                 for (uint32_t w = 0; w < parts; ++w)
@@ -233,7 +262,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, kMaxWaves == 4 ? 2 : 4) void gemm_s
         for (uint32_t row0 = wave * kRowsPerWave; row0 < rows; row0 += waves * kRowsPerWave) {
             const uint32_t row = row0 + lane / BN;  // (below BM: BM is a multiple of kRowsPerWave)
             float s = part[0][row][col];
-            for (uint32_t w = 1; w < parts; ++w) s += part[w][row][col];
+            for (uint32_t w = 1; w < slots; ++w) s += part[w][row][col];
             int corr = 0;
             if (corrected)
                 for (uint32_t w = 0; w < parts; ++w) corr += part_a[w][row] + part_w[w][col];
@@ -247,7 +276,8 @@ __global__ __launch_bounds__(64 * kMaxWaves, kMaxWaves == 4 ? 2 : 4) void gemm_s
 }
 
 // The digits of an operand; false if a coefficient is not the common factor times a power of two, or offsets leave 32 bits.
-bool make_digits(const Planes &pl, int64_t plane_stride, bool bits, SliceOperand &op, int &kind, int64_t &gcd_out, int64_t &sum_abs_over_gcd) {
+// bits: a +-1 plane as 0 / 1; one: a lone 0 / 1 plane by itself and not as half of a pair.
+bool make_digits(const Planes &pl, int64_t plane_stride, bool bits, bool one, SliceOperand &op, int &kind, int64_t &gcd_out, int64_t &sum_abs_over_gcd) {
     std::memset(&op, 0, sizeof(op));
     int64_t gcd = 0;
     for (int p = 0; p < pl.count; ++p) {
@@ -275,7 +305,7 @@ bool make_digits(const Planes &pl, int64_t plane_stride, bool bits, SliceOperand
         order[i] = p;
     }
     const bool sign = pl.mode == QNN_PLANE_SIGN;
-    kind = sign ? (bits ? kOne : kPm1) : (bits && pl.count == 1 ? kOne : kPair);
+    kind = sign ? (bits ? kOne : kPm1) : (one && pl.count == 1 ? kOne : kPair);
     for (int i = 0; i < pl.count; ++i) {
         SliceDigit &e = op.d[op.count++];
         const int p = order[i];
@@ -312,7 +342,7 @@ bool slice_args(const GemmArgs &g, bool bits, SliceArgs &sc, int &kind_a, int &k
     if (g.A.rows_are_bytes) return false;
     const bool pix = g.A.rows_are_pixels != 0;
     int64_t ga, gw, sa, sw;
-    if (!make_digits(g.pa, g.A.plane_stride, bits, sc.a, kind_a, ga, sa) || !make_digits(g.pw, g.strideW, bits, sc.w, kind_w, gw, sw)) return false;
+    if (!make_digits(g.pa, g.A.plane_stride, bits, true, sc.a, kind_a, ga, sa) || !make_digits(g.pw, g.strideW, bits, bits, sc.w, kind_w, gw, sw)) return false;
     const int64_t row_words = pix ? g.A.Cw : g.Kw;
     if (row_words < (pix ? 1 : 4)) return false;
     if (pix && (g.A.KH > 15 || g.A.KW > 15)) return false;  // (which taps lie inside the image: sixteen bits each way, one spare)
@@ -368,10 +398,14 @@ typedef void (*SliceFn)(const GemmArgs, const SliceArgs, uint32_t, uint32_t);
 template <int kRows, int BMb, int BNb, int kMaxWaves>
 SliceFn slice_kernel(int ka, int kw) {
     if (ka == kPm1) return kw == kPm1 ? gemm_slice_kernel<kPm1, kPm1, kRows, BMb, BNb, kMaxWaves> : gemm_slice_kernel<kPm1, kPair, kRows, BMb, BNb, kMaxWaves>;
+    if (ka == kOne) return kw == kPm1 ? gemm_slice_kernel<kOne, kPm1, kRows, BMb, BNb, kMaxWaves> : gemm_slice_kernel<kOne, kPair, kRows, BMb, BNb, kMaxWaves>;
     return kw == kPm1 ? gemm_slice_kernel<kPair, kPm1, kRows, BMb, BNb, kMaxWaves> : gemm_slice_kernel<kPair, kPair, kRows, BMb, BNb, kMaxWaves>;
 }
 template <int kRows>
-SliceFn slice_kernel(int ka, int kw, bool large) { return large ? slice_kernel<kRows, 2, 2, 4>(ka, kw) : slice_kernel<kRows, 1, 1, 16>(ka, kw); }
+SliceFn slice_kernel(int ka, int kw, bool large, bool four) {
+    if (large) return slice_kernel<kRows, 2, 2, 4>(ka, kw);
+    return four ? slice_kernel<kRows, 1, 1, 4>(ka, kw) : slice_kernel<kRows, 1, 1, 16>(ka, kw);
+}
 
 }  // namespace
 
@@ -414,7 +448,8 @@ int launch_gemm_slice(const GemmArgs &g, hipStream_t s) {
     // (never fewer than four waves: those without a chunk of k still share the epilogue; 64 x 64 tiles, 1000 x 1000 x 128: 7.1 -> 4.8 us)
     const int most = large ? 4 : 16, least = 4;
     const int waves = items < least ? least : (items < most ? (int)items : most);
-    const SliceFn fn = !pix ? slice_kernel<kMatrix>(ka, kw, large) : (g.A.Cw < 4 ? slice_kernel<kNarrowPatches>(ka, kw, large) : slice_kernel<kPatches>(ka, kw, large));
+    const bool four = waves == 4;
+    const SliceFn fn = !pix ? slice_kernel<kMatrix>(ka, kw, large, four) : (g.A.Cw < 4 ? slice_kernel<kNarrowPatches>(ka, kw, large, four) : slice_kernel<kPatches>(ka, kw, large, four));
     return QNN_LAUNCH("gemm_slice", fn, dim3((unsigned)(tiles_m * tiles_n)), dim3(64u * waves), 0, s, g, sc, (uint32_t)tiles_m, (uint32_t)tiles_n);
 }
 
