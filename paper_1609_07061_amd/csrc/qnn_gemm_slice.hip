@@ -436,21 +436,28 @@ int launch_gemm_slice(const GemmArgs &g, hipStream_t s) {
     int ka, kw;
     if (!slice_args(g, false, sc, ka, kw)) return fail(QNN_ERR_UNSUPPORTED, "sliced matrix-core kernel cannot take these arguments");
     const bool pix = g.A.rows_are_pixels != 0;
-    // Tile by the number of tiles: 128 x 128 where there are enough of them for the chip (2048^3, 256 tiles, 11.5 us against 13.9
-    // with 64 x 64; 1024 x 1024 x 4096, 64 tiles, 13.3 against 7.7; convolutions pay more per group of k: from 384 tiles on),
-    // 32 x 32 with k shared by up to sixteen waves where 64 x 64 tiles are few (256 x 1024 x 8192, 64 tiles, 5.9 against 9.6 us;
-    // 1000 x 1000 x 1000, 256 tiles, 5.8 against 5.2) or mostly padding.
-    if (ceil_div(g.M, 128) * ceil_div(g.N, 128) >= (pix ? 384 : 192) && g.M >= 96 && g.N >= 96) return launch_gemm_tile(g, s);
-    const bool large = ceil_div(g.M, 64) * ceil_div(g.N, 64) >= 160 && g.M > 32 && g.N > 32;
-    const int64_t items = (int64_t)sc.chunks * sc.a.count * sc.w.count;
-    const int64_t edge = large ? 64 : 32, tiles_m = ceil_div(g.M, edge), tiles_n = ceil_div(g.N, edge);
-    if (tiles_m * tiles_n > 0x7FFFFFFFLL) return fail(QNN_ERR_SHAPE, "gemm: too many tiles");
-    // (never fewer than four waves: those without a chunk of k still share the epilogue; 64 x 64 tiles, 1000 x 1000 x 128: 7.1 -> 4.8 us)
-    const int most = large ? 4 : 16, least = 4;
-    const int waves = items < least ? least : (items < most ? (int)items : most);
-    const bool four = waves == 4;
+    // Tile by the number of tiles (the lines are counts for 256 compute units): 128 x 128 where there are enough of them for the chip
+    // (1024 x 1024 x 4096, 64 tiles, 13.3 us against 7.7 with 64 x 64; convolutions pay more per group of k: from 384 tiles on), 32 x 32
+    // with k shared by up to sixteen waves where 64 x 64 tiles are few (256 x 1024 x 8192, 64 tiles, 5.9 against 9.6 us; 1000 x 1000 x
+    // 1000, 256 tiles, 5.8 against 5.2) or mostly padding.
+    // Single planes on both sides: four workgroups with 64 x 64 tiles share a compute unit, and while about one round of them is all
+    // there is they beat the larger tiles (GPU time, 128 x 128 -> 64 x 64: 1800 x 1800 x 500, 841 tiles, 9.8 -> 6.5 us, x 4000 17.9 -> 14.0;
+    // 40000 x 96 x 256, 1250 tiles, 11.2 -> 8.0; 1999 x 3001 x 2048, 1504 tiles, 18.2 -> 19.4), with threshold output only while k is
+    // short (1800 x 1800 x 500 7.5 -> 6.7, x 2048 11.0 -> 11.5).
+    const int64_t items = (int64_t)sc.chunks * sc.a.count * sc.w.count, tiles64 = ceil_div(g.M, 64) * ceil_div(g.N, 64);
+    const bool one_round = ka != kPair && kw != kPair && (g.epi.T ? tiles64 <= 1024 && items <= 2 : tiles64 <= 1280);
+    if (!one_round && ceil_div(g.M, 128) * ceil_div(g.N, 128) >= (pix ? 384 : 192) && g.M >= 96 && g.N >= 96) return launch_gemm_tile(g, s);
+    const bool large = tiles64 >= 160 && g.M > 32 && g.N > 32;
+    const int64_t edge = large ? 64 : 32, tiles_m = ceil_div(g.M, edge), tiles_n = ceil_div(g.N, edge), tiles = tiles_m * tiles_n;
+    if (tiles > 0x7FFFFFFFLL) return fail(QNN_ERR_SHAPE, "gemm: too many tiles");
+    // 32 x 32 tiles: four waves each where there are more tiles than workgroups of sixteen waves fit on the chip (100000 x 10 x 4096 25.6
+    // -> 17.6 us, 32768 outputs of 20 rows x 4096 with 4 x 4 planes 43.8 -> 34.3), unless the rows are long and the tiles not much more
+    // than that (20000 x 10 x 16384 17.0 against 18.5).  Never fewer than four: waves without a chunk of k still share the epilogue
+    // (64 x 64 tiles, 1000 x 1000 x 128: 7.1 -> 4.8 us).
+    const bool four = large || items <= 4 || (tiles > 512 && (tiles > 1024 || items <= 32));
+    const int waves = four ? 4 : (items < 16 ? (int)items : 16);
     const SliceFn fn = !pix ? slice_kernel<kMatrix>(ka, kw, large, four) : (g.A.Cw < 4 ? slice_kernel<kNarrowPatches>(ka, kw, large, four) : slice_kernel<kPatches>(ka, kw, large, four));
-    return QNN_LAUNCH("gemm_slice", fn, dim3((unsigned)(tiles_m * tiles_n)), dim3(64u * waves), 0, s, g, sc, (uint32_t)tiles_m, (uint32_t)tiles_n);
+    return QNN_LAUNCH("gemm_slice", fn, dim3((unsigned)tiles), dim3(64u * waves), 0, s, g, sc, (uint32_t)tiles_m, (uint32_t)tiles_n);
 }
 
 }  // namespace qnn

@@ -8,7 +8,7 @@ import torch
 
 import oracle
 import qnn_inputs as qi
-from qnn_testlib import dev, host, host_u32, np_pack_bits, np_pack_pm1
+from qnn_testlib import dev, host, host_u32, kernels_of, np_pack_bits, np_pack_pm1
 
 pytestmark = pytest.mark.gpu
 
@@ -90,3 +90,24 @@ def test_convolution_of_sign_maps_without_padding(seed, cin):
     a, w = qi.pm1(seed, 1230, (2, 9, 9, cin)), qi.pm1(seed, 1231, (37, 3, 3, cin))
     got = q.qnn_bitplane_conv2d(dev(np_pack_pm1(a)[None]), [1], q.PLANE_SIGN, cin, dev(np_pack_pm1(w)[None]), [1], q.PLANE_SIGN, 0, 1)
     assert np.array_equal(host(got), oracle.conv2d(a.astype(np.int32), w.astype(np.int32), 0, 1))
+
+
+def test_kernel_by_the_number_of_tiles():
+    """Which of the kernels the library takes (GPU of 256 compute units)."""
+    import paper_1609_07061_amd as q
+
+    def product(planes, M, N, K):
+        A = torch.zeros((planes, M, (K + 31) // 32), dtype=torch.int32, device="cuda")
+        W = torch.zeros((1, N, (K + 31) // 32), dtype=torch.int32, device="cuda")
+        mode = q.PLANE_SIGN if planes == 1 else q.PLANE_BIT
+        return kernels_of(lambda: q.qnn_bitplane_gemm(A, [1 << p for p in range(planes)], mode, W, [1], q.PLANE_SIGN, K))
+
+    small, many, large = "gemm_slice_kernel<0, 0, 0, 1, 1, 16>", "gemm_slice_kernel<0, 0, 0, 1, 1, 4>", "gemm_slice_kernel<0, 0, 0, 2, 2, 4>"
+    assert product(1, 20, 1000, 2000) == [small]
+    assert product(1, 20, 1000, 1000) == [many]          # four chunks of k, four waves
+    assert product(1, 20000, 10, 2000) == [many]         # 625 tiles
+    assert product(1, 20000, 10, 16000) == [small]       # ... of long rows
+    assert product(1, 1000, 1000, 300) == [large]
+    assert product(1, 40000, 96, 300) == [large]         # 1250 tiles
+    assert product(1, 1999, 3001, 300) == ["gemm_tile_kernel<2, 2, 0, false>"]
+    assert product(2, 1800, 1800, 300) == ["gemm_tile_kernel<1, 2, 0, false>"]
