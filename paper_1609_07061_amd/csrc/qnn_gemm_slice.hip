@@ -413,8 +413,12 @@ SliceFn slice_kernel(int ka, int kw, bool large, bool four) {
 //   vector-ALU route: everything (32 x 4096 x 4096 20 -> 4.5; 20 x 4096 x 2048 with 4 x 4 planes 134 -> 8; convolution of four
 //     13 x 13 maps, 384 -> 256 channels, 39 -> 5; 1000 x 1000 x 1000 8.7 -> 5.3);
 //   single planes that miss the panel-fed kernel's layout: everything (1999 x 3001 x 2500 82 -> 21; 8000^3 640 -> 234);
-//   single planes that fit it: while its 256 x 128 tiles leave compute units idle (256 x 1024 x 8192 24 -> 6; 8192 x 256 x 8192
-//     25 -> 14; 2048^3 12.9 -> 11.5), not beyond (4096^3 33 against 38);
+//   single planes that fit it, int32 sums: while 64 x 64 tiles make one round at most (256 x 1024 x 8192 24 -> 6; 10000 x 256 x 8192, 628
+//     tiles, 25 -> 19; 2048^3, 1024, 12.8 -> 11.2), and while the panels' 256 x 128 tiles leave compute units idle and rows are short
+//     (3000 x 2048, 192 such tiles, x 1024 11.2 -> 9.7, x 2048 13.4 and 13.7, x 4096 18.0 against 19.7, x 8192 26.8 against 32.5);
+//   the same with threshold output, which costs the panel-fed kernel less: while 64 x 64 tiles are few (512 x 4096 x 4096, 512 tiles, 14.7
+//     -> 11.4; 10000 x 256 x 2048, 628, 10.4 -> 10.3; 1500 x 2048 x 2048, 768, 10.6 against 11.2; 20000 x 256 x 4096, 1252, 15.0 against
+//     21.0);
 //   several planes merged in LDS: everything (256 maps, 2-bit activations, 64 -> 28; 1000 x 4096 x 2048 with 4 x 4 planes
 //     45 -> 30), but not large products of four digit pairs, which are faster as bytes: from 5e10 element products on (2240 x 4096 x
 //     2048 with 4 x 4 planes 45 against 57), or 3e10 where compute units hold two 128 x 128 tiles (2000 x 3000 x 1500 34 against 42,
@@ -423,7 +427,11 @@ bool slice_preferred(const GemmArgs &g, int route) {
     SliceArgs sc;
     int ka, kw;
     if (!slice_args(g, false, sc, ka, kw)) return false;
-    if (route == QNN_ENGINE_MFMA_FP4 && panel_takes(g)) return ceil_div(g.M, 256) * ceil_div(g.N, 128) < 256;
+    if (route == QNN_ENGINE_MFMA_FP4 && panel_takes(g)) {
+        const int64_t tiles64 = ceil_div(g.M, 64) * ceil_div(g.N, 64);
+        if (g.epi.T) return tiles64 <= 640;
+        return tiles64 <= 1024 || (g.K <= 2048 && ceil_div(g.M, 256) * ceil_div(g.N, 128) < 256);
+    }
     if (route == QNN_ENGINE_MFMA_LDS && sc.a.count * sc.w.count >= 4) {
         const long double work = (long double)g.M * (long double)g.N * (long double)g.K * (sc.a.count * sc.w.count);
         return work < (ceil_div(g.M, 128) * ceil_div(g.N, 128) > 256 ? 3e10L : 5e10L);

@@ -111,3 +111,23 @@ def test_kernel_by_the_number_of_tiles():
     assert product(1, 40000, 96, 300) == [large]         # 1250 tiles
     assert product(1, 1999, 3001, 300) == ["gemm_tile_kernel<2, 2, 0, false>"]
     assert product(2, 1800, 1800, 300) == ["gemm_tile_kernel<1, 2, 0, false>"]
+
+
+def test_panels_or_tiles_for_single_planes_of_whole_groups():
+    """Rows of whole 128-byte groups, which the panel-fed kernel takes too: by the number of tiles, the row length and the output."""
+    import paper_1609_07061_amd as q
+
+    def kernel(M, N, K, sign):
+        A = torch.zeros((M, K // 32), dtype=torch.int32, device="cuda")
+        W, T = torch.zeros((N, K // 32), dtype=torch.int32, device="cuda"), torch.zeros(N, dtype=torch.int32, device="cuda")
+        found = kernels_of(lambda: q.qnn_binary_gemm_sign(A, W, K, T) if sign else q.qnn_binary_gemm(A, W, K))
+        assert len(found) == 1
+        return found[0].split("<")[0]
+
+    panel, small, tile = "gemm_panel_kernel", "gemm_slice_kernel", "gemm_tile_kernel"
+    assert [kernel(10000, 256, K, False) for K in (1024, 8192)] == [small, small]        # 628 tiles of 64 x 64
+    assert [kernel(10000, 256, K, True) for K in (1024, 8192)] == [small, small]
+    assert [kernel(1500, 2048, K, True) for K in (1024, 8192)] == [panel, panel]         # 768
+    assert [kernel(3000, 2048, K, False) for K in (1024, 2048, 4096)] == [tile, tile, panel]  # 1504; 192 tiles of 256 x 128
+    assert [kernel(3000, 2048, K, True) for K in (1024, 4096)] == [panel, panel]
+    assert [kernel(3000, 4096, K, sign) for K in (1024, 4096) for sign in (False, True)] == [panel] * 4
