@@ -155,7 +155,7 @@ bool mfma_preferred(const GemmArgs &g) {
            g.N >= 256;
 }
 
-static int compute_units() {
+int compute_units() {
     static thread_local int cus = 0;
     if (cus == 0) {
         int dev = 0, n = 0;
@@ -178,16 +178,16 @@ struct BytesTiles {
     bool tail;
     int64_t tiles_m, tiles_n;
     unsigned grid;
+    double rounds;  // by that cost
 };
 static BytesTiles bytes_tiles(int64_t M, int64_t N, int cus) {
     constexpr double kRound[5] = {0.0, 0.0, 1.0, 1.22, 1.41}, kHalves = 1.03;
-    BytesTiles t = {4, false, 0, ceil_div(N, 256), 0};
-    double best = 0.0;
+    BytesTiles t = {4, false, 0, ceil_div(N, 256), 0, 0.0};
     for (int blocks = 4; blocks >= 2; --blocks) {
         const int64_t tiles_m = ceil_div(M, 64 * blocks), total = tiles_m * t.tiles_n, whole = total / cus, rest = total % cus;
         const bool tail = blocks == 4 && cus % 16 == 0 && whole > 0 && rest != 0 && 2 * rest <= cus;
         const double cost = kRound[blocks] * (double)whole + (tail ? kHalves : (rest ? kRound[blocks] : 0.0));
-        if (blocks == 4 || cost < best) t.blocks = blocks, t.tail = tail, t.tiles_m = tiles_m, t.grid = (unsigned)(total < cus ? total : cus), best = cost;
+        if (blocks == 4 || cost < t.rounds) t.blocks = blocks, t.tail = tail, t.tiles_m = tiles_m, t.grid = (unsigned)(total < cus ? total : cus), t.rounds = cost;
     }
     return t;
 }
@@ -443,6 +443,17 @@ int launch_backward_bytes(const BackwardArgs &b, int8_t *gt, bool &no_memory, hi
     if (rc == QNN_OK) rc = bytes_panel::launch_transpose_to_bytes(b.A, b.M, b.K, b.lda, reinterpret_cast<uint8_t *>(w8), pm, nullptr, 0, s);
     if (rc == QNN_OK) rc = launch_values_product(gw, gt, w8, pm, 2 * scale, col_sums, -scale, s);
     return mem.give_back(rc);
+}
+
+// Merged once per call: products of 300 x 300 to 128000 x 256 rows and 512 to 30000 elements of k within 10 % as a rule (merge of both
+// operands, groups of k by the tiles' rounds, store of C); merged per workgroup: rounds of 256 x 256 tiles (8192^3 of eight planes 881 us,
+// 10000 x 4096 x 4096 361, 8192 x 8192 x 1024 197).
+double stage_us(const GemmArgs &g) {
+    const double elements = (double)g.M * (double)g.N;
+    if (values_path(g))
+        return 13.0 + 0.87 * bytes_tiles(g.M, g.N, compute_units()).rounds * (double)ceil_div(g.K, bytes_panel::kGroupK) + 0.85e-6 * elements +
+               0.32e-6 * (double)(g.M + g.N) * (double)g.K;
+    return 5.0 + 25e-3 * (double)ceil_div(ceil_div(g.M, 256) * ceil_div(g.N, 256), compute_units()) * (double)g.K + 0.8e-6 * elements;
 }
 
 bool stage_supports(const GemmArgs &g) {

@@ -409,6 +409,18 @@ SliceFn slice_kernel(int ka, int kw, bool large, bool four) {
 
 }  // namespace
 
+// About how long a product takes on the tiled kernel (microseconds): a pair of digits costs a latency per element of k and, for each
+// tile of a compute unit, the making of its operands (375 products of 1 to 16 pairs within 7 % as a rule, at most 22).  Below 192 tiles,
+// which go to smaller ones, a rough figure (1024 x 1024 x 8192: 49 and 29 for 4 x 4 and 4 x 1 planes, measured 50 and 20).
+static double tile_us(const GemmArgs &g, const SliceArgs &sc, int ka, int kw) {
+    const int pairs_of_planes = (ka == kPair ? 1 : 0) + (kw == kPair ? 1 : 0);
+    constexpr double kLatency[3] = {0.9e-3, 1.2e-3, 0.9e-3}, kTile[3] = {1.3e-3, 1.6e-3, 2.0e-3}, kStore[3] = {0.53e-6, 0.53e-6, 0.76e-6};
+    const int64_t tiles = ceil_div(g.M, 128) * ceil_div(g.N, 128);
+    const double tiles_each = tiles < 192 ? (double)tiles / compute_units() : (double)ceil_div(tiles, compute_units());
+    const double k = 256.0 * sc.chunks * sc.a.count * sc.w.count;
+    return 2.8 + k * (kLatency[pairs_of_planes] + kTile[pairs_of_planes] * tiles_each) + kStore[pairs_of_planes] * (double)g.M * (double)g.N;
+}
+
 // Where the library's own choice goes to these kernels.  Measured (us, GPU time; route of the shape -> best of these):
 //   vector-ALU route: everything (32 x 4096 x 4096 20 -> 4.5; 20 x 4096 x 2048 with 4 x 4 planes 134 -> 8; convolution of four
 //     13 x 13 maps, 384 -> 256 channels, 39 -> 5; 1000 x 1000 x 1000 8.7 -> 5.3);
@@ -419,10 +431,10 @@ SliceFn slice_kernel(int ka, int kw, bool large, bool four) {
 //   the same with threshold output, which costs the panel-fed kernel less: while 64 x 64 tiles are few (512 x 4096 x 4096, 512 tiles, 14.7
 //     -> 11.4; 10000 x 256 x 2048, 628, 10.4 -> 10.3; 1500 x 2048 x 2048, 768, 10.6 against 11.2; 20000 x 256 x 4096, 1252, 15.0 against
 //     21.0);
-//   several planes merged in LDS: everything (256 maps, 2-bit activations, 64 -> 28; 1000 x 4096 x 2048 with 4 x 4 planes
-//     45 -> 30), but not large products of four digit pairs, which are faster as bytes: from 5e10 element products on (2240 x 4096 x
-//     2048 with 4 x 4 planes 45 against 57), or 3e10 where compute units hold two 128 x 128 tiles (2000 x 3000 x 1500 34 against 42,
-//     2240 x 2048 x 2048 37 against 42; below, 1500 x 4096 x 1000 30 against 26; 256 tiles: 1000 x 4096 x 2048 38 against 31).
+//   several planes that the kernels with merged planes take: everything that makes no 192 tiles of 128 x 128 (1024 x 1024 x 8192 with 4 x 4
+//     planes 81 -> 50; 1000 x 1000 x 16384 144 -> 100), and by the expected times else: the tiled kernel's time grows with the pairs of
+//     digits, that of merged planes does not (4096^3 with 4, 5, 7 planes x 1: 69, 101, 129 on tiles, 77 merged; 2240 x 4096 x 2048: 28,
+//     39, 51 and 42; 2 x 2 and 4 x 4 planes: 25, 62 and 42).  Of 375 products on both sides the choice cost 0.3 % of the time, at most 15 %.
 bool slice_preferred(const GemmArgs &g, int route) {
     SliceArgs sc;
     int ka, kw;
@@ -432,10 +444,7 @@ bool slice_preferred(const GemmArgs &g, int route) {
         if (g.epi.T) return tiles64 <= 640;
         return tiles64 <= 1024 || (g.K <= 2048 && ceil_div(g.M, 256) * ceil_div(g.N, 128) < 256);
     }
-    if (route == QNN_ENGINE_MFMA_LDS && sc.a.count * sc.w.count >= 4) {
-        const long double work = (long double)g.M * (long double)g.N * (long double)g.K * (sc.a.count * sc.w.count);
-        return work < (ceil_div(g.M, 128) * ceil_div(g.N, 128) > 256 ? 3e10L : 5e10L);
-    }
+    if (route == QNN_ENGINE_MFMA_LDS && ceil_div(g.M, 128) * ceil_div(g.N, 128) >= 192) return tile_us(g, sc, ka, kw) <= stage_us(g);
     return true;
 }
 

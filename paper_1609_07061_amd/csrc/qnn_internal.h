@@ -114,6 +114,8 @@ bool mfma_preferred(const GemmArgs &g);  // whether AUTO should pick it for this
 int launch_gemm_mfma(const GemmArgs &g, hipStream_t s, bool fp4 = false);
 // The same engine's kernel for operands of several bit planes, which expands them once per workgroup into LDS.
 bool stage_supports(const GemmArgs &g);
+double stage_us(const GemmArgs &g);  // about how long it takes there (microseconds)
+int compute_units();
 int launch_gemm_stage(const GemmArgs &g, hipStream_t s);
 // FP4 matrix-core kernels for products of any size and layout (qnn_gemm_slice.hip: small tiles whose waves share k;
 // qnn_gemm_tile.hip: larger tiles).  slice_preferred: whether they take the product and beat the engine (`route`) that the shape

@@ -131,3 +131,27 @@ def test_panels_or_tiles_for_single_planes_of_whole_groups():
     assert [kernel(3000, 2048, K, False) for K in (1024, 2048, 4096)] == [tile, tile, panel]  # 1504; 192 tiles of 256 x 128
     assert [kernel(3000, 2048, K, True) for K in (1024, 4096)] == [panel, panel]
     assert [kernel(3000, 4096, K, sign) for K in (1024, 4096) for sign in (False, True)] == [panel] * 4
+
+
+def test_tiles_or_merged_planes_by_the_pairs_of_digits():
+    """Large products of several planes: each pair of digits is a product of its own on the tiles, one for all pairs on merged planes."""
+    import paper_1609_07061_amd as q
+
+    def merged(pa, pw, M, N, K, sign=False):
+        A = torch.zeros((pa, M, (K + 31) // 32), dtype=torch.int32, device="cuda")
+        W = torch.zeros((pw, N, (K + 31) // 32), dtype=torch.int32, device="cuda")
+        T = torch.zeros(N, dtype=torch.int32, device="cuda")
+        ca, cw = [1 << p for p in range(pa)], [1 << p for p in range(pw)]
+        if sign:
+            found = kernels_of(lambda: q.qnn_bitplane_gemm_sign(A, ca, 0, W, cw, 0 if pw > 1 else 1, K, T))
+        else:
+            found = kernels_of(lambda: q.qnn_bitplane_gemm(A, ca, 0, W, cw, 0 if pw > 1 else 1, K))
+        return found[-1].startswith(("gemm_bytes_panel", "gemm_stage"))
+
+    assert [merged(p, 1, 4096, 4096, 4096) for p in (2, 4, 5, 7)] == [False, False, True, True]
+    assert [merged(p, p, 2240, 4096, 2048) for p in (2, 4)] == [False, True]
+    assert [merged(p, 1, 2240, 4096, 2048) for p in (2, 4, 7)] == [False, False, True]
+    assert not merged(4, 4, 1000, 1000, 16384)  # 64 tiles
+    # eight unsigned planes do not fit a signed byte: merged per workgroup, in rounds of 256 x 256 tiles
+    assert [merged(8, 1, M, N, K) for M, N, K in ((8192, 8192, 8192), (8192, 8192, 1024), (5000, 4096, 4096))] == [True, False, False]
+    assert [merged(8, 1, M, N, K, True) for M, N, K in ((8192, 8192, 8192), (5000, 4096, 4096))] == [True, False]
