@@ -409,7 +409,8 @@ GemmArgs backward_product(const BackwardArgs &b, int64_t M, int64_t N, int64_t K
 
 }  // namespace
 
-// Where each of the two products would go to the byte kernel anyway, its operands are made in fewer passes: the gradient's planes
+// Where the byte kernel takes both products and is no slower over the two than the tiled kernel behind bit transposes (3000 x 2048 x 2048
+// with four +-1 planes 84 against 93 us, 1000 x 4096 x 4096 with four planes 102 against 82), the operands are made in fewer passes: the gradient's planes
 // become bytes in both orders in one pass (instead of a transposition of all planes and a merge per product), the +-1 matrices
 // are transposed straight to bytes, as 0 / 1 (sum g w = 2 sum g b - sum g, the sums from the same pass: half of the products are
 // zero, and the card's power limit, which holds the clock of these kernels down, gives back 6 %: 159 -> 149 us at
@@ -417,9 +418,13 @@ GemmArgs backward_product(const BackwardArgs &b, int64_t M, int64_t N, int64_t K
 bool backward_bytes_preferred(const BackwardArgs &b) {
     if (!bytes_panel::merge_both_supports(b.pg)) return false;
     const GemmArgs ga = backward_product(b, b.M, b.K, b.N, b.gA, b.ld_ga), gw = backward_product(b, b.N, b.K, b.M, b.gW, b.ld_gw);
-    for (const GemmArgs *g : {&ga, &gw})
-        if (!mfma_preferred(*g) || !values_path(*g) || slice_preferred(*g, QNN_ENGINE_MFMA_LDS)) return false;
-    return true;
+    // (the transposes: three launches, two bits of traffic per bit at 2 TB/s)
+    double merged = 0.0, digits = 9.0 + 0.125e-6 * ((double)b.pg.count * b.M * b.N + (double)b.N * b.K + (double)b.M * b.K);
+    for (const GemmArgs *g : {&ga, &gw}) {
+        if (!mfma_preferred(*g) || !values_path(*g)) return false;
+        merged += stage_us(*g), digits += slice_us(*g);
+    }
+    return merged <= digits;
 }
 
 int launch_backward_bytes(const BackwardArgs &b, int8_t *gt, bool &no_memory, hipStream_t s) {

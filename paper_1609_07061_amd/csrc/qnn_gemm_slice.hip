@@ -421,6 +421,12 @@ static double tile_us(const GemmArgs &g, const SliceArgs &sc, int ka, int kw) {
     return 2.8 + k * (kLatency[pairs_of_planes] + kTile[pairs_of_planes] * tiles_each) + kStore[pairs_of_planes] * (double)g.M * (double)g.N;
 }
 
+double slice_us(const GemmArgs &g) {
+    SliceArgs sc;
+    int ka, kw;
+    return slice_args(g, false, sc, ka, kw) ? tile_us(g, sc, ka, kw) : 1e30;
+}
+
 // Where the library's own choice goes to these kernels.  Measured (us, GPU time; route of the shape -> best of these):
 //   vector-ALU route: everything (32 x 4096 x 4096 20 -> 4.5; 20 x 4096 x 2048 with 4 x 4 planes 134 -> 8; convolution of four
 //     13 x 13 maps, 384 -> 256 channels, 39 -> 5; 1000 x 1000 x 1000 8.7 -> 5.3);

@@ -121,6 +121,7 @@ int launch_gemm_stage(const GemmArgs &g, hipStream_t s);
 // qnn_gemm_tile.hip: larger tiles).  slice_preferred: whether they take the product and beat the engine (`route`) that the shape
 // would go to otherwise; launch_gemm_slice chooses between the two.
 bool slice_preferred(const GemmArgs &g, int route);
+double slice_us(const GemmArgs &g);  // about how long it takes there (microseconds; 1e30 if not taken)
 int launch_gemm_slice(const GemmArgs &g, hipStream_t s);
 int launch_gemm_tile(const GemmArgs &g, hipStream_t s);
 // Both products of the backward step from bytes (g_a = g W into gA, g_W = g^T a into gW): whether they take this way, and the
