@@ -8,7 +8,7 @@ import torch
 
 import oracle
 import qnn_inputs as qi
-from qnn_testlib import dev, host, np_pack_bits, np_pack_pm1
+from qnn_testlib import dev, host, kernels_of, np_pack_bits, np_pack_pm1
 
 pytestmark = pytest.mark.gpu
 
@@ -16,7 +16,8 @@ VALUES = [1, 2, 4, 8, 16, 32, 64, -128]
 
 
 @pytest.mark.parametrize("M,N,K", [(2560, 2600, 2050), (2817, 2433, 2049), (2400, 2304, 2273)])
-@pytest.mark.parametrize("coef,mode", [(VALUES, 0), ([-3 * c for c in VALUES], 0), ([64, 1, 2, -4, 16, 8, 32], 0), ([1, -2, 4, 8, 16, -32], 1)])
+@pytest.mark.parametrize("coef,mode", [(VALUES, 0), ([-3 * c for c in VALUES], 0), ([-3 * c for c in VALUES[:7]], 0),
+                                       ([64, 1, 2, -4, 16, 8, 32], 0), ([1, -2, 4, 8, 16, -32], 1)])
 def test_large_backward_step(seed, M, N, K, coef, mode):
     import paper_1609_07061_amd as q
 
@@ -25,7 +26,10 @@ def test_large_backward_step(seed, M, N, K, coef, mode):
     w, a = qi.pm1(seed, 1301, (N, K)), qi.pm1(seed, 1302, (M, K))
     Nw = (N + 31) // 32
     G = dev(np_pack_bits(planes.astype(np.uint8), Nw + 1))[:, :, :Nw]  # rows and planes with a gap
-    ga, gw = q.qnn_binary_backward(G, coef, mode, N, dev(np_pack_pm1(w)), dev(np_pack_pm1(a)), K)
+    W, A = dev(np_pack_pm1(w)), dev(np_pack_pm1(a))
+    ga, gw = q.qnn_binary_backward(G, coef, mode, N, W, A, K)
+    fits = coef[-1] != 384  # (the values / -3 run to 128: no bytes)
+    assert ("merge_transpose_kernel" in kernels_of(lambda: q.qnn_binary_backward(G, coef, mode, N, W, A, K))) == fits
     want_ga = torch.from_numpy(g).double().cuda() @ torch.from_numpy(w.astype(np.float64)).cuda()
     want_gw = torch.from_numpy(np.ascontiguousarray(g.T)).double().cuda() @ torch.from_numpy(a.astype(np.float64)).cuda()
     assert torch.equal(ga, want_ga.to(torch.int32)), (M, N, K, coef)
@@ -83,3 +87,15 @@ def test_pool_that_holds_the_operands_of_one_product_only(seed, small_pool):
     want_ga = torch.from_numpy(g).double().cuda() @ torch.from_numpy(w.astype(np.float64)).cuda()
     want_gw = torch.from_numpy(np.ascontiguousarray(g.T)).double().cuda() @ torch.from_numpy(a.astype(np.float64)).cuda()
     assert torch.equal(ga, want_ga.to(torch.int32)) and torch.equal(gw, want_gw.to(torch.int32))
+
+
+@pytest.mark.parametrize("planes,M,N,K,from_bytes", [(8, 1024, 1024, 1024, False), (4, 3000, 2048, 2048, False), (6, 3000, 2048, 2048, True),
+                                                     (8, 1000, 4096, 4096, True), (8, 64, 4096, 4096, False)])
+def test_way_by_the_expected_times(planes, M, N, K, from_bytes):
+    import paper_1609_07061_amd as q
+
+    G = torch.zeros((planes, M, N // 32), dtype=torch.int32, device="cuda")
+    W, A = torch.zeros((N, K // 32), dtype=torch.int32, device="cuda"), torch.zeros((M, K // 32), dtype=torch.int32, device="cuda")
+    coef = [1 << p for p in range(planes - 1)] + [-(1 << (planes - 1))]
+    kernels = kernels_of(lambda: q.qnn_binary_backward(G, coef, 0, N, W, A, K))
+    assert ("merge_transpose_kernel" in kernels) == from_bytes, kernels
