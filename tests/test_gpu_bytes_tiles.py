@@ -6,18 +6,20 @@ import torch
 
 import oracle
 import qnn_inputs as qi
-from qnn_testlib import dev, host, np_pack_bits
+from qnn_testlib import dev, host, kernels_of, np_pack_bits
 
 pytestmark = pytest.mark.gpu
 
-# tiles of 256 rows on 256 compute units: half a round (taken as 128 rows), 0.56 and 0.75 rounds (192), 1.25 rounds (halves), one
-SHAPES = [(1793, 4081, 600), (2230, 4096, 513), (3071, 4090, 640), (5000, 4100, 513), (4096, 4096, 512)]
+# tiles of 256 rows on 256 compute units: half a round (taken as 128 rows), 0.56 and 0.75 rounds (192), 1.25 rounds (halves), one; the
+# kernel's arguments for that: halves in the last round, rows / 64
+SHAPES = [(1793, 4081, 600, "false, 2"), (2230, 4096, 513, "false, 3"), (3071, 4090, 640, "false, 3"), (5000, 4100, 513, "true, 4"),
+          (4096, 4096, 512, "false, 4")]
 PLANES = [([1, 2, 4, -8], 0, [1, 2, 4, -8], 0), ([1, 4, 16, -64], 0, [2, 1, -4], 1), ([3, 5, -7], 0, [1, 3], 1)]
 
 
-@pytest.mark.parametrize("M,N,K", SHAPES)
+@pytest.mark.parametrize("M,N,K,tile", SHAPES)
 @pytest.mark.parametrize("ca,ma,cw,mw", PLANES)
-def test_merged_products(seed, M, N, K, ca, ma, cw, mw):
+def test_merged_products(seed, M, N, K, tile, ca, ma, cw, mw):
     import paper_1609_07061_amd as q
 
     def operand(stream, coef, mode, rows):
@@ -34,6 +36,8 @@ def test_merged_products(seed, M, N, K, ca, ma, cw, mw):
         want = torch.from_numpy(va).cuda().double() @ torch.from_numpy(vw).cuda().double().t().contiguous()
         assert torch.equal(C, want.to(torch.int32)), (M, N, K, ca)
     assert bool((wide[:, 0] == 7).all()) and bool((wide[:, 1 + N:] == 7).all())
+    kernels = kernels_of(lambda: q.qnn_bitplane_gemm(A, ca, ma, W, cw, mw, K, out=C, engine=q.ENGINE_MFMA_LDS))
+    assert kernels[-1] == f"gemm_bytes_panel_kernel<false, {tile}>", kernels
     rows = np.array([0, M - 1])
     assert np.array_equal(host(C)[rows], oracle.gemm_int(va[rows].astype(np.int32), vw.astype(np.int32)))
 

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import oracle
-from qnn_testlib import host, host_u32
+from qnn_testlib import host, host_u32, kernels_of
 
 pytestmark = pytest.mark.gpu
 
@@ -58,6 +58,10 @@ def test_saturated_operands(M, N, ca, ma, cw, mw, K):
     bit = host((want >= T[None]).to(torch.uint8))
     got = q.qnn_bitplane_gemm_sign(A, ca, ma, W, cw, mw, K, T)
     assert np.array_equal(host_u32(got), oracle.pack_bits(np.where(bit != 0, 1, -1).astype(np.int8))), (M, N, K)
+    if M == 1700:
+        assert kernels_of(lambda: q.qnn_bitplane_gemm_sign(A, ca, ma, W, cw, mw, K, T))[-1].startswith("gemm_tile_kernel")
+        if 255 in (sum(ca), sum(cw)) or K < 512:  # (other products may be merged to bytes)
+            assert kernels_of(lambda: q.qnn_bitplane_gemm(A, ca, ma, W, cw, mw, K))[-1].startswith("gemm_tile_kernel")
 
 
 @pytest.mark.parametrize("M,N", [(1700, 3400), (700, 1000), (40, 33)])
@@ -86,6 +90,8 @@ def test_long_rows_of_signs(M, N, K):
     got = q.qnn_binary_gemm(A, W, K)
     assert torch.equal(got, want), (M, N, K, int((got != want).sum()))
     T = want[0] + torch.arange(N, device="cuda", dtype=torch.int32) % 3 - 1
+    if M == 1700:
+        assert kernels_of(lambda: q.qnn_binary_gemm(A, W, K))[0].startswith("gemm_tile_kernel")
     got = q.qnn_binary_gemm_sign(A, W, K, T)
     bit = host((want >= T[None]).to(torch.uint8))
     assert np.array_equal(host_u32(got), oracle.pack_bits(np.where(bit != 0, 1, -1).astype(np.int8))), (M, N, K)
