@@ -16,8 +16,9 @@
 // pieces beyond K are read from the row's start instead (valid memory, any value): they meet weights that are zero.
 // Workgroup tile 256 x 256 on eight waves of 128 x 64, two per SIMD: a load to LDS holds the issuing wave for tens of cycles and
 // every group ends in a barrier; with one wave of 128 x 128 per SIMD (the earlier shape of this kernel) the matrix cores waited
-// with it.  A group takes 2875 cycles of which 2048 are matrix-core time; at that rate the card's power limit holds the clock at
-// 1.9 GHz (random int8 operands).  Where rounds of such tiles leave much of the chip idle, tiles have 192 or 128 rows (see bytes_tiles).  4096 x 4096 x 10000: 168 -> 141 us; first layer 10000 x 784 -> 4096: 59 -> 48.5 us.
+// with it.  A group takes 2600 cycles of which 2048 are matrix-core time (1.08 us on zeros; random operands, under whose switching the
+// card lowers its clock from 2.4 to about 2.1 GHz, 1.30 us).  Where rounds of such tiles leave much of the chip idle, tiles have 192 or
+// 128 rows (see bytes_tiles).  4096 x 4096 x 10000: 168 -> 125 us; first layer 10000 x 784 -> 4096: 59 -> 44 us.
 // The same kernel, with kCodes = false, multiplies two operands that are int8 values already (bit planes merged to one
 // byte per element by merge_planes_kernel, Sec. 2.6 / Sec. 3: the weighted sum of the plane products is the product of
 // the values the planes stand for), with int32 sums as output and no correction terms.

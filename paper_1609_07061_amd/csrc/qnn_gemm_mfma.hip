@@ -167,12 +167,13 @@ int compute_units() {
     return cus;
 }
 
-// Tiles of the byte-operand kernel: 64 `blocks` rows x 256 columns, taken in rounds of one tile per compute unit.  A round costs
-// 1.41, 1.22 and 1.0 us per group of k with 256, 192 and 128 rows (reads of LDS and matrix cores overlap worse the fewer products
-// an operand feeds), and one of halved 256-row tiles, possible where the last round has tiles for at most half of the compute
-// units, 1.03; the fewest rounds by that cost are taken.  With 256 rows -> as chosen, merge of the planes included: 2240 x 4096 x
-// 2048 (144 -> 192 tiles) 50.7 -> 48.4 us, x 4096 69.5 -> 62.8; 2000 x 3000 x 1500 (96 -> 192) 43.0 -> 35.0; 10000 x 4096 x 4096
-// stays (2.5 rounds: 193 us against 208 with 192 rows), 10000 x 784 -> 4096 likewise.
+// Tiles of the byte-operand kernel: 64 `blocks` rows x 256 columns, taken in rounds of one tile per compute unit.  In units of a
+// round of 128 rows, rounds of 256 and 192 rows cost 1.41 and 1.22 (reads of LDS and matrix cores overlap worse the fewer products
+// an operand feeds; per group of k, random operands: 0.94, 1.23 and 1.30 us with 128, 192, 256 rows), and one of halved 256-row tiles,
+// possible where the last round has tiles for at most half of the compute units, 1.03; the fewest rounds by that cost are taken.  (The
+// measured costs would take halves where 192 rows are faster: 7757 x 4231 x 4096, 179 us against 169.)  With 256 rows -> as chosen,
+// merge of 4 x 4 planes included: 2240 x 4096 x 2048 (144 -> 192 tiles) 45.5 -> 43.6 us, x 4096 64.3 -> 59.2; 1000 x 4096 x 4096 (64 ->
+// 128) 58.7 -> 44.9; 2000 x 3000 x 1500 (96 -> 192) 39.8 -> 32.0; 10000 x 4096 x 4096 keeps 2.5 rounds of 256 rows.
 struct BytesTiles {
     int blocks;
     bool tail;
@@ -413,8 +414,8 @@ GemmArgs backward_product(const BackwardArgs &b, int64_t M, int64_t N, int64_t K
 // with four +-1 planes 84 against 93 us, 1000 x 4096 x 4096 with four planes 102 against 82), the operands are made in fewer passes: the gradient's planes
 // become bytes in both orders in one pass (instead of a transposition of all planes and a merge per product), the +-1 matrices
 // are transposed straight to bytes, as 0 / 1 (sum g w = 2 sum g b - sum g, the sums from the same pass: half of the products are
-// zero, and the card's power limit, which holds the clock of these kernels down, gives back 6 %: 159 -> 149 us at
-// 4096 x 4096 x 10000).  10000 x 4096 x 4096 with eight planes: operands 115 -> 64 us.
+// zero, and the clock, which the card lowers with the switching of the operands, drops less: 159 -> 149 us at 4096 x 4096 x 10000 when
+// that was measured, 125 now).  10000 x 4096 x 4096 with eight planes: operands 115 -> 64 us.
 bool backward_bytes_preferred(const BackwardArgs &b) {
     if (!bytes_panel::merge_both_supports(b.pg)) return false;
     const GemmArgs ga = backward_product(b, b.M, b.K, b.N, b.gA, b.ld_ga), gw = backward_product(b, b.N, b.K, b.M, b.gW, b.ld_gw);

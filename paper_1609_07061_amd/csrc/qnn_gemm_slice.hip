@@ -427,7 +427,8 @@ double slice_us(const GemmArgs &g) {
     return slice_args(g, false, sc, ka, kw) ? tile_us(g, sc, ka, kw) : 1e30;
 }
 
-// Where the library's own choice goes to these kernels.  Measured (us, GPU time; route of the shape -> best of these):
+// Where the library's own choice goes to these kernels.  Measured (us, GPU time; route of the shape -> best of these; numbers of tiles are
+// counts for 256 compute units):
 //   vector-ALU route: everything (32 x 4096 x 4096 20 -> 4.5; 20 x 4096 x 2048 with 4 x 4 planes 134 -> 8; convolution of four
 //     13 x 13 maps, 384 -> 256 channels, 39 -> 5; 1000 x 1000 x 1000 8.7 -> 5.3);
 //   single planes that miss the panel-fed kernel's layout: everything (1999 x 3001 x 2500 82 -> 21; 8000^3 640 -> 234);

@@ -449,7 +449,7 @@ bool conv_map_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N) {
     return 9 * Cw * 32 < 8388608 && ceil_div(M, kTile) * ceil_div(N, kTile) <= 0x7FFFFFFFLL;
 }
 
-// From 48 tiles on: the App. A ConvNet of width 128 on 4, 16, 64, 256 images of 32 x 32 takes 57, 74, 83, 140 us with the line at 48
+// From 48 tiles on (of 256 compute units): the App. A ConvNet of width 128 on 4, 16, 64, 256 images of 32 x 32 takes 57, 74, 83, 140 us with the line at 48
 // tiles, 77, 78, 84, 143 with every convolution on its map's plane, 58, 86, 137, 209 with none (other widths and sizes alike).
 bool conv_map_preferred(int64_t B, int64_t H, int64_t Wd, int64_t N) { return ceil_div(B * H * Wd, kTile) * ceil_div(N, kTile) >= 48; }
 
