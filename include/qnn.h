@@ -108,7 +108,8 @@ int qnn_binary_gemm_sign(const uint32_t *A, int64_t lda_words, const uint32_t *W
  * coefA, coefW: HOST int32 arrays (e.g. 1,2,4,...,128 for 8-bit unsigned inputs; 1,2,4,-8 for 4-bit two's
  * complement).  1 <= Pa, Pb <= QNN_MAX_PLANES.  QNN_ERR_OVERFLOW if (sum|coefA|)(sum|coefW|) K >= 2^31.
  * Large products (M, N >= 256, K >= 512, M N K >= 2^31) of multi-plane operands whose values fit int8 are computed
- * from the values where the library expects that to be faster than plane by plane (and always with QNN_ENGINE_MFMA_LDS): both operands' planes are merged to one byte per element in temporary device memory of
+ * from the values where the library expects that to be faster than plane by plane, and always with
+ * QNN_ENGINE_MFMA_LDS: both operands' planes are merged to one byte per element in temporary device memory of
  * (M + N) * roundup(K, 128) bytes that the call takes from, and returns to, the memory pool of `stream`
  * (hipMallocAsync / hipFreeAsync: stream-ordered, no synchronization); QNN_ERR_HIP if the pool cannot supply it. */
 int qnn_bitplane_gemm(const uint32_t *A, int Pa, const int32_t *coefA, int modeA, int64_t lda_words,
