@@ -39,6 +39,20 @@ __device__ __forceinline__ void split_32_codes(const uint32_t (&codes)[8], int n
     for (int p = 0; p < 4; ++p) word[p] = lo4[p], word[p + 4] = hi4[p];
 }
 
+// word[q] bit c = bit q of code c  ->  codes[j] byte i = code 4 j + i (the inverse of split_32_codes: both of its
+// stages are their own inverses)
+__device__ __forceinline__ void join_32_codes(const uint32_t (&word)[8], uint32_t (&codes)[8]) {
+    const uint32_t lo4[4] = {word[0], word[1], word[2], word[3]}, hi4[4] = {word[4], word[5], word[6], word[7]};
+    uint32_t L[4], H[4];
+    transpose_4x4_bytes(lo4, L);
+    transpose_4x4_bytes(hi4, H);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        transpose_8x8_bits(L[g], H[g]);
+        codes[2 * g] = L[g], codes[2 * g + 1] = H[g];
+    }
+}
+
 // 32 x 32 bit matrix held as 32 words (x[k] bit c = element (k, c)), transposed in place: five rounds of exchanges
 // of 16-, 8-, 4-, 2- and 1-bit blocks between words 16, 8, 4, 2 and 1 apart; the first two rounds move whole bytes
 // and are byte permutes.

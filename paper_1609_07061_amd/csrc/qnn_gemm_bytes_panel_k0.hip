@@ -75,19 +75,6 @@ struct MergeOperand {
 __device__ __forceinline__ uint32_t add_bytes(uint32_t x, uint32_t y) {  // byte-wise sum mod 256
     return ((x & 0x7F7F7F7Fu) + (y & 0x7F7F7F7Fu)) ^ ((x ^ y) & 0x80808080u);
 }
-// word[q] bit c = bit q of code c  ->  codes[j] byte i = code 4 j + i (the inverse of split_32_codes: both of its
-// stages are their own inverses)
-__device__ __forceinline__ void join_32_codes(const uint32_t (&word)[8], uint32_t (&codes)[8]) {
-    const uint32_t lo4[4] = {word[0], word[1], word[2], word[3]}, hi4[4] = {word[4], word[5], word[6], word[7]};
-    uint32_t L[4], H[4];
-    transpose_4x4_bytes(lo4, L);
-    transpose_4x4_bytes(hi4, H);
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        transpose_8x8_bits(L[g], H[g]);
-        codes[2 * g] = L[g], codes[2 * g + 1] = H[g];
-    }
-}
 // grid: x = groups of four rows, y = groups of 64 output words, z = operand
 __global__ __launch_bounds__(256) void merge_planes_kernel(const MergeOperand a, const MergeOperand w, int64_t K, int64_t ld_out) {
     const MergeOperand &op = blockIdx.z == 0 ? a : w;
@@ -151,129 +138,6 @@ __global__ __launch_bounds__(256) void merge_planes_kernel(const MergeOperand a,
     uint4 *dst = reinterpret_cast<uint4 *>(op.out + r * ld_out + 32 * j);
     dst[0] = make_uint4(o[0], o[1], o[2], o[3]);
     dst[1] = make_uint4(o[4], o[5], o[6], o[7]);
-}
-
-// Both byte forms of a gradient at once, for the two products of the backward step: out[m][n] (rows of ld_out bytes) and
-// out_t[n][m] (rows of ld_t), with the sums of every row and column added to row_sums / col_sums.  Planes as in
-// merge_planes_kernel with multipliers +-2^q: src[q] is the plane that holds bit q (-1: none), inv[q] its inversion.
-// Bound: memory (a byte is written twice and one bit per plane read once).  A workgroup takes 128 rows x 256 columns, a thread four
-// rows x one word: the planes' words become 32 bytes per row (bit-matrix transposition in registers), 4 x 4 byte transpositions
-// turn four rows' bytes into dwords along m, and LDS collects those to 128 contiguous bytes per column.  LDS: column n at dword
-// 36 n, its dwords rotated by 8 (n / 32 mod 4) and moved on by 32 for the upper half, so that the 64 dword writes of a wave (eight
-// words x eight row groups) fall on 64 banks.
-struct MergeBoth {
-    const uint32_t *planes;
-    int64_t plane_stride, ld;  // words
-    int64_t M, N;
-    int src[8];
-    uint32_t inv[8];
-    int32_t neg_sum, bias;
-    int twice;
-    int8_t *out, *out_t;
-    int64_t ld_out, ld_t;
-    int32_t *row_sums, *col_sums;
-};
-__global__ __launch_bounds__(256) void merge_transpose_kernel(const MergeBoth a) {
-    constexpr int kPitch = 36;
-    __shared__ __attribute__((aligned(16))) uint32_t s_t[256 * kPitch + 32];
-    const int t = threadIdx.x, j = t & 7, rg = t >> 3;
-    const int64_t m0 = (int64_t)blockIdx.y * 128, j0 = (int64_t)blockIdx.x * 8;
-    const int64_t jw = j0 + j, Nw = (a.N + 31) / 32;
-    uint32_t o[4][8];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t m = m0 + 4 * rg + i;
-        const bool in = m < a.M && jw < Nw;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) o[i][q] = (in && a.src[q] >= 0) ? a.planes[a.src[q] * a.plane_stride + m * a.ld + jw] : 0u;
-    }
-    const uint32_t minus = (uint32_t)((-a.neg_sum) & 0xFF) * 0x01010101u, bias = (uint32_t)(a.bias & 0xFF) * 0x01010101u;
-    const int64_t left = a.N - 32 * jw;  // columns of this word that exist
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t m = m0 + 4 * rg + i;
-        uint32_t r8[8], v[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) r8[q] = o[i][q] ^ a.inv[q];
-        join_32_codes(r8, v);
-        int32_t sum = 0;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            v[q] = add_bytes(v[q], minus);
-            if (a.twice) v[q] = add_bytes(add_bytes(v[q], v[q]), bias);
-        }
-        if (m >= a.M || left < 32) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int64_t have = m < a.M ? left - 4 * q : 0;
-                v[q] &= have >= 4 ? 0xFFFFFFFFu : (have <= 0 ? 0u : (1u << (8 * (int)have)) - 1u);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            sum = __builtin_amdgcn_sdot4((int)v[q], 0x01010101, sum, false);
-            o[i][q] = v[q];
-        }
-        if (m < a.M && 32 * jw < a.ld_out) {
-            uint4 *dst = reinterpret_cast<uint4 *>(a.out + m * a.ld_out + 32 * jw);
-            dst[0] = make_uint4(v[0], v[1], v[2], v[3]);
-            dst[1] = make_uint4(v[4], v[5], v[6], v[7]);
-        }
-#pragma unroll
-        for (int d = 1; d < 8; d <<= 1) sum += __shfl_xor(sum, d, 64);
-        if (j == 0 && m < a.M) atomicAdd(&a.row_sums[m], sum);
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const uint32_t rows[4] = {o[0][q], o[1][q], o[2][q], o[3][q]};
-        uint32_t cols[4];
-        transpose_4x4_bytes(rows, cols);
-#pragma unroll
-        for (int p = 0; p < 4; ++p) s_t[(32 * j + 4 * q + p) * kPitch + ((rg + 8 * (j & 3)) & 31) + 32 * (j >> 2)] = cols[p];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int idx = t + 256 * u, nl = idx >> 3, pc = idx & 7, jn = nl >> 5;
-        const int64_t n = 32 * j0 + nl;
-        const uint4 x = *reinterpret_cast<const uint4 *>(&s_t[nl * kPitch + ((4 * pc + 8 * (jn & 3)) & 31) + 32 * (jn >> 2)]);
-        int32_t sum = __builtin_amdgcn_sdot4((int)x.x, 0x01010101, 0, false);
-        sum = __builtin_amdgcn_sdot4((int)x.y, 0x01010101, sum, false);
-        sum = __builtin_amdgcn_sdot4((int)x.z, 0x01010101, sum, false);
-        sum = __builtin_amdgcn_sdot4((int)x.w, 0x01010101, sum, false);
-#pragma unroll
-        for (int d = 1; d < 8; d <<= 1) sum += __shfl_xor(sum, d, 64);
-        if (n < a.N) {
-            *reinterpret_cast<uint4 *>(a.out_t + n * a.ld_t + m0 + 16 * pc) = x;
-            if (pc == 0) atomicAdd(&a.col_sums[n], sum);
-        }
-    }
-}
-
-// A packed bit matrix transposed to bytes 0 / 1: out[c][r] = bit (r, c) for r < rows, 0 for rows <= r < ld_out (a multiple of
-// 128).  A thread takes four rows x one word: the words' bits s, s + 8, s + 16, s + 24 as bytes, a 4 x 4 byte transposition, and a
-// wave stores 256 contiguous bytes of one output row per instruction.  Also clears n_clear words at `clear`.
-__global__ __launch_bounds__(256) void transpose_to_bytes_kernel(const uint32_t *__restrict__ in, int64_t rows, int64_t cols, int64_t ld,
-                                                                 uint8_t *__restrict__ out, int64_t ld_out, int32_t *__restrict__ clear,
-                                                                 int64_t n_clear) {
-    const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-    for (int64_t i = block * 256 + threadIdx.x; i < n_clear; i += (int64_t)gridDim.x * gridDim.y * 256) clear[i] = 0;
-    const int64_t j = (int64_t)blockIdx.y * 4 + (threadIdx.x >> 6), r = 4 * ((int64_t)blockIdx.x * 64 + (threadIdx.x & 63));
-    if (j >= (cols + 31) / 32 || r >= ld_out) return;
-    uint32_t w[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = r + i < rows ? in[(r + i) * ld + j] : 0u;
-    uint8_t *dst = out + 32 * j * ld_out + r;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        uint32_t b[4], c[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) b[i] = (w[i] >> s) & 0x01010101u;
-        transpose_4x4_bytes(b, c);
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
-            if (32 * j + s + 8 * p < cols) *reinterpret_cast<uint32_t *>(dst + (int64_t)(s + 8 * p) * ld_out) = c[p];
-    }
 }
 
 // Multipliers and bias of an operand's merge, and the factor `scale` with value = scale * (merged int8); false if the
@@ -356,34 +220,6 @@ int launch_merge_planes(const GemmArgs &g, int8_t *outA, int8_t *outW, int64_t l
                       g.K, ld_out);
 }
 
-bool merge_both_supports(const Planes &pl) {
-    MergeOperand op;
-    int64_t scale;
-    return merge_plan(pl, op, scale) && op.pow2;
-}
-
-int launch_merge_transpose(const Planes &pl, const uint32_t *planes, int64_t plane_stride, int64_t ld, int64_t M, int64_t N, int8_t *out,
-                           int64_t ld_out, int8_t *out_t, int64_t ld_t, int32_t *row_sums, int32_t *col_sums, int64_t &scale, hipStream_t s) {
-    MergeOperand op;
-    if (!merge_plan(pl, op, scale) || !op.pow2) return fail(QNN_ERR_UNSUPPORTED, "merged values do not fit int8");
-    MergeBoth a;
-    a.planes = planes, a.plane_stride = plane_stride, a.ld = ld, a.M = M, a.N = N;
-    for (int q = 0; q < 8; ++q) a.src[q] = op.src[q], a.inv[q] = op.inv[q];
-    a.neg_sum = op.neg_sum, a.bias = op.bias, a.twice = op.twice;
-    a.out = out, a.ld_out = ld_out, a.out_t = out_t, a.ld_t = ld_t, a.row_sums = row_sums, a.col_sums = col_sums;
-    const int64_t bx = ceil_div(ld_out, 256), by = ceil_div(ld_t, 128);
-    if (bx > 0x7FFFFFFFLL || by > 65535) return fail(QNN_ERR_SHAPE, "merge: too many elements");
-    return QNN_LAUNCH("merge_transpose", merge_transpose_kernel, dim3((unsigned)bx, (unsigned)by), dim3(256), 0, s, a);
-}
-
-int launch_transpose_to_bytes(const uint32_t *in, int64_t rows, int64_t cols, int64_t ld, uint8_t *out, int64_t ld_out, int32_t *clear,
-                              int64_t n_clear, hipStream_t s) {
-    const int64_t bx = ceil_div(ld_out, 256), by = ceil_div((cols + 31) / 32, 4);
-    if (bx > 0x7FFFFFFFLL || by > 65535) return fail(QNN_ERR_SHAPE, "transpose: too many elements");
-    return QNN_LAUNCH("transpose_to_bytes", transpose_to_bytes_kernel, dim3((unsigned)bx, (unsigned)by), dim3(256), 0, s, in, rows, cols, ld, out,
-                      ld_out, clear, n_clear);
-}
-
 KernelFn kernel(bool tail, int blocks) { return kernel_of<true>(tail, blocks); }
 
 int launch_expand_weights(const uint32_t *W, int64_t N, int64_t K, int64_t ldw, int8_t *out, int64_t ld_out, int32_t *rw_scaled,
@@ -394,4 +230,13 @@ int launch_expand_weights(const uint32_t *W, int64_t N, int64_t K, int64_t ldw, 
 }
 
 }  // namespace bytes_panel
+
+bool merge_code(const Planes &pl, MergeCode &c) {
+    bytes_panel::MergeOperand op;
+    if (!bytes_panel::merge_plan(pl, op, c.scale) || !op.pow2) return false;
+    for (int q = 0; q < 8; ++q) c.src[q] = op.src[q], c.inv[q] = op.inv[q];
+    c.neg_sum = op.neg_sum, c.bias = op.bias, c.twice = op.twice;
+    return true;
+}
+
 }  // namespace qnn

@@ -259,15 +259,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const Gem
             for (int i = 0; i < WI; ++i)
 #pragma unroll
                 for (int j = 0; j < WB; ++j) asm volatile("" : "+v"(acc[i][j]));
-            if constexpr (!kCodes) {
-                if (g.row_sums) {  // (the epilogue adds the two k halves of a lane's row)
-#pragma unroll
-                    for (int j = 0; j < WB; ++j) {
-                        const int64_t m = m_wave + 32 * j + (lane & 31);
-                        ra[j] = lane < 32 ? g.row_sums[m < g.M ? m : g.M - 1] : 0;
-                    }
-                }
-            }
             panel::wave_finish<kSign, WI, kLoadsPerGroup, kCodes>(g, mc, acc, ra, rw, rw_tab, thr_tab, flip_tab, stage_w, m_wave, n_wave);
         }
     };

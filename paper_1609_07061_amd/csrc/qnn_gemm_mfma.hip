@@ -338,9 +338,8 @@ bool values_path(const GemmArgs &g) {
     return bytes_panel::merge_supports(g.pa, g.pw);
 }
 
-// C = alpha S + c_row (sum of the left row) of two operands of int8 values, rows of `pitch` bytes
-int launch_values_product(const GemmArgs &g, const int8_t *a8, const int8_t *w8, int64_t pitch, int64_t alpha, const int32_t *row_sums, int64_t c_row,
-                          hipStream_t s) {
+// C = alpha S of two operands of int8 values, rows of `pitch` bytes
+int launch_values_product(const GemmArgs &g, const int8_t *a8, const int8_t *w8, int64_t pitch, int64_t alpha, hipStream_t s) {
     GemmArgs v = g;
     v.A.base = reinterpret_cast<const uint32_t *>(a8);
     v.A.ld = pitch;
@@ -349,10 +348,9 @@ int launch_values_product(const GemmArgs &g, const int8_t *a8, const int8_t *w8,
     v.w_bytes = w8;
     v.ld_w_bytes = pitch;
     v.rw_scaled = nullptr;
-    v.row_sums = row_sums;
     MfmaConst mc;
     std::memset(&mc, 0, sizeof(mc));
-    mc.alpha = (uint32_t)alpha, mc.cRA = (uint32_t)c_row;
+    mc.alpha = (uint32_t)alpha;
     mc.alpha_shift = -1;
     for (int sh = 0; sh < 31; ++sh)
         if (alpha == ((int64_t)1 << sh)) mc.alpha_shift = sh;
@@ -360,28 +358,6 @@ int launch_values_product(const GemmArgs &g, const int8_t *a8, const int8_t *w8,
     return QNN_LAUNCH("gemm_values", bytes_panel::kernel_values(bt.tail, bt.blocks), dim3(bt.grid), dim3(bytes_panel::kThreads), 0, s, v, mc,
                       (uint32_t)bt.tiles_m, (uint32_t)bt.tiles_n, (uint32_t)ceil_div(g.K, bytes_panel::kGroupK));
 }
-
-// Temporary device memory from the stream's pool, given back in stream order.
-struct PoolMemory {
-    void *ptr = nullptr;
-    hipStream_t s;
-    explicit PoolMemory(hipStream_t stream) : s(stream) {}
-    int take(size_t bytes) {
-        if (hipMallocAsync(&ptr, bytes, s) != hipSuccess || !ptr) {
-            (void)hipGetLastError();
-            ptr = nullptr;
-            return fail(QNN_ERR_HIP, "gemm: no memory for the merged operands (%zu bytes)", bytes);
-        }
-        return QNN_OK;
-    }
-    int give_back(int rc) {
-        if (ptr && hipFreeAsync(ptr, s) != hipSuccess) {
-            (void)hipGetLastError();
-            if (rc == QNN_OK) rc = fail(QNN_ERR_HIP, "gemm: returning the merged operands' memory failed");
-        }
-        return rc;
-    }
-};
 
 int launch_values(const GemmArgs &g, hipStream_t s) {
     const int64_t pitch = values_pitch(g.K);
@@ -391,7 +367,7 @@ int launch_values(const GemmArgs &g, hipStream_t s) {
     int8_t *a8 = static_cast<int8_t *>(mem.ptr), *w8 = a8 + bytes_a;  // (bytes_a is a multiple of 128)
     int64_t scale = 0;
     int rc = bytes_panel::launch_merge_planes(g, a8, w8, pitch, scale, s);
-    if (rc == QNN_OK) rc = launch_values_product(g, a8, w8, pitch, scale, nullptr, 0, s);
+    if (rc == QNN_OK) rc = launch_values_product(g, a8, w8, pitch, scale, s);
     return mem.give_back(rc);
 }
 
@@ -410,45 +386,25 @@ GemmArgs backward_product(const BackwardArgs &b, int64_t M, int64_t N, int64_t K
 
 }  // namespace
 
-// Where the byte kernel takes both products and is no slower over the two than the tiled kernel behind bit transposes (3000 x 2048 x 2048
-// with four +-1 planes 84 against 93 us, 1000 x 4096 x 4096 with four planes 102 against 82), the operands are made in fewer passes: the gradient's planes
-// become bytes in both orders in one pass (instead of a transposition of all planes and a merge per product), the +-1 matrices
-// are transposed straight to bytes, as 0 / 1 (sum g w = 2 sum g b - sum g, the sums from the same pass: half of the products are
-// zero, and the clock, which the card lowers with the switching of the operands, drops less: 159 -> 149 us at 4096 x 4096 x 10000 when
-// that was measured, 125 now).  10000 x 4096 x 4096 with eight planes: operands 115 -> 64 us.
-bool backward_bytes_preferred(const BackwardArgs &b) {
-    if (!bytes_panel::merge_both_supports(b.pg)) return false;
+// Whether the step takes the way of qnn_gemm_mixed.hip (FP6 or int8 gradients) or products of bit planes behind bit transposes.
+//   More than four planes: by the expected times, with int8 gradients, the slower ones, and only where those of the planes, which the
+//   estimates of the products undershoot, are 10 % higher (us behind the quantizer, planes -> FP6 / int8; eight planes: 10000 x 4096 x 4096 356 ->
+//   220 / 340; 1009 x 1280 x 2784 62 -> 39; 7572 x 2368 x 444 158 -> 72; 3611 x 448 x 512 46 against 41 / 48; six planes: 3031 x 2083 x 906 85 ->
+//   - / 63, 393 x 3517 x 960 41 against - / 50).
+//   Up to four planes, which make two pairs of digits at most: where merging them to bytes for each product would be faster than the
+//   tiled kernel (a line that leaves steps to the planes which are faster here: 3000 x 2048 x 2048 with four planes 79 against 54).
+bool backward_mixed_preferred(const BackwardArgs &b) {
+    if (!mixed::backward_supports(b)) return false;
     const GemmArgs ga = backward_product(b, b.M, b.K, b.N, b.gA, b.ld_ga), gw = backward_product(b, b.N, b.K, b.M, b.gW, b.ld_gw);
     // (the transposes: three launches, two bits of traffic per bit at 2 TB/s)
-    double merged = 0.0, digits = 9.0 + 0.125e-6 * ((double)b.pg.count * b.M * b.N + (double)b.N * b.K + (double)b.M * b.K);
+    const double digits = 9.0 + 0.125e-6 * ((double)b.pg.count * b.M * b.N + (double)b.N * b.K + (double)b.M * b.K) + slice_us(ga) + slice_us(gw);
+    if (b.pg.count > 4 && digits < 1e9) return mixed::backward_us(b) <= 1.1 * digits;
+    double merged = 0.0;
     for (const GemmArgs *g : {&ga, &gw}) {
         if (!mfma_preferred(*g) || !values_path(*g)) return false;
-        merged += stage_us(*g), digits += slice_us(*g);
+        merged += stage_us(*g);
     }
     return merged <= digits;
-}
-
-int launch_backward_bytes(const BackwardArgs &b, int8_t *gt, bool &no_memory, hipStream_t s) {
-    const int64_t pn = values_pitch(b.N), pm = values_pitch(b.M);
-    const size_t size_g = (size_t)b.M * pn, size_gt = gt ? 0 : (size_t)b.N * pm, size_w = (size_t)b.K * (pn > pm ? pn : pm);
-    const size_t sums = ((size_t)(b.M + b.N) * 4 + 255) / 256 * 256;
-    PoolMemory mem(s);
-    const int taken = mem.take(sums + size_g + size_gt + size_w);
-    no_memory = taken != QNN_OK;
-    if (no_memory) return taken;
-    int32_t *row_sums = static_cast<int32_t *>(mem.ptr), *col_sums = row_sums + b.M;
-    int8_t *g8 = static_cast<int8_t *>(mem.ptr) + sums;  // (all sizes are multiples of 128)
-    if (!gt) gt = g8 + size_g;
-    int8_t *w8 = g8 + size_g + size_gt;  // the transposed weights, then the transposed activations
-    int64_t scale = 0;
-    const GemmArgs ga = backward_product(b, b.M, b.K, b.N, b.gA, b.ld_ga), gw = backward_product(b, b.N, b.K, b.M, b.gW, b.ld_gw);
-    int rc = bytes_panel::launch_transpose_to_bytes(b.W, b.N, b.K, b.ldw, reinterpret_cast<uint8_t *>(w8), pn, row_sums, b.M + b.N, s);
-    if (rc == QNN_OK)
-        rc = bytes_panel::launch_merge_transpose(b.pg, b.G, b.strideG, b.ldg, b.M, b.N, g8, pn, gt, pm, row_sums, col_sums, scale, s);
-    if (rc == QNN_OK) rc = launch_values_product(ga, g8, w8, pn, 2 * scale, row_sums, -scale, s);
-    if (rc == QNN_OK) rc = bytes_panel::launch_transpose_to_bytes(b.A, b.M, b.K, b.lda, reinterpret_cast<uint8_t *>(w8), pm, nullptr, 0, s);
-    if (rc == QNN_OK) rc = launch_values_product(gw, gt, w8, pm, 2 * scale, col_sums, -scale, s);
-    return mem.give_back(rc);
 }
 
 // Merged once per call: products of 300 x 300 to 128000 x 256 rows and 512 to 30000 elements of k within 10 % as a rule (merge of both

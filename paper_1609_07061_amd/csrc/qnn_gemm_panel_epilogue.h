@@ -58,7 +58,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &g, const MfmaConst
     constexpr bool kFast = kTile != kAny;
     // The edge of C goes through LDS too, except in the widest tile, whose registers are full: there it made the whole kernel 0.5 %
     // slower (8192^3, which has no edge: 180.7 -> 181.6 us)
-    constexpr bool kScatterEdge = WBN == 4;
+    constexpr bool kScatterEdge = WBN * WB == 16;
     const int64_t Nw = (g.N + 31) / 32;
 
     // lane coordinates re-derived behind an opaque copy: index arithmetic computed before the tile loop and kept
@@ -247,7 +247,7 @@ __device__ __forceinline__ void wave_finish(const GemmArgs &g, const MfmaConst &
             wave_epilogue<kSign, WBN, kInside, kLoadsAfter, kRwInLds>(g, mc, acc, ra, rw, rw_tab, thr_tab, flip_tab, stage_w, m_wave, n_wave, scale);
             return;
         }
-        if constexpr (!kSign && WBN < 4) {
+        if constexpr (!kSign && WBN * WB < 16) {
             if (wide && columns_inside) {
                 wave_epilogue<kSign, WBN, kLower, kLoadsAfter, kRwInLds>(g, mc, acc, ra, rw, rw_tab, thr_tab, flip_tab, stage_w, m_wave, n_wave, scale);
                 return;

@@ -76,8 +76,6 @@ struct GemmArgs {
     const int8_t *w_bytes;
     int64_t ld_w_bytes;
     const int32_t *rw_scaled;
-    // Optional, with operands of int8 values only: sums of the left operand's rows (the epilogue's term cRA * sum)
-    const int32_t *row_sums;
     // Only for convolutions of +-1 maps on the tiled FP4 kernel: class_thr[cls * class_ld + n] is the threshold of filter n for a pixel
     // of border class cls (bit 0: first row, 1: last row, 2: first column, 3: last column).
     const int32_t *class_thr;
@@ -124,9 +122,9 @@ bool slice_preferred(const GemmArgs &g, int route);
 double slice_us(const GemmArgs &g);  // about how long it takes there (microseconds; 1e30 if not taken)
 int launch_gemm_slice(const GemmArgs &g, hipStream_t s);
 int launch_gemm_tile(const GemmArgs &g, hipStream_t s);
-// Both products of the backward step from bytes (g_a = g W into gA, g_W = g^T a into gW): whether they take this way, and the
-// launches.  gt: where the transposed gradient goes if it holds N * roundup(M, 128) bytes, else null.  no_memory: the stream's pool could
-// not supply the operands; nothing has been launched then.
+// Both products of the backward step from FP6 gradients (g_a = g W into gA, g_W = g^T a into gW): whether they take this way, and the
+// launches (qnn_gemm_mixed.hip).  no_memory: the stream's pool could not supply what the workspace does not hold; nothing has
+// been launched then.
 struct BackwardArgs {
     Planes pg;
     const uint32_t *G, *W, *A;
@@ -134,9 +132,46 @@ struct BackwardArgs {
     int32_t *gA, *gW;
     int64_t ld_ga, ld_gw, M, N, K;
 };
-bool backward_bytes_preferred(const BackwardArgs &b);
-int launch_backward_bytes(const BackwardArgs &b, int8_t *gt, bool &no_memory, hipStream_t s);
+bool backward_mixed_preferred(const BackwardArgs &b);
+namespace mixed {
+bool backward_supports(const BackwardArgs &b);
+double backward_us(const BackwardArgs &b);  // about how long it takes (microseconds) where the gradient is int8
+int launch_backward(const BackwardArgs &b, void *workspace, size_t workspace_bytes, bool &no_memory, hipStream_t s);
+}
 bool panel_takes(const GemmArgs &g);  // whether the FP4 route would use the panel-fed kernel
+
+// How planes with multipliers +-2^q stand for a byte: the plane of bit q (-1: none), its inversion; value = scale ((sum 2^q bit -
+// neg_sum) [* 2 + bias]), the number in brackets within int8.
+struct MergeCode {
+    int src[8];
+    uint32_t inv[8];
+    int32_t neg_sum, bias;
+    int twice;
+    int64_t scale;
+};
+bool merge_code(const Planes &pl, MergeCode &c);  // false: other multipliers, or values beyond int8
+
+// Temporary device memory from the stream's pool, given back in stream order.
+struct PoolMemory {
+    void *ptr = nullptr;
+    hipStream_t s;
+    explicit PoolMemory(hipStream_t stream) : s(stream) {}
+    int take(size_t bytes) {
+        if (hipMallocAsync(&ptr, bytes, s) != hipSuccess || !ptr) {
+            (void)hipGetLastError();
+            ptr = nullptr;
+            return fail(QNN_ERR_HIP, "gemm: no memory for the merged operands (%zu bytes)", bytes);
+        }
+        return QNN_OK;
+    }
+    int give_back(int rc) {
+        if (ptr && hipFreeAsync(ptr, s) != hipSuccess) {
+            (void)hipGetLastError();
+            if (rc == QNN_OK) rc = fail(QNN_ERR_HIP, "gemm: returning the merged operands' memory failed");
+        }
+        return rc;
+    }
+};
 
 // Expansion of packed +-1 weights (N rows of K elements) to one int8 per element (row pitch ld_out, a multiple of 128,
 // zeros beyond K) and rw_scaled[n] = 128 * (sum of the weights of row n): operands of the uint8-input kernel.
@@ -146,13 +181,6 @@ namespace bytes_panel {
 // merge_supports: whether the values of both operands fit int8.
 bool merge_supports(const Planes &pa, const Planes &pw);
 int launch_merge_planes(const GemmArgs &g, int8_t *outA, int8_t *outW, int64_t ld_out, int64_t &scale, hipStream_t s);
-// The backward step's operands as bytes: a gradient (planes with multipliers +-2^q) in both orders with its row and column sums,
-// and a packed bit matrix transposed to bytes 0 / 1 (which also clears n_clear words).
-bool merge_both_supports(const Planes &pl);
-int launch_merge_transpose(const Planes &pl, const uint32_t *planes, int64_t plane_stride, int64_t ld, int64_t M, int64_t N, int8_t *out,
-                           int64_t ld_out, int8_t *out_t, int64_t ld_t, int32_t *row_sums, int32_t *col_sums, int64_t &scale, hipStream_t s);
-int launch_transpose_to_bytes(const uint32_t *in, int64_t rows, int64_t cols, int64_t ld, uint8_t *out, int64_t ld_out, int32_t *clear,
-                              int64_t n_clear, hipStream_t s);
 int launch_expand_weights(const uint32_t *W, int64_t N, int64_t K, int64_t ldw, int8_t *out, int64_t ld_out, int32_t *rw_scaled,
                           hipStream_t s);
 }

@@ -477,10 +477,9 @@ extern "C" int qnn_binary_backward(const uint32_t *G, int Pg, const int32_t *coe
     b.gA = gA, b.gW = gW, b.ld_ga = ld_ga, b.ld_gw = ld_gw, b.M = M, b.N = N, b.K = K;
     // (what the products refuse is left to them)
     const bool valid = (modeG == QNN_PLANE_BIT || modeG == QNN_PLANE_SIGN) && b.strideG >= 0 && aligned4(G) && aligned4(gA) && aligned4(gW);
-    if (valid && backward_bytes_preferred(b)) {
-        // (eight planes of the transposed gradient take as much of the workspace as its bytes)
+    if (valid && backward_mixed_preferred(b)) {
         bool no_memory;
-        rc = launch_backward_bytes(b, Pg == 8 ? reinterpret_cast<int8_t *>(Gt) : nullptr, no_memory, st);
+        rc = mixed::launch_backward(b, workspace, workspace_bytes, no_memory, st);
         if (rc == QNN_OK) note_engine(QNN_ENGINE_MFMA_LDS);
         // a pool that cannot hold the operands of both products may hold those of one, which the way below asks for
         if (!no_memory) return rc;

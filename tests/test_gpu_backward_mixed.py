@@ -1,0 +1,75 @@
+"""The backward step on FP6 or int8 gradients: sizes one off its tiles (128 x 128, 128 x 256) and its groups of 256 and 128; gradients whose
+values are all E3M2 numbers (three leading bits), and the same with a single one that is not, which turns both images to int8."""
+import pytest
+import torch
+
+from qnn_testlib import kernels_of
+
+pytestmark = pytest.mark.gpu
+
+EXACT = sorted({s * m << e for s in (1, -1) for m in (0, 4, 5, 6, 7) for e in range(5) if m << e <= 112} | {1, 2, 3, -1, -2, -3, -128})
+COEF = [1, 2, 4, 8, 16, 32, 64, -128]
+
+
+def _step(q, v, coef, K, planes=None, mode=0):
+    M, N = v.shape
+    w, a = (torch.randint(0, 2, (r, K), device="cuda") * 2 - 1 for r in (N, M))
+    G = q.qnn_pack_bitplanes((v & 255).to(torch.uint8), 8) if planes is None else planes
+    W, A = q.qnn_pack_sign(w.float()), q.qnn_pack_sign(a.float())
+
+    def call():
+        return q.qnn_binary_backward(G, coef, mode, N, W, A, K)
+
+    ga, gw = call()
+    assert kernels_of(call)[:2] == ["transpose_to_image_kernel", "merge_transpose_kernel"]
+    assert torch.equal(ga, (v.double() @ w.double()).to(torch.int32))
+    assert torch.equal(gw, (v.t().contiguous().double() @ a.double()).to(torch.int32))
+
+
+@pytest.mark.parametrize("M,N,K", [(1281, 2050, 2049), (2305, 1151, 1100), (4100, 2817, 385), (1000, 4096, 4100), (8192, 2304, 257)])
+@pytest.mark.parametrize("kind", ["exact", "one other", "any"])
+def test_formats(seed, M, N, K, kind):
+    import paper_1609_07061_amd as q
+
+    torch.manual_seed(seed)
+    v = torch.tensor(EXACT, device="cuda")[torch.randint(0, len(EXACT), (M, N), device="cuda")]
+    if kind == "one other":
+        v[M - 1, N - 1] = -127
+    elif kind == "any":
+        v = torch.randint(-128, 128, (M, N), device="cuda")
+    _step(q, v, COEF, K)
+
+
+@pytest.mark.parametrize("value", [1, 7, -7, 9, -9, 17, 33, 65, 127, -127, 112, -128, 120])
+def test_one_value_decides(seed, value):
+    """A gradient of zeros but for one row of `value`: eight bits, and six +-1 planes of which all sums are odd."""
+    import paper_1609_07061_amd as q
+
+    torch.manual_seed(seed)
+    M, N, K = 1009, 1280, 2784
+    v = torch.zeros((M, N), dtype=torch.int64, device="cuda")
+    v[500] = value
+    _step(q, v, COEF, K)
+    if value % 2 and abs(value) < 64:
+        v = torch.ones((M, N), dtype=torch.int64, device="cuda")
+        v[500] = value
+        u = (v + 63) // 2  # v = sum of +-2^p over six planes
+        _step(q, v, [1, 2, 4, 8, 16, 32], K, planes=q.qnn_pack_bitplanes(u.to(torch.uint8), 6), mode=1)
+
+
+def test_largest_sums():
+    """60 000 rows of -128 against weights of +1 in their larger half: sums up to 7.6e6 with steps of 128, and odd ones beside them."""
+    import paper_1609_07061_amd as q
+
+    M, N, K = 60000, 2048, 1024
+    for odd in (64, 127):
+        v = torch.full((M, N), -128, dtype=torch.int64, device="cuda")
+        v[:, ::3] = 1
+        v[::7, ::5] = odd
+        w, a = torch.ones((N, K), device="cuda"), torch.ones((M, K), device="cuda")
+        w[:, ::2] *= -1
+        a[::3, 1::2] *= -1
+        G, W, A = q.qnn_pack_bitplanes((v & 255).to(torch.uint8), 8), q.qnn_pack_sign(w), q.qnn_pack_sign(a)
+        ga, gw = q.qnn_binary_backward(G, COEF, 0, N, W, A, K)
+        assert torch.equal(ga, (v.double() @ w.double()).to(torch.int32))
+        assert torch.equal(gw, (v.t().contiguous().double() @ a.double()).to(torch.int32))
