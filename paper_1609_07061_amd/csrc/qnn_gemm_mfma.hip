@@ -200,6 +200,31 @@ static bool panel_layout(const GemmArgs &g, const Variant *v, bool vec) {
     return vec && spans32 && !g.A.rows_are_pixels && !g.A.rows_are_bytes && v->WPL == 4 && g.Kw % panel::kGroupWords == 0;
 }
 
+// Which of the panel-fed kernels and tiles: by the time of their rounds (us; k = thousands of 1024 elements).  Tiles of 128 x 256 or 128 x
+// 128, two workgroups on a compute unit: a round with two and with one on a unit; a thinly filled last round and the padding of a ragged
+// edge (128 columns under 256-column tiles: half of every tile) both show.  (128 x 256 -> 128 x 128: 10000 x 4096 x 4096 with thresholds
+// 55.7 and 64.2, 3000 x 4096 x 4096 24.2 and 19.3, 10000 x 2048 x 2048 21.5 and 19.6, 262144 x 128 x 1024 36.9 and 21.9, 700 x 4096 x 4096
+// 15.8 and 10.5; before, on 256 x 256 and 256 x 128 tiles of one workgroup, 60.3, 24.9, 26.1, 24.4, 14.7.)  Int32 sums on 256 x 256 tiles of one
+// workgroup where that costs less: rounds of 9.5 + 4.1 k against 8.2 + 4.55 k.
+struct PanelTiles {
+    bool narrow, wide;
+    PanelTiles(const GemmArgs &g, int64_t cus) {
+        const double k = (double)g.Kw / 32.0, store = g.epi.T ? 0.0 : 4.7;
+        // (a last round of few tiles runs at a higher clock: 6144^3, two rounds and 128 tiles of 128 x 256, 81.8, of 128 x 128 88.7)
+        auto rounds = [cus](int64_t tiles, double two, double one) {
+            const int64_t whole = tiles / (2 * cus), rest = tiles % (2 * cus);
+            const double last = rest > cus ? two : (whole > 0 ? (0.4 + 0.6 * (double)rest / (double)cus) * one : one);
+            return (double)whole * two + (rest == 0 ? 0.0 : last);
+        };
+        const int64_t tm = ceil_div(g.M, panel::BM);
+        const double large = rounds(tm * ceil_div(g.N, 256), 3.5 + store + 4.55 * k, 2.2 + 0.7 * store + 2.55 * k);
+        const double small = rounds(tm * ceil_div(g.N, 128), 2.2 + 0.6 * store + 2.4 * k, 1.2 + 0.4 * store + 1.6 * k);
+        narrow = small < 0.98 * large;
+        wide = !g.epi.T && g.Kw % panel::kWideGroupWords == 0 &&
+               (double)ceil_div(ceil_div(g.M, 256) * ceil_div(g.N, 256), cus) * (9.5 + 4.125 * k) < (narrow ? small : large);
+    }
+};
+
 bool panel_takes(const GemmArgs &g) {
     const Variant *v;
     MfmaConst mc;
@@ -225,28 +250,17 @@ int launch_gemm_mfma(const GemmArgs &g, hipStream_t s, bool fp4) {
         MfmaConst pc = mc;
         if (make_code(g.pa, pc.a, aA, bA, xA0) && make_code(g.pw, pc.w, aW, bW, xW0) &&
             fill_consts(g, aA, bA, xA0, aW, bW, xW0, ngroups * panel::kGroupWords * 32, pc)) {
-            // Tile schedule by cost, in units of a round of 256 x 128 tiles: a round of 256 x 256 tiles costs 1.86 with
-            // long rows (measured at K = 4096) and two with short ones, where the epilogue dominates.  The rounds count
-            // whole tiles, so the padding of a ragged edge (128 columns under 256-column tiles: half of every tile) and
-            // a thinly filled last round both show.  Third schedule: wide tiles with the last round's tiles halved
-            // (each half to a workgroup of its own, 1.17 for that round), possible when that round has tiles for at most
-            // half of the workgroups and worth it only for long rows.
-            const int64_t tiles_n2 = ceil_div(g.N, BN / 2);
-            const double wide_round = ngroups >= 4 ? 1.86 : 2.0, half_round = 1.17;
-            const double cost_wide = (double)ceil_div(total, cus) * wide_round;
-            const double cost_narrow = (double)ceil_div(tiles_m * tiles_n2, cus);
-            bool narrow = cost_narrow < cost_wide;
-            bool tail = false;
-            if (cus % 16 == 0 && total > cus && total % cus != 0 && 2 * (total % cus) <= cus && ngroups >= 4) {
-                const double cost_tail = (double)(total / cus) * wide_round + half_round;
-                tail = cost_tail < (narrow ? cost_narrow : cost_wide);
+            const PanelTiles pt(g, cus);
+            if (pt.wide) {
+                const unsigned wgrid = (unsigned)(total < cus ? total : cus);
+                return QNN_LAUNCH("gemm_panel_wide", panel::wide_kernel(), dim3(wgrid), dim3(panel::kThreads), 0, s, g, pc, (uint32_t)tiles_m, (uint32_t)tiles_n,
+                                  (uint32_t)(g.Kw / panel::kWideGroupWords));
             }
-            narrow = narrow && !tail;
-            const panel::KernelFn pf = panel::find_kernel(g.epi.T != nullptr, narrow, tail);
-            const int64_t ptotal = narrow ? tiles_m * tiles_n2 : total;
-            const unsigned pgrid = (unsigned)(ptotal < cus ? ptotal : cus);
-            return QNN_LAUNCH("gemm_panel", pf, dim3(pgrid), dim3(panel::kThreads), 0, s, g, pc, (uint32_t)tiles_m,
-                              (uint32_t)(narrow ? tiles_n2 : tiles_n), (uint32_t)ngroups);
+            const panel::KernelFn pf = panel::find_kernel(g.epi.T != nullptr, pt.narrow);
+            const int64_t pm = ceil_div(g.M, panel::BM), pn = ceil_div(g.N, pt.narrow ? 128 : 256);
+            if (pm * pn > 0x7FFFFFFFLL) return fail(QNN_ERR_SHAPE, "gemm: too many tiles");
+            const unsigned pgrid = (unsigned)(pm * pn < 2 * cus ? pm * pn : 2 * cus);
+            return QNN_LAUNCH("gemm_panel", pf, dim3(pgrid), dim3(panel::kThreads), 0, s, g, pc, (uint32_t)pm, (uint32_t)pn, (uint32_t)ngroups);
         }
     }
     // uint8 left operand with the weights expanded to bytes beforehand: the panel-fed kernel (threshold epilogue)

@@ -448,7 +448,7 @@ bool slice_preferred(const GemmArgs &g, int route) {
     if (!slice_args(g, false, sc, ka, kw)) return false;
     if (route == QNN_ENGINE_MFMA_FP4 && panel_takes(g)) {
         const int64_t tiles64 = ceil_div(g.M, 64) * ceil_div(g.N, 64);
-        if (g.epi.T) return tiles64 <= 640;
+        if (g.epi.T) return tiles64 <= (g.N < 512 || g.K > 4096 ? 640 : 256);
         return tiles64 <= 1024 || (g.K <= 2048 && ceil_div(g.M, 256) * ceil_div(g.N, 128) < 256);
     }
     if (route == QNN_ENGINE_MFMA_LDS && ceil_div(g.M, 128) * ceil_div(g.N, 128) >= 192) return tile_us(g, sc, ka, kw) <= stage_us(g);

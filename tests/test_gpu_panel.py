@@ -1,0 +1,47 @@
+"""The panel-fed FP4 kernels: sizes one off their tiles (128 x 128, 128 x 256, 256 x 256) and rows of one, three and more groups of 512."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from qnn_testlib import host, host_u32, kernels_of
+
+pytestmark = pytest.mark.gpu
+
+
+def _operands(seed, M, N, K):
+    torch.manual_seed(seed)
+    a, w = (torch.randint(0, 2, (rows, K), device="cuda") * 2 - 1 for rows in (M, N))
+    return a, w, (a.double() @ w.double().t().contiguous()).to(torch.int32)
+
+
+@pytest.mark.parametrize("M,N", [(129, 33), (127, 257), (1025, 2047), (385, 1281), (8200, 130), (2100, 4100)])
+@pytest.mark.parametrize("K", [512, 1536, 4608])
+def test_edges(seed, M, N, K):
+    import paper_1609_07061_amd as q
+
+    a, w, want = _operands(seed, M, N, K)
+    A, W = q.qnn_pack_sign(a.float()), q.qnn_pack_sign(w.float())
+    T = want[0] + torch.arange(N, device="cuda", dtype=torch.int32) % 3 - 1
+    flip = (torch.arange(N, device="cuda") % 5 == 0).to(torch.uint8)
+    wide = torch.full((M, N + 3), 7, dtype=torch.int32, device="cuda")
+    for C in (torch.empty((M, N), dtype=torch.int32, device="cuda"), wide[:, 1:1 + N]):
+        q.qnn_binary_gemm(A, W, K, out=C, engine=q.ENGINE_MFMA_FP4)
+        assert torch.equal(C, want), (M, N, K)
+    assert bool((wide[:, 0] == 7).all()) and bool((wide[:, 1 + N:] == 7).all())
+    assert kernels_of(lambda: q.qnn_binary_gemm(A, W, K, out=C, engine=q.ENGINE_MFMA_FP4))[0].startswith("gemm_panel_kernel")
+    got = q.qnn_binary_gemm_sign(A, W, K, T, flip, engine=q.ENGINE_MFMA_FP4)
+    bit = host(((want >= T[None]) != (flip[None] != 0)).to(torch.int8))
+    assert np.array_equal(host_u32(got), oracle.pack_bits((2 * bit - 1).astype(np.int8))), (M, N, K)
+    assert kernels_of(lambda: q.qnn_binary_gemm_sign(A, W, K, T, engine=q.ENGINE_MFMA_FP4))[0].startswith("gemm_panel_kernel<true")
+
+
+@pytest.mark.parametrize("M,N", [(4090, 4091), (4096, 4096)])
+def test_wide_tiles(seed, M, N):
+    import paper_1609_07061_amd as q
+
+    K = 10240
+    a, w, want = _operands(seed, M, N, K)
+    A, W = q.qnn_pack_sign(a.float()), q.qnn_pack_sign(w.float())
+    assert torch.equal(q.qnn_binary_gemm(A, W, K), want)
+    assert kernels_of(lambda: q.qnn_binary_gemm(A, W, K)) == ["gemm_panel_wide_kernel"]
