@@ -193,43 +193,54 @@ static BytesTiles bytes_tiles(int64_t M, int64_t N, int cus) {
     return t;
 }
 
-// Layout conditions of the panel-fed kernel: single planes, rows of whole 128-byte groups on 16-byte boundaries (row offsets are
-// 32-bit and formed for up to one tile beyond the last row before they are clamped).
-static bool panel_layout(const GemmArgs &g, const Variant *v, bool vec) {
+// What the panel-fed kernels take: single planes of matrices that span less than 4 GiB with a tile beyond the last row (row offsets are
+// 32-bit, and the wide kernel forms them before it clamps them).
+static bool panel_layout(const GemmArgs &g) {
     const bool spans32 = 4.0L * (long double)(g.M + 256) * g.A.ld < 4294967296.0L && 4.0L * (long double)(g.N + 256) * g.ldw < 4294967296.0L;
-    return vec && spans32 && !g.A.rows_are_pixels && !g.A.rows_are_bytes && v->WPL == 4 && g.Kw % panel::kGroupWords == 0;
+    return spans32 && g.pa.count == 1 && g.pw.count == 1 && !g.A.rows_are_pixels && !g.A.rows_are_bytes;
 }
 
-// Which of the panel-fed kernels and tiles: by the time of their rounds (us; k = thousands of 1024 elements).  Tiles of 128 x 256 or 128 x
-// 128, two workgroups on a compute unit: a round with two and with one on a unit; a thinly filled last round and the padding of a ragged
-// edge (128 columns under 256-column tiles: half of every tile) both show.  (128 x 256 -> 128 x 128: 10000 x 4096 x 4096 with thresholds
-// 55.7 and 64.2, 3000 x 4096 x 4096 24.2 and 19.3, 10000 x 2048 x 2048 21.5 and 19.6, 262144 x 128 x 1024 36.9 and 21.9, 700 x 4096 x 4096
-// 15.8 and 10.5; before, on 256 x 256 and 256 x 128 tiles of one workgroup, 60.3, 24.9, 26.1, 24.4, 14.7.)  Int32 sums on 256 x 256 tiles of one
-// workgroup where that costs less: rounds of 9.5 + 4.1 k against 8.2 + 4.55 k.
+// Which of the panel-fed kernels and tiles: by the time of their rounds (us; k = thousands of 1024 elements).  Tiles of 128 x 256, 256 x 128
+// or 128 x 128, two workgroups on a compute unit (three with 128 x 128 and thresholds, whose registers allow it: first 128-filter
+// convolution of the App. A network on 256 images, 2048 tiles, 30.8 -> 26.1): a round with two and with one on a unit; a thinly filled last round
+// and the padding of a ragged edge both show.  (128 x 256 -> 128 x 128: 10000 x 4096 x 4096 with thresholds 55.7 and 64.2, 3000 x 4096 x
+// 4096 24.2 and 19.3, 10000 x 2048 x 2048 21.5 and 19.6, 262144 x 128 x 1024 36.9 and 21.9, 700 x 4096 x 4096 15.8 and 10.5; before, on 256
+// x 256 and 256 x 128 tiles of one workgroup, 60.3, 24.9, 26.1, 24.4, 14.7.)  Int32 sums on 256 x 256 tiles of one workgroup where
+// that costs less: rounds of 9.5 + 4.1 k against 8.2 + 4.55 k.
 struct PanelTiles {
-    bool narrow, wide;
-    PanelTiles(const GemmArgs &g, int64_t cus) {
-        const double k = (double)g.Kw / 32.0, store = g.epi.T ? 0.0 : 4.7;
+    panel::Shape shape;
+    int per;    // workgroups on a compute unit
+    bool wide;  // 256 x 256, one workgroup
+    PanelTiles(int64_t M, int64_t N, int64_t Kw, bool sign, bool map, int64_t cus) {
+        const double k = (double)Kw / 32.0;
         // (a last round of few tiles runs at a higher clock: 6144^3, two rounds and 128 tiles of 128 x 256, 81.8, of 128 x 128 88.7)
         auto rounds = [cus](int64_t tiles, double two, double one) {
             const int64_t whole = tiles / (2 * cus), rest = tiles % (2 * cus);
             const double last = rest > cus ? two : (whole > 0 ? (0.4 + 0.6 * (double)rest / (double)cus) * one : one);
             return (double)whole * two + (rest == 0 ? 0.0 : last);
         };
-        const int64_t tm = ceil_div(g.M, panel::BM);
-        const double large = rounds(tm * ceil_div(g.N, 256), 3.5 + store + 4.55 * k, 2.2 + 0.7 * store + 2.55 * k);
-        const double small = rounds(tm * ceil_div(g.N, 128), 2.2 + 0.6 * store + 2.4 * k, 1.2 + 0.4 * store + 1.6 * k);
-        narrow = small < 0.98 * large;
-        wide = !g.epi.T && g.Kw % panel::kWideGroupWords == 0 &&
-               (double)ceil_div(ceil_div(g.M, 256) * ceil_div(g.N, 256), cus) * (9.5 + 4.125 * k) < (narrow ? small : large);
+        const int64_t tm = ceil_div(M, 128), tn = ceil_div(N, 128);
+        const double end = sign ? (map ? 3.0 : 0.0) : 4.7;  // what the epilogue takes beyond that of plain thresholds
+        const double two = 3.5 + end + 4.55 * k, one = 2.2 + 0.7 * end + 2.55 * k;
+        const double large = rounds(tm * ceil_div(N, 256), two, one), tall = rounds(ceil_div(M, 256) * tn, two, one);
+        const double small = rounds(tm * tn, 2.2 + (map ? 0.5 : 0.6 * end) + 2.4 * k, 1.2 + (map ? 0.3 : 0.4 * end) + 1.6 * k);
+        const double best = large <= tall ? large : tall;
+        shape = small < 0.98 * best ? panel::k128x128 : (large <= tall ? panel::k128x256 : panel::k256x128);
+        per = shape == panel::k128x128 && sign ? 3 : 2;
+        wide = !sign && Kw % panel::kWideGroupWords == 0 && (double)ceil_div(ceil_div(M, 256) * ceil_div(N, 256), cus) * (9.5 + 4.125 * k) < (small < 0.98 * best ? small : best);
     }
 };
+
+void panel_shape(int64_t M, int64_t N, int64_t Kw, int &shape, int &per) {
+    const PanelTiles t(M, N, Kw, true, true, compute_units());
+    shape = t.shape, per = t.per;
+}
 
 bool panel_takes(const GemmArgs &g) {
     const Variant *v;
     MfmaConst mc;
     bool vec;
-    return prepare(g, true, v, mc, vec) && panel_layout(g, v, vec);
+    return g.K >= 512 && prepare(g, true, v, mc, vec) && panel_layout(g);
 }
 
 int launch_gemm_mfma(const GemmArgs &g, hipStream_t s, bool fp4) {
@@ -243,24 +254,28 @@ int launch_gemm_mfma(const GemmArgs &g, hipStream_t s, bool fp4) {
     const int cus = compute_units();
     const int64_t total = tiles_m * tiles_n;
     const unsigned grid = (unsigned)(total < cus ? total : cus);
-    // single-plane products on the FP4 path whose rows are made of whole, aligned 16-byte groups: the panel-fed kernel
-    if (fp4 && panel_layout(g, v, vec)) {
-        const int64_t ngroups = ceil_div(g.Kw, panel::kGroupWords);
+    // single-plane products on the FP4 path: the panel-fed kernels
+    if (fp4 && panel_layout(g)) {
+        const bool whole = vec && g.Kw % panel::kGroupWords == 0;
         int64_t aA, bA, xA0, aW, bW, xW0;
         MfmaConst pc = mc;
+        panel::PanelArgs pa;
+        std::memset(&pa, 0, sizeof(pa));
+        pa.steps = (uint32_t)(whole ? g.Kw / 8 : ceil_div(g.Kw, 8));
         if (make_code(g.pa, pc.a, aA, bA, xA0) && make_code(g.pw, pc.w, aW, bW, xW0) &&
-            fill_consts(g, aA, bA, xA0, aW, bW, xW0, ngroups * panel::kGroupWords * 32, pc)) {
-            const PanelTiles pt(g, cus);
-            if (pt.wide) {
+            fill_consts(g, aA, bA, xA0, aW, bW, xW0, (int64_t)pa.steps * 256, pc)) {
+            const PanelTiles pt(g.M, g.N, g.Kw, g.epi.T != nullptr, false, cus);
+            if (pt.wide && whole) {
                 const unsigned wgrid = (unsigned)(total < cus ? total : cus);
                 return QNN_LAUNCH("gemm_panel_wide", panel::wide_kernel(), dim3(wgrid), dim3(panel::kThreads), 0, s, g, pc, (uint32_t)tiles_m, (uint32_t)tiles_n,
                                   (uint32_t)(g.Kw / panel::kWideGroupWords));
             }
-            const panel::KernelFn pf = panel::find_kernel(g.epi.T != nullptr, pt.narrow);
-            const int64_t pm = ceil_div(g.M, panel::BM), pn = ceil_div(g.N, pt.narrow ? 128 : 256);
+            const int64_t pm = ceil_div(g.M, panel::rows_of(pt.shape)), pn = ceil_div(g.N, panel::columns_of(pt.shape)), per = pt.per * cus;
             if (pm * pn > 0x7FFFFFFFLL) return fail(QNN_ERR_SHAPE, "gemm: too many tiles");
-            const unsigned pgrid = (unsigned)(pm * pn < 2 * cus ? pm * pn : 2 * cus);
-            return QNN_LAUNCH("gemm_panel", pf, dim3(pgrid), dim3(panel::kThreads), 0, s, g, pc, (uint32_t)pm, (uint32_t)pn, (uint32_t)ngroups);
+            pa.tiles_m = (uint32_t)pm, pa.tiles_n = (uint32_t)pn;
+            pa.a_bytes = (uint32_t)(((g.M - 1) * g.A.ld + g.Kw) * 4), pa.w_bytes = (uint32_t)(((g.N - 1) * g.ldw + g.Kw) * 4);
+            const unsigned pgrid = (unsigned)(pm * pn < per ? pm * pn : per);
+            return QNN_LAUNCH("gemm_panel", panel::find_kernel(g.epi.T != nullptr, pt.shape, whole), dim3(pgrid), dim3(panel::kThreads), 0, s, g, pc, pa);
         }
     }
     // uint8 left operand with the weights expanded to bytes beforehand: the panel-fed kernel (threshold epilogue)

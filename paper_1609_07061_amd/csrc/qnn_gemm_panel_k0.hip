@@ -5,12 +5,22 @@
 namespace qnn {
 namespace panel {
 
-KernelFn find_kernel(bool sign, bool narrow) {
-    if (narrow) return sign ? gemm_panel_kernel<true, 2> : gemm_panel_kernel<false, 2>;
-    return sign ? gemm_panel_kernel<true, 4> : gemm_panel_kernel<false, 4>;
+namespace {
+template <bool kSign, int kRows>
+KernelFn find(Shape t) {
+    if (t == k128x256) return gemm_panel_kernel<kSign, 2, 4, kRows>;
+    return t == k128x128 ? gemm_panel_kernel<kSign, 2, 2, kRows> : gemm_panel_kernel<kSign, 4, 4, kRows>;
 }
-
-KernelFn wide_kernel() { return panel_wide::gemm_panel_wide_kernel; }
+}  // namespace
+KernelFn find_kernel(bool sign, Shape t, bool whole) {
+    if (whole) return sign ? find<true, kWholeRows>(t) : find<false, kWholeRows>(t);
+    return sign ? find<true, kAnyRows>(t) : find<false, kAnyRows>(t);
+}
+MapFn map_kernel(Shape t) {
+    if (t == k128x256) return gemm_tile_kernel<2, 4, WB, true>;
+    return t == k128x128 ? gemm_tile_kernel<2, 2, WB, true> : gemm_tile_kernel<4, 4, WB, true>;
+}
+WideFn wide_kernel() { return panel_wide::gemm_panel_wide_kernel; }
 
 }  // namespace panel
 }  // namespace qnn

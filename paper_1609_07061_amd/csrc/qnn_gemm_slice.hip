@@ -431,8 +431,8 @@ double slice_us(const GemmArgs &g) {
 // counts for 256 compute units):
 //   vector-ALU route: everything (32 x 4096 x 4096 20 -> 4.5; 20 x 4096 x 2048 with 4 x 4 planes 134 -> 8; convolution of four
 //     13 x 13 maps, 384 -> 256 channels, 39 -> 5; 1000 x 1000 x 1000 8.7 -> 5.3);
-//   single planes that miss the panel-fed kernel's layout: everything (1999 x 3001 x 2500 82 -> 21; 8000^3 640 -> 234);
-//   single planes that fit it, int32 sums: while 64 x 64 tiles make one round at most (256 x 1024 x 8192 24 -> 6; 10000 x 256 x 8192, 628
+//   single planes that the panel-fed kernel does not take or rows below 512 elements: everything (1999 x 3001 x 2500 82 -> 21);
+//   other single planes, int32 sums: while 64 x 64 tiles make one round at most (256 x 1024 x 8192 24 -> 6; 10000 x 256 x 8192, 628
 //     tiles, 25 -> 19; 2048^3, 1024, 12.8 -> 11.2), and while the panels' 256 x 128 tiles leave compute units idle and rows are short
 //     (3000 x 2048, 192 such tiles, x 1024 11.2 -> 9.7, x 2048 13.4 and 13.7, x 4096 18.0 against 19.7, x 8192 26.8 against 32.5);
 //   the same with threshold output, which costs the panel-fed kernel less: while 64 x 64 tiles are few (512 x 4096 x 4096, 512 tiles, 14.7
@@ -448,7 +448,7 @@ bool slice_preferred(const GemmArgs &g, int route) {
     if (!slice_args(g, false, sc, ka, kw)) return false;
     if (route == QNN_ENGINE_MFMA_FP4 && panel_takes(g)) {
         const int64_t tiles64 = ceil_div(g.M, 64) * ceil_div(g.N, 64);
-        if (g.epi.T) return tiles64 <= (g.N < 512 || g.K > 4096 ? 640 : 256);
+        if (g.epi.T) return tiles64 <= (g.N < 512 || g.K > 4096 ? 640 : 288);
         return tiles64 <= 1024 || (g.K <= 2048 && ceil_div(g.M, 256) * ceil_div(g.N, 128) < 256);
     }
     if (route == QNN_ENGINE_MFMA_LDS && ceil_div(g.M, 128) * ceil_div(g.N, 128) >= 192) return tile_us(g, sc, ka, kw) <= stage_us(g);

@@ -19,6 +19,7 @@
 //     r sits at piece c xor (r / 2 mod 8), r / 4 mod 4 in groups of four, so that writes (whole rows of a group) and reads (32
 //     rows, one piece) use all banks.
 //   * Epilogue through LDS: a 32 x 64 block per wave at a time, so that C leaves as 256-byte pieces of rows.
+#include "qnn_gemm_panel_kernel.h"
 #include "qnn_gemm_slice.h"
 
 namespace qnn {
@@ -38,17 +39,14 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// kMap (3 x 3 "same" convolutions of +-1 maps, pad 1, stride 1, threshold output): the left operand is the map's plane "value is -1"
-// (0 outside the image), the filters enter as +-1.  With a = 1 - 2 p inside the image, conv = sum_{taps inside} sum_c w - 2 S,
-// S = sum_k p w, so a pixel's bit is (S > class_thr[class][n]) xor flip[n], class = which of the image's borders the pixel lies on
-// (see prepare_block).  A lane keeps a filter, so the class is one for the whole wave and row, and the 2 x 2 max-pooling
-// that may follow (OR of the four bits where the threshold does not flip, AND where it does) is three exchanges of packed words.
+// (kMap: false; the kernel for +-1 maps of the same name is in qnn_gemm_panel_kernel.h)
 template <int kA, int kW, int kRows, bool kMap = false>
 __global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) void gemm_tile_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
+    static_assert(!kMap, "matrices and patches of images");
     constexpr bool kPixels = kRows != kMatrix;
     constexpr int NA = kA == kPair ? 2 : 1, NW = kW == kPair ? 2 : 1;  // planes of a digit
     // 16-byte pieces of a row per group (two of them make a chunk of 256 elements)
-    constexpr int kPieces = kMap || (kA == kPair && kW == kPair && !kPixels) ? 8 : 4;
+    constexpr int kPieces = kA == kPair && kW == kPair && !kPixels ? 8 : 4;
     constexpr int kRowBytes = 16 * kPieces, kPlaneBytes = kTile * kRowBytes;    // a group of one plane of an operand
     constexpr int kLoads = kPieces / 2, kLoadRows = kTile / kLoads;            // per plane: loads of a wave, rows of a load of the workgroup
     constexpr uint32_t kSwizzle = kPieces == 8 ? 1 : 2;                        // rows of this power of two share an order of pieces
@@ -60,17 +58,6 @@ __global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) v
     uint32_t tm, tn;
     tile_of_block(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
     const uint32_t m0 = tm * kTile, n0 = tn * kTile;
-    // kMap: thresholds of nine border classes (row class 0 = interior, 1 = first row, 2 = last row; column class likewise; 3 row +
-    // column) for the wave's 64 filters.  The table in memory is indexed by four bits (first row, last row, first column, last).
-    __shared__ float thr_tab[kMap ? 4 : 1][kMap ? 9 * 64 : 1];
-    if constexpr (kMap) {
-#pragma unroll
-        for (uint32_t c9 = 0; c9 < 9; ++c9) {
-            const uint32_t rc = c9 / 3, cc = c9 % 3;
-            const uint32_t c16 = (rc == 1 ? 1u : 0u) | (rc == 2 ? 2u : 0u) | (cc == 1 ? 4u : 0u) | (cc == 2 ? 8u : 0u);
-            thr_tab[wave][64 * c9 + lane] = __int_as_float(g.class_thr[c16 * (uint32_t)g.class_ld + n0 + 64u * wn + lane]);
-        }
-    }
 
     // ------------------------------------------------------------------------------------------------ loads
     // load i of a plane: piece lane mod kPieces of rows kLoadRows i + prow
@@ -141,7 +128,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) v
                 }
             }
         }
-        if (!kMap && sc.clear_w && (kPixels || tail)) {
+        if (sc.clear_w && (kPixels || tail)) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const uint32_t keep = (uint32_t)e >= x.skip ? 0xFFFFFFFFu : 0u;
@@ -152,7 +139,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) v
                 }
             }
         }
-        if (!kMap && sc.modified) {
+        if (sc.modified) {
 #pragma unroll
             for (int i = 0; i < kLoads; ++i) {
                 apply_inversion<kA>(da.inv0, da.inv1, da.use1, x.a[0][i], x.a[NA - 1][i]);
@@ -160,7 +147,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) v
             }
         }
         // (pieces beyond the last chunk are not multiplied: they count only where they are zero)
-        if (!kMap && (!sc.modified || (uint32_t)kPieces * G + piece0 < 2u * sc.chunks)) {
+        if ((!sc.modified || (uint32_t)kPieces * G + piece0 < 2u * sc.chunks)) {
             if (sc.sum_a) {
 #pragma unroll
                 for (int i = 0; i < kLoads; ++i) sum_a[i] = add_sum<kA>(x.a[0][i], x.a[NA - 1][i], sum_a[i]);
@@ -246,7 +233,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) v
         __syncthreads();
         const uint32_t left = sc.chunks - kPieces / 2u * G;
         const bool pair_ends = G + 1u == groups;
-        if (!kMap && pair_ends && sc.corrected) {  // weigh the row sums of this pair
+        if (pair_ends && sc.corrected) {  // weigh the row sums of this pair
             const int shift = sc.a.d[ia].lg + sc.w.d[iw].lg;
             const int a_fac = (sc.w.d[iw].offset2 << shift) >> 1, w_fac = (sc.a.d[ia].offset2 << shift) >> 1;
 #pragma unroll
@@ -267,7 +254,6 @@ __global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) v
 
     // ------------------------------------------------------------------------------------------------ epilogue
     // register v of block [i][j] is C[m][n], m = 32 j + lane mod 32, n = 32 i + 8 (v / 4) + 4 kg + v mod 4 of the wave's tile
-    if constexpr (!kMap) {
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
         if (sc.corrected) {
@@ -278,7 +264,6 @@ __global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) v
         if (piece0 == 0)
             corr_a[kLoadRows * i + prow] = (int)((uint32_t)corr_a4[i] * sc.alpha), corr_w[kLoadRows * i + prow] = (int)((uint32_t)corr_w4[i] * sc.alpha - sc.c0);
     }
-    }
     __syncthreads();
     float *const stage = reinterpret_cast<float *>(lds) + wave * (32 * kStagePitch);
     // (the host has checked that the sums and alpha_sum are below 2^23 in magnitude: a 24-bit product, full rate)
@@ -286,72 +271,6 @@ __global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) v
     auto times_alpha = [alpha_sum](const float s) __attribute__((always_inline)) { return __mul24((int)s, alpha_sum); };
     const int64_t n_wave = (int64_t)n0 + 64 * wn;
     const bool vec = (g.epi.ldc % 4 == 0) && (reinterpret_cast<uintptr_t>(g.epi.C) % 16 == 0);
-    if constexpr (kMap) {
-        const int64_t n = n_wave + lane;
-        const unsigned long long live = __ballot(n < g.N), flips = __ballot(n < g.N && g.epi.flip && g.epi.flip[n] != 0);
-        const uint32_t m_wave = __builtin_amdgcn_readfirstlane(m0 + 64u * wm);
-        // where the thresholds of the pixel m_wave + lane begin in the table
-        uint32_t row0, x, y, img_rem;
-        const uint32_t m_lane = m_wave + lane;
-        (void)quotient(m_lane, (uint32_t)(g.A.H * g.A.Wd), sc.inv_hw, img_rem);
-        y = quotient(img_rem, (uint32_t)g.A.Wd, sc.inv_w, x);
-        const uint32_t c9 = 3u * (y == 0u ? 1u : (y + 1u == (uint32_t)g.A.H ? 2u : 0u)) + (x == 0u ? 1u : (x + 1u == (uint32_t)g.A.Wd ? 2u : 0u));
-        const int row_thr = (int)(64u * c9);
-        row0 = quotient(m_wave, (uint32_t)g.A.Wd, sc.inv_w, x);  // row of the first pixel, over all images
-        uint32_t word[2];  // lane 2 s + h: word h of pixel 32 j + s
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                    *reinterpret_cast<f32x4 *>(&stage[r * kStagePitch + 32 * i + 8 * q + 4 * kg]) = v;
-                }
-            wave_lds_fence();
-            uint32_t mine = 0;
-#pragma unroll
-            for (int s = 0; s < 32; ++s) {
-                const uint32_t first = (uint32_t)__builtin_amdgcn_readlane(row_thr, 32 * j + s);
-                const unsigned long long bits = (__ballot(stage[s * kStagePitch + lane] > thr_tab[wave][first + lane]) ^ flips) & live;
-                asm("v_writelane_b32 %0, %1, %2" : "+v"(mine) : "s"((uint32_t)bits), "n"(2 * s));
-                asm("v_writelane_b32 %0, %1, %2" : "+v"(mine) : "s"((uint32_t)(bits >> 32)), "n"(2 * s + 1));
-            }
-            word[j] = mine;
-            wave_lds_fence();
-        }
-        const int64_t n_word = n_wave + 32 * (lane & 1u);
-        if (n_word >= g.N) return;
-        if (!g.pool_and) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int64_t m = (int64_t)m_wave + 32 * j + (lane >> 1);
-                if (m < g.M) g.epi.out_bits[m * g.epi.ldo + n_word / 32] = word[j];
-            }
-            return;
-        }
-        // 2 x 2 max-pooling of whole row pairs (maps 8, 16 or 32 pixels wide with an even height: the 64 pixels are 8, 4 or 2
-        // rows, the first of them even)
-        const uint32_t mask = g.pool_and[n_word / 32] ^ g.pool_invert;
-        auto merge = [mask](const uint32_t a, const uint32_t b) { return ((a | b) & ~mask) | (a & b & mask); };
-        const uint32_t below = g.A.Wd == 16 ? 32u : 16u;  // lanes between a pixel and the one below it (8 or 16 wide)
-        uint32_t pooled[2];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            uint32_t v = g.A.Wd == 32 ? merge(word[0], word[1]) : merge(word[j], (uint32_t)__shfl_xor((int)word[j], (int)below, 64));
-            pooled[j] = merge(v, (uint32_t)__shfl_xor((int)v, 2, 64));
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const uint32_t s = 32u * j + (lane >> 1), sy = s / (uint32_t)g.A.Wd, sx = s - sy * (uint32_t)g.A.Wd;
-            const int64_t m = (int64_t)m_wave + s;
-            if (m < g.M && ((sy | sx) & 1u) == 0u) {
-                const int64_t row = (int64_t)row0 + sy;  // (over all images: their heights are even)
-                g.epi.out_bits[(row / 2 * (g.A.Wd / 2) + sx / 2) * g.epi.ldo + n_word / 32] = pooled[j];
-            }
-        }
-        return;
-    }
     int32_t T = 0;
     bool live = false, flip = false;
     if (g.epi.T) {
@@ -475,10 +394,16 @@ int launch_conv_map(const uint32_t *plane, int64_t B, int H, int Wd, int64_t C, 
     SliceArgs sc;
     int ka, kw;
     if (!slice_args(g, true, sc, ka, kw)) return fail(QNN_ERR_UNSUPPORTED, "convolution of a +-1 map: shape not supported");
-    sc.w.d[0].scale = 127 * 0x01010101;  // the filters' words as +-1 operands (kPm1)
-    const int64_t tiles_m = ceil_div(g.M, kTile), tiles_n = ceil_div(g.N, kTile);
-    const TileFn fn = Cw < 4 ? gemm_tile_kernel<kOne, kPm1, kNarrowPatches, true> : gemm_tile_kernel<kOne, kPm1, kPatches, true>;
-    return QNN_LAUNCH("conv_map", fn, dim3((unsigned)(tiles_m * tiles_n)), dim3(kTileThreads), 0, s, g, sc, (uint32_t)tiles_m, (uint32_t)tiles_n);
+    panel::PanelArgs x;
+    std::memset(&x, 0, sizeof(x));
+    x.sc = sc, x.steps = (uint32_t)ceil_div(9 * (int64_t)sc.ppt, 2);
+    x.a_bytes = (uint32_t)(g.M * Cw * 4), x.w_bytes = (uint32_t)(N * 9 * Cw * 4);
+    int which, per;
+    panel_shape(g.M, N, 8 * (int64_t)x.steps, which, per);
+    const panel::Shape shape = (panel::Shape)which;
+    const int64_t tiles_m = ceil_div(g.M, panel::rows_of(shape)), tiles_n = ceil_div(N, panel::columns_of(shape)), total = tiles_m * tiles_n, cus = compute_units();
+    x.tiles_m = (uint32_t)tiles_m, x.tiles_n = (uint32_t)tiles_n;
+    return QNN_LAUNCH("conv_map", panel::map_kernel(shape), dim3((unsigned)(total < per * cus ? total : per * cus)), dim3(panel::kThreads), 0, s, g, x);
 }
 
 }  // namespace qnn

@@ -138,7 +138,8 @@ bool backward_supports(const BackwardArgs &b);
 double backward_us(const BackwardArgs &b);  // about how long it takes (microseconds) where the gradient is int8
 int launch_backward(const BackwardArgs &b, void *workspace, size_t workspace_bytes, bool &no_memory, hipStream_t s);
 }
-bool panel_takes(const GemmArgs &g);  // whether the FP4 route would use the panel-fed kernel
+bool panel_takes(const GemmArgs &g);  // whether the FP4 route would use the panel-fed kernel (on rows that it pays for: 1999 x 3001 x 300 7.0 us on tiles, 8.2 on panels)
+void panel_shape(int64_t M, int64_t N, int64_t Kw, int &shape, int &per);  // ... a +-1 map with which tiles (panel::Shape)
 
 // How planes with multipliers +-2^q stand for a byte: the plane of bit q (-1: none), its inversion; value = scale ((sum 2^q bit -
 // neg_sum) [* 2 + bias]), the number in brackets within int8.
@@ -191,7 +192,7 @@ int launch_threshold_sign(const int32_t *C, int64_t ldc, int64_t M, int64_t N, c
                           uint32_t *out, int64_t ldo, hipStream_t s);
 
 // 3 x 3 "same" convolution of a +-1 feature map (held as its plane "value is -1", [B][H][Wd][ceil(C / 32)] words) with +-1 filters
-// and threshold output, on the tiled FP4 kernel.  bit = (conv >= T[n]) xor !flip_complement[n]: the caller passes the COMPLEMENT of
+// and threshold output, on the panel-fed FP4 kernel.  bit = (conv >= T[n]) xor !flip_complement[n]: the caller passes the COMPLEMENT of
 // its flip flags.  class_thr (16 x conv_class_ld(N) words) is written beforehand, on the same stream, by
 // launch_conv_first or launch_conv_class_thr (for all convolutions of a network at once).  The 2 x 2 max-pooling that follows is done along if
 // conv_map_pools (pool_and = packed flip flags of the filters, pool_invert = the map holds inverted bits; null: no pooling).

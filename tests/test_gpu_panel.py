@@ -1,4 +1,5 @@
-"""The panel-fed FP4 kernels: sizes one off their tiles (128 x 128, 128 x 256, 256 x 256) and rows of one, three and more groups of 512."""
+"""The panel-fed FP4 kernels: sizes one off their tiles (128 x 128, 128 x 256, 256 x 128, 256 x 256), rows of one, three and more groups of
+512, and rows of any length: one word, a piece or a step more or less than a group, at any pitch."""
 import numpy as np
 import pytest
 import torch
@@ -16,12 +17,14 @@ def _operands(seed, M, N, K):
 
 
 @pytest.mark.parametrize("M,N", [(129, 33), (127, 257), (1025, 2047), (385, 1281), (8200, 130), (2100, 4100)])
-@pytest.mark.parametrize("K", [512, 1536, 4608])
+@pytest.mark.parametrize("K", [512, 1536, 4608, 481, 513, 768, 800, 1153, 2500])
 def test_edges(seed, M, N, K):
     import paper_1609_07061_amd as q
 
     a, w, want = _operands(seed, M, N, K)
     A, W = q.qnn_pack_sign(a.float()), q.qnn_pack_sign(w.float())
+    if K % 128:  # rows with a gap that holds anything
+        A, W = (torch.cat([x, torch.full((x.shape[0], 3), -1, dtype=torch.int32, device="cuda")], 1)[:, :-3] for x in (A, W))
     T = want[0] + torch.arange(N, device="cuda", dtype=torch.int32) % 3 - 1
     flip = (torch.arange(N, device="cuda") % 5 == 0).to(torch.uint8)
     wide = torch.full((M, N + 3), 7, dtype=torch.int32, device="cuda")
