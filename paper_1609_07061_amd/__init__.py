@@ -13,6 +13,12 @@ from typing import Optional, Sequence
 
 import torch
 
+try:
+    from . import _native
+except ImportError as e:
+    raise ImportError(f"the binding's native part cannot be loaded ({e}): build it first with `python paper_1609_07061_amd/build.py` "
+                      "(or __graft_entry__.build())") from e
+
 PLANE_BIT, PLANE_SIGN = 0, 1
 ENGINE_AUTO, ENGINE_VALU, ENGINE_MFMA, ENGINE_MFMA_FP4, ENGINE_MFMA_LDS = 0, 1, 2, 3, 4
 
@@ -80,6 +86,10 @@ _lib.qnn_binary_backward_workspace_bytes.restype = _sz
 _lib.qnn_last_engine.restype = C.c_int
 _lib.qnn_last_error.restype = C.c_char_p
 _lib.qnn_version.restype = C.c_char_p
+
+# The calls made per layer or time step marshal their arguments in C++ where everything is as usual (status -1: it is not, see there)
+_native.bind(*[C.cast(getattr(_lib, n), C.c_void_p).value for n in ("qnn_pack_sign", "qnn_linear_quant_planes", "qnn_binary_gemm",
+                                                                    "qnn_binary_gemm_sign", "qnn_bitplane_gemm", "qnn_bitplane_conv2d")])
 
 _lib.qnn_last_engines.argtypes = [_vp, _int]
 _lib.qnn_last_engines.restype = C.c_int
@@ -199,6 +209,9 @@ def qnn_version() -> str:
 
 
 def qnn_pack_sign(x: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
+    if out is not None and (status := _native.pack_sign(x, out, _stream)) >= 0:
+        _check(status)
+        return out
     rows, K, ldx = _rows_ld(x, "x")
     if out is None:
         out = torch.empty((rows, words_for(K)), dtype=torch.int32, device=x.device)
@@ -221,6 +234,9 @@ def qnn_pack_bitplanes(v: torch.Tensor, nbits: int, out: Optional[torch.Tensor] 
 
 def qnn_linear_quant_planes(x: torch.Tensor, step: float, qmin: int, qmax: int, nbits: int,
                             out: Optional[torch.Tensor] = None) -> torch.Tensor:
+    if out is not None and (status := _native.linear_quant_planes(x, step, qmin, qmax, nbits, out, _stream)) >= 0:
+        _check(status)
+        return out
     rows, K, ldx = _rows_ld(x, "x")
     if out is None:
         out = torch.empty((nbits, rows, words_for(K)), dtype=torch.int32, device=x.device)
@@ -318,6 +334,9 @@ def qnn_binary_backward(G: torch.Tensor, coefG: Sequence[int], modeG: int, N: in
 
 def qnn_binary_gemm(A: torch.Tensor, W: torch.Tensor, K: int, out: Optional[torch.Tensor] = None,
                     engine: Optional[int] = None) -> torch.Tensor:
+    if out is not None and engine is None and (status := _native.binary_gemm(A, W, K, out, _stream)) >= 0:
+        _check(status)
+        return out
     M, _, lda = _rows_ld(A, "A")
     N, _, ldw = _rows_ld(W, "W")
     if out is None:
@@ -334,6 +353,9 @@ def qnn_binary_gemm(A: torch.Tensor, W: torch.Tensor, K: int, out: Optional[torc
 def qnn_binary_gemm_sign(A: torch.Tensor, W: torch.Tensor, K: int, T: torch.Tensor,
                          flip: Optional[torch.Tensor] = None, out: Optional[torch.Tensor] = None,
                          engine: int = ENGINE_AUTO) -> torch.Tensor:
+    if out is not None and (status := _native.binary_gemm_sign(A, W, K, T, flip, out, engine, _stream)) >= 0:
+        _check(status)
+        return out
     M, _, lda = _rows_ld(A, "A")
     N, _, ldw = _rows_ld(W, "W")
     if out is None:
@@ -349,6 +371,9 @@ def qnn_bitplane_gemm(A: torch.Tensor, coefA: Sequence[int], modeA: int, W: torc
                       modeW: int, K: int, out: Optional[torch.Tensor] = None,
                       engine: Optional[int] = None) -> torch.Tensor:
     """engine None -> qnn_bitplane_gemm; an engine -> qnn_bitplane_gemm_ex."""
+    if out is not None and engine is None and (status := _native.bitplane_gemm(A, coefA, modeA, W, coefW, modeW, K, out, _stream)) >= 0:
+        _check(status)
+        return out
     Pa, M, _, lda, sa = _planes_ld(A, "A")
     Pb, N, _, ldw, sw = _planes_ld(W, "W")
     if len(coefA) != Pa or len(coefW) != Pb:
@@ -457,6 +482,10 @@ def qnn_bitplane_conv2d(A: torch.Tensor, coefA: Sequence[int], modeA: int, Cin: 
                         coefW: Sequence[int], modeW: int, pad: int, stride: int = 1,
                         out: Optional[torch.Tensor] = None, engine: Optional[int] = None) -> torch.Tensor:
     """A: [Pa][B][H][W][Cw] packed planes (dense); W: [Pb][Cout][KH][KW][Cw] packed planes (dense)."""
+    if out is not None and engine is None and (
+            status := _native.bitplane_conv2d(A, coefA, modeA, Cin, W, coefW, modeW, pad, stride, out, _stream)) >= 0:
+        _check(status)
+        return out
     if A.dim() != 5 or W.dim() != 5 or not A.is_contiguous() or not W.is_contiguous():
         raise ValueError("A must be dense [Pa][B][H][W][Cw] and W dense [Pb][Cout][KH][KW][Cw]")
     Pa, B, H, Wd, Cw = A.shape

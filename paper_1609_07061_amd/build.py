@@ -11,6 +11,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libqnn.so")
+NATIVE = os.path.join(PKG, "_native.so")
 SOURCES = ["qnn_api.hip", "qnn_probe.hip", "qnn_pack.hip", "qnn_quant.hip", "qnn_dedup.hip", "qnn_conv_first.hip", "qnn_gemm_valu.hip", "qnn_gemm_slice.hip", "qnn_gemm_tile.hip", "qnn_gemm_mfma.hip", "qnn_gemm_mfma_k0.hip",
            "qnn_gemm_mfma_k1.hip", "qnn_gemm_mfma_k2.hip", "qnn_gemm_mfma_k3.hip", "qnn_gemm_mfma_k4.hip", "qnn_gemm_stage_k0.hip",
            "qnn_gemm_stage_k1.hip", "qnn_gemm_stage_k2.hip", "qnn_gemm_panel_k0.hip", "qnn_gemm_bytes_panel_k0.hip",
@@ -69,13 +70,31 @@ def build(force: bool = False, verbose: bool = False) -> str:
             raise RuntimeError("hipcc failed:\n" + " ".join(cmd) + "\n" + r.stdout + r.stderr)
         return r.stderr
 
+    pool = ThreadPoolExecutor(max_workers=1)
+    binding = pool.submit(_build_binding, run) if force or _stale(NATIVE, [os.path.join(CSRC, "qnn_binding.cpp")]) else None
     with ThreadPoolExecutor(max_workers=min(8, max(1, len(jobs)))) as ex:
         for err in ex.map(run, jobs):
             if verbose and err.strip():
                 print(err, file=sys.stderr)
     if force or jobs or _stale(LIB, objs):
         run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-fno-gpu-rdc", "-o", LIB, *objs])
+    if binding is not None:
+        binding.result()
+    pool.shutdown()
     return LIB
+
+
+def _build_binding(run) -> None:
+    """The binding's native part, against the torch that is installed."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+
+    src = os.path.join(CSRC, "qnn_binding.cpp")
+    run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+         *[f"-I{d}" for d in (*include_paths(), sysconfig.get_paths()["include"])], src, "-o", NATIVE,
+         *[f"-L{d}" for d in library_paths()], "-ltorch_python", "-ltorch_cpu", "-lc10"])
 
 
 if __name__ == "__main__":
