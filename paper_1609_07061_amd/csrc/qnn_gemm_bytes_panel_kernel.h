@@ -1,27 +1,17 @@
-// Matrix-core engine, panel-fed kernel for a left operand given as uint8 codes (the first layer of Alg. 4 on 8-bit
-// inputs: by Eq. (FirstLayer) the eight weighted plane products are x . w on the codes themselves).
+// Matrix-core engine, panel-fed kernel for two operands of int8 values: bit planes merged to one byte per element by
+// merge_planes_kernel (Sec. 2.6 / Sec. 3: the weighted sum of the plane products is the product of the values the planes stand for),
+// with int32 sums as output and no correction terms.
 //
-// 16 consecutive codes of a row, minus 128, are an int8 operand of v_mfma_i32_32x32x32_i8 as they stand.  The weights
-// are expanded ONCE per call, by a small kernel of their own, from packed bits to one int8 (+1 / -1, 0 beyond K) per
-// element; expanding them in every wave that multiplies them costs more vector-ALU instructions than the matrix cores
-// leave room for (eight to eleven per matrix-core instruction in a kernel that did so; the instruction stream of the one
-// wave a SIMD holds was the bound, at a quarter of the matrix-core rate).  With both operands as bytes the main loop
-// is loads to LDS, LDS reads, one xor per activation register and the matrix-core instructions:
-//   C[m][n] = sum_k (x[m][k] - 128) w[n][k]  +  128 sum_k w[n][k],
-// the second term per weight row, written by the expansion kernel and added in the epilogue.
-// As in gemm_panel_kernel the operands come in through LDS: the rows the workgroup shares are loaded as whole 128-byte
+// With both operands as bytes the main loop is loads to LDS, LDS reads and the matrix-core instructions (v_mfma_i32_32x32x32_i8).
+// As in gemm_panel_wide_kernel the operands come in through LDS: the rows the workgroup shares are loaded as whole 128-byte
 // lines straight to LDS (global_load_lds), a group of 128 elements of k (four steps of 32) at a time into two group
 // buffers; 16-byte piece c of row r sits at piece c xor (r / 2 mod 8), which puts the 16 rows that a ds_read_b128 serves at a time
-// on 16 different quarters of the banks (with r mod 8 rows r and r + 8 met: half of the LDS cycles were conflicts).  Activation
-// pieces beyond K are read from the row's start instead (valid memory, any value): they meet weights that are zero.
+// on 16 different quarters of the banks (with r mod 8 rows r and r + 8 met: half of the LDS cycles were conflicts).
 // Workgroup tile 256 x 256 on eight waves of 128 x 64, two per SIMD: a load to LDS holds the issuing wave for tens of cycles and
 // every group ends in a barrier; with one wave of 128 x 128 per SIMD (the earlier shape of this kernel) the matrix cores waited
 // with it.  A group takes 2600 cycles of which 2048 are matrix-core time (1.08 us on zeros; random operands, under whose switching the
 // card lowers its clock from 2.4 to about 2.1 GHz, 1.30 us).  Where rounds of such tiles leave much of the chip idle, tiles have 192 or
-// 128 rows (see bytes_tiles).  4096 x 4096 x 10000: 168 -> 125 us; first layer 10000 x 784 -> 4096: 59 -> 44 us.
-// The same kernel, with kCodes = false, multiplies two operands that are int8 values already (bit planes merged to one
-// byte per element by merge_planes_kernel, Sec. 2.6 / Sec. 3: the weighted sum of the plane products is the product of
-// the values the planes stand for), with int32 sums as output and no correction terms.
+// 128 rows (see bytes_tiles).
 #pragma once
 #include "qnn_gemm_mfma_kernel.h"
 #include "qnn_gemm_panel_epilogue.h"
@@ -40,22 +30,19 @@ constexpr int kPanelBytes = BM * kRowBytes;            // one operand's rows of 
 constexpr int kGroupBytes = 2 * kPanelBytes;
 constexpr int kGroupK = 128;
 
-// kCodes: the left operand holds uint8 codes (the kernel subtracts 128 and adds the weight rows' term g.rw_scaled), threshold
-// output; otherwise int8 values with int32 output.
+// kThresholds: never; sums are what it leaves.
 // kTail (grid = a multiple of 16 workgroups, fewer than there are tiles, and at most half a grid of tiles in the last round): that
 // round's tiles are taken as halves of 128 columns by two workgroups each.
 // WB: blocks of 32 rows per wave, so the tile has 64 WB rows: 256, 192 or 128 (see bytes_tiles).
-template <bool kCodes, bool kTail, int WB>
+template <bool kThresholds, bool kTail, int WB>
 __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const GemmArgs g, const MfmaConst mc, uint32_t tiles_m,
                                                                        uint32_t tiles_n, uint32_t ngroups) {
-    constexpr bool kSign = kCodes;
+    static_assert(!kThresholds, "int32 sums");
     constexpr int kLoadsPerGroup = WB + 4;  // loads to LDS that a wave issues per group
     static_assert(!kTail || WB == 4, "halves of whole tiles");
-    // One LDS array: two group buffers, then either the per-wave tables of the threshold epilogue (thresholds, flip flags,
-    // weight rows' terms: 64 entries each) or the per-wave 32 x 32 staging blocks of the int32 epilogue (all 160 KiB).
+    // One LDS array: two group buffers, then the per-wave 32 x 32 staging blocks of the epilogue (all 160 KiB).
     constexpr int kRingBytes = 2 * kGroupBytes;
-    constexpr int kTableBytes = 64 * 4;
-    constexpr int kTailBytes = kSign ? 3 * (kThreads / 64) * kTableBytes : (kThreads / 64) * 32 * 32 * 4;
+    constexpr int kStageBytes = 32 * 32 * 4, kTailBytes = (kThreads / 64) * kStageBytes;
     static_assert(kRingBytes + kTailBytes <= 160 * 1024, "LDS of a compute unit");
     __shared__ __attribute__((aligned(16))) uint8_t lds[kRingBytes + kTailBytes];
     const int t = threadIdx.x;
@@ -64,12 +51,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const Gem
     const int wm = wave >> 2, wn = wave & 3;
     const uint32_t total_tiles = tiles_m * tiles_n;
     const uint32_t K = (uint32_t)g.K;
-    // this wave's tables / staging block
-    uint8_t *const tail = lds + kRingBytes;
-    uint32_t *const rw_tab = kSign ? reinterpret_cast<uint32_t *>(tail + (3 * wave) * kTableBytes) : nullptr;
-    int32_t *const thr_tab = kSign ? reinterpret_cast<int32_t *>(tail + (3 * wave + 1) * kTableBytes) : nullptr;
-    uint32_t *const flip_tab = kSign ? reinterpret_cast<uint32_t *>(tail + (3 * wave + 2) * kTableBytes) : nullptr;
-    int32_t *const stage_w = kSign ? nullptr : reinterpret_cast<int32_t *>(tail + wave * (32 * 32 * 4));
+    int32_t *const stage_w = reinterpret_cast<int32_t *>(lds + kRingBytes + wave * kStageBytes);
 
     // lane-dependent values are re-derived behind an opaque copy wherever they are used (address arithmetic that the
     // compiler computes once before the loops ends up spilled, and a reload in the main loop stalls the wave)
@@ -78,7 +60,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const Gem
         return x;
     };
     const uint32_t tid = (uint32_t)t;
-    if constexpr (kSign) flip_tab[lane] = 0u;  // flip flags default to "none"
     const uint32_t lds_base = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t *)lds);
 
     // ------------------------------------------------------------------------------------------------ producer
@@ -193,28 +174,11 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const Gem
         v16i acc[WI][WB];  // [n block][m block]
         int32_t ra[WB], rw[WI];
         auto multiply = [&](Frags &f) __attribute__((always_inline)) {
-            if constexpr (kCodes) {
-#pragma unroll
-                for (int b = 0; b < WB; ++b)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) f.a[b][e] ^= (int)0x80808080u;  // the codes minus 128
-            }
 #pragma unroll
             for (int j = 0; j < WB; ++j)
 #pragma unroll
                 for (int i = 0; i < WI; ++i) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f.w[i], f.a[j], acc[i][j], 0, 0, 0);
         };
-        // thresholds, flip flags and the weight rows' terms 128 sum_k w[n][k] of a tile, straight into this wave's tables
-        auto load_tables = [&](const int64_t n_wave) __attribute__((always_inline)) {
-            if constexpr (kSign) {
-                panel::load_thresholds_to_lds<WI>(g, n_wave, thr_tab, flip_tab);
-                const uint32_t rw_lds = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint32_t *)rw_tab);
-                int64_t n = n_wave + (threadIdx.x & 63u);
-                if (n > g.N - 1) n = g.N - 1;
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(rw_lds), "v"((uint32_t)n * 4u), "s"(g.rw_scaled) : "memory");
-            }
-        };
-
         Frags f0, f1;
         fetch(0, rd, f0);
         uint32_t vb = first_vb;
@@ -232,8 +196,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const Gem
 #pragma unroll
                     for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
             }
-            // on their way before the tile's first group; a group's loads follow
-            load_tables(n_wave);
             for (uint32_t G = 0; G < ngroups; ++G) {
                 const uint32_t other = rd ^ (uint32_t)kGroupBytes;
                 p_advance();
@@ -259,7 +221,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const Gem
             for (int i = 0; i < WI; ++i)
 #pragma unroll
                 for (int j = 0; j < WB; ++j) asm volatile("" : "+v"(acc[i][j]));
-            panel::wave_finish<kSign, WI, kLoadsPerGroup, kCodes>(g, mc, acc, ra, rw, rw_tab, thr_tab, flip_tab, stage_w, m_wave, n_wave);
+            panel::wave_finish<false, WI, kLoadsPerGroup>(g, mc, acc, ra, rw, nullptr, nullptr, nullptr, stage_w, m_wave, n_wave);
         }
     };
     run_tiles(std::integral_constant<int, 2>{}, vb0, n_mine, 0u);
@@ -271,8 +233,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const Gem
 
 typedef void (*KernelFn)(const GemmArgs, const MfmaConst, uint32_t, uint32_t, uint32_t);
 // blocks: rows of a tile / 64 (four with tail)
-KernelFn kernel(bool tail, int blocks);         // uint8 codes, threshold output
-KernelFn kernel_values(bool tail, int blocks);  // int8 values, int32 output
+KernelFn kernel_values(bool tail, int blocks);
 
 }  // namespace bytes_panel
 }  // namespace qnn

@@ -278,16 +278,7 @@ int launch_gemm_mfma(const GemmArgs &g, hipStream_t s, bool fp4) {
             return QNN_LAUNCH("gemm_panel", panel::find_kernel(g.epi.T != nullptr, pt.shape, whole), dim3(pgrid), dim3(panel::kThreads), 0, s, g, pc, pa);
         }
     }
-    // uint8 left operand with the weights expanded to bytes beforehand: the panel-fed kernel (threshold epilogue)
-    if (g.A.rows_are_bytes && g.w_bytes && g.rw_scaled && g.epi.T && (long double)g.M * g.A.ld < 4294967296.0L &&
-        (long double)g.N * g.ld_w_bytes < 4294967296.0L && g.ld_w_bytes % bytes_panel::kGroupK == 0 && g.ld_w_bytes >= g.K) {
-        MfmaConst pc = mc;
-        pc.alpha = 1, pc.alpha_shift = 0, pc.cRA = 0, pc.cRW = 1, pc.c0 = 0, pc.needRW = 1;
-        const int64_t ngroups = ceil_div(g.K, bytes_panel::kGroupK);
-        const BytesTiles bt = bytes_tiles(g.M, g.N, cus);
-        return QNN_LAUNCH("gemm_bytes_panel", bytes_panel::kernel(bt.tail, bt.blocks), dim3(bt.grid), dim3(bytes_panel::kThreads), 0, s, g, pc,
-                          (uint32_t)bt.tiles_m, (uint32_t)bt.tiles_n, (uint32_t)ngroups);
-    }
+    if (codes::supports(g)) return codes::launch(g, s);
     const KernelFn fn = g.A.rows_are_bytes ? byte_kernels()[g.epi.T ? 1 : 0]
                         : fp4              ? (vec ? v->fp4_vec : v->fp4_any)
                                            : (vec ? v->fn_vec : v->fn_any);
@@ -376,7 +367,6 @@ int launch_values_product(const GemmArgs &g, const int8_t *a8, const int8_t *w8,
     v.A.rows_are_bytes = 1;
     v.w_bytes = w8;
     v.ld_w_bytes = pitch;
-    v.rw_scaled = nullptr;
     MfmaConst mc;
     std::memset(&mc, 0, sizeof(mc));
     mc.alpha = (uint32_t)alpha;

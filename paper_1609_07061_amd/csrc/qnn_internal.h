@@ -70,11 +70,12 @@ struct GemmArgs {
     Epilogue epi;
     int64_t M, N, K;  // K = true number of elements per row (not words)
     int64_t Kw;       // words per row = ceil(K/32) (for pixels: KH*KW*Cw)
-    // Optional, with a left operand of uint8 codes only: the +-1 weights expanded to one int8 per element (row pitch
-    // ld_w_bytes, a multiple of 128, zeros beyond K) and 128 * (sum of the weights of row n), both written by
-    // bytes_panel::launch_expand_weights earlier on the same stream.  Null: the kernels expand the packed bits.
+    // Right operand of int8 values instead of planes (left operand: rows_are_bytes too): row pitch ld_w_bytes, a multiple of 128
     const int8_t *w_bytes;
     int64_t ld_w_bytes;
+    // Optional, with a left operand of uint8 codes only: the +-1 weights as the image of qnn_gemm_codes.hip and 128 * (sum of the
+    // weights of row n), both written by codes::launch_weight_image earlier on the same stream.  Null: the kernels expand the packed bits.
+    const uint32_t *w_image;
     const int32_t *rw_scaled;
     // Only for convolutions of +-1 maps on the tiled FP4 kernel: class_thr[cls * class_ld + n] is the threshold of filter n for a pixel
     // of border class cls (bit 0: first row, 1: last row, 2: first column, 3: last column).
@@ -174,16 +175,22 @@ struct PoolMemory {
     }
 };
 
-// Expansion of packed +-1 weights (N rows of K elements) to one int8 per element (row pitch ld_out, a multiple of 128,
-// zeros beyond K) and rw_scaled[n] = 128 * (sum of the weights of row n): operands of the uint8-input kernel.
+// Products of uint8 codes and +-1 weights that stay bits (qnn_gemm_codes.hip), threshold output: w_image (image_bytes(N, K) bytes) and
+// rw_scaled (N words) of the arguments are written by launch_weight_image, earlier on the same stream.
+namespace codes {
+size_t image_bytes(int64_t N, int64_t K);
+bool supports(const GemmArgs &g);
+int launch_weight_image(const GemmArgs &g, hipStream_t s);
+int launch(const GemmArgs &g, hipStream_t s);
+}  // namespace codes
+
+// Operands of the int8 kernel.
 namespace bytes_panel {
 // Bit planes of both operands of `g` merged to one int8 per element (rows of ld_out bytes, a multiple of 128, zeros
 // beyond K): value = scale_of_operand * int8, and `scale` returns the product of the two operands' factors.
 // merge_supports: whether the values of both operands fit int8.
 bool merge_supports(const Planes &pa, const Planes &pw);
 int launch_merge_planes(const GemmArgs &g, int8_t *outA, int8_t *outW, int64_t ld_out, int64_t &scale, hipStream_t s);
-int launch_expand_weights(const uint32_t *W, int64_t N, int64_t K, int64_t ldw, int8_t *out, int64_t ld_out, int32_t *rw_scaled,
-                          hipStream_t s);
 }
 int launch_pack_sign(const float *x, int64_t rows, int64_t K, int64_t ldx, uint32_t *out, int64_t ldo, hipStream_t s);
 int launch_pack_bitplanes(const uint8_t *v, int64_t rows, int64_t K, int64_t ldv, int nbits, uint32_t *planes,
