@@ -653,7 +653,8 @@ struct NetStep {
     enum Kind { kPack, kOnes, kGemm, kPool, kFirstConv, kConvPrep, kConvMap } kind;
     GemmArgs g;      // kGemm (convolution or fully connected)
     int engine;      // kGemm
-    // kPack / kOnes / kPool operands
+    OnesJob ones;    // kOnes, and done along by kPool
+    // kPack / kPool operands
     const void *src;
     void *dst, *dst2;
     int64_t rows, n;
@@ -738,7 +739,7 @@ int run_net(const NetPlan &plan, hipStream_t s) {
                                            static_cast<uint32_t *>(st.dst), st.b, st.rows * st.b, s);
                 break;
             case NetStep::kOnes:
-                rc = launch_ones_plane(static_cast<uint32_t *>(st.dst), st.rows, st.a, st.b, s);
+                rc = launch_ones_plane(st.ones, s);
                 break;
             case NetStep::kGemm:
                 rc = launch_on(st.g, st.engine, plan.free_choice, s);
@@ -770,7 +771,7 @@ int run_net(const NetPlan &plan, hipStream_t s) {
                 break;
             case NetStep::kPool:
                 rc = launch_pool_bits(static_cast<const uint32_t *>(st.src), st.rows, st.a, st.b, st.c, st.mask, st.invert,
-                                      static_cast<uint32_t *>(st.dst), static_cast<uint32_t *>(st.dst2), (int)st.n, s);
+                                      static_cast<uint32_t *>(st.dst), static_cast<uint32_t *>(st.dst2), (int)st.n, st.ones, s);
                 break;
         }
         if (rc) return rc;
@@ -882,6 +883,7 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
         uint32_t *kept_bits = inverted ? kept + B * ho * wo * Cwo : kept;  // where the output bits go
         uint32_t *conv_dst = pool[l] ? words(L.tmp) : kept_bits;
         const uint8_t *fl = inverted ? reinterpret_cast<const uint8_t *>(ws + L.flag_inv[l]) : (flip ? flip[l] : nullptr);
+        const int before = plan.n - 1;
         NetStep &st = push();
         st.kind = NetStep::kGemm;
         const Epilogue e{nullptr, 0, T[l], fl, conv_dst, Cwo};
@@ -921,9 +923,13 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
             pl.n = co;
         }
         if (ones_needed && !pool[l] && !(l == 0 && first_direct)) {
-            NetStep &on = push();
-            on.kind = NetStep::kOnes;
-            on.dst = kept, on.rows = B * ho * wo, on.a = (int)Cwo, on.b = (int)co;
+            // (the pooling before this convolution, if any, fills it: this buffer was last read by the convolution before that)
+            NetStep *on = before >= 0 && plan.step[before].kind == NetStep::kPool ? &plan.step[before] : nullptr;
+            if (!on) {
+                on = &push();
+                on->kind = NetStep::kOnes;
+            }
+            on->ones = OnesJob{kept, B * ho * wo, (int)Cwo, (int)co};
         }
         h = ho, w = wo, cin = co;
         a_planes = kept, a_count = 2, a_coef = kCoefPm1, a_stride = B * h * w * Cwo;

@@ -239,9 +239,15 @@ int launch_conv_first(const uint8_t *x, int64_t B, int H, int Wd, int C0, const 
                       const uint8_t *flip, bool flip_all, uint32_t *out, uint32_t *ones, int64_t ldo, const ConvPrepJobs &jobs,
                       const FlagJobs &flags, hipStream_t s);
 
-// ones (may be null) receives the "inside the image" plane of the pooled map (first C bits of every pixel set)
+// rows x Cw words to be filled with the first C bits of every row: a map's "inside the image" plane (rows = 0: nothing)
+struct OnesJob {
+    uint32_t *out;
+    int64_t rows;
+    int Cw, C;
+};
+// ones (may be null) receives the "inside the image" plane of the pooled map; later: the one of another map
 int launch_pool_bits(const uint32_t *in, int64_t B, int H, int Wd, int Cw, const uint32_t *use_and, bool invert_all,
-                     uint32_t *out, uint32_t *ones, int C, hipStream_t s);
-int launch_ones_plane(uint32_t *out, int64_t rows, int Cw, int C, hipStream_t s);
+                     uint32_t *out, uint32_t *ones, int C, const OnesJob &later, hipStream_t s);
+int launch_ones_plane(const OnesJob &job, hipStream_t s);
 
 }  // namespace qnn

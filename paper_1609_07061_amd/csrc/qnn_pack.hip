@@ -303,6 +303,16 @@ __global__ __launch_bounds__(kBlock) void threshold_sign_vec4_kernel(const int32
     }
 }
 
+// rows x Cw words with the first C bits of every row set (the "inside the image" plane of a +-1 feature map whose
+// zero padding must contribute exactly 0: value = plane0 - 2 * plane1, so 01 = +1, 11 = -1, 00 = 0).
+__device__ __forceinline__ void fill_ones(const OnesJob &job, const uint32_t block, const uint32_t blocks) {
+    const int64_t total = job.rows * job.Cw;
+    const uint32_t tail = (job.C % 32) ? ((1u << (job.C % 32)) - 1u) : 0xFFFFFFFFu;
+    for (int64_t i = (int64_t)block * kBlock + threadIdx.x; i < total; i += (int64_t)blocks * kBlock)
+        job.out[i] = ((int)(i % job.Cw) == job.Cw - 1) ? tail : 0xFFFFFFFFu;
+}
+__global__ __launch_bounds__(kBlock) void ones_plane_kernel(const OnesJob job) { fill_ones(job, blockIdx.x, gridDim.x); }
+
 // 2 x 2 max-pooling of a binarized feature map, on the packed bits (App. A: "convolution and 2 x 2 max-pooling layers"
 // followed by "BatchNorm and Binarization layers").  Pooling acts on the convolution's sums and BatchNorm + sign come
 // after it; per channel BatchNorm is monotone, increasing for a positive scale and decreasing for a negative one, so
@@ -311,14 +321,20 @@ __global__ __launch_bounds__(kBlock) void threshold_sign_vec4_kernel(const int32
 // (packed like the data) saying which; `invert_all` swaps the roles for maps stored with inverted bits.
 // One thread per output word; in [B][H][W][Cw], out [B][H/2][W/2][Cw].
 // `ones` (may be null): a second output of the same shape that receives the "inside the image" plane of the pooled map,
-// the first C bits of every pixel set (see ones_plane_kernel).
+// the first C bits of every pixel set (see fill_ones).  Workgroups from pool_blocks on fill another such plane, that of a later map: a launch
+// of its own for it stands in the way of a small network's next product (App. A network, four images: 62.2 -> 56.5 us).
 __global__ __launch_bounds__(kBlock) void pool_bits_kernel(const uint32_t *__restrict__ in, int64_t B, int H, int Wd, int Cw,
                                                            const uint32_t *__restrict__ use_and, uint32_t invert_all,
-                                                           uint32_t *__restrict__ out, uint32_t *__restrict__ ones, int C) {
+                                                           uint32_t *__restrict__ out, uint32_t *__restrict__ ones, int C, const OnesJob later,
+                                                           uint32_t pool_blocks) {
+    if (blockIdx.x >= pool_blocks) {
+        fill_ones(later, blockIdx.x - pool_blocks, gridDim.x - pool_blocks);
+        return;
+    }
     const uint32_t tail = (C % 32) ? ((1u << (C % 32)) - 1u) : 0xFFFFFFFFu;
     const int Ho = H / 2, Wo = Wd / 2;
     const int64_t total = B * Ho * Wo * Cw;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < total; i += (int64_t)gridDim.x * kBlock) {
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < total; i += (int64_t)pool_blocks * kBlock) {
         const int c = (int)(i % Cw);
         int64_t p = i / Cw;
         const int xo = (int)(p % Wo);
@@ -331,15 +347,6 @@ __global__ __launch_bounds__(kBlock) void pool_bits_kernel(const uint32_t *__res
         out[i] = ((v00 | v01 | v10 | v11) & ~m) | ((v00 & v01 & v10 & v11) & m);
         if (ones) ones[i] = c == Cw - 1 ? tail : 0xFFFFFFFFu;
     }
-}
-
-// rows x Cw words with the first C bits of every row set (the "inside the image" plane of a +-1 feature map whose
-// zero padding must contribute exactly 0: value = plane0 - 2 * plane1, so 01 = +1, 11 = -1, 00 = 0).
-__global__ __launch_bounds__(kBlock) void ones_plane_kernel(uint32_t *__restrict__ out, int64_t rows, int Cw, int C) {
-    const int64_t total = rows * Cw;
-    const uint32_t tail = (C % 32) ? ((1u << (C % 32)) - 1u) : 0xFFFFFFFFu;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < total; i += (int64_t)gridDim.x * kBlock)
-        out[i] = ((int)(i % Cw) == Cw - 1) ? tail : 0xFFFFFFFFu;
 }
 
 int grid_for(int64_t total_chunks) {
@@ -405,17 +412,17 @@ int launch_threshold_sign(const int32_t *C, int64_t ldc, int64_t M, int64_t N, c
 }
 
 int launch_pool_bits(const uint32_t *in, int64_t B, int H, int Wd, int Cw, const uint32_t *use_and, bool invert_all,
-                     uint32_t *out, uint32_t *ones, int C, hipStream_t s) {
+                     uint32_t *out, uint32_t *ones, int C, const OnesJob &later, hipStream_t s) {
     const int64_t total = B * (H / 2) * (Wd / 2) * Cw;
-    if (total == 0) return QNN_OK;
-    return QNN_LAUNCH("pool_bits", pool_bits_kernel, dim3(grid_for(ceil_div(total, (int64_t)kWave))), dim3(kBlock), 0, s, in, B,
-                      H, Wd, Cw, use_and, invert_all ? 0xFFFFFFFFu : 0u, out, ones, C);
+    if (total == 0) return launch_ones_plane(later, s);
+    const int pool_blocks = grid_for(ceil_div(total, (int64_t)kWave)), later_blocks = grid_for(ceil_div(later.rows * later.Cw, (int64_t)kWave));
+    return QNN_LAUNCH("pool_bits", pool_bits_kernel, dim3(pool_blocks + later_blocks), dim3(kBlock), 0, s, in, B, H, Wd, Cw, use_and,
+                      invert_all ? 0xFFFFFFFFu : 0u, out, ones, C, later, (uint32_t)pool_blocks);
 }
 
-int launch_ones_plane(uint32_t *out, int64_t rows, int Cw, int C, hipStream_t s) {
-    if (rows * Cw == 0) return QNN_OK;
-    return QNN_LAUNCH("ones_plane", ones_plane_kernel, dim3(grid_for(ceil_div(rows * Cw, (int64_t)kWave))), dim3(kBlock), 0, s,
-                      out, rows, Cw, C);
+int launch_ones_plane(const OnesJob &job, hipStream_t s) {
+    if (job.rows * job.Cw == 0) return QNN_OK;
+    return QNN_LAUNCH("ones_plane", ones_plane_kernel, dim3(grid_for(ceil_div(job.rows * job.Cw, (int64_t)kWave))), dim3(kBlock), 0, s, job);
 }
 
 }  // namespace qnn
