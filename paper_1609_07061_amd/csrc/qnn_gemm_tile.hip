@@ -4,15 +4,16 @@
 // Bound: the vector instructions that make the operands, 13 to 19 per matrix-core instruction by the counters (about twice the
 // matrix cores' time), and the waits between them.  A workgroup of four waves owns a 128 x 128 tile of C, a wave 64 x 64 of it (2 x 2
 // blocks, so that an operand feeds two products); three workgroups share a compute unit (two where both operands have two planes) and
-// fill each other's waits.  1999 x 3001 x 2500: 84.5 -> 19.8 us against one operand row per lane; 2-bit convolution 256 x 13 x 13, 384 ->
-// 256 channels: 62.6 -> 26.9 us against planes merged to bytes in LDS.
+// fill each other's waits.  2-bit convolution 256 x 13 x 13, 384 -> 256 channels: 62.6 -> 26.9 us against planes merged to bytes in LDS.
+// (Single planes of 512 elements and more go to qnn_gemm_panel_kernel.h, whose loads write LDS by themselves: 1999 x 3001 x 2500 19.9 ->
+// 17.2 us.)
 //   * Loads: a wave reads sixteen rows x 64 contiguous bytes, or eight x 128, per instruction (an instruction whose 64 lanes read
 //     64 rows costs the address path of the compute unit 64 cycles, eight rows 16 to 19), 16 bytes per lane at any 4-byte
 //     alignment, a group ahead of the multiplication, into registers.  A group is four pieces of a row: of eight, the loads in
 //     flight take the registers of the third workgroup, and that costs more than half as many barriers give (GPU time, eight ->
 //     four pieces: 2-bit convolution 256 x 13 x 13, 384 -> 256 channels, 34.1 -> 27.8 us, 4-bit 54.3 -> 46.3; products
 //     3000 x 4096 x 3000 23.8 -> 21.9).  It is eight where that brings no third workgroup or takes none away: matrices of
-//     two planes a digit on both sides (1000 x 4096 x 2048 of 4 bits: 30.4 us against 32.8 with four) and convolutions of +-1 maps.
+//     two planes a digit on both sides (1000 x 4096 x 2048 of 4 bits: 30.4 us against 32.8 with four).
 //     The last piece of a row is read four words from its end and the words an earlier piece has brought are cleared, so nothing
 //     beyond a row is read.
 //   * The words go to LDS once per workgroup, already cleared and, for two planes of a digit, already interleaved; piece c of row
