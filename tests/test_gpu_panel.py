@@ -48,3 +48,18 @@ def test_wide_tiles(seed, M, N):
     A, W = q.qnn_pack_sign(a.float()), q.qnn_pack_sign(w.float())
     assert torch.equal(q.qnn_binary_gemm(A, W, K), want)
     assert kernels_of(lambda: q.qnn_binary_gemm(A, W, K)) == ["gemm_panel_wide_kernel"]
+
+
+@pytest.mark.parametrize("M,N,K,panel", [
+    (4187, 1024, 3860, False), (1999, 3001, 2500, True),    # 264 and 384 tiles of 128 x 128
+    (1226, 4800, 922, False), (4187, 2048, 922, True),      # short rows: 380 and 528
+    (2376, 3953, 640, False), (2960, 2603, 1401, False), (2960, 2603, 2100, True),  # C word by word
+    (2428, 7085, 2552, False), (2428, 7088, 2552, True),    # 1064 tiles
+])
+def test_where_rows_of_other_lengths_leave_the_tiled_kernels(seed, M, N, K, panel):
+    import paper_1609_07061_amd as q
+
+    a, w, want = _operands(seed, M, N, K)
+    A, W = q.qnn_pack_sign(a.float()), q.qnn_pack_sign(w.float())
+    assert torch.equal(q.qnn_binary_gemm(A, W, K), want)
+    assert kernels_of(lambda: q.qnn_binary_gemm(A, W, K))[0].startswith("gemm_panel_kernel") == panel
