@@ -408,8 +408,10 @@ GemmArgs backward_product(const BackwardArgs &b, int64_t M, int64_t N, int64_t K
 // Whether the step takes the way of qnn_gemm_mixed.hip (FP6 or int8 gradients) or products of bit planes behind bit transposes.
 //   More than four planes: by the expected times, with int8 gradients, the slower ones, and only where those of the planes, which the
 //   estimates of the products undershoot, are 10 % higher (us behind the quantizer, planes -> FP6 / int8; eight planes: 10000 x 4096 x 4096 356 ->
-//   220 / 340; 1009 x 1280 x 2784 62 -> 39; 7572 x 2368 x 444 158 -> 72; 3611 x 448 x 512 46 against 41 / 48; six planes: 3031 x 2083 x 906 85 ->
-//   - / 63, 393 x 3517 x 960 41 against - / 50).
+//   220 / 340; 1009 x 1280 x 2784 62 -> 39; 7572 x 2368 x 444 158 -> 72 / 90; 1718 x 452 x 1895 55 -> 42 / 45; six planes: 3031 x 2083 x 906 82 ->
+//   51 / 60).  Where a product has few tiles and long rows, the planes' kernels split k and this way's do not (10000 x 300 x 300 58 against 60 /
+//   82, 20000 x 100 x 1000 90 against 100 / 139, 393 x 3517 x 960 44 against 43 / 48, all left to the planes).  A gradient that turns out int8
+//   can lose where 128 x 256 tiles make between one and two rounds (7708 x 7094 x 1521, five planes, 221 -> 177 / 255).
 //   Up to four planes, which make two pairs of digits at most: where merging them to bytes for each product would be faster than the
 //   tiled kernel (a line that leaves steps to the planes which are faster here: 3000 x 2048 x 2048 with four planes 79 against 54).
 bool backward_mixed_preferred(const BackwardArgs &b) {

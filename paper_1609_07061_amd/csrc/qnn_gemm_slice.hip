@@ -421,10 +421,31 @@ static double tile_us(const GemmArgs &g, const SliceArgs &sc, int ka, int kw) {
     return 2.8 + k * (kLatency[pairs_of_planes] + kTile[pairs_of_planes] * tiles_each) + kStore[pairs_of_planes] * (double)g.M * (double)g.N;
 }
 
+// 32 x 32 tiles: four waves each or sixteen (see launch_gemm_slice)
+static bool four_waves(int64_t items, int64_t tiles) { return items <= 4 || (tiles > 512 && (tiles > 1024 || items <= 32)); }
+
+// The same on the tiles that take over below 192, 64 x 64 or 32 x 32 (220 products of five to eight planes and a +-1 plane, 64 to 30000
+// rows and columns, 256 to 20000 elements of k: within 15 % as a rule, at most 23).
+static double small_tile_us(const GemmArgs &g, const SliceArgs &sc) {
+    const double cus = compute_units(), elements = (double)g.M * (double)g.N;
+    const int64_t items = (int64_t)sc.chunks * sc.a.count * sc.w.count, tiles64 = ceil_div(g.M, 64) * ceil_div(g.N, 64), tiles32 = ceil_div(g.M, 32) * ceil_div(g.N, 32);
+    const double k = 256.0 * (double)items;
+    if (tiles64 >= 160 && g.M > 32 && g.N > 32)
+        return 4.0 + k * (0.44e-3 + 0.23e-3 * (double)tiles64 / cus + 0.57e-3 * (double)ceil_div(tiles64, compute_units())) + 2.3e-6 * elements;
+    if (four_waves(items, tiles32)) return 4.0 + 0.535e-3 * k * (double)tiles32 / cus;
+    return 4.0 + k * (0.063e-3 * (double)tiles32 / cus + 0.307e-3 * (double)ceil_div(tiles32, compute_units())) + 2.7e-6 * elements;
+}
+
+// (For the choice against another way of the backward step, whose other launches take longer than it assumes: a quarter is added to the small
+// tiles' time, and tile_us's rough figure stays where it is the smaller.)
 double slice_us(const GemmArgs &g) {
     SliceArgs sc;
     int ka, kw;
-    return slice_args(g, false, sc, ka, kw) ? tile_us(g, sc, ka, kw) : 1e30;
+    if (!slice_args(g, false, sc, ka, kw)) return 1e30;
+    const double tiled = tile_us(g, sc, ka, kw);
+    if (ceil_div(g.M, 128) * ceil_div(g.N, 128) >= 192 && g.M >= 96 && g.N >= 96) return tiled;
+    const double small = 1.25 * small_tile_us(g, sc);
+    return small < tiled ? small : tiled;
 }
 
 // Where the library's own choice goes to these kernels.  Measured (us, GPU time; route of the shape -> best of these; numbers of tiles are
@@ -491,7 +512,7 @@ int launch_gemm_slice(const GemmArgs &g, hipStream_t s) {
     // -> 17.6 us, 32768 outputs of 20 rows x 4096 with 4 x 4 planes 43.8 -> 34.3), unless the rows are long and the tiles not much more
     // than that (20000 x 10 x 16384 17.0 against 18.5).  Never fewer than four: waves without a chunk of k still share the epilogue
     // (64 x 64 tiles, 1000 x 1000 x 128: 7.1 -> 4.8 us).
-    const bool four = large || items <= 4 || (tiles > 512 && (tiles > 1024 || items <= 32));
+    const bool four = large || four_waves(items, tiles);
     const int waves = four ? 4 : (items < 16 ? (int)items : 16);
     const SliceFn fn = !pix ? slice_kernel<kMatrix>(ka, kw, large, four) : (g.A.Cw < 4 ? slice_kernel<kNarrowPatches>(ka, kw, large, four) : slice_kernel<kPatches>(ka, kw, large, four));
     return QNN_LAUNCH("gemm_slice", fn, dim3((unsigned)tiles), dim3(64u * waves), 0, s, g, sc, (uint32_t)tiles_m, (uint32_t)tiles_n);

@@ -11,7 +11,7 @@ EXACT = sorted({s * m << e for s in (1, -1) for m in (0, 4, 5, 6, 7) for e in ra
 COEF = [1, 2, 4, 8, 16, 32, 64, -128]
 
 
-def _step(q, v, coef, K, planes=None, mode=0):
+def _step(q, v, coef, K, planes=None, mode=0, mixed=True):
     M, N = v.shape
     w, a = (torch.randint(0, 2, (r, K), device="cuda") * 2 - 1 for r in (N, M))
     G = q.qnn_pack_bitplanes((v & 255).to(torch.uint8), 8) if planes is None else planes
@@ -21,7 +21,9 @@ def _step(q, v, coef, K, planes=None, mode=0):
         return q.qnn_binary_backward(G, coef, mode, N, W, A, K)
 
     ga, gw = call()
-    assert kernels_of(call)[:2] == ["transpose_to_image_kernel", "merge_transpose_kernel"]
+    kernels = kernels_of(call)
+    assert (kernels[:2] == ["transpose_to_image_kernel", "merge_transpose_kernel"]) == mixed, kernels
+    assert sum(k.startswith("gemm_mixed_kernel") for k in kernels) == (2 if mixed else 0), kernels
     assert torch.equal(ga, (v.double() @ w.double()).to(torch.int32))
     assert torch.equal(gw, (v.t().contiguous().double() @ a.double()).to(torch.int32))
 
@@ -73,3 +75,14 @@ def test_largest_sums():
         ga, gw = q.qnn_binary_backward(G, COEF, 0, N, W, A, K)
         assert torch.equal(ga, (v.double() @ w.double()).to(torch.int32))
         assert torch.equal(gw, (v.t().contiguous().double() @ a.double()).to(torch.int32))
+
+
+@pytest.mark.parametrize("M,N,K,mixed", [
+    (10000, 300, 300, False), (20000, 100, 1000, False), (7735, 325, 473, False), (393, 3517, 960, False),  # few tiles, long rows
+    (1718, 452, 1895, True), (1451, 3329, 367, True), (300, 300, 20000, True),
+])
+def test_where_thin_steps_stay_on_the_planes(seed, M, N, K, mixed):
+    import paper_1609_07061_amd as q
+
+    torch.manual_seed(seed)
+    _step(q, torch.randint(-128, 128, (M, N), device="cuda"), COEF, K, mixed=mixed)
