@@ -281,10 +281,12 @@ int qnn_transpose_bits(const uint32_t *in, int64_t rows, int64_t cols, int64_t l
  * gA: DEVICE int32 [M][ld_ga]; gW: DEVICE int32 [N][ld_gw].  coefG: HOST.  workspace: DEVICE, 256-byte aligned,
  * qnn_binary_backward_workspace_bytes(...) bytes (the transposed operands).  QNN_ERR_OVERFLOW if
  * (sum |coefG|) * max(M, N) >= 2^31.
- * Large steps are computed from bytes like the large products of qnn_bitplane_gemm, with up to (M + N) * roundup(max(M, N), 128) +
- * K * roundup(max(M, N), 128) + roundup(4 * (M + N), 256) bytes of temporary memory from the pool of `stream` (with eight planes the
- * transposed gradient lies in the workspace).  If the pool cannot supply that, the products are formed one after the other, each with the
- * memory that qnn_bitplane_gemm takes for it; QNN_ERR_HIP if the pool cannot supply that either. */
+ * Where the library expects it to be faster (large steps, and smaller ones of five planes and more), the gradient is brought into the order
+ * of the matrix cores' operands, FP6 or bytes, once per call and along both axes, the transposed operands in bits.  What of that the
+ * workspace does not hold is temporary memory from the pool of `stream`: up to M * roundup(N, 128) + N * roundup(M, 128) +
+ * K * roundup(max(M, N), 128) + roundup(4 * (M + N), 256) bytes (with eight planes the transposed gradient, N * roundup(M, 128), lies in the
+ * workspace).  If the pool cannot supply that, the products are formed one after the other, each with the memory that qnn_bitplane_gemm
+ * takes for it; QNN_ERR_HIP if the pool cannot supply that either. */
 int qnn_binary_backward(const uint32_t *G, int Pg, const int32_t *coefG, int modeG, int64_t ldg_words,
                         int64_t strideG_words, const uint32_t *W, int64_t ldw_words, const uint32_t *A,
                         int64_t lda_words, int32_t *gA, int64_t ld_ga, int32_t *gW, int64_t ld_gw, int64_t M, int64_t N,

@@ -110,10 +110,11 @@ __device__ __forceinline__ uint32_t add_bytes(uint32_t x, uint32_t y) {  // byte
 // One row's 32 elements word .. + 31 (signed bytes) into a values image
 struct Image {
     uint8_t *base;
-    uint32_t rows, groups;  // rows of a group; groups of 256
+    uint32_t rows, groups, halves;  // rows of a group; groups of 256, of 128 (int8)
 };
 __device__ __forceinline__ void put(const Image &im, const bool as_bytes, const uint32_t G, const uint32_t c, const uint32_t row, const uint32_t (&bytes)[8]) {
     if (as_bytes) {
+        if (2u * G + (c >> 2) >= im.halves) return;  // (a half group of zeros at the end, which is not multiplied)
         uint32_t o[8];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {  // elements 0 2 4 6 1 3 5 7
@@ -204,11 +205,20 @@ __global__ __launch_bounds__(256) void merge_transpose_kernel(const Gradient a, 
     }
 }
 
-uint32_t padded(int64_t rows) { return (uint32_t)(ceil_div(rows, 256) * 256); }
+// Sizes of images.  A group has as many rows as the operand, rounded up to whole lines: what a tile reads beyond them belongs to the group
+// behind it, or is the room left behind the last one.  (Groups of whole tiles took up to 255 rows more each, and eight planes of a
+// transposed gradient then no longer fitted the workspace that holds them as planes.)
+uint32_t padded(int64_t rows) { return (uint32_t)(ceil_div(rows, 8) * 8); }
 constexpr int kGroupK = 256;
 uint32_t groups_of(int64_t k) { return (uint32_t)ceil_div(k, kGroupK); }
-size_t values_bytes(int64_t rows, int64_t k) { return (size_t)groups_of(k) * padded(rows) * kGroupK; }
-size_t bits_bytes(int64_t rows, int64_t k) { return (size_t)groups_of(k) * padded(rows) * (kGroupK / 8); }
+uint32_t halves_of(int64_t k) { return k <= kGroupK / 2 ? 2u : (uint32_t)ceil_div(k, kGroupK / 2); }  // at least two (the kernel relies on it)
+size_t beyond(int64_t rows, int64_t tile) { return (size_t)(ceil_div(rows, tile) * tile - padded(rows)); }  // rows a last tile reads
+// int8: 128 bytes a row and half group, FP6: 192 a row and group
+size_t values_bytes(int64_t rows, int64_t k) {
+    const size_t as_bytes = (size_t)halves_of(k) * 128, as_fp6 = (size_t)groups_of(k) * 192;
+    return (as_bytes > as_fp6 ? as_bytes : as_fp6) * padded(rows) + beyond(rows, 128) * 128;
+}
+size_t bits_bytes(int64_t rows, int64_t k) { return (size_t)groups_of(k) * padded(rows) * (kGroupK / 8) + beyond(rows, 256) * 16; }
 
 // Tiles of 128 x 256 or 128 x 128, two workgroups on a compute unit, by the time of their rounds (us per group of k, with two and with one
 // workgroup on a unit; FP6: 10000 x 4096 x 4096, 1264 and 2528 tiles, 93 against 109 us, 1000 x 4096 x 4096, 128 and 256, 22.2 against 17.4;
@@ -234,7 +244,7 @@ int launch_product(const uint8_t *a, const uint8_t *w, const uint32_t *inexact, 
     MixedArgs x;
     std::memset(&g, 0, sizeof(g));
     g.M = M, g.N = N, g.K = K, g.epi.C = C, g.epi.ldc = ldc;
-    x.a = a, x.w = w, x.inexact = inexact, x.rows_a = padded(M), x.rows_w = padded(N), x.groups = groups_of(K);
+    x.a = a, x.w = w, x.inexact = inexact, x.rows_a = padded(M), x.rows_w = padded(N), x.groups = groups_of(K), x.halves = halves_of(K);
     x.alpha = alpha, x.alpha_shift = -1;
     for (int sh = 0; sh < 31; ++sh)
         if (alpha == ((int64_t)1 << sh)) x.alpha_shift = sh;
@@ -306,7 +316,7 @@ int launch_backward(const BackwardArgs &b, void *workspace, size_t workspace_byt
     Gradient g;
     merge_code(b.pg, g.code);
     g.planes = b.G, g.plane_stride = b.strideG, g.ld = b.ldg, g.M = b.M, g.N = b.N, g.inexact = reinterpret_cast<uint32_t *>(part[0]);
-    const Image out = {part[2], padded(b.M), groups_of(b.N)}, out_t = {part[1], padded(b.N), groups_of(b.M)};
+    const Image out = {part[2], padded(b.M), groups_of(b.N), halves_of(b.N)}, out_t = {part[1], padded(b.N), groups_of(b.M), halves_of(b.M)};
     const int32_t alpha = (int32_t)g.code.scale;
     int rc = QNN_LAUNCH("transpose_to_image", transpose_to_image_kernel, dim3(w.blocks + x.blocks + kFlags), dim3(256), 0, s, g, w, x);
     if (rc == QNN_OK) rc = QNN_LAUNCH("merge_transpose", merge_transpose_kernel, dim3(out.groups, 2u * out_t.groups), dim3(256), 0, s, g, out, out_t);

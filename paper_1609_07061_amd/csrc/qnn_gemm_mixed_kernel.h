@@ -21,8 +21,8 @@
 //   bits, groups of 128: [group][row][4 words]; bit t of nibble j of word i is the INVERTED bit of element 32 t + 8 i + j, so that
 //     step t finds its operand in bit t of every nibble: shifted to the sign position and combined with 0x2 it is the E2M1 value +-1
 //     (two instructions per register); every other nibble's bit at the bottom of a byte is an int8 value 0 / 1.
-//   Rows are padded to whole tiles; what the padding holds does not matter (its results are not stored).  Elements of k beyond the last
-//   are zero values.
+//   A tile at the lower edge reads rows that are not the group's (its results there are not stored); they lie in the group behind it, or in
+//   room behind the last one (see values_bytes).  Elements of k beyond the last are zero values.
 // Workgroup: four waves on a tile of 32 MB WM x 32 NB (4 / WM), two group buffers behind one barrier per group, and TWO workgroups on a
 // compute unit, so that one multiplies while the other waits at its barrier or stores its tile: 128 x 256 tiles, 10000 x 4096 x 4096, 93 us
 // against 107 of one workgroup of eight waves with the same waves on 256 x 256 (4096 x 4096 x 10000 87 against 103; int8 136 against 155,
@@ -48,7 +48,7 @@ struct MixedArgs {
     const uint8_t *a, *w;             // images
     const uint32_t *inexact;          // [kFlags]: int8 image if any is set
     uint32_t rows_a, rows_w;          // rows of an image's group
-    uint32_t groups;                  // of 256 elements
+    uint32_t groups, halves;          // of 256 elements, of 128 (int8)
     uint32_t tiles_m, tiles_n;
     int32_t alpha;                    // C = alpha S
     int alpha_shift;                  // alpha = 2^alpha_shift, or -1
@@ -62,7 +62,10 @@ __device__ __forceinline__ void product(const GemmArgs &g, const MixedArgs &x, u
     constexpr uint32_t kGroup = kLow + kHigh + kBits;
     const uint32_t lane = threadIdx.x & 63u, r = lane & 31u, kg = lane >> 5;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave / WN, wn = wave % WN;
-    const uint32_t total = x.tiles_m * x.tiles_n, groups = kBytes ? 2u * x.groups : x.groups;
+    const uint32_t total = x.tiles_m * x.tiles_n, groups = kBytes ? x.halves : x.groups;
+    // (where the loads ahead of the loop may enter a second tile, the code in front of the loop grows and the int8 loop, unchanged, runs
+    // 5 % slower: 8111 x 1008 x 638, second product, 40.8 against 42.9 us)
+    if constexpr (kBytes) __builtin_assume(groups >= 2u);
     const uint32_t lds_base = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t *)lds);
     int32_t *const stage_w = reinterpret_cast<int32_t *>(lds + 2 * kGroup + wave * 4096);
     auto opaque = [](uint32_t v) __attribute__((always_inline)) {

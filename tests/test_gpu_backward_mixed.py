@@ -1,5 +1,7 @@
 """The backward step on FP6 or int8 gradients: sizes one off its tiles (128 x 128, 128 x 256) and its groups of 256 and 128; gradients whose
 values are all E3M2 numbers (three leading bits), and the same with a single one that is not, which turns both images to int8."""
+import ctypes
+
 import pytest
 import torch
 
@@ -28,7 +30,8 @@ def _step(q, v, coef, K, planes=None, mode=0, mixed=True):
     assert torch.equal(gw, (v.t().contiguous().double() @ a.double()).to(torch.int32))
 
 
-@pytest.mark.parametrize("M,N,K", [(1281, 2050, 2049), (2305, 1151, 1100), (4100, 2817, 385), (1000, 4096, 4100), (8192, 2304, 257)])
+@pytest.mark.parametrize("M,N,K", [(1281, 2050, 2049), (2305, 1151, 1100), (4100, 2817, 385), (1000, 4096, 4100), (8192, 2304, 257),
+                                   (128, 6000, 4096), (8000, 128, 4096), (100, 4000, 4096)])  # half groups of k: one alone, one with less
 @pytest.mark.parametrize("kind", ["exact", "one other", "any"])
 def test_formats(seed, M, N, K, kind):
     import paper_1609_07061_amd as q
@@ -86,3 +89,41 @@ def test_where_thin_steps_stay_on_the_planes(seed, M, N, K, mixed):
 
     torch.manual_seed(seed)
     _step(q, torch.randint(-128, 128, (M, N), device="cuda"), COEF, K, mixed=mixed)
+
+
+def _hip():
+    """The HIP runtime that this process has loaded."""
+    with open("/proc/self/maps") as f:
+        return ctypes.CDLL(next(w for line in f for w in line.split() if "libamdhip64.so" in w))
+
+
+_USED_HIGH = 8  # hipMemPoolAttrUsedMemHigh
+
+
+def _roundup(v, to):
+    return (v + to - 1) // to * to
+
+
+@pytest.mark.parametrize("M,N,K,P", [(7572, 2368, 444, 8), (20000, 4000, 300, 8), (2561, 2305, 1025, 8), (1281, 2050, 2049, 8), (3031, 2083, 906, 6),
+                                     (17596, 1675, 760, 5), (1451, 3329, 367, 8)])
+def test_memory_from_the_pool(seed, M, N, K, P):
+    """No more than the header states: nothing for a transposed gradient of eight planes, which lies in the workspace."""
+    import paper_1609_07061_amd as q
+
+    torch.manual_seed(seed)
+    v = torch.randint(-(1 << (P - 1)), 1 << (P - 1), (M, N), device="cuda")
+    w, a = (torch.randint(0, 2, (r, K), device="cuda") * 2 - 1 for r in (N, M))
+    G = q.qnn_pack_bitplanes((v & ((1 << P) - 1)).to(torch.uint8), P)
+    W, A, coef = q.qnn_pack_sign(w.float()), q.qnn_pack_sign(a.float()), [1 << p for p in range(P - 1)] + [-(1 << (P - 1))]
+    hip, pool, used = _hip(), ctypes.c_void_p(), ctypes.c_uint64(0)
+    assert hip.hipDeviceGetDefaultMemPool(ctypes.byref(pool), torch.cuda.current_device()) == 0
+    torch.cuda.synchronize()
+    assert hip.hipMemPoolSetAttribute(pool, _USED_HIGH, ctypes.byref(used)) == 0
+    ga, gw = q.qnn_binary_backward(G, coef, 0, N, W, A, K)
+    torch.cuda.synchronize()
+    assert hip.hipMemPoolGetAttribute(pool, _USED_HIGH, ctypes.byref(used)) == 0
+    pitch_n, pitch_m = _roundup(N, 128), _roundup(M, 128)
+    stated = M * pitch_n + (0 if P == 8 else N * pitch_m) + K * max(pitch_n, pitch_m) + _roundup(4 * (M + N), 256)
+    assert 0 < used.value <= _roundup(stated, 4096), (used.value, stated)
+    assert torch.equal(ga, (v.double() @ w.double()).to(torch.int32))
+    assert torch.equal(gw, (v.t().contiguous().double() @ a.double()).to(torch.int32))
