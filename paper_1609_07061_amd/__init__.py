@@ -9,15 +9,12 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import sys
+import types
+import warnings
 from typing import Optional, Sequence
 
 import torch
-
-try:
-    from . import _native
-except ImportError as e:
-    raise ImportError(f"the binding's native part cannot be loaded ({e}): build it first with `python paper_1609_07061_amd/build.py` "
-                      "(or __graft_entry__.build())") from e
 
 PLANE_BIT, PLANE_SIGN = 0, 1
 ENGINE_AUTO, ENGINE_VALU, ENGINE_MFMA, ENGINE_MFMA_FP4, ENGINE_MFMA_LDS = 0, 1, 2, 3, 4
@@ -87,9 +84,28 @@ _lib.qnn_last_engine.restype = C.c_int
 _lib.qnn_last_error.restype = C.c_char_p
 _lib.qnn_version.restype = C.c_char_p
 
-# The calls made per layer or time step marshal their arguments in C++ where everything is as usual (status -1: it is not, see there)
-_native.bind(*[C.cast(getattr(_lib, n), C.c_void_p).value for n in ("qnn_pack_sign", "qnn_linear_quant_planes", "qnn_binary_gemm",
-                                                                    "qnn_binary_gemm_sign", "qnn_bitplane_gemm", "qnn_bitplane_conv2d")])
+# The calls made per layer or time step marshal their arguments in C++ where everything is as usual (status -1: it is not, see there).
+# Without that part, or with one that was built for another torch or Python, every call is marshalled here.
+_MARSHALLED = {"pack_sign": "qnn_pack_sign", "linear_quant_planes": "qnn_linear_quant_planes", "binary_gemm": "qnn_binary_gemm",
+               "binary_gemm_sign": "qnn_binary_gemm_sign", "bitplane_gemm": "qnn_bitplane_gemm", "bitplane_conv2d": "qnn_bitplane_conv2d"}
+
+
+def _load_native():
+    here = f"torch {torch.__version__}, {sys.implementation.cache_tag}"
+    try:
+        from . import _native as native
+
+        if native.BUILT_FOR != here:
+            raise ImportError(f"it was built for {native.BUILT_FOR}, this is {here}")
+        native.bind(*[C.cast(getattr(_lib, n), C.c_void_p).value for n in _MARSHALLED.values()])
+        return native
+    except (ImportError, AttributeError) as e:
+        warnings.warn(f"calls take about 3 us longer on the host, because the binding's native part cannot be used ({e}); "
+                      "`python paper_1609_07061_amd/build.py` builds it", stacklevel=3)
+        return types.SimpleNamespace(**{n: lambda *args: -1 for n in _MARSHALLED})
+
+
+_native = _load_native()
 
 _lib.qnn_last_engines.argtypes = [_vp, _int]
 _lib.qnn_last_engines.restype = C.c_int

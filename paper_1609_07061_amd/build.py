@@ -12,6 +12,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libqnn.so")
 NATIVE = os.path.join(PKG, "_native.so")
+NATIVE_STAMP = os.path.join(OBJ, "native.txt")  # what _native.so was built for
 SOURCES = ["qnn_api.hip", "qnn_probe.hip", "qnn_pack.hip", "qnn_quant.hip", "qnn_dedup.hip", "qnn_conv_first.hip", "qnn_gemm_valu.hip", "qnn_gemm_slice.hip", "qnn_gemm_tile.hip", "qnn_gemm_mfma.hip", "qnn_gemm_mfma_k0.hip",
            "qnn_gemm_mfma_k1.hip", "qnn_gemm_mfma_k2.hip", "qnn_gemm_mfma_k3.hip", "qnn_gemm_mfma_k4.hip", "qnn_gemm_stage_k0.hip",
            "qnn_gemm_stage_k1.hip", "qnn_gemm_stage_k2.hip", "qnn_gemm_panel_k0.hip", "qnn_gemm_bytes_panel_k0.hip",
@@ -67,11 +68,11 @@ def build(force: bool = False, verbose: bool = False) -> str:
             print(" ".join(cmd), flush=True)
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
-            raise RuntimeError("hipcc failed:\n" + " ".join(cmd) + "\n" + r.stdout + r.stderr)
+            raise RuntimeError(f"{cmd[0]} failed:\n" + " ".join(cmd) + "\n" + r.stdout + r.stderr)
         return r.stderr
 
     pool = ThreadPoolExecutor(max_workers=1)
-    binding = pool.submit(_build_binding, run) if force or _stale(NATIVE, [os.path.join(CSRC, "qnn_binding.cpp")]) else None
+    binding = pool.submit(_build_binding, run) if force or _binding_stale() else None
     with ThreadPoolExecutor(max_workers=min(8, max(1, len(jobs)))) as ex:
         for err in ex.map(run, jobs):
             if verbose and err.strip():
@@ -84,17 +85,41 @@ def build(force: bool = False, verbose: bool = False) -> str:
     return LIB
 
 
+def _built_for() -> str:
+    """What the binding's native part depends on beside its source: this torch and this Python (as in __init__.py)."""
+    import torch
+
+    return f"torch {torch.__version__}, {sys.implementation.cache_tag}"
+
+
+def _binding_stale() -> bool:
+    if _stale(NATIVE, [os.path.join(CSRC, "qnn_binding.cpp")]) or not os.path.exists(NATIVE_STAMP):
+        return True
+    with open(NATIVE_STAMP) as f:
+        return f.read() != _built_for()
+
+
 def _build_binding(run) -> None:
-    """The binding's native part, against the torch that is installed."""
+    """The binding's native part, against the torch that is installed.  It only shortens the host side of some calls: where it cannot be
+    built (no g++, no headers of torch or Python) the library is complete without it, and the package says so when it is imported."""
     import sysconfig
 
     import torch
     from torch.utils.cpp_extension import include_paths, library_paths
 
     src = os.path.join(CSRC, "qnn_binding.cpp")
-    run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-         *[f"-I{d}" for d in (*include_paths(), sysconfig.get_paths()["include"])], src, "-o", NATIVE,
-         *[f"-L{d}" for d in library_paths()], "-ltorch_python", "-ltorch_cpu", "-lc10"])
+    for old in (NATIVE, NATIVE_STAMP):
+        if os.path.exists(old):
+            os.remove(old)
+    try:
+        run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+             f'-DQNN_BUILT_FOR="{_built_for()}"', *[f"-I{d}" for d in (*include_paths(), sysconfig.get_paths()["include"])], src, "-o", NATIVE,
+             *[f"-L{d}" for d in library_paths()], "-ltorch_python", "-ltorch_cpu", "-lc10"])
+    except (OSError, RuntimeError) as e:
+        print(f"the binding's native part was not built: {e}", file=sys.stderr)
+        return
+    with open(NATIVE_STAMP, "w") as f:
+        f.write(_built_for())
 
 
 if __name__ == "__main__":

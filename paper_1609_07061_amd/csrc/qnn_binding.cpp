@@ -204,4 +204,12 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, kMethods, 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__native() { return PyModule_Create(&kModule); }
+// (BUILT_FOR: the torch and Python whose headers this was compiled with; with others, whose classes may be laid out differently, it is not used)
+PyMODINIT_FUNC PyInit__native() {
+    PyObject *const m = PyModule_Create(&kModule);
+    if (m && PyModule_AddStringConstant(m, "BUILT_FOR", QNN_BUILT_FOR) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}
