@@ -155,9 +155,9 @@ bool merge_plan(const Planes &pl, MergeOperand &op, int64_t &scale) {
 }  // namespace
 
 KernelFn kernel_values(bool tail, int blocks) {
-    if (tail) return gemm_bytes_panel_kernel<false, true, 4>;
-    if (blocks == 4) return gemm_bytes_panel_kernel<false, false, 4>;
-    return blocks == 3 ? gemm_bytes_panel_kernel<false, false, 3> : gemm_bytes_panel_kernel<false, false, 2>;
+    if (tail) return gemm_bytes_panel_kernel<true, 4>;
+    if (blocks == 4) return gemm_bytes_panel_kernel<false, 4>;
+    return blocks == 3 ? gemm_bytes_panel_kernel<false, 3> : gemm_bytes_panel_kernel<false, 2>;
 }
 
 bool merge_supports(const Planes &pa, const Planes &pw) {

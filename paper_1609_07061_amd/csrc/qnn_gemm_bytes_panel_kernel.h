@@ -30,14 +30,12 @@ constexpr int kPanelBytes = BM * kRowBytes;            // one operand's rows of 
 constexpr int kGroupBytes = 2 * kPanelBytes;
 constexpr int kGroupK = 128;
 
-// kThresholds: never; sums are what it leaves.
 // kTail (grid = a multiple of 16 workgroups, fewer than there are tiles, and at most half a grid of tiles in the last round): that
 // round's tiles are taken as halves of 128 columns by two workgroups each.
 // WB: blocks of 32 rows per wave, so the tile has 64 WB rows: 256, 192 or 128 (see bytes_tiles).
-template <bool kThresholds, bool kTail, int WB>
+template <bool kTail, int WB>
 __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const GemmArgs g, const MfmaConst mc, uint32_t tiles_m,
                                                                        uint32_t tiles_n, uint32_t ngroups) {
-    static_assert(!kThresholds, "int32 sums");
     constexpr int kLoadsPerGroup = WB + 4;  // loads to LDS that a wave issues per group
     static_assert(!kTail || WB == 4, "halves of whole tiles");
     // One LDS array: two group buffers, then the per-wave 32 x 32 staging blocks of the epilogue (all 160 KiB).
@@ -46,7 +44,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const Gem
     static_assert(kRingBytes + kTailBytes <= 160 * 1024, "LDS of a compute unit");
     __shared__ __attribute__((aligned(16))) uint8_t lds[kRingBytes + kTailBytes];
     const int t = threadIdx.x;
-    const int lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = wave >> 2, wn = wave & 3;
     const uint32_t total_tiles = tiles_m * tiles_n;

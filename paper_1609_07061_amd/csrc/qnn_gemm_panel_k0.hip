@@ -17,8 +17,8 @@ KernelFn find_kernel(bool sign, Shape t, bool whole) {
     return sign ? find<true, kAnyRows>(t) : find<false, kAnyRows>(t);
 }
 MapFn map_kernel(Shape t) {
-    if (t == k128x256) return gemm_tile_kernel<2, 4, WB, true>;
-    return t == k128x128 ? gemm_tile_kernel<2, 2, WB, true> : gemm_tile_kernel<4, 4, WB, true>;
+    if (t == k128x256) return gemm_map_kernel<2, 4>;
+    return t == k128x128 ? gemm_map_kernel<2, 2> : gemm_map_kernel<4, 4>;
 }
 WideFn wide_kernel() { return panel_wide::gemm_panel_wide_kernel; }
 

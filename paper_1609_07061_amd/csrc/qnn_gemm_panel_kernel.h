@@ -16,7 +16,7 @@
 //     threshold epilogue or waits at its barrier.
 //   * Rows (kRows): whole 64-byte groups on 16-byte boundaries; any others, starting at any word, through loads that check the
 //     operand's bounds (buffer_load ... lds: what lies beyond reads as zero), the words beyond a row's end cleared in registers in its
-//     last steps; or the 3 x 3 patches of a +-1 map (gemm_tile_kernel below).
+//     last steps; or the 3 x 3 patches of a +-1 map (gemm_map_kernel below).
 // Requirements (otherwise other kernels take the product): one plane per operand, operands that span less than 4 GiB each.
 #pragma once
 #include "qnn_gemm_mfma_kernel.h"
@@ -431,10 +431,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_panel_kernel(const GemmArgs 
     panel_product<(Rows)kRows, kSign, WM, WBN>(g, mc, x, lds);
 }
 
-// The same for a +-1 map; the arguments: waves along m, blocks of a wave's columns, blocks of its rows, and that it is a map.
-template <int WM, int WBN, int kBlocksM, bool kIsMap>
-__global__ __launch_bounds__(kThreads, 2) void gemm_tile_kernel(const GemmArgs g, const PanelArgs x) {
-    static_assert(kBlocksM == WB && kIsMap && kLdsBytes<kMapRows, true, WM, WBN> <= 80 * 1024, "two workgroups on a compute unit");
+// The same for a +-1 map
+template <int WM, int WBN>
+__global__ __launch_bounds__(kThreads, 2) void gemm_map_kernel(const GemmArgs g, const PanelArgs x) {
+    static_assert(kLdsBytes<kMapRows, true, WM, WBN> <= 80 * 1024, "two workgroups on a compute unit");
     __shared__ __attribute__((aligned(16))) uint8_t lds[kLdsBytes<kMapRows, true, WM, WBN>];
     const MfmaConst none = {};
     panel_product<kMapRows, true, WM, WBN>(g, none, x, lds);

@@ -57,7 +57,6 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_wide_kernel(const Gemm
     __shared__ __attribute__((aligned(16))) int32_t stage[kThreads / 64][32 * 32];
 
     const int t = threadIdx.x;
-    const int lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     constexpr int kLoadsPerGroup = 16;  // loads to LDS that a wave issues per group

@@ -40,10 +40,8 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// (kMap: false; the kernel for +-1 maps of the same name is in qnn_gemm_panel_kernel.h)
-template <int kA, int kW, int kRows, bool kMap = false>
+template <int kA, int kW, int kRows>
 __global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) void gemm_tile_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
-    static_assert(!kMap, "matrices and patches of images");
     constexpr bool kPixels = kRows != kMatrix;
     constexpr int NA = kA == kPair ? 2 : 1, NW = kW == kPair ? 2 : 1;  // planes of a digit
     // 16-byte pieces of a row per group (two of them make a chunk of 256 elements)

@@ -34,7 +34,7 @@ def dev(a: np.ndarray) -> torch.Tensor:
 
 
 def kernels_of(call) -> list:
-    """The library's kernels that `call` launches, in order, by name and template arguments ("gemm_tile_kernel<0, 0, 0, false>")."""
+    """The library's kernels that `call` launches, in order, by name and template arguments ("gemm_tile_kernel<0, 0, 0>")."""
     import re
 
     from torch.profiler import ProfilerActivity, profile

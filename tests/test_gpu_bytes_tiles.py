@@ -37,7 +37,7 @@ def test_merged_products(seed, M, N, K, tile, ca, ma, cw, mw):
         assert torch.equal(C, want.to(torch.int32)), (M, N, K, ca)
     assert bool((wide[:, 0] == 7).all()) and bool((wide[:, 1 + N:] == 7).all())
     kernels = kernels_of(lambda: q.qnn_bitplane_gemm(A, ca, ma, W, cw, mw, K, out=C, engine=q.ENGINE_MFMA_LDS))
-    assert kernels[-1] == f"gemm_bytes_panel_kernel<false, {tile}>", kernels
+    assert kernels[-1] == f"gemm_bytes_panel_kernel<{tile}>", kernels
     rows = np.array([0, M - 1])
     assert np.array_equal(host(C)[rows], oracle.gemm_int(va[rows].astype(np.int32), vw.astype(np.int32)))
 

@@ -109,8 +109,8 @@ def test_kernel_by_the_number_of_tiles():
     assert product(1, 20000, 10, 16000) == [small]       # ... of long rows
     assert product(1, 1000, 1000, 300) == [large]
     assert product(1, 40000, 96, 300) == [large]         # 1250 tiles
-    assert product(1, 1999, 3001, 300) == ["gemm_tile_kernel<2, 2, 0, false>"]
-    assert product(2, 1800, 1800, 300) == ["gemm_tile_kernel<1, 2, 0, false>"]
+    assert product(1, 1999, 3001, 300) == ["gemm_tile_kernel<2, 2, 0>"]
+    assert product(2, 1800, 1800, 300) == ["gemm_tile_kernel<1, 2, 0>"]
 
 
 def test_panels_or_tiles_for_single_planes_of_whole_groups():
