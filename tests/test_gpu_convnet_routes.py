@@ -3,9 +3,11 @@ kernel; the FP4 engine takes it at any size, the library itself from 48 tiles of
 where the maps are 8, 16 or 32 pixels wide and of even height, and on the map's 2-bit code on the kernels for any size."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
-from test_gpu_convnet import _case, _run
+from qnn_testlib import dev, host
+from test_gpu_convnet import _case, _products, _run
 
 pytestmark = pytest.mark.gpu
 
@@ -29,3 +31,46 @@ def test_both_ways_of_a_convolution(seed, B, H, Wd, couts, pools, fcs, with_flip
     for engine in (q.ENGINE_AUTO, q.ENGINE_MFMA_FP4):
         got = _run(q, (x, conv_w, pools, fc_w, T, flip), couts, fcs, engine=engine, with_flip=with_flip)
         assert np.array_equal(got, want), engine
+
+
+def _conv(x, w):
+    """3 x 3 "same" convolution, channels last, in double precision, on the GPU (the oracle takes minutes for these layers)."""
+    B, H, Wd, C = x.shape
+    w2 = w.reshape(w.shape[0], -1).double().t().contiguous()
+    out = []
+    for part in x.split(max(1, (1 << 27) // (H * Wd * 9 * C))):
+        p = torch.nn.functional.pad(part.double(), (0, 0, 1, 1, 1, 1))
+        patches = torch.stack([p[:, y:y + H, z:z + Wd] for y in range(3) for z in range(3)], dim=3)
+        out.append((patches.reshape(-1, 9 * C) @ w2).reshape(-1, H, Wd, w.shape[0]))
+    return torch.cat(out)
+
+
+def _bits(sums, T, flip):
+    return torch.where((sums >= T) != (flip != 0), 1.0, -1.0)
+
+
+@pytest.mark.parametrize("B,H,Wd,cin,N,pool,tile", [
+    (13, 29, 31, 990, 1056, 0, "2, 4"),   # 128 x 256, pixels and filters ragged (32 filters in the last tile), 31 words of channels
+    (57, 12, 16, 990, 1056, 1, "2, 4"),   # ... pooled along
+    (26, 29, 31, 990, 800, 0, "4, 4"),    # 256 x 128
+    (123, 12, 16, 990, 800, 1, "4, 4"),
+    (37, 21, 30, 100, 96, 0, "2, 2"),
+])
+@pytest.mark.parametrize("with_flip", [True, False])
+def test_tiles_of_wide_layers(seed, B, H, Wd, cin, N, pool, tile, with_flip):
+    import paper_1609_07061_amd as q
+
+    couts, pools, fcs = [cin, N], [0, pool], [5]
+    case = _case(seed, B, H, Wd, 3, couts, pools, fcs, 2300, span=40)
+    x, conv_w, _, fc_w, T, flip = case
+    got = _run(q, case, couts, fcs, with_flip=with_flip)
+    flips = [dev(f) if with_flip else torch.zeros(len(f), dtype=torch.uint8, device="cuda") for f in flip]
+    h = _bits(_conv(dev(x), dev(conv_w[0])), dev(T[0]), flips[0])
+    z = _conv(h, dev(conv_w[1]))
+    if pool:
+        z = z.reshape(B, H // 2, 2, Wd // 2, 2, N).amax(dim=(2, 4))
+    h = _bits(z, dev(T[1]), flips[1]).reshape(B, -1)
+    want = h.double() @ dev(fc_w[0]).double().t().contiguous()
+    assert np.array_equal(got, host(want.to(torch.int32)))
+    kernels = _products(q, case, couts, fcs)
+    assert kernels[1] == f"gemm_map_kernel<{tile}>", kernels
