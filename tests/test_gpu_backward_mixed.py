@@ -62,6 +62,32 @@ def test_one_value_decides(seed, value):
         _step(q, v, [1, 2, 4, 8, 16, 32], K, planes=q.qnn_pack_bitplanes(u.to(torch.uint8), 6), mode=1)
 
 
+@pytest.mark.parametrize("kind", ["exact", "one other"])
+def test_sums_up_to_the_bound(seed, kind):
+    """131 071 rows of -128 but for the last ones, small odd values: sums close to the bound of 2^24 whose lowest bits count, added to
+    accumulators that are close to it already."""
+    import paper_1609_07061_amd as q
+
+    torch.manual_seed(seed)
+    M, N, K = 131071, 2048, 1024
+    v = torch.full((M, N), -128, dtype=torch.int64, device="cuda")
+    v[M - 255:] = torch.tensor([-7, -5, -3, -1, 1, 3, 5, 7], device="cuda")[torch.randint(0, 8, (255, N), device="cuda")]
+    if kind == "one other":
+        v[5, 7] = 127  # (both images are int8 then)
+    w, a = torch.ones((N, K), device="cuda"), torch.randint(0, 2, (M, K), device="cuda").float() * 2 - 1
+    w[::3, ::2] = -1
+    a[:, :400], a[:, 400:800] = 1, -1
+    G, W, A = q.qnn_pack_bitplanes((v & 255).to(torch.uint8), 8), q.qnn_pack_sign(w), q.qnn_pack_sign(a)
+    ws = torch.empty(q.qnn_binary_backward_workspace_bytes(M, N, K, 8), dtype=torch.uint8, device="cuda")
+    ga, gw = q.qnn_binary_backward(G, COEF, 0, N, W, A, K, workspace=ws)
+    kernels = kernels_of(lambda: q.qnn_binary_backward(G, COEF, 0, N, W, A, K, workspace=ws))
+    assert sum(k.startswith("gemm_mixed_kernel") for k in kernels) == 2, kernels
+    want = (v.t().contiguous().double() @ a.double()).to(torch.int32)
+    assert int(want.abs().max()) > 2 ** 24 - 2 ** 16 and bool((want[:, :400] % 2 != 0).any())
+    assert torch.equal(gw, want)
+    assert torch.equal(ga, (v.double() @ w.double()).to(torch.int32))
+
+
 def test_largest_sums():
     """60 000 rows of -128 against weights of +1 in their larger half: sums up to 7.6e6 with steps of 128, and odd ones beside them."""
     import paper_1609_07061_amd as q
@@ -78,6 +104,8 @@ def test_largest_sums():
         ga, gw = q.qnn_binary_backward(G, COEF, 0, N, W, A, K)
         assert torch.equal(ga, (v.double() @ w.double()).to(torch.int32))
         assert torch.equal(gw, (v.t().contiguous().double() @ a.double()).to(torch.int32))
+        kernels = kernels_of(lambda: q.qnn_binary_backward(G, COEF, 0, N, W, A, K))
+        assert sum(k.startswith("gemm_mixed_kernel") for k in kernels) == 2, kernels
 
 
 @pytest.mark.parametrize("M,N,K,mixed", [
