@@ -456,11 +456,14 @@ double slice_us(const GemmArgs &g) {
 //   other single planes, int32 sums: while 64 x 64 tiles make one round at most (256 x 1024 x 8192 24 -> 6; 10000 x 256 x 8192, 628
 //     tiles, 25 -> 19; 2048^3, 1024, 12.8 -> 11.2), and while the panels' 256 x 128 tiles leave compute units idle and rows are short
 //     (3000 x 2048, 192 such tiles, x 1024 11.2 -> 9.7, x 2048 13.4 and 13.7, x 4096 18.0 against 19.7, x 8192 26.8 against 32.5);
-//   int32 sums of rows that are no whole groups of 1024: also where 128 x 128 tiles, three workgroups of which share a compute unit here
-//     and two there, are few or rows short, and more so where C leaves word by word, which takes longer there (panels -> here: 4187 x 1024
-//     x 3860 19.3 -> 18.3, 1226 x 4800 x 922 10.7 -> 9.9, 3456 x 2603 x 1101 19.7 -> 18.8, 2376 x 3953 x 640 18.9 -> 17.9, 3584 x 5682 x 640 29.8 ->
-//     25.0; 1792 x 2760 x 4416, 308 tiles, 18.8 -> 18.7), and just beyond one round of 128 x 256 there (2428 x 7085 x 2552 40.1 -> 36.6).
-//     Against that, with longer rows: 320 to 400 tiles 10 to 17 % slower here, 400 to 768 4 to 19 %;
+//   int32 sums of rows that are no whole groups of 1024 (447 products of 160 to 2600 tiles of 128 x 128, t, rows of 512 to 7000; here / panels):
+//     C in 16-byte pieces: while its 64 x 64 tiles make one round here, five a compute unit (t <= 320 .66 to 1.05, beyond 1.04 to 1.4);
+//     C word by word, which takes the panels longer where their tiles do not make one round, two a unit: while 64 x 64 tiles are at most three a
+//       unit (t <= 200 .87 to 1.0, 216 to 512 1.02 to 1.2), and beyond one round with short rows: t up to 1024, where 128 x 256 tiles make one,
+//       K < 1400 (516 x 673 .90, 759 x 1406 .99, 854 x 2993 1.1), just behind it (t = 1026 to 1280) K < 4000 (.82 to .96, K above 4800 1.0), from there on
+//       K < 2500 (.82 to 1.03, above 1.02 to 1.16).
+//     With C's lines in no cache (six outputs in turn, 350 MB) the panels fall back by up to a third more beyond t = 900: their parts of a
+//       line arrive further apart.
 //   the same with threshold output, which costs the panel-fed kernel less: while 64 x 64 tiles are few (512 x 4096 x 4096, 512 tiles, 14.7
 //     -> 11.4; 10000 x 256 x 2048, 628, 10.4 -> 10.3; 1500 x 2048 x 2048, 768, 10.6 against 11.2; 20000 x 256 x 4096, 1252, 15.0 against
 //     21.0);
@@ -475,13 +478,12 @@ bool slice_preferred(const GemmArgs &g, int route) {
     if (route == QNN_ENGINE_MFMA_FP4 && panel_takes(g)) {
         const int64_t tiles64 = ceil_div(g.M, 64) * ceil_div(g.N, 64);
         if (g.epi.T) return tiles64 <= (g.N < 512 || g.K > 4096 ? 640 : 288);
-        const int64_t tiles = ceil_div(g.M, 128) * ceil_div(g.N, 128);
         const bool whole = g.Kw % 32 == 0 && g.A.ld % 4 == 0 && g.ldw % 4 == 0 && (reinterpret_cast<uintptr_t>(g.A.base) | reinterpret_cast<uintptr_t>(g.W)) % 16 == 0;
         if (!whole) {
+            const int64_t cus = compute_units(), tiles = ceil_div(g.M, 128) * ceil_div(g.N, 128);
             const bool words = g.epi.ldc % 4 != 0 || reinterpret_cast<uintptr_t>(g.epi.C) % 16 != 0;  // C leaves word by word
-            if (tiles <= 320 || (g.K < 2048 && tiles <= (words ? 600 : 400)) || (g.K < 1024 && (words || tiles <= 512)) ||
-                (words && g.K < 3500 && tiles > 1024 && tiles <= 1160))
-                return true;
+            if (!words) return tiles64 <= 5 * cus;
+            return tiles64 <= 3 * cus || (tiles > 2 * cus && g.K < (tiles <= 4 * cus ? 1400 : (tiles <= 5 * cus ? 4000 : 2500)));
         }
         return tiles64 <= 1024 || (g.K <= 2048 && ceil_div(g.M, 256) * ceil_div(g.N, 128) < 256);
     }

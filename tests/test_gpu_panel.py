@@ -85,11 +85,13 @@ def test_wide_tiles(seed, M, N):
     assert kernels_of(lambda: q.qnn_binary_gemm(A, W, K)) == ["gemm_panel_wide_kernel"]
 
 
-@pytest.mark.parametrize("M,N,K,panel", [
-    (4187, 1024, 3860, False), (1999, 3001, 2500, True),    # 264 and 384 tiles of 128 x 128
-    (1226, 4800, 922, False), (4187, 2048, 922, True),      # short rows: 380 and 528
-    (2376, 3953, 640, False), (2960, 2603, 1401, False), (2960, 2603, 2100, True),  # C word by word
-    (2428, 7085, 2552, False), (2428, 7088, 2552, True),    # 1064 tiles
+@pytest.mark.parametrize("M,N,K,panel", [  # (GPU of 256 compute units)
+    (4187, 1024, 3860, False), (1999, 3000, 600, True),     # C in 16-byte pieces: 1056 and 1504 tiles of 64 x 64
+    (1270, 2303, 513, False), (1503, 2557, 1199, True),     # C word by word: 720 and 960
+    (1999, 3001, 2500, True), (3053, 2174, 513, True),      # ... 384 and 408 tiles of 128 x 128
+    (2376, 3953, 640, False), (2376, 3953, 1500, True),     # 589
+    (2428, 7085, 2552, False), (2428, 7088, 2552, True), (3296, 6079, 5301, True),  # 1064, in 16-byte pieces, 1248
+    (4861, 5809, 1090, False), (3535, 6269, 3378, True),    # 1748, 1372
 ])
 def test_where_rows_of_other_lengths_leave_the_tiled_kernels(seed, M, N, K, panel):
     import paper_1609_07061_amd as q
