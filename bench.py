@@ -265,7 +265,7 @@ def main():
             extra["backward_hidden_layer_8bit_gradients"] = {
                 "parity_sample_ok": bool(ok), "ms": msb if ok else None,
                 "effective_integer_tmacs": imac / (msb * 1e-3) / 1e12 if ok else None,
-                "note": "LogQuant of the fp32 gradient to 8 planes, gradient to bytes in both orders, weights and activations transposed to bytes, two int8 products"}
+                "note": "LogQuant of the fp32 gradient to 8 planes, gradient to FP6 in both orders, weights and activations transposed as bits, two FP6 x FP4 products"}
 
         jobs.append((2, job_bwd))
 

@@ -144,7 +144,8 @@ __device__ __forceinline__ void put(const Image &im, const bool as_bytes, const 
 // become 32 bytes per row (bit-matrix transposition in registers), which the conversion instruction packs for out; 4 x 4 byte
 // transpositions turn four rows' bytes into dwords along m, and LDS collects those to 32 bytes per column for out_t.  LDS: column n at
 // dword 36 n, its dwords rotated by 8 (n / 32 mod 4) and moved on by 32 for the upper half, so that the 64 dword writes of a wave (eight
-// words x eight row groups) fall on 64 banks.
+// words x eight row groups) fall on 64 banks.  The 16-byte reads of a column's pieces meet in twos (36 dwords a column): half of the LDS
+// cycles at 10000 x 4096.
 __global__ __launch_bounds__(256) void merge_transpose_kernel(const Gradient a, const Image out, const Image out_t) {
     constexpr int kPitch = 36;
     __shared__ __attribute__((aligned(16))) uint32_t s_t[256 * kPitch + 32];

@@ -77,11 +77,11 @@ struct GemmArgs {
     // weights of row n), both written by codes::launch_weight_image earlier on the same stream.  Null: the kernels expand the packed bits.
     const uint32_t *w_image;
     const int32_t *rw_scaled;
-    // Only for convolutions of +-1 maps on the tiled FP4 kernel: class_thr[cls * class_ld + n] is the threshold of filter n for a pixel
+    // Only for convolutions of +-1 maps (gemm_map_kernel): class_thr[cls * class_ld + n] is the threshold of filter n for a pixel
     // of border class cls (bit 0: first row, 1: last row, 2: first column, 3: last column).
     const int32_t *class_thr;
     int64_t class_ld;
-    const uint32_t *pool_and;  // tiled kernel on a +-1 map: 2 x 2 max-pooling follows; packed flags of the filters whose bits are AND-ed
+    const uint32_t *pool_and;  // +-1 maps: 2 x 2 max-pooling follows; packed flags of the filters whose bits are AND-ed
     uint32_t pool_invert;      // ... inverted with this
 };
 
