@@ -459,7 +459,8 @@ double slice_us(const GemmArgs &g) {
 //   int32 sums of rows that are no whole groups of 1024 (447 products of 160 to 2600 tiles of 128 x 128, t, rows of 512 to 7000; here / panels):
 //     C in 16-byte pieces: while its 64 x 64 tiles make one round here, five a compute unit (t <= 320 .66 to 1.05, beyond 1.04 to 1.4);
 //     C word by word, which takes the panels longer where their tiles do not make one round, two a unit: while 64 x 64 tiles are at most three a
-//       unit (t <= 200 .87 to 1.0, 216 to 512 1.02 to 1.2), and beyond one round with short rows: t up to 1024, where 128 x 256 tiles make one,
+//       unit (t <= 200 .87 to 1.0, 216 to 512 1.02 to 1.2), or four where ragged edges make more than one 128 x 128 tile of them a unit (2502 x
+//       1573 x 3584, t = 260, .87), and beyond one round with short rows: t up to 1024, where 128 x 256 tiles make one,
 //       K < 1400 (516 x 673 .90, 759 x 1406 .99, 854 x 2993 1.1), just behind it (t = 1026 to 1280) K < 4000 (.82 to .96, K above 4800 1.0), from there on
 //       K < 2500 (.82 to 1.03, above 1.02 to 1.16).
 //     With C's lines in no cache (six outputs in turn, 350 MB) the panels fall back by up to a third more beyond t = 900: their parts of a
@@ -483,7 +484,8 @@ bool slice_preferred(const GemmArgs &g, int route) {
             const int64_t cus = compute_units(), tiles = ceil_div(g.M, 128) * ceil_div(g.N, 128);
             const bool words = g.epi.ldc % 4 != 0 || reinterpret_cast<uintptr_t>(g.epi.C) % 16 != 0;  // C leaves word by word
             if (!words) return tiles64 <= 5 * cus;
-            return tiles64 <= 3 * cus || (tiles > 2 * cus && g.K < (tiles <= 4 * cus ? 1400 : (tiles <= 5 * cus ? 4000 : 2500)));
+            if (tiles64 <= (tiles > cus ? 4 : 3) * cus) return true;
+            return tiles > 2 * cus && g.K < (tiles <= 4 * cus ? 1400 : (tiles <= 5 * cus ? 4000 : 2500));
         }
         return tiles64 <= 1024 || (g.K <= 2048 && ceil_div(g.M, 256) * ceil_div(g.N, 128) < 256);
     }

@@ -87,7 +87,7 @@ def test_wide_tiles(seed, M, N):
 
 @pytest.mark.parametrize("M,N,K,panel", [  # (GPU of 256 compute units)
     (4187, 1024, 3860, False), (1999, 3000, 600, True),     # C in 16-byte pieces: 1056 and 1504 tiles of 64 x 64
-    (1270, 2303, 513, False), (1503, 2557, 1199, True),     # C word by word: 720 and 960
+    (1270, 2303, 513, False), (1503, 2557, 1199, True), (2502, 1573, 3584, False),  # C word by word: 720, 960 and 1000
     (1999, 3001, 2500, True), (3053, 2174, 513, True),      # ... 384 and 408 tiles of 128 x 128
     (2376, 3953, 640, False), (2376, 3953, 1500, True),     # 589
     (2428, 7085, 2552, False), (2428, 7088, 2552, True), (3296, 6079, 5301, True),  # 1064, in 16-byte pieces, 1248
