@@ -155,3 +155,32 @@ def test_memory_from_the_pool(seed, M, N, K, P):
     assert 0 < used.value <= _roundup(stated, 4096), (used.value, stated)
     assert torch.equal(ga, (v.double() @ w.double()).to(torch.int32))
     assert torch.equal(gw, (v.t().contiguous().double() @ a.double()).to(torch.int32))
+
+
+@pytest.mark.parametrize("M,N,K", [(1009, 1280, 2784), (1451, 3329, 367)])
+def test_captured_step(seed, M, N, K):
+    """In a graph, with its memory from the pool: new gradients, FP6 ones and others, and eager work between the replays."""
+    import paper_1609_07061_amd as q
+
+    torch.manual_seed(seed)
+    w, a = (torch.randint(0, 2, (r, K), device="cuda") * 2 - 1 for r in (N, M))
+    W, A = q.qnn_pack_sign(w.float()), q.qnn_pack_sign(a.float())
+    values = [torch.tensor(EXACT, device="cuda")[torch.randint(0, len(EXACT), (M, N), device="cuda")], torch.randint(-128, 128, (M, N), device="cuda")]
+    G = q.qnn_pack_bitplanes((values[0] & 255).to(torch.uint8), 8)
+    ws = torch.empty(q.qnn_binary_backward_workspace_bytes(M, N, K, 8), dtype=torch.uint8, device="cuda")
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        q.qnn_binary_backward(G, COEF, 0, N, W, A, K, workspace=ws)
+    torch.cuda.current_stream().wait_stream(stream)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ga, gw = q.qnn_binary_backward(G, COEF, 0, N, W, A, K, workspace=ws)
+    for i in (0, 1, 0, 0, 1):
+        q.qnn_pack_bitplanes((values[i] & 255).to(torch.uint8), 8, out=G)
+        ga.zero_(), gw.zero_()
+        graph.replay()
+        assert torch.equal(ga, (values[i].double() @ w.double()).to(torch.int32)), i
+        assert torch.equal(gw, (values[i].t().contiguous().double() @ a.double()).to(torch.int32)), i
+        eager = q.qnn_binary_backward(G, COEF, 0, N, W, A, K)
+        assert torch.equal(eager[0], ga) and torch.equal(eager[1], gw)
