@@ -218,7 +218,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bytes_panel_kernel(const Gem
             for (int i = 0; i < WI; ++i)
 #pragma unroll
                 for (int j = 0; j < WB; ++j) asm volatile("" : "+v"(acc[i][j]));
-            panel::wave_finish<false, WI, kLoadsPerGroup>(g, mc, acc, ra, rw, nullptr, nullptr, nullptr, stage_w, m_wave, n_wave);
+            panel::wave_finish<false, WI, kLoadsPerGroup, panel::kNoTerms>(g, mc, acc, ra, rw, nullptr, nullptr, nullptr, stage_w, m_wave, n_wave);
         }
     };
     run_tiles(std::integral_constant<int, 2>{}, vb0, n_mine, 0u);

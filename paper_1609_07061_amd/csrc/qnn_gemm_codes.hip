@@ -7,6 +7,9 @@
 //   sum_k (x[m][k] - 128) w[n][k],  and C[m][n] is that plus 128 sum_k w[n][k],
 // a term per weight row that the image kernel writes as well.  Pieces of 16 elements beyond K read as zeros, i.e. -128, and meet as many
 // weights of +64 as of -64.
+//   The sums start from -64 (T - term), so that a finished sum's sign is its bit and the epilogue is one instruction per element; with the
+// comparison at the end (shift, scale, two terms, difference, sign) that was six, a quarter of the instructions of a tile of 784 codes:
+// 10000 x 784 -> 4096 38.5 -> 34.3 us.
 // Workgroup: four waves of 64 x 32 NB on a tile of 128 x 64 NB, two on a compute unit (they cover each other's barriers and thresholds); both
 // operands of a group of 128 elements of k come in straight to LDS, two group buffers.
 // Bound: the card's power.  8192 x 4096 x 4096 takes 116 us with 56 % of the cycles in matrix instructions on random codes, 88 on constant
@@ -14,8 +17,6 @@
 // 256 x 256 tiles on a unit (or, for fewer rows than the weights' bytes leave room for in the workspace, bits expanded by every wave;
 // whole forward step with a 10-neuron second layer): 10000 x 784 -> 4096 59 -> 51 us, 4096 x 784 -> 4096 34.5 -> 26, 2000 x 784 -> 4096 28 ->
 // 19.7, 10000 x 4096 -> 4096 174 -> 155, 3000 x 3072 -> 1000 33 -> 28.
-#include <cstring>
-
 #include "qnn_gemm_mfma_kernel.h"
 #include "qnn_gemm_panel_epilogue.h"
 
@@ -24,7 +25,6 @@ namespace codes {
 
 namespace {
 
-using mfma::MfmaConst;
 using mfma::v16i;
 using mfma::v4i;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -41,18 +41,19 @@ struct CodesArgs {
 };
 
 template <int NB>
-__global__ __launch_bounds__(kThreads, 2) void gemm_codes_kernel(const GemmArgs g, const MfmaConst mc, const CodesArgs x) {
+__global__ __launch_bounds__(kThreads, 2) void gemm_codes_kernel(const GemmArgs g, const CodesArgs x) {
     constexpr uint32_t kTable = 32 * NB, kLoadsA = kPanel / 4096, kLoads = kLoadsA + 1;  // of 1024 bytes each, per wave
-    // two group buffers; per wave the thresholds, flip flags and weight rows' terms of its columns
-    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kGroup + 4 * 3 * kTable * 4];
+    // two group buffers; per wave the thresholds, flip flags and weight rows' terms of its columns as they arrive, and what its sums start from
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kGroup + 4 * 4 * kTable * 4];
     static_assert(sizeof(lds) <= 80 * 1024, "two workgroups on a compute unit");
     const uint32_t lane = threadIdx.x & 63u, r = lane & 31u, kg = lane >> 5;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave >> 1, wn = wave & 1u;
     const uint32_t total = x.tiles_m * x.tiles_n, groups = (x.halves + 1u) / 2u, K = (uint32_t)g.K;
     const uint32_t lds_base = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t *)lds);
-    uint32_t *const rw_tab = reinterpret_cast<uint32_t *>(lds + 2 * kGroup) + wave * 3u * kTable;
+    uint32_t *const rw_tab = reinterpret_cast<uint32_t *>(lds + 2 * kGroup) + wave * 4u * kTable;
     int32_t *const thr_tab = reinterpret_cast<int32_t *>(rw_tab + kTable);
     uint32_t *const flip_tab = rw_tab + 2 * kTable;
+    int32_t *const start_tab = thr_tab + 2 * kTable;
 #pragma unroll
     for (uint32_t h = 0; h < kTable; h += 64) flip_tab[h + lane] = 0u;  // flip flags default to "none"
     auto opaque = [](uint32_t v) __attribute__((always_inline)) {  // keeps address arithmetic where it is used
@@ -107,6 +108,22 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_codes_kernel(const GemmArgs 
     // the next group has landed and this wave's LDS reads have returned
     auto barrier = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
+    // thresholds, flip flags and weight rows' terms of a tile on their way to the wave's tables
+    auto load_columns = [&](const uint32_t vb) __attribute__((always_inline)) {
+        uint32_t tm, tn;
+        tile_of_block(vb, total, x.tiles_m, x.tiles_n, tm, tn);
+        const int64_t n0 = (int64_t)tn * (64 * NB) + wn * (32 * NB);
+        panel::load_thresholds_to_lds<NB>(g, n0, thr_tab, flip_tab);
+        const uint32_t rw_lds = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint32_t *)rw_tab);
+#pragma unroll
+        for (uint32_t h = 0; h < kTable; h += 64) {
+            int64_t n = n0 + h + opaque(lane);
+            if (n > g.N - 1) n = g.N - 1;
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(rw_lds + 4u * h), "v"((uint32_t)n * 4u), "s"(g.rw_scaled) : "memory");
+        }
+    };
+
+    load_columns(vb0);
     p_locate(vb0);
     p_piece();
 #pragma unroll
@@ -162,22 +179,38 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_codes_kernel(const GemmArgs 
         uint32_t tile_m, tile_n;
         tile_of_block(vb, total, x.tiles_m, x.tiles_n, tile_m, tile_n);
         const int64_t m_wave = (int64_t)tile_m * kBM + wm * (32 * kMB), n_wave = (int64_t)tile_n * (64 * NB) + wn * (32 * NB);
+        // What has arrived (before a barrier): the sums start from -64 (T - term), so that a sum's sign is its bit.  |s| < 2^24, so a
+        // difference clamped there decides the same, and 64 (s - difference) stays within 32 bits.
+        uint32_t flips[NB];
 #pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-            for (int j = 0; j < kMB; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
-        // on their way before the tile's first barrier
-        panel::load_thresholds_to_lds<NB>(g, n_wave, thr_tab, flip_tab);
-        const uint32_t rw_lds = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint32_t *)rw_tab);
-#pragma unroll
-        for (uint32_t h = 0; h < kTable; h += 64) {
-            int64_t n = n_wave + h + lane;
-            if (n > g.N - 1) n = g.N - 1;
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(rw_lds + 4u * h), "v"((uint32_t)n * 4u), "s"(g.rw_scaled) : "memory");
+        for (uint32_t h = 0; h < kTable / 64; ++h) {
+            const uint32_t at = 64u * h + opaque(lane);
+            constexpr int32_t kMost = 1 << 24, kMostT = 1 << 26;
+            const int32_t t = thr_tab[at];
+            int32_t d = (t < -kMostT ? -kMostT : (t > kMostT ? kMostT : t)) - (int32_t)rw_tab[at];
+            d = d < -kMost ? -kMost : (d > kMost ? kMost : d);
+            start_tab[at] = -64 * d;
+            const uint64_t flip = __ballot(flip_tab[at] == 0u);
+            flips[2 * h] = (uint32_t)flip, flips[2 * h + 1] = (uint32_t)(flip >> 32);
         }
-        for (uint32_t G = 0; G < groups; ++G) {
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the wave's own LDS operations are done
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int32_t *const start_of = start_tab + 32 * i + 4u * (opaque(lane) >> 5);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const v4i start = *reinterpret_cast<const v4i *>(start_of + 8 * q);
+#pragma unroll
+                for (int j = 0; j < kMB; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] = start[e];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (done + 1u < n_mine) load_columns(vb + gridDim.x);
+        uint32_t G = 0;
+        do {  // (a loop that might not run would hold the sums' start and the sums in registers of their own)
             const uint32_t other = kGroup - rd;
             p_advance();
             fetch(1, rd, nxt);
@@ -201,17 +234,33 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_codes_kernel(const GemmArgs 
             });
             multiply(nxt, 1, nothing);
             rd = other;
-        }
-        // The sums are pinned here: otherwise the compiler moves matrix-core instructions down into the epilogue's blocks
+        } while (++G < groups);
+        // The sums are pinned here: otherwise the compiler moves matrix-core instructions down into the epilogue
 #pragma unroll
         for (int i = 0; i < NB; ++i)
 #pragma unroll
+            for (int j = 0; j < kMB; ++j) asm volatile("" : "+v"(acc[i][j]));
+        uint32_t word[NB];
+        const uint32_t kg_here = opaque(lane) >> 5;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            uint32_t both[kMB];
+#pragma unroll
             for (int j = 0; j < kMB; ++j) {
-                asm volatile("" : "+v"(acc[i][j]));
-                acc[i][j] >>= 6;
+                uint32_t bits = 0;  // register 4 q + e: column 8 q + 4 kg + e of the block's 32
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    uint32_t nib = 0;
+#pragma unroll
+                    for (int e = 3; e >= 0; --e) nib = __builtin_amdgcn_alignbit(nib, (uint32_t)acc[i][j][4 * q + e], 31);
+                    bits |= nib << (8 * q);
+                }
+                both[j] = mfma::or_halves(bits << (4u * kg_here));
             }
-        int32_t ra[kMB] = {}, rw[NB] = {};
-        panel::wave_finish<true, NB, (int)kLoads, true>(g, mc, acc, ra, rw, rw_tab, thr_tab, flip_tab, nullptr, m_wave, n_wave);
+            word[i] = (kg_here ? both[1] : both[0]) ^ flips[i];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        panel::store_words<NB>(g, word, m_wave + opaque(lane), n_wave);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the loads beyond the last tile)
 }
@@ -270,9 +319,6 @@ int launch_weight_image(const GemmArgs &g, hipStream_t s) {
 }
 
 int launch(const GemmArgs &g, hipStream_t s) {
-    MfmaConst mc;
-    std::memset(&mc, 0, sizeof(mc));
-    mc.alpha = 1, mc.alpha_shift = 0, mc.cRW = 1, mc.needRW = 1;
     const int64_t cus = compute_units(), tiles_m = ceil_div(g.M, kBM);
     // 128 x 256 or 128 x 128 by the time of their rounds, with two workgroups and with one on a unit (whole forward step with a 10-neuron
     // second layer, us, 128 x 256 / 128 x 128: 10000 x 784 -> 4096 51 / 60, -> 2048 31.0 / 31.6, -> 1000 23.6 / 22.8, 3000 x 3072 -> 1000 34 / 28;
@@ -289,7 +335,7 @@ int launch(const GemmArgs &g, hipStream_t s) {
     x.a_bytes = (uint32_t)((g.M - 1) * g.A.ld + g.K), x.image_blocks = (uint32_t)blocks_of(g.N), x.halves = (uint32_t)ceil_div(g.K, 64);
     x.tiles_m = (uint32_t)tiles_m, x.tiles_n = (uint32_t)(total / tiles_m);
     return QNN_LAUNCH("gemm_codes", (is_wide ? gemm_codes_kernel<4> : gemm_codes_kernel<2>), dim3((unsigned)(total < 2 * cus ? total : 2 * cus)),
-                      dim3(kThreads), 0, s, g, mc, x);
+                      dim3(kThreads), 0, s, g, x);
 }
 
 }  // namespace codes

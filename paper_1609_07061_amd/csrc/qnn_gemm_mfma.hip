@@ -81,6 +81,8 @@ bool fill_consts(const GemmArgs &g, int64_t aA, int64_t bA, int64_t xA0, int64_t
     mc.cRW = (uint32_t)(bA * aW);
     mc.c0 = (uint32_t)(g.K * bA * bW - aA * aW * npad * xA0 * xW0);
     mc.needRW = mc.cRW != 0;
+    auto unit = [](const Planes &pl) { return pl.count == 1 && (pl.coef[0] == 1 || pl.coef[0] == -1); };
+    mc.units = !g.A.rows_are_bytes && unit(g.pa) && unit(g.pw);
     // the row sums are over the true K: RA = sum_p d_p pop_p - K * off; fold the constant part into c0
     mc.c0 += (uint32_t)(aA * bW * (g.K * xA0)) + (uint32_t)(bA * aW * (g.K * xW0));
     mc.alpha_shift = -1;

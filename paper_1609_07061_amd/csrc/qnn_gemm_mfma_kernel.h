@@ -57,6 +57,7 @@ struct MfmaConst {
     uint32_t alpha, cRA, cRW, c0;  // C = alpha * S + cRA * RA[m] + cRW * RW[n] + c0   (mod 2^32)
     int needRW;  // cRW != 0: the weight-row sums are needed (the activation-row sums are always formed)
     int alpha_shift;  // alpha == 1 << alpha_shift, or -1 if alpha is not a positive power of two
+    int units;        // single planes with coefficients +-1: C and its terms are below 2^20 in magnitude
     uint32_t msteps;  // macro steps of 2 * WPL words, rounded up to an even count
 };
 

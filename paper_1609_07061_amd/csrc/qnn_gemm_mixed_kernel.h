@@ -273,7 +273,7 @@ __device__ __forceinline__ void product(const GemmArgs &g, const MixedArgs &x, u
 #pragma unroll
             for (int j = 0; j < MB; ++j) asm volatile("" : "+v"(acc[i][j]));
         int32_t rw[NB] = {};
-        panel::wave_finish<false, NB, 0>(g, mc, acc, ra, rw, nullptr, nullptr, nullptr, stage_w, m_wave, n_wave);
+        panel::wave_finish<false, NB, 0, kBytes ? panel::kRowTerms : panel::kNoTerms>(g, mc, acc, ra, rw, nullptr, nullptr, nullptr, stage_w, m_wave, n_wave);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the loads beyond the last tile)
 }

@@ -419,7 +419,7 @@ __device__ __forceinline__ void panel_product(const GemmArgs &g, const MfmaConst
         if constexpr (kRows == kMapRows)
             map_finish<WBN>(g, x.sc, acc, ra, class_tab, flip_tab, (uint32_t)m_wave, (uint32_t)n_wave);
         else
-            wave_finish<kSign, WBN, kLoads>(g, mc, acc, ra, rw, rw_tab, thr_tab, flip_tab, stage_w, m_wave, n_wave);
+            wave_finish<kSign, WBN, kLoads, kBothTerms>(g, mc, acc, ra, rw, rw_tab, thr_tab, flip_tab, stage_w, m_wave, n_wave);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the loads beyond the last tile)
 }

@@ -318,7 +318,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_panel_wide_kernel(const Gemm
     };
 
     auto finish = [&](const int64_t m_wave, const int64_t n_wave) __attribute__((always_inline)) {
-        panel::wave_finish<false, WB, kLoadsPerGroup>(g, mc, acc, ra, rw, rw_table[wave], nullptr, nullptr, stage[wave], m_wave, n_wave);
+        panel::wave_finish<false, WB, kLoadsPerGroup, panel::kBothTerms>(g, mc, acc, ra, rw, rw_table[wave], nullptr, nullptr, stage[wave], m_wave, n_wave);
     };
 
     Step buf0, buf1;
