@@ -16,7 +16,7 @@ NATIVE_STAMP = os.path.join(OBJ, "native.txt")  # what _native.so was built for
 SOURCES = ["qnn_api.hip", "qnn_probe.hip", "qnn_pack.hip", "qnn_quant.hip", "qnn_dedup.hip", "qnn_conv_first.hip", "qnn_gemm_valu.hip", "qnn_gemm_slice.hip", "qnn_gemm_tile.hip", "qnn_gemm_mfma.hip", "qnn_gemm_mfma_k0.hip",
            "qnn_gemm_mfma_k1.hip", "qnn_gemm_mfma_k2.hip", "qnn_gemm_mfma_k3.hip", "qnn_gemm_mfma_k4.hip", "qnn_gemm_stage_k0.hip",
            "qnn_gemm_stage_k1.hip", "qnn_gemm_stage_k2.hip", "qnn_gemm_panel_k0.hip", "qnn_gemm_bytes_panel_k0.hip",
-           "qnn_gemm_mixed.hip", "qnn_gemm_codes.hip"]
+           "qnn_gemm_mixed.hip", "qnn_gemm_codes.hip", "qnn_gemm_image.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc", "-ffp-contract=off",

@@ -110,7 +110,10 @@ int resolve_engine(const GemmArgs &g, int engine, int &chosen) {
 // goes there, and that is the engine on record.
 int launch_on(const GemmArgs &g, int chosen, bool free_choice, hipStream_t s) {
     int rc;
-    if (free_choice && slice_preferred(g, chosen)) {
+    if (free_choice && image::conv_preferred(g)) {
+        rc = image::launch_conv(g, s);
+        chosen = QNN_ENGINE_MFMA_FP4;
+    } else if (free_choice && slice_preferred(g, chosen)) {
         rc = launch_gemm_slice(g, s);
         chosen = QNN_ENGINE_MFMA_FP4;
     } else if (chosen == QNN_ENGINE_VALU) {
@@ -762,8 +765,11 @@ int run_net(const NetPlan &plan, hipStream_t s) {
                 // src = plane "value is -1" of the input map, w = filters, dst = output bits, dst2 = class thresholds;
                 // rows = B, a / b / c = H / W / C, n = filters; complemented flips and the output pitch in g.epi; mask (may be
                 // null) / invert = the pooling done along
-                rc = launch_conv_map(static_cast<const uint32_t *>(st.src), st.rows, st.a, st.b, st.c, st.w, st.n, st.g.epi.flip,
-                                     static_cast<uint32_t *>(st.dst), st.g.epi.ldo, static_cast<const int32_t *>(st.dst2), st.mask, st.invert, s);
+                // (no class thresholds: on the kernel that holds the pixels in LDS)
+                rc = st.dst2 ? launch_conv_map(static_cast<const uint32_t *>(st.src), st.rows, st.a, st.b, st.c, st.w, st.n, st.g.epi.flip,
+                                               static_cast<uint32_t *>(st.dst), st.g.epi.ldo, static_cast<const int32_t *>(st.dst2), st.mask, st.invert, s)
+                             : image::launch_map(static_cast<const uint32_t *>(st.src), st.rows, st.a, st.b, st.c, st.w, st.n, st.g.epi.T, st.g.epi.flip,
+                                                 static_cast<uint32_t *>(st.dst), st.ones.out, st.g.epi.ldo, st.mask, st.invert, s);
                 if (rc == QNN_OK) {
                     g_last_engine = QNN_ENGINE_MFMA_FP4;
                     if (g_engine_count < 2 * QNN_MAX_LAYERS) g_engines[g_engine_count++] = QNN_ENGINE_MFMA_FP4;
@@ -832,16 +838,26 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
         plan.flags.inv[l] = ws + L.flag_inv[l];
     }
     // whether a convolution (not the first) reads its map as the plane "value is -1" (tiled FP4 kernel) or as the 2-bit code
-    auto on_plane = [&](int64_t hh, int64_t ww, int64_t cc, int64_t co) {
+    auto on_plane = [&](int64_t hh, int64_t ww, int64_t cc, int l) {
+        const int64_t co = cout[l];
         return (engine == QNN_ENGINE_AUTO || engine == QNN_ENGINE_MFMA_FP4) && conv_map_supports(B, hh, ww, cc, co) &&
-               (engine != QNN_ENGINE_AUTO || conv_map_preferred(B, hh, ww, co));
+               (engine != QNN_ENGINE_AUTO || conv_map_preferred(B, hh, ww, cc, co, pool[l] != 0));
     };
-    // thresholds per border class of the convolutions on planes
+    // ... and whether that kernel finds room for its pixels in LDS, with the pooling that follows or without
+    auto in_lds = [&](int64_t hh, int64_t ww, int64_t cc, int64_t co, bool pooled) { return image::map_supports(B, hh, ww, cc, co, pooled); };
+    // whether a convolution's output is pooled along (without that kernel not where the next one reads a 2-bit code, whose other plane the pooling
+    // kernel writes)
+    auto pools_along = [&](int l, int64_t hh, int64_t ww, int64_t cc) {
+        if (!pool[l] || !on_plane(hh, ww, cc, l)) return false;
+        if (in_lds(hh, ww, cc, cout[l], true)) return true;
+        return conv_map_pools(hh, ww) && (l + 1 >= n_conv || on_plane(hh / 2, ww / 2, cout[l], l + 1));
+    };
+    // thresholds per border class of the convolutions on planes whose pixels do not fit there
     plan.prep.count = 0;
     {
         int64_t hh = H, ww = Wd, cc = C0;
         for (int l = 0; l < n_conv; ++l) {
-            if (l > 0 && on_plane(hh, ww, cc, cout[l])) {
+            if (l > 0 && on_plane(hh, ww, cc, l) && !in_lds(hh, ww, cc, cout[l], pools_along(l, hh, ww, cc))) {
                 const int j = plan.prep.count++;
                 plan.prep.W[j] = W[l], plan.prep.T[j] = T[l];
                 plan.prep.out[j] = reinterpret_cast<int32_t *>(ws + L.class_thr[l]);
@@ -887,14 +903,16 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
         NetStep &st = push();
         st.kind = NetStep::kGemm;
         const Epilogue e{nullptr, 0, T[l], fl, conv_dst, Cwo};
-        const bool on_map = l > 0 && on_plane(h, w, cin, co);
+        const bool on_map = l > 0 && on_plane(h, w, cin, l);
         // the next convolution reads this layer's output: as a plane it takes "value is -1" alone,
         // otherwise the 2-bit code, whose plane "inside the image" is then written too
-        const bool ones_needed = inverted && !on_plane(ho, wo, co, cout[l + 1]);
-        const bool pooled_along = on_map && pool[l] && !ones_needed && conv_map_pools(h, w);
+        const bool ones_needed = inverted && !on_plane(ho, wo, co, l + 1);
+        const bool pooled_along = l > 0 && pools_along(l, h, w, cin);
+        const bool map_in_lds = on_map && in_lds(h, w, cin, co, pooled_along), ones_along = map_in_lds && ones_needed && pooled_along == (pool[l] != 0);
         if (on_map) {
             st.kind = NetStep::kConvMap;
-            st.src = a_planes + a_stride, st.w = W[l], st.dst = pooled_along ? kept_bits : conv_dst, st.dst2 = ws + L.class_thr[l];
+            st.src = a_planes + a_stride, st.w = W[l], st.dst = pooled_along ? kept_bits : conv_dst, st.dst2 = map_in_lds ? nullptr : ws + L.class_thr[l];
+            if (ones_along) st.ones.out = kept;
             st.rows = B, st.a = (int)h, st.b = (int)w, st.c = (int)cin, st.n = co;
             st.g.epi = e;
             st.g.epi.flip = inverted ? (flip ? flip[l] : nullptr) : reinterpret_cast<const uint8_t *>(ws + L.flag_inv[l]);
@@ -922,7 +940,7 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
             pl.dst2 = ones_needed ? kept : nullptr;  // the ones plane of the pooled output, written alongside
             pl.n = co;
         }
-        if (ones_needed && !pool[l] && !(l == 0 && first_direct)) {
+        if (ones_needed && !pool[l] && !ones_along && !(l == 0 && first_direct)) {
             // (the pooling before this convolution, if any, fills it: this buffer was last read by the convolution before that)
             NetStep *on = before >= 0 && plan.step[before].kind == NetStep::kPool ? &plan.step[before] : nullptr;
             if (!on) {

@@ -85,7 +85,6 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &g, const MfmaConst
     // The edge of C goes through LDS too, except in the widest tile, whose registers are full: there it made the whole kernel 0.5 %
     // slower (8192^3, which has no edge: 180.7 -> 181.6 us)
     constexpr bool kScatterEdge = WBN * WB == 16;
-    const int64_t Nw = (g.N + 31) / 32;
     static_assert(!kSign || kTerms == kBothTerms, "thresholds: both row sums");
 
     // lane coordinates re-derived behind an opaque copy: index arithmetic computed before the tile loop and kept

@@ -367,9 +367,18 @@ bool conv_map_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N) {
     return 9 * Cw * 32 < 8388608 && ceil_div(M, kTile) * ceil_div(N, kTile) <= 0x7FFFFFFFLL;
 }
 
-// From 48 tiles on (of 256 compute units): the App. A ConvNet of width 128 on 4, 16, 64, 256 images of 32 x 32 takes 57, 74, 83, 140 us with the line at 48
-// tiles, 77, 78, 84, 143 with every convolution on its map's plane, 58, 86, 137, 209 with none (other widths and sizes alike).
-bool conv_map_preferred(int64_t B, int64_t H, int64_t Wd, int64_t N) { return ceil_div(B * H * Wd, kTile) * ceil_div(N, kTile) >= 48; }
+// Tiles of 128 x 128 from which on a map is read as its plane, against its 2-bit code on the sliced kernel (App. A ConvNets, width / images of
+// 16 x 16 to 32 x 32, us, every convolution on the code -> all of them on planes):
+//   Pixels that fit LDS (qnn_gemm_image.hip): from 16 tiles on (128 / 16 of 32 x 32 66 -> 52, 128 / 8 of 24 x 24 56 -> 51, and 53 from four on); and where
+//   channels and filters are whole words, of up to 128 channels always (32 / 1 51 -> 36, 64 / 1 51 -> 40), up to 256 where the pooling goes
+//   along (96 / 1 51 -> 45); beyond that the sliced kernel's sixteen waves a tile are the faster ones (200 / 1 of 16 x 16 55 -> 73, 256 / 1 54 -> 74).
+//   Others: from 48 on (128 / 4, 16, 64, 256 of 32 x 32 57, 74, 83, 140 with the line there, 77, 78, 84, 143 with planes alone, 58, 86, 137, 209 with
+//   none, all before the kernel that holds the pixels in LDS).
+bool conv_map_preferred(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N, bool pooled) {
+    const int64_t tiles = ceil_div(B * H * Wd, kTile) * ceil_div(N, kTile), Cw = words_for(C);
+    if (!image::map_supports(B, H, Wd, C, N, pooled)) return tiles >= 48;
+    return tiles >= 16 || (C % 32 == 0 && N % 32 == 0 && Cw <= (pooled ? 8 : 4));
+}
 
 int64_t conv_class_ld(int64_t N) { return ceil_div(N, kTile) * kTile; }
 

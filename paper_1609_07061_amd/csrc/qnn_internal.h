@@ -204,11 +204,22 @@ int launch_threshold_sign(const int32_t *C, int64_t ldc, int64_t M, int64_t N, c
 // launch_conv_first or launch_conv_class_thr (for all convolutions of a network at once).  The 2 x 2 max-pooling that follows is done along if
 // conv_map_pools (pool_and = packed flip flags of the filters, pool_invert = the map holds inverted bits; null: no pooling).
 bool conv_map_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N);
-bool conv_map_preferred(int64_t B, int64_t H, int64_t Wd, int64_t N);  // against the map's 2-bit code
+bool conv_map_preferred(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N, bool pooled);  // against the map's 2-bit code
 bool conv_map_pools(int64_t H, int64_t Wd);
 int64_t conv_class_ld(int64_t N);
 int launch_conv_map(const uint32_t *plane, int64_t B, int H, int Wd, int64_t C, const uint32_t *W, int64_t N, const uint8_t *flip_complement,
                     uint32_t *out, int64_t ldo, const int32_t *class_thr, const uint32_t *pool_and, bool pool_invert, hipStream_t s);
+// The same by the kernel that holds a tile's pixels in LDS as operands (qnn_gemm_image.hip), which needs no class thresholds and pools maps of
+// any size along; map_supports: whether a tile's pixels fit there.  ones (may be null): also writes the "inside the image" plane of the output.
+namespace image {
+bool map_supports(int64_t B, int64_t H, int64_t W, int64_t C, int64_t N, bool pooled);
+int launch_map(const uint32_t *plane, int64_t B, int H, int W, int64_t C, const uint32_t *filters, int64_t N, const int32_t *T, const uint8_t *flip_complement,
+               uint32_t *out, uint32_t *ones, int64_t ldo, const uint32_t *pool_and, bool pool_invert, hipStream_t s);
+// ... and of an image of bit planes: whether the kernel takes the convolution, whether it is expected to be the fastest, the launch
+bool conv_supports(const GemmArgs &g);
+bool conv_preferred(const GemmArgs &g);
+int launch_conv(const GemmArgs &g, hipStream_t s);
+}  // namespace image
 struct ConvPrepJobs {
     int count;
     const uint32_t *W[2 * QNN_MAX_LAYERS];  // [N][9][Cw] filter bits
