@@ -36,8 +36,8 @@ struct LinearQ {
     __device__ __forceinline__ int32_t operator()(float x) const {
         // correctly rounded quotient, then the nearest integer with ties to even
         float r = rintf(inv != 0.0f ? __fmul_rn(x, inv) : __fdiv_rn(x, step));
-        if (r != r) r = 0.0f;                 // NaN quantizes like 0
-        return r <= (float)qmin ? qmin : (r >= (float)qmax ? qmax : (int32_t)r);
+        r = r == r ? r : 0.0f;  // NaN quantizes like 0
+        return (int32_t)__builtin_amdgcn_fmed3f(r, (float)qmin, (float)qmax);
     }
 };
 
@@ -69,6 +69,23 @@ struct LogQ {
         const int32_t c = e - emin + 1;
         const int32_t v = as_value ? (int32_t)(1u << (c - 1)) : c;
         return (b >> 31) ? -v : v;
+    }
+};
+
+// The same where no magnitude down to 2^emin is a denormal float and infinity does not stay below 2^emax (emin >= -125, emax <= 128), in a third of
+// the instructions, which bound the kernel (46 per element of 28 and more that the memory leaves time for): adding 2^23 less the smallest mantissa
+// above sqrt(2)'s carries into the exponent where log2 |x| rounds up, so that the rounded exponent is one addition and one shift away; 1 shifted by
+// it and back by one is the value, or 0 where it lies below.
+struct LogQNormal {
+    int32_t shift, most;  // (2^23 - 0x3504F4) - ((emin + 126) << 23); emax - emin + 1
+    int as_value;
+    __device__ __forceinline__ int32_t operator()(float x) const {
+        const uint32_t b = __float_as_uint(x);
+        int32_t c = (int32_t)((b & 0x7FFFFFFFu) + (uint32_t)shift) >> 23;  // e - emin + 1
+        c = c < 0 ? 0 : (c > most ? most : c);
+        c = x == x ? c : 0;
+        const int32_t v = as_value ? (int32_t)((1u << c) >> 1) : c, sign = (int32_t)b >> 31;
+        return (v ^ sign) - sign;
     }
 };
 
@@ -118,61 +135,59 @@ __global__ __launch_bounds__(kBlock) void quant_planes_kernel(const float *__res
     }
 }
 
-// Rows made of whole, 16-byte aligned groups of four floats: a wave takes 2048 consecutive elements of a row.  Lane l
-// loads four consecutive floats of each of eight 1 KiB pieces (whole lines per load), quantizes them and leaves the
+// Rows made of whole, 16-byte aligned groups of four floats: a wave takes 256 kPieces consecutive elements of a row.  Lane l
+// loads four consecutive floats of each of the 1 KiB pieces (whole lines per load), quantizes them and leaves the
 // four codes as one dword in a wave-private LDS area; then it reads back the 32 consecutive codes of "its" output
 // word and splits them into planes by bit-matrix transposition (about 3 instructions per element and eight planes,
 // where one ballot per plane and 64 elements costs four per element and plane).  LDS operations of a wave execute in
 // order, so only the compiler has to be kept from reordering the two passes.
-template <typename Q>
+template <int kPieces, typename Q>
 __global__ __launch_bounds__(kBlock) void quant_planes_vec_kernel(const float *__restrict__ x, const float *__restrict__ gate,
                                                                   int64_t rows, int64_t K, int64_t ldx, int64_t ldg, Q q,
                                                                   int nbits, uint32_t *__restrict__ planes, int64_t ld,
-                                                                  int64_t plane_stride, int64_t chunks_per_row,
-                                                                  int64_t total_chunks) {
-    constexpr int kChunk = 2048;
+                                                                  int64_t plane_stride, uint32_t chunks_per_row,
+                                                                  uint32_t total_chunks) {
+    constexpr int kChunk = 256 * kPieces;
     __shared__ __attribute__((aligned(16))) uint32_t codes[kWavesPerBlock][kChunk / 4];
     const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-    const int64_t wave0 = (int64_t)blockIdx.x * kWavesPerBlock + wave;
-    const int64_t wave_stride = (int64_t)gridDim.x * kWavesPerBlock;
-    const int64_t Kw = (K + 31) / 32;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t wave_stride = gridDim.x * kWavesPerBlock;
+    const uint32_t Kw = (uint32_t)((K + 31) / 32), k_end = (uint32_t)K;
     typedef float f32x4 __attribute__((ext_vector_type(4)));
-    for (int64_t chunk = wave0; chunk < total_chunks; chunk += wave_stride) {
-        const int64_t r = chunk / chunks_per_row;
-        const int64_t k0 = (chunk - r * chunks_per_row) * kChunk;
-        f32x4 v[8], gt[8];
+    for (uint32_t chunk = blockIdx.x * kWavesPerBlock + wave; chunk < total_chunks; chunk += wave_stride) {
+        const uint32_t r = chunk / chunks_per_row;
+        const uint32_t k0 = (chunk - r * chunks_per_row) * kChunk;
+        const float *const row = x + r * ldx, *const gate_row = gate + r * ldg;
+        f32x4 v[kPieces], gt[kPieces];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int64_t k = k0 + c * 256 + 4 * lane;  // K is a multiple of 4: a group is all inside or outside
+        for (int c = 0; c < kPieces; ++c) {
+            const uint32_t k = k0 + c * 256 + 4 * lane;  // K is a multiple of 4: a group is all inside or outside
             v[c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f}, gt[c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            if (k < K) v[c] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(x + r * ldx + k));
-            if (gate && k < K) gt[c] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(gate + r * ldg + k));
+            if (k < k_end) v[c] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(row + k));
+            if (gate && k < k_end) gt[c] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(gate_row + k));
         }
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int64_t k = k0 + c * 256 + 4 * lane;
-            uint32_t four = 0;
+        for (int c = 0; c < kPieces; ++c) {
+            uint32_t cd[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                int32_t cd = q(v[c][i]);
-                if (!(fabsf(gt[c][i]) <= 1.0f)) cd = 0;
-                four |= ((uint32_t)cd & 0xFFu) << (8 * i);
-            }
-            codes[wave][c * 64 + lane] = (k < K) ? four : 0u;
+            for (int i = 0; i < 4; ++i) cd[i] = fabsf(gt[c][i]) <= 1.0f ? (uint32_t)q(v[c][i]) : 0u;
+            // the low bytes of the four (elements beyond the row are zeros, and quantize to 0 or are cleared below)
+            const uint32_t lo = __builtin_amdgcn_perm(cd[1], cd[0], 0x0C0C0400u), hi = __builtin_amdgcn_perm(cd[3], cd[2], 0x04000C0Cu);
+            codes[wave][c * 64 + lane] = k0 + c * 256 + 4 * lane < k_end ? lo | hi : 0u;
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const uint4 c0 = *reinterpret_cast<const uint4 *>(&codes[wave][8 * lane]);
-        const uint4 c1 = *reinterpret_cast<const uint4 *>(&codes[wave][8 * lane + 4]);
+        const int mine_at = 8 * kPieces < kWave ? lane & (8 * kPieces - 1) : lane;  // (fewer words than lanes: the others repeat them)
+        const uint4 c0 = *reinterpret_cast<const uint4 *>(&codes[wave][8 * mine_at]);
+        const uint4 c1 = *reinterpret_cast<const uint4 *>(&codes[wave][8 * mine_at + 4]);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         const uint32_t mine[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
         uint32_t word[8];
         split_32_codes(mine, nbits, word);
-        const int64_t w = k0 / 32 + lane;
-        if (w < Kw) {
+        const uint32_t w = k0 / 32 + lane;
+        if (lane < 8 * kPieces && w < Kw) {
             uint32_t *dst = planes + r * ld + w;
 #pragma unroll
             for (int p = 0; p < 8; ++p)
@@ -184,13 +199,18 @@ __global__ __launch_bounds__(kBlock) void quant_planes_vec_kernel(const float *_
 template <typename Q>
 int launch_quant(const char *what, const float *x, const float *gate, int64_t rows, int64_t K, int64_t ldx, int64_t ldg,
                  const Q &q, int nbits, uint32_t *planes, int64_t ld, int64_t plane_stride, hipStream_t s) {
-    const bool vec = K >= 1024 && K % 4 == 0 && ldx % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
+    const int64_t few = ceil_div(K, (int64_t)512), many = ceil_div(K, (int64_t)2048);
+    const bool vec = K >= 1024 && K < 0x7FFFF000 && rows * few < 0x7FFF0000 && K % 4 == 0 && ldx % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
                      (!gate || (ldg % 4 == 0 && reinterpret_cast<uintptr_t>(gate) % 16 == 0));
     if (vec) {
-        const int64_t cpr = ceil_div(K, (int64_t)2048);
-        const int64_t total = rows * cpr;
-        return QNN_LAUNCH(what, (quant_planes_vec_kernel<Q>), dim3(grid_for_chunks(total)), dim3(kBlock), 0, s, x, gate, rows, K, ldx,
-                          ldg, q, nbits, planes, ld, plane_stride, cpr, total);
+        // 512 elements a wave while that makes no more than about one round of waves (LinearQ to 4 planes, us, before / 2048 / 512: 20 x 2048 5.4 / 4.4 /
+        // 2.9, 2240 x 2048 8.0 / 6.9 / 6.5, 5000 x 2048 12.5 / 10.4 / 10.9; gated LogQ to 8: 20 x 4096 7.0 / 4.4 / 3.0, 2240 x 2048 14.4 / 10.4 / 8.7, 5000 x
+        // 4096 35.9 / 33.0 / 32.9, 10000 x 4096 66.0 / 63.0 / 66.2)
+        const bool small = rows * few <= 16384;
+        const int64_t cpr = small ? few : many, total = rows * cpr;
+        auto kernel = small ? quant_planes_vec_kernel<2, Q> : quant_planes_vec_kernel<8, Q>;
+        return QNN_LAUNCH(what, kernel, dim3(grid_for_chunks(total)), dim3(kBlock), 0, s, x, gate, rows, K, ldx,
+                          ldg, q, nbits, planes, ld, plane_stride, (uint32_t)cpr, (uint32_t)total);
     }
     constexpr int kUnroll = 8;
     const int64_t cpr = ceil_div(K, (int64_t)kUnroll * kWave);
@@ -398,6 +418,10 @@ extern "C" int qnn_log_quant_planes(const float *x, const float *gate, int64_t r
         return fail(QNN_ERR_SHAPE, "log_quant_planes: %lld magnitudes do not fit %d-bit two's complement %s",
                     (long long)levels, nbits, as_value ? "values" : "codes");
     if (rows == 0) return QNN_OK;
+    if (emin >= -125 && emax <= 128)
+        return launch_quant("log_quant_planes", x, gate, rows, K, ldx, ld_gate,
+                            LogQNormal{(int32_t)((uint32_t)(0x800000 - 0x3504F4) - ((uint32_t)(emin + 126) << 23)), emax - emin + 1, as_value ? 1 : 0}, nbits, planes,
+                            ld_words, plane_stride_words, static_cast<hipStream_t>(stream));
     return launch_quant("log_quant_planes", x, gate, rows, K, ldx, ld_gate, LogQ{emin, emax, as_value ? 1 : 0}, nbits, planes,
                         ld_words, plane_stride_words, static_cast<hipStream_t>(stream));
 }
