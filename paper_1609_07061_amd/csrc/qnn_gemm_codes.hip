@@ -37,7 +37,7 @@ struct CodesArgs {
     uint32_t a_bytes;  // size of the codes
     uint32_t image_blocks;
     uint32_t halves;   // of groups, ceil(K / 64)
-    uint32_t tiles_m, tiles_n;
+    Tiles tiles;
 };
 
 template <int NB>
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_codes_kernel(const GemmArgs 
     static_assert(sizeof(lds) <= 80 * 1024, "two workgroups on a compute unit");
     const uint32_t lane = threadIdx.x & 63u, r = lane & 31u, kg = lane >> 5;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave >> 1, wn = wave & 1u;
-    const uint32_t total = x.tiles_m * x.tiles_n, groups = (x.halves + 1u) / 2u, K = (uint32_t)g.K;
+    const uint32_t total = x.tiles.total, groups = (x.halves + 1u) / 2u, K = (uint32_t)g.K;
     const uint32_t lds_base = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t *)lds);
     uint32_t *const rw_tab = reinterpret_cast<uint32_t *>(lds + 2 * kGroup) + wave * 4u * kTable;
     int32_t *const thr_tab = reinterpret_cast<int32_t *>(rw_tab + kTable);
@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_codes_kernel(const GemmArgs 
     const uint8_t *p_w;
     auto p_locate = [&](const uint32_t vb) __attribute__((always_inline)) {
         uint32_t tm, tn;
-        tile_of_block(vb, total, x.tiles_m, x.tiles_n, tm, tn);
+        tile_of_block(vb, x.tiles, tm, tn);
         const uint32_t last = (uint32_t)(g.M - 1), row = 8u * wave + (opaque(lane) >> 3);
 #pragma unroll
         for (uint32_t i = 0; i < kLoadsA; ++i) {
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_codes_kernel(const GemmArgs 
     // thresholds, flip flags and weight rows' terms of a tile on their way to the wave's tables
     auto load_columns = [&](const uint32_t vb) __attribute__((always_inline)) {
         uint32_t tm, tn;
-        tile_of_block(vb, total, x.tiles_m, x.tiles_n, tm, tn);
+        tile_of_block(vb, x.tiles, tm, tn);
         const int64_t n0 = (int64_t)tn * (64 * NB) + wn * (32 * NB);
         panel::load_thresholds_to_lds<NB>(g, n0, thr_tab, flip_tab);
         const uint32_t rw_lds = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint32_t *)rw_tab);
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_codes_kernel(const GemmArgs 
     uint32_t vb = vb0;
     for (uint32_t done = 0; done < n_mine; ++done, vb += gridDim.x) {
         uint32_t tile_m, tile_n;
-        tile_of_block(vb, total, x.tiles_m, x.tiles_n, tile_m, tile_n);
+        tile_of_block(vb, x.tiles, tile_m, tile_n);
         const int64_t m_wave = (int64_t)tile_m * kBM + wm * (32 * kMB), n_wave = (int64_t)tile_n * (64 * NB) + wn * (32 * NB);
         // What has arrived (before a barrier): the sums start from -64 (T - term), so that a sum's sign is its bit.  |s| < 2^24, so a
         // difference clamped there decides the same, and 64 (s - difference) stays within 32 bits.
@@ -333,7 +333,7 @@ int launch(const GemmArgs &g, hipStream_t s) {
     if (total > 0x7FFFFFFF) return fail(QNN_ERR_SHAPE, "gemm: too many tiles");
     CodesArgs x;
     x.a_bytes = (uint32_t)((g.M - 1) * g.A.ld + g.K), x.image_blocks = (uint32_t)blocks_of(g.N), x.halves = (uint32_t)ceil_div(g.K, 64);
-    x.tiles_m = (uint32_t)tiles_m, x.tiles_n = (uint32_t)(total / tiles_m);
+    x.tiles = make_tiles(tiles_m, total / tiles_m);
     return QNN_LAUNCH("gemm_codes", (is_wide ? gemm_codes_kernel<4> : gemm_codes_kernel<2>), dim3((unsigned)(total < 2 * cus ? total : 2 * cus)),
                       dim3(kThreads), 0, s, g, x);
 }

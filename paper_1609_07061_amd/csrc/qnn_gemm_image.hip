@@ -32,7 +32,6 @@ namespace {
 
 using mfma::v16f;
 using mfma::v4i;
-using slice::quotient;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));  // a 16-byte load at any word
 
@@ -488,8 +487,6 @@ int64_t tile_pixels(int64_t H, int64_t W, bool pooled, int64_t tile) {
 
 constexpr int64_t kMostLds = 80 * 1024;  // two workgroups on a compute unit
 
-uint32_t inverse(int64_t v) { return v > 1 ? (uint32_t)(4294967296LL / v) : 0xFFFFFFFFu; }
-
 // Everything but the operands; false if the kernels cannot take the shape.
 bool plan(int64_t B, int64_t H, int64_t W, int64_t C, int64_t N, bool pooled, int PB, int64_t &M, ImageArgs &x, int64_t &lds_bytes) {
     std::memset(&x, 0, sizeof(x));
@@ -503,9 +500,9 @@ bool plan(int64_t B, int64_t H, int64_t W, int64_t C, int64_t N, bool pooled, in
     if (pixels * pitch < 4 * 4096) lds_bytes += 4 * 4096 - pixels * pitch;  // (the blocks of int32 sums)
     if (lds_bytes > kMostLds || ceil_div(M, tile) * ceil_div(N, 128) > 0x7FFFFFFFLL) return false;
     x.H = (uint32_t)H, x.W = (uint32_t)W, x.Cw = (uint32_t)Cw, x.C = (uint32_t)C, x.images = (uint32_t)B;
-    x.inv_w1 = inverse(W + 1), x.inv_h1 = inverse(H + 1), x.inv_pieces = inverse(ceil_div(Cw, 4)), x.inv_words = inverse(Cw);
-    x.inv_tiles_n = inverse(ceil_div(N, 128)), x.plane_bytes = (uint32_t)(B * H * W * Cw * 4);
-    x.row = (uint32_t)row, x.all = (uint32_t)all, x.inv_row = inverse(row), x.inv_all = inverse(all);
+    x.inv_w1 = inverse_of(W + 1), x.inv_h1 = inverse_of(H + 1), x.inv_pieces = inverse_of(ceil_div(Cw, 4)), x.inv_words = inverse_of(Cw);
+    x.inv_tiles_n = inverse_of(ceil_div(N, 128)), x.plane_bytes = (uint32_t)(B * H * W * Cw * 4);
+    x.row = (uint32_t)row, x.all = (uint32_t)all, x.inv_row = inverse_of(row), x.inv_all = inverse_of(all);
     x.pitch = (uint32_t)pitch, x.tile_bytes = (uint32_t)(pixels * pitch < 4 * 4096 ? 4 * 4096 : pixels * pitch);
     x.tiles_m = (uint32_t)ceil_div(M, tile), x.tiles_n = (uint32_t)ceil_div(N, 128), x.w_bytes = (uint32_t)(N * 9 * Cw * 4);
     return true;

@@ -274,7 +274,7 @@ int launch_gemm_mfma(const GemmArgs &g, hipStream_t s, bool fp4) {
             }
             const int64_t pm = ceil_div(g.M, panel::rows_of(pt.shape)), pn = ceil_div(g.N, panel::columns_of(pt.shape)), per = pt.per * cus;
             if (pm * pn > 0x7FFFFFFFLL) return fail(QNN_ERR_SHAPE, "gemm: too many tiles");
-            pa.tiles_m = (uint32_t)pm, pa.tiles_n = (uint32_t)pn;
+            pa.tiles = make_tiles(pm, pn);
             pa.a_bytes = (uint32_t)(((g.M - 1) * g.A.ld + g.Kw) * 4), pa.w_bytes = (uint32_t)(((g.N - 1) * g.ldw + g.Kw) * 4);
             const unsigned pgrid = (unsigned)(pm * pn < per ? pm * pn : per);
             return QNN_LAUNCH("gemm_panel", panel::find_kernel(g.epi.T != nullptr, pt.shape, whole), dim3(pgrid), dim3(panel::kThreads), 0, s, g, pc, pa);

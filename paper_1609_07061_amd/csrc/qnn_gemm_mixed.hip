@@ -252,7 +252,7 @@ int launch_product(const uint8_t *a, const uint8_t *w, const uint32_t *inexact, 
     const int64_t cus = compute_units(), tiles_m = ceil_div(M, 128);
     const bool is_wide = Tiles(M, N, cus).wide;
     const int64_t total = tiles_m * ceil_div(N, is_wide ? 256 : 128);
-    x.tiles_m = (uint32_t)tiles_m, x.tiles_n = (uint32_t)(total / tiles_m);
+    x.tiles = make_tiles(tiles_m, total / tiles_m);
     return QNN_LAUNCH("gemm_mixed", (is_wide ? gemm_mixed_kernel<4, 2, 4, 2> : gemm_mixed_kernel<4, 2, 2, 2>), dim3((unsigned)(total < 2 * cus ? total : 2 * cus)),
                       dim3(256), 0, s, g, x);
 }

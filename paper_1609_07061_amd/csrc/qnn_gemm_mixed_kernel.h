@@ -49,7 +49,7 @@ struct MixedArgs {
     const uint32_t *inexact;          // [kFlags]: int8 image if any is set
     uint32_t rows_a, rows_w;          // rows of an image's group
     uint32_t groups, halves;          // of 256 elements, of 128 (int8)
-    uint32_t tiles_m, tiles_n;
+    Tiles tiles;
     int32_t alpha;                    // C = alpha S
     int alpha_shift;                  // alpha = 2^alpha_shift, or -1
 };
@@ -62,7 +62,7 @@ __device__ __forceinline__ void product(const GemmArgs &g, const MixedArgs &x, u
     constexpr uint32_t kGroup = kLow + kHigh + kBits;
     const uint32_t lane = threadIdx.x & 63u, r = lane & 31u, kg = lane >> 5;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave / WN, wn = wave % WN;
-    const uint32_t total = x.tiles_m * x.tiles_n, groups = kBytes ? x.halves : x.groups;
+    const uint32_t total = x.tiles.total, groups = kBytes ? x.halves : x.groups;
     // (where the loads ahead of the loop may enter a second tile, the code in front of the loop grows and the int8 loop, unchanged, runs
     // 5 % slower: 8111 x 1008 x 638, second product, 40.8 against 42.9 us)
     if constexpr (kBytes) __builtin_assume(groups >= 2u);
@@ -84,7 +84,7 @@ __device__ __forceinline__ void product(const GemmArgs &g, const MixedArgs &x, u
     constexpr uint32_t kHighPieces = kHigh / 1024u, kHighPerStep = kHighStep ? kHighStep / 1024u : 1u, kBitPieces = kBits / 1024u, kBitPerGroup = BN * 16 / 1024u;
     auto p_locate = [&](const uint32_t vb) __attribute__((always_inline)) {
         uint32_t tm, tn;
-        tile_of_block(vb, total, x.tiles_m, x.tiles_n, tm, tn);
+        tile_of_block(vb, x.tiles, tm, tn);
         p_low = x.a + (uint64_t)tm * (BM * 128u) + wave * 1024u;
         p_high = high_image + (uint64_t)tm * (BM * 16u);
         p_bits = x.w + (uint64_t)tn * (BN * 16u);
@@ -216,7 +216,7 @@ __device__ __forceinline__ void product(const GemmArgs &g, const MixedArgs &x, u
     uint32_t vb = vb0;
     for (uint32_t done = 0; done < n_mine; ++done, vb += gridDim.x) {
         uint32_t tile_m, tile_n;
-        tile_of_block(vb, total, x.tiles_m, x.tiles_n, tile_m, tile_n);
+        tile_of_block(vb, x.tiles, tile_m, tile_n);
         const int64_t m_wave = (int64_t)tile_m * BM + wm * (32 * MB), n_wave = (int64_t)tile_n * BN + wn * (32 * NB);
 #pragma unroll
         for (int j = 0; j < MB; ++j) ra[j] = 0;

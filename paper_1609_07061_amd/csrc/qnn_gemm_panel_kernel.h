@@ -141,7 +141,7 @@ __device__ __forceinline__ void map_finish(const GemmArgs &g, const slice::Slice
 
 enum Rows { kWholeRows = 0, kAnyRows = 1, kMapRows = 2 };
 struct PanelArgs {
-    uint32_t tiles_m, tiles_n;
+    Tiles tiles;
     uint32_t steps;             // of 256 elements
     uint32_t a_bytes, w_bytes;  // kAnyRows, kMapRows: sizes of the operands
     slice::SliceArgs sc;        // kMapRows: how the patches are found
@@ -164,11 +164,11 @@ __device__ __forceinline__ void panel_product(const GemmArgs &g, const MfmaConst
     static_assert(kRows != kMapRows || kSign, "maps are thresholded");
     constexpr int WN = 4 / WM, BM = 64 * WM, WTN = 32 * WBN, BN = WN * WTN;  // rows of the tile, columns of a wave / of the tile
     constexpr uint32_t kPanelBytes = BM * kRowBytes, kGroupBytes = kPanelBytes + BN * kRowBytes;
-    const uint32_t tiles_m = x.tiles_m, tiles_n = x.tiles_n, ngroups = (x.steps + 1u) / 2u;
+    const uint32_t ngroups = (x.steps + 1u) / 2u;
 
     const uint32_t lane = threadIdx.x & 63u, r = lane & 31u, kg = lane >> 5;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave / WN, wn = wave % WN;
-    const uint32_t total_tiles = tiles_m * tiles_n;
+    const uint32_t total_tiles = x.tiles.total;
     auto opaque = [](uint32_t x) __attribute__((always_inline)) {
         asm volatile("" : "+v"(x));
         return x;
@@ -197,7 +197,7 @@ __device__ __forceinline__ void panel_product(const GemmArgs &g, const MfmaConst
     uint32_t off[kLoads], in[kRows == kMapRows ? kLoadsA : 1];  // kMapRows: of the patch, and which of its taps lie inside (see patch_of)
     auto p_locate = [&](const uint32_t vb) __attribute__((always_inline)) {
         uint32_t tm, tn;
-        tile_of_block(vb, total_tiles, tiles_m, tiles_n, tm, tn);
+        tile_of_block(vb, x.tiles, tm, tn);
         const uint32_t ln = opaque(lane), row = 16u * wave + (ln >> 2), piece = ((ln & 3u) ^ (ln >> 4)) << 4;
 #pragma unroll
         for (int i = 0; i < kLoads; ++i) {
@@ -364,7 +364,7 @@ __device__ __forceinline__ void panel_product(const GemmArgs &g, const MfmaConst
     uint32_t vb = vb0;
     for (uint32_t done = 0; done < n_mine; ++done, vb += gridDim.x) {
         uint32_t tile_m, tile_n;
-        tile_of_block(vb, total_tiles, tiles_m, tiles_n, tile_m, tile_n);
+        tile_of_block(vb, x.tiles, tile_m, tile_n);
         const int64_t m_wave = (int64_t)tile_m * BM + wm * (32 * WB), n_wave = (int64_t)tile_n * BN + wn * WTN;
 #pragma unroll
         for (int j = 0; j < WB; ++j) ra[j] = 0;

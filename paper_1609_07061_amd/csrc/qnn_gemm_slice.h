@@ -9,6 +9,8 @@
 namespace qnn {
 namespace slice {
 
+using qnn::quotient;
+
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -141,13 +143,6 @@ __device__ __forceinline__ u32x4 load_piece(const uint8_t *p, const SliceArgs &s
 struct Patch {
     uint32_t off, in;
 };
-// a / d and the remainder for a < 2^31 (the product with floor(2^32 / d) falls short by less than one)
-__device__ __forceinline__ uint32_t quotient(const uint32_t a, const uint32_t d, const uint32_t inv, uint32_t &rem) {
-    uint32_t q = __umulhi(a, inv);
-    rem = a - q * d;
-    if (rem >= d) ++q, rem -= d;
-    return q;
-}
 __device__ __forceinline__ Patch patch_of(const GemmArgs &g, const SliceArgs &sc, const uint32_t m) {
     const uint32_t per = (uint32_t)(g.A.Ho * g.A.Wo);
     uint32_t rem, xo;

@@ -29,7 +29,7 @@ namespace {
 // 220 registers; held to three they spill: convolutions of 2-bit maps with few tiles are 3 to 8 % slower).
 constexpr int waves_per_simd(int ka, int kw, int blocks) { return blocks == 2 && (ka == kPair || kw == kPair) ? 2 : 4; }
 template <int kA, int kW, int kRows, int BMb, int BNb, int kMaxWaves>
-__global__ __launch_bounds__(64 * kMaxWaves, waves_per_simd(kA, kW, BMb)) void gemm_slice_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
+__global__ __launch_bounds__(64 * kMaxWaves, waves_per_simd(kA, kW, BMb)) void gemm_slice_kernel(const GemmArgs g, const SliceArgs sc, const Tiles tiles) {
     constexpr bool kPixels = kRows != kMatrix;
     constexpr int BM = 32 * BMb, BN = 32 * BNb, kPitch = BN + 4;
     constexpr int NA = kA == kPair ? 2 : 1, NW = kW == kPair ? 2 : 1;  // planes of a digit
@@ -41,7 +41,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, waves_per_simd(kA, kW, BMb)) void g
     const uint32_t t = threadIdx.x, lane = t & 63u, r = lane & 31u, kg = lane >> 5;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6), waves = blockDim.x >> 6;
     uint32_t tm, tn;
-    tile_of_block(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
+    tile_of_block(blockIdx.x, tiles, tm, tn);
     const uint32_t m0 = tm * BM, n0 = tn * BN;
 
     // rows of this lane (rows beyond the last repeat it and are not stored)
@@ -62,6 +62,15 @@ __global__ __launch_bounds__(64 * kMaxWaves, waves_per_simd(kA, kW, BMb)) void g
         uint32_t n = n0 + 32 * b + r;
         n = n < (uint32_t)g.N ? n : (uint32_t)g.N - 1u;
         w_off[b] = n * (uint32_t)(g.ldw * 4);
+    }
+
+    // thresholds and flip flags of the epilogue, asked for before the operands
+    int32_t threshold = 0;
+    uint32_t flip_flag = 0u;
+    if (g.epi.T) {
+        const uint32_t n = n0 + lane % BN, at = n < (uint32_t)g.N ? n : (uint32_t)g.N - 1u;
+        threshold = g.epi.T[at];
+        if (g.epi.flip) flip_flag = g.epi.flip[at];
     }
 
     struct Chunk {
@@ -159,25 +168,21 @@ __global__ __launch_bounds__(64 * kMaxWaves, waves_per_simd(kA, kW, BMb)) void g
     const uint32_t pairs = (uint32_t)(sc.a.count * sc.w.count);
     // waves that have an item (workgroups of more than four waves are made no larger)
     const uint32_t parts = kMaxWaves > 4 || pairs * sc.chunks > waves ? waves : pairs * sc.chunks;
-    uint32_t pair = 0, c = wave;
+    uint32_t pair = 0, c = wave, ia = 0, iw = 0;  // pair ia * (digits of the right operand) + iw
     auto settle = [&]() __attribute__((always_inline)) {
-        while (c >= sc.chunks && pair < pairs) c -= sc.chunks, ++pair;
+        while (c >= sc.chunks && pair < pairs) {
+            c -= sc.chunks, ++pair;
+            if (++iw == (uint32_t)sc.w.count) iw = 0, ++ia;
+        }
     };
     settle();
     Chunk cur, nxt;
-    uint32_t ia = 0, iw = 0;
-    if (pair < pairs) {
-        ia = pair / (uint32_t)sc.w.count, iw = pair - ia * (uint32_t)sc.w.count;
-        load(cur, sc.a.d[ia], sc.w.d[iw], c);
-    }
+    if (pair < pairs) load(cur, sc.a.d[ia], sc.w.d[iw], c);
     while (pair < pairs) {
         const uint32_t c_now = c, ia_now = ia, iw_now = iw;
         c += waves;
         settle();
-        if (pair < pairs) {
-            ia = pair / (uint32_t)sc.w.count, iw = pair - ia * (uint32_t)sc.w.count;
-            load(nxt, sc.a.d[ia], sc.w.d[iw], c);
-        }
+        if (pair < pairs) load(nxt, sc.a.d[ia], sc.w.d[iw], c);
         const bool clear = !kPixels && 8u * c_now + 8u > sc.row_words;
         multiply(cur, sc.a.d[ia_now], sc.w.d[iw_now], clear);
         cur = nxt;
@@ -257,8 +262,8 @@ __global__ __launch_bounds__(64 * kMaxWaves, waves_per_simd(kA, kW, BMb)) void g
         const uint32_t col = lane % BN;
         const int64_t n = (int64_t)n0 + col;
         const bool live = n < g.N;
-        const int32_t T = live ? g.epi.T[n] : 0;
-        const bool flip = live && g.epi.flip && g.epi.flip[n] != 0;
+        const int32_t T = threshold;
+        const bool flip = live && flip_flag != 0u;
         for (uint32_t row0 = wave * kRowsPerWave; row0 < rows; row0 += waves * kRowsPerWave) {
             const uint32_t row = row0 + lane / BN;  // (below BM: BM is a multiple of kRowsPerWave)
             float s = part[0][row][col];
@@ -352,9 +357,8 @@ bool slice_args(const GemmArgs &g, bool bits, SliceArgs &sc, int &kind_a, int &k
     sc.magic_ppt = ppt > 1 ? magic(ppt) : 0u, sc.magic_kw = pix && g.A.KW > 1 ? magic(g.A.KW) : 0u;
     sc.chunks = (uint32_t)ceil_div(pieces, 2);
     if (pix) {
-        auto inverse = [](int64_t v) { return v > 1 ? (uint32_t)(4294967296LL / v) : 0xFFFFFFFFu; };
         if ((int64_t)g.A.Ho * g.A.Wo > 0x7FFFFFFFLL) return false;
-        sc.inv_hw = inverse((int64_t)g.A.Ho * g.A.Wo), sc.inv_w = inverse(g.A.Wo);
+        sc.inv_hw = inverse_of((int64_t)g.A.Ho * g.A.Wo), sc.inv_w = inverse_of(g.A.Wo);
     }
     // |S| in units of the common factors stays below 2^23: exact float sums, and with |alpha_sum| below 2^23 a 24-bit product in the
     // tiled kernel's epilogue.  (The same conditions whether or not +-1 planes enter as 0 / 1: what one kernel takes the other takes.)
@@ -394,7 +398,7 @@ bool slice_args(const GemmArgs &g, bool bits, SliceArgs &sc, int &kind_a, int &k
 
 namespace {
 
-typedef void (*SliceFn)(const GemmArgs, const SliceArgs, uint32_t, uint32_t);
+typedef void (*SliceFn)(const GemmArgs, const SliceArgs, const Tiles);
 template <int kRows, int BMb, int BNb, int kMaxWaves>
 SliceFn slice_kernel(int ka, int kw) {
     if (ka == kPm1) return kw == kPm1 ? gemm_slice_kernel<kPm1, kPm1, kRows, BMb, BNb, kMaxWaves> : gemm_slice_kernel<kPm1, kPair, kRows, BMb, BNb, kMaxWaves>;
@@ -519,7 +523,7 @@ int launch_gemm_slice(const GemmArgs &g, hipStream_t s) {
     const bool four = large || four_waves(items, tiles);
     const int waves = four ? 4 : (items < 16 ? (int)items : 16);
     const SliceFn fn = !pix ? slice_kernel<kMatrix>(ka, kw, large, four) : (g.A.Cw < 4 ? slice_kernel<kNarrowPatches>(ka, kw, large, four) : slice_kernel<kPatches>(ka, kw, large, four));
-    return QNN_LAUNCH("gemm_slice", fn, dim3((unsigned)tiles), dim3(64u * waves), 0, s, g, sc, (uint32_t)tiles_m, (uint32_t)tiles_n);
+    return QNN_LAUNCH("gemm_slice", fn, dim3((unsigned)tiles), dim3(64u * waves), 0, s, g, sc, make_tiles(tiles_m, tiles_n));
 }
 
 }  // namespace qnn

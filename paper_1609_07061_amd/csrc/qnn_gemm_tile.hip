@@ -41,7 +41,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 }
 
 template <int kA, int kW, int kRows>
-__global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) void gemm_tile_kernel(const GemmArgs g, const SliceArgs sc, uint32_t tiles_m, uint32_t tiles_n) {
+__global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) void gemm_tile_kernel(const GemmArgs g, const SliceArgs sc, const Tiles tiles) {
     constexpr bool kPixels = kRows != kMatrix;
     constexpr int NA = kA == kPair ? 2 : 1, NW = kW == kPair ? 2 : 1;  // planes of a digit
     // 16-byte pieces of a row per group (two of them make a chunk of 256 elements)
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) v
     const uint32_t t = threadIdx.x, lane = t & 63u, r = lane & 31u, kg = lane >> 5;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave >> 1, wn = wave & 1u;
     uint32_t tm, tn;
-    tile_of_block(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
+    tile_of_block(blockIdx.x, tiles, tm, tn);
     const uint32_t m0 = tm * kTile, n0 = tn * kTile;
 
     // ------------------------------------------------------------------------------------------------ loads
@@ -337,7 +337,7 @@ __global__ __launch_bounds__(kTileThreads, kA == kPair && kW == kPair ? 2 : 3) v
     }
 }
 
-typedef void (*TileFn)(const GemmArgs, const SliceArgs, uint32_t, uint32_t);
+typedef void (*TileFn)(const GemmArgs, const SliceArgs, const Tiles);
 template <int kRows>
 TileFn tile_kernel(int ka, int kw) {
     if (ka == kOne) return kw == kOne ? gemm_tile_kernel<kOne, kOne, kRows> : gemm_tile_kernel<kOne, kPair, kRows>;
@@ -353,7 +353,7 @@ int launch_gemm_tile(const GemmArgs &g, hipStream_t s) {
     const int64_t tiles_m = ceil_div(g.M, kTile), tiles_n = ceil_div(g.N, kTile);
     if (tiles_m * tiles_n > 0x7FFFFFFFLL) return fail(QNN_ERR_SHAPE, "gemm: too many tiles");
     const TileFn fn = !g.A.rows_are_pixels ? tile_kernel<kMatrix>(ka, kw) : (g.A.Cw < 4 ? tile_kernel<kNarrowPatches>(ka, kw) : tile_kernel<kPatches>(ka, kw));
-    return QNN_LAUNCH("gemm_tile", fn, dim3((unsigned)(tiles_m * tiles_n)), dim3(kTileThreads), 0, s, g, sc, (uint32_t)tiles_m, (uint32_t)tiles_n);
+    return QNN_LAUNCH("gemm_tile", fn, dim3((unsigned)(tiles_m * tiles_n)), dim3(kTileThreads), 0, s, g, sc, make_tiles(tiles_m, tiles_n));
 }
 
 // ---------------------------------------------------------------------------------------------------- convolution of a +-1 map
@@ -410,7 +410,7 @@ int launch_conv_map(const uint32_t *plane, int64_t B, int H, int Wd, int64_t C, 
     panel_shape(g.M, N, 8 * (int64_t)x.steps, which, per);
     const panel::Shape shape = (panel::Shape)which;
     const int64_t tiles_m = ceil_div(g.M, panel::rows_of(shape)), tiles_n = ceil_div(N, panel::columns_of(shape)), total = tiles_m * tiles_n, cus = compute_units();
-    x.tiles_m = (uint32_t)tiles_m, x.tiles_n = (uint32_t)tiles_n;
+    x.tiles = make_tiles(tiles_m, tiles_n);
     return QNN_LAUNCH("conv_map", panel::map_kernel(shape), dim3((unsigned)(total < per * cus ? total : per * cus)), dim3(panel::kThreads), 0, s, g, x);
 }
 
