@@ -368,6 +368,55 @@ int launch_transpose(const uint32_t *in, int64_t rows, int64_t cols, int64_t ld_
                       in, rows, cols, ld_in, in_plane_stride, out, ld_out, out_plane_stride, out_words, row_blocks, units);
 }
 
+// The three transpositions of a backward step on bit planes in one launch (three launches of 3 to 4 us each depend on the one before, which is most of what
+// a small step takes: 73 x 384 x 640 29 -> 23 us, 303 x 2752 x 384 48 -> 31).  A thread takes 32 rows x one word, a workgroup 256 rows x 32 words, any layout; eight threads
+// write the eight words of an output row.
+struct TransposeJob {
+    const uint32_t *in;
+    uint32_t *out;
+    int64_t rows, cols, ld_in, in_plane_stride, ld_out, out_plane_stride;
+    uint32_t out_words;                    // words of an output row that are written (zeros beyond the input's rows)
+    uint32_t across, down, inv_across, inv_down;  // blocks of 32 words and of 256 rows
+    uint32_t blocks;                       // of all planes
+};
+struct TransposeJobs {
+    TransposeJob job[3];
+};
+TransposeJob transpose_job(const uint32_t *in, int64_t rows, int64_t cols, int64_t ld_in, int64_t in_plane_stride, int planes, uint32_t *out, int64_t ld_out,
+                           int64_t out_plane_stride, int64_t out_words) {
+    TransposeJob j = {in, out, rows, cols, ld_in, in_plane_stride, ld_out, out_plane_stride, (uint32_t)out_words, 0, 0, 0, 0, 0};
+    j.across = (uint32_t)ceil_div(words_for(cols), 32), j.down = (uint32_t)ceil_div(out_words, 8);
+    j.inv_across = inverse_of(j.across), j.inv_down = inverse_of(j.down), j.blocks = j.across * j.down * (uint32_t)planes;
+    return j;
+}
+__global__ __launch_bounds__(256) void transpose_jobs_kernel(const TransposeJobs jobs) {
+    uint32_t block = blockIdx.x;
+    int which = 0;
+    if (block >= jobs.job[0].blocks) {
+        block -= jobs.job[0].blocks, which = 1;
+        if (block >= jobs.job[1].blocks) block -= jobs.job[1].blocks, which = 2;
+    }
+    const TransposeJob &job = jobs.job[which];
+    uint32_t bx, by;
+    const uint32_t plane = quotient(quotient(block, job.across, job.inv_across, bx), job.down, job.inv_down, by);
+    const uint32_t j = 32u * bx + (threadIdx.x >> 3), word = 8u * by + (threadIdx.x & 7u);
+    if ((int64_t)j >= (job.cols + 31) / 32 || word >= job.out_words) return;
+    const uint32_t *const in = job.in + (int64_t)plane * job.in_plane_stride + j;
+    uint32_t x[32];
+#pragma unroll
+    for (int k = 0; k < 32; ++k) {
+        const int64_t row = 32 * (int64_t)word + k;
+        x[k] = row < job.rows ? in[row * job.ld_in] : 0u;
+    }
+    transpose_32x32_bits(x);
+    uint32_t *const out = job.out + (int64_t)plane * job.out_plane_stride + word;
+#pragma unroll
+    for (int c = 0; c < 32; ++c) {
+        const int64_t row = 32 * (int64_t)j + c;
+        if (row < job.cols) out[row * job.ld_out] = x[c];
+    }
+}
+
 int check_planes_out(const char *what, int64_t rows, int64_t K, int64_t ldx, int nbits, const void *x, const void *planes,
                      int64_t ld_words, int64_t plane_stride_words) {
     if (rows < 0 || K < 1) return fail(QNN_ERR_SHAPE, "%s: rows = %lld, K = %lld", what, (long long)rows, (long long)K);
@@ -508,15 +557,19 @@ extern "C" int qnn_binary_backward(const uint32_t *G, int Pg, const int32_t *coe
         // a pool that cannot hold the operands of both products may hold those of one, which the way below asks for
         if (!no_memory) return rc;
     }
-    // g_a = g W: the reduction runs over n, so W (N x K, packed along k) is needed packed along n
-    if ((rc = launch_transpose(W, N, K, ldw_words, 0, 1, Wt, ldn, 0, pad ? ldn : words_for(N), st))) return rc;
+    // g_a = g W: the reduction runs over n, so W (N x K, packed along k) is needed packed along n; g_W = g^T a: over the samples m, so both
+    // operands are needed packed along m
+    const int64_t red_m = pad ? ldm * 32 : M;
+    const int64_t strideG = Pg > 1 ? strideG_words : 0, words_n = pad ? ldn : words_for(N), words_m = pad ? ldm : words_for(M);
+    const TransposeJobs jobs = {{transpose_job(W, N, K, ldw_words, 0, 1, Wt, ldn, 0, words_n), transpose_job(G, M, N, ldg_words, strideG, Pg, Gt, ldm, N * ldm, words_m),
+                                 transpose_job(A, M, K, lda_words, 0, 1, At, ldm, 0, words_m)}};
+    uint64_t blocks = 0;
+    for (const TransposeJob &j : jobs.job) blocks += (uint64_t)j.across * j.down * (&j == &jobs.job[1] ? Pg : 1);
+    if (blocks > 0x7FFFFFFFULL) return fail(QNN_ERR_SHAPE, "binary_backward: too many elements");
+    if ((rc = QNN_LAUNCH("transpose_bits", transpose_jobs_kernel, dim3((unsigned)blocks), dim3(256), 0, st, jobs))) return rc;
     if ((rc = qnn_bitplane_gemm(G, Pg, coefG, modeG, ldg_words, strideG_words, Wt, 1, &one, QNN_PLANE_SIGN, ldn, 0, gA, ld_ga,
                                 M, K, N, stream)))
         return rc;
-    // g_W = g^T a: the reduction runs over the samples m, so both operands are needed packed along m
-    const int64_t red_m = pad ? ldm * 32 : M;
-    if ((rc = launch_transpose(G, M, N, ldg_words, strideG_words, Pg, Gt, ldm, N * ldm, pad ? ldm : words_for(M), st))) return rc;
-    if ((rc = launch_transpose(A, M, K, lda_words, 0, 1, At, ldm, 0, pad ? ldm : words_for(M), st))) return rc;
     return qnn_bitplane_gemm(Gt, Pg, coefG, modeG, ldm, N * ldm, At, 1, &one, QNN_PLANE_SIGN, ldm, 0, gW, ld_gw, N, K, red_m,
                              stream);
 }
