@@ -346,6 +346,7 @@ size_t qnn_binary_mlp_workspace_bytes(int64_t batch, int in_bits, int n_layers, 
 namespace {
 struct MlpPlan {
     bool pack_planes;  // the input planes are materialised (otherwise the first layer reads the 8-bit codes)
+    bool few_rows;     // ... on the kernel for few rows
     bool order_w;      // the first layer's weights are put in the order of its operands first (into the unused plane area)
     const uint8_t *x;
     int64_t batch, in_dim, ldx, ld0, plane_stride;
@@ -414,7 +415,7 @@ int plan_mlp(const uint8_t *x, int64_t batch, int64_t ldx, int in_bits, int n_la
     for (int p = 0; p < in_bits; ++p) coef[p] = 1 << p;
     const Epilogue e0{nullptr, 0, T[0], flip ? flip[0] : nullptr, act[0], mlp_ldw(dims[1])};
     plan.pack_planes = true;
-    plan.order_w = false;
+    plan.order_w = plan.few_rows = false;
     if (in_bits == 8 && engine != QNN_ENGINE_VALU) {
         GemmArgs &g = plan.g[0];
         std::memset(&g, 0, sizeof(g));
@@ -429,14 +430,19 @@ int plan_mlp(const uint8_t *x, int64_t batch, int64_t ldx, int in_bits, int n_la
         g.epi = e0;
         g.M = batch, g.N = dims[1], g.K = dims[0], g.Kw = words_for(dims[0]);
         if (int rc = check_range(g)) return rc;
-        if (mfma_supports(g) && (engine != QNN_ENGINE_AUTO || mfma_preferred(g))) {
+        // The plane area of the workspace is free where codes are multiplied: if it holds them, the weights go there as bits in the order of the
+        // operands, with their row sums.  Otherwise few rows go to the kernel without an image, more to the one that expands bits per wave.
+        const size_t ib = round256(codes::image_bytes(dims[1], dims[0]));
+        const bool has_image = ib + round256((size_t)dims[1] * 4) <= off;
+        if (engine == QNN_ENGINE_AUTO && codes::small_preferred(g, mfma_preferred(g), has_image)) {
+            if (!aligned4(W[0]) || !aligned4(T[0])) return fail(QNN_ERR_ALIGN, "mlp: pointer not 4-byte aligned");
+            plan.engine[0] = QNN_ENGINE_MFMA;
+            plan.pack_planes = false, plan.few_rows = true;
+        } else if (mfma_supports(g) && (engine != QNN_ENGINE_AUTO || mfma_preferred(g))) {
             if (!aligned4(W[0]) || !aligned4(T[0])) return fail(QNN_ERR_ALIGN, "mlp: pointer not 4-byte aligned");
             plan.engine[0] = QNN_ENGINE_MFMA;
             plan.pack_planes = false;
-            // The plane area of the workspace is free then: if it holds them, the weights go there as bits in the order of the
-            // operands, with their row sums.  Otherwise the kernel expands bits per wave.
-            const size_t ib = round256(codes::image_bytes(dims[1], dims[0]));
-            if (ib + round256((size_t)dims[1] * 4) <= off) {
+            if (has_image) {
                 g.w_image = reinterpret_cast<uint32_t *>(ws);
                 g.rw_scaled = reinterpret_cast<int32_t *>(ws + ib);
                 plan.order_w = codes::supports(g);
@@ -477,8 +483,14 @@ int run_mlp(const MlpPlan &plan, hipStream_t s) {
             return rc;
     if (plan.order_w)
         if (int rc = codes::launch_weight_image(plan.g[0], s)) return rc;
-    for (int l = 0; l < plan.n; ++l)
+    for (int l = 0; l < plan.n; ++l) {
+        if (l == 0 && plan.few_rows) {
+            if (int rc = codes::launch_small(plan.g[0], s)) return rc;
+            g_last_engine = g_engines[g_engine_count++] = plan.engine[0];
+            continue;
+        }
         if (int rc = launch_on(plan.g[l], plan.engine[l], plan.free_choice, s)) return rc;
+    }
     return QNN_OK;
 }
 

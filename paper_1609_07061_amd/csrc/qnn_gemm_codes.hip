@@ -301,6 +301,73 @@ __global__ __launch_bounds__(256) void weight_image_kernel(const uint32_t *__res
     }
 }
 
+// The same product for few rows, straight from the weights' bits: tiles of 32 x 32 whose waves share k, 32 elements at a time.  Bound: latency, so all
+// loads of a wave that fit its registers are on their way together, the sums meet once in LDS, and no launch prepares anything (bit planes and their
+// product took two launches and four products of digits).  A word's half of 16 bits becomes 0 / 1 bytes, four with one multiplication:
+// with y = x - 128, sum x w = 2 sum y b - sum y + 128 (2 pop - K).
+template <int kWaves>
+__global__ __launch_bounds__(64 * kWaves) void gemm_codes_small_kernel(const GemmArgs g, const Tiles tiles) {
+    constexpr uint32_t kAhead = kWaves == 16 ? 2 : 4;  // units of 32 elements whose loads are on their way together
+    __shared__ __attribute__((aligned(16))) int32_t part[kWaves][32][36];
+    __shared__ int32_t part_a[kWaves][32], part_w[kWaves][32];
+    const uint32_t lane = threadIdx.x & 63u, r = lane & 31u, kg = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t tm, tn;
+    tile_of_block(blockIdx.x, tiles, tm, tn);
+    const uint32_t M = (uint32_t)g.M, N = (uint32_t)g.N, K = (uint32_t)g.K, m0 = 32u * tm, n0 = 32u * tn, units = (K + 31u) / 32u;
+    // (rows beyond the last repeat it and are not stored)
+    const uint8_t *const codes = reinterpret_cast<const uint8_t *>(g.A.base) + (uint64_t)(m0 + r < M ? m0 + r : M - 1u) * (uint64_t)g.A.ld;
+    const uint32_t n = n0 + r < N ? n0 + r : N - 1u;
+    const uint32_t *const weights = g.W + (uint64_t)n * (uint64_t)g.ldw;
+    const int32_t T = g.epi.T[n];
+    const uint32_t flip = g.epi.flip ? g.epi.flip[n] : 0u;
+    v16i acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0;
+    int32_t sum = 0, pop = 0;
+    for (uint32_t u0 = wave; u0 < units; u0 += kWaves * kAhead) {
+        v4i a[kAhead];
+        uint32_t word[kAhead];
+        bool in[kAhead];
+#pragma unroll
+        for (uint32_t i = 0; i < kAhead; ++i) {
+            const uint32_t u = u0 + kWaves * i, k = 32u * u + 16u * kg;
+            in[i] = k < K;  // (K is a multiple of 16)
+            a[i] = *reinterpret_cast<const v4i *>(codes + (in[i] ? k : 0u));
+            word[i] = weights[u < units ? u : 0u];
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < kAhead; ++i) {
+            const uint32_t bits = in[i] ? (word[i] >> (16u * kg)) & 0xFFFFu : 0u;
+            v4i w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                a[i][e] = in[i] ? a[i][e] ^ (int)0x80808080u : 0;
+                sum = __builtin_amdgcn_sdot4(a[i][e], 0x01010101, sum, false);
+                w[e] = (int)(__umul24((bits >> (4 * e)) & 0xFu, 0x00204081u) & 0x01010101u);
+            }
+            pop += __builtin_popcount(bits);
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w, a[i], acc, 0, 0, 0);
+        }
+    }
+    // register 4 q + e: row r of the tile, column 8 q + 4 kg + e
+#pragma unroll
+    for (int q = 0; q < 4; ++q) *reinterpret_cast<v4i *>(&part[wave][r][8 * q + 4 * kg]) = v4i{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    sum = mfma::sum_halves(sum), pop = mfma::sum_halves(pop);
+    if (kg == 0) part_a[wave][r] = sum, part_w[wave][r] = pop;
+    __syncthreads();
+    // a lane keeps its column, a ballot packs two rows
+    const bool live = n0 + r < N;
+    for (uint32_t row0 = 2u * wave; row0 < 32u; row0 += 2u * kWaves) {
+        const uint32_t row = row0 + kg;
+        int32_t s = 0, sa = 0, sw = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) s += part[w][row][r], sa += part_a[w][row], sw += part_w[w][r];
+        const int32_t value = 2 * s - sa + 128 * (2 * sw - (int32_t)K);
+        const uint64_t bits = __ballot(live && ((value >= T) != (flip != 0u)));
+        if (r == 0u && m0 + row < M) g.epi.out_bits[(int64_t)(m0 + row) * g.epi.ldo + tn] = (uint32_t)(bits >> lane);
+    }
+}
+
 // (a tile of 128 columns brings in the block beyond its own too)
 int64_t blocks_of(int64_t N) { return ceil_div(N, kBlockRows) + 1; }
 
@@ -311,6 +378,28 @@ size_t image_bytes(int64_t N, int64_t K) { return (size_t)(ceil_div(K, kGroupK) 
 bool supports(const GemmArgs &g) {
     // (the sums are below 64 x 128 K; offsets into the codes are 32-bit)
     return g.A.rows_are_bytes && g.w_image && g.rw_scaled && g.epi.T && g.K < 131072 && (long double)g.M * g.A.ld < 4294967296.0L && g.N < 0x7FFFFFF0;
+}
+
+// Forward step with a 10-neuron second layer, us, otherwise / this.  No room for the image, so that bits would be expanded per wave: always (4096 neurons,
+// 784 codes, 300 rows 37.3 / 23.4; 3072 codes, 500 rows 79 / 50; 32 codes, 512 neurons, 4000 rows 27.6 / 7.8).  Where bit planes would be packed: sums
+// beyond 2^24, for which only the VALU is left, always (65536 codes, 512 neurons, 200 rows 2530 / 122); otherwise up to 8192 codes and
+// 49152 steps of 32 codes (784 codes, 512 neurons: 32 rows 14.0 / 10.6, 3000 rows 27.3 / 19.1; 3072 codes, 512 neurons, 1000 rows 22.9 / 17.4; beyond that
+// 4096 neurons, 200 rows 27.0 / 28.7; 12288 codes, 512 neurons, 32 rows 26.6 / 27.1, 2000 rows 73 / 91).
+bool small_preferred(const GemmArgs &g, bool large, bool has_image) {
+    if (large && has_image) return false;
+    if (!(g.A.rows_are_bytes && g.epi.T && g.K < 131072 && g.K % 16 == 0 && g.A.ld % 16 == 0 && reinterpret_cast<uintptr_t>(g.A.base) % 16 == 0 &&
+          g.pw.mode == QNN_PLANE_SIGN && g.pw.count == 1 && g.pw.coef[0] == 1 && g.M < 0x7FFFFFE0 && g.N < 0x7FFFFFE0))
+        return false;
+    const int64_t tiles = ceil_div(g.M, 32) * ceil_div(g.N, 32), steps = ceil_div(g.K, 32);
+    if (tiles >= 1 << 24) return false;
+    return large || 255 * g.K > 1 << 24 || (steps <= 256 && tiles * steps <= 49152);
+}
+
+int launch_small(const GemmArgs &g, hipStream_t s) {
+    const int64_t m = ceil_div(g.M, 32), n = ceil_div(g.N, 32);
+    const bool many = m * n > 512;
+    return QNN_LAUNCH("gemm_codes_small", (many ? gemm_codes_small_kernel<4> : gemm_codes_small_kernel<16>), dim3((unsigned)(m * n)), dim3(many ? 256 : 1024), 0, s, g,
+                      make_tiles(m, n));
 }
 
 int launch_weight_image(const GemmArgs &g, hipStream_t s) {

@@ -211,6 +211,9 @@ namespace codes {
 size_t image_bytes(int64_t N, int64_t K);
 bool supports(const GemmArgs &g);
 int launch_weight_image(const GemmArgs &g, hipStream_t s);
+// ... few rows, without an image (codes and rows on 16-byte boundaries)
+bool small_preferred(const GemmArgs &g, bool large, bool has_image);  // large: codes would be multiplied otherwise too, with an image of the weights or without
+int launch_small(const GemmArgs &g, hipStream_t s);
 int launch(const GemmArgs &g, hipStream_t s);
 }  // namespace codes
 
