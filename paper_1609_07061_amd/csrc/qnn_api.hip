@@ -665,7 +665,7 @@ int qnn_bitplane_conv2d(const uint32_t *A, int Pa, const int32_t *coefA, int mod
 namespace {
 constexpr int kMaxNetLayers = 2 * QNN_MAX_LAYERS;
 struct NetStep {
-    enum Kind { kPack, kOnes, kGemm, kPool, kFirstConv, kConvPrep, kConvMap } kind;
+    enum Kind { kPack, kOnes, kGemm, kPool, kFirstConv, kConvPrep, kConvMap, kConvSlice } kind;
     GemmArgs g;      // kGemm (convolution or fully connected)
     int engine;      // kGemm
     OnesJob ones;    // kOnes, and done along by kPool
@@ -675,7 +675,7 @@ struct NetStep {
     int64_t rows, n;
     int a, b, c;
     const uint32_t *mask;
-    const uint32_t *w;  // kConvMap: filters
+    const uint32_t *w;  // kConvMap, kConvSlice: filters
     bool invert;
 };
 struct NetPlan {
@@ -787,6 +787,15 @@ int run_net(const NetPlan &plan, hipStream_t s) {
                     if (g_engine_count < 2 * QNN_MAX_LAYERS) g_engines[g_engine_count++] = QNN_ENGINE_MFMA_FP4;
                 }
                 break;
+            case NetStep::kConvSlice:
+                // operands as for kConvMap; thresholds, flips and the output pitch in g.epi
+                rc = slice::launch_map(static_cast<const uint32_t *>(st.src), st.rows, st.a, st.b, st.c, st.w, st.n, st.g.epi.T, st.g.epi.flip,
+                                       static_cast<uint32_t *>(st.dst), st.g.epi.ldo, st.mask, st.invert, s);
+                if (rc == QNN_OK) {
+                    g_last_engine = QNN_ENGINE_MFMA_FP4;
+                    if (g_engine_count < 2 * QNN_MAX_LAYERS) g_engines[g_engine_count++] = QNN_ENGINE_MFMA_FP4;
+                }
+                break;
             case NetStep::kPool:
                 rc = launch_pool_bits(static_cast<const uint32_t *>(st.src), st.rows, st.a, st.b, st.c, st.mask, st.invert,
                                       static_cast<uint32_t *>(st.dst), static_cast<uint32_t *>(st.dst2), (int)st.n, st.ones, s);
@@ -857,12 +866,18 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
     };
     // ... and whether that kernel finds room for its pixels in LDS, with the pooling that follows or without
     auto in_lds = [&](int64_t hh, int64_t ww, int64_t cc, int64_t co, bool pooled) { return image::map_supports(B, hh, ww, cc, co, pooled); };
+    // ... or where tiles are few, on the sliced kernel; all of these need the one plane alone
+    auto on_slice = [&](int64_t hh, int64_t ww, int64_t cc, int l) {
+        return engine == QNN_ENGINE_AUTO && !on_plane(hh, ww, cc, l) && slice::map_supports(B, hh, ww, cc, cout[l], pool[l] != 0);
+    };
+    auto reads_plane = [&](int64_t hh, int64_t ww, int64_t cc, int l) { return on_plane(hh, ww, cc, l) || on_slice(hh, ww, cc, l); };
     // whether a convolution's output is pooled along (without that kernel not where the next one reads a 2-bit code, whose other plane the pooling
     // kernel writes)
     auto pools_along = [&](int l, int64_t hh, int64_t ww, int64_t cc) {
-        if (!pool[l] || !on_plane(hh, ww, cc, l)) return false;
-        if (in_lds(hh, ww, cc, cout[l], true)) return true;
-        return conv_map_pools(hh, ww) && (l + 1 >= n_conv || on_plane(hh / 2, ww / 2, cout[l], l + 1));
+        if (!pool[l] || !reads_plane(hh, ww, cc, l)) return false;
+        if (on_plane(hh, ww, cc, l) && in_lds(hh, ww, cc, cout[l], true)) return true;
+        if (on_plane(hh, ww, cc, l) && !conv_map_pools(hh, ww)) return false;
+        return l + 1 >= n_conv || reads_plane(hh / 2, ww / 2, cout[l], l + 1);
     };
     // thresholds per border class of the convolutions on planes whose pixels do not fit there
     plan.prep.count = 0;
@@ -918,7 +933,7 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
         const bool on_map = l > 0 && on_plane(h, w, cin, l);
         // the next convolution reads this layer's output: as a plane it takes "value is -1" alone,
         // otherwise the 2-bit code, whose plane "inside the image" is then written too
-        const bool ones_needed = inverted && !on_plane(ho, wo, co, l + 1);
+        const bool ones_needed = inverted && !reads_plane(ho, wo, co, l + 1);
         const bool pooled_along = l > 0 && pools_along(l, h, w, cin);
         const bool map_in_lds = on_map && in_lds(h, w, cin, co, pooled_along), ones_along = map_in_lds && ones_needed && pooled_along == (pool[l] != 0);
         if (on_map) {
@@ -928,6 +943,12 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
             st.rows = B, st.a = (int)h, st.b = (int)w, st.c = (int)cin, st.n = co;
             st.g.epi = e;
             st.g.epi.flip = inverted ? (flip ? flip[l] : nullptr) : reinterpret_cast<const uint8_t *>(ws + L.flag_inv[l]);
+            if (pooled_along) st.mask = words(L.flag_bits[l]), st.invert = inverted;
+        } else if (l > 0 && on_slice(h, w, cin, l)) {
+            st.kind = NetStep::kConvSlice;
+            st.src = a_planes + a_stride, st.w = W[l], st.dst = pooled_along ? kept_bits : conv_dst;
+            st.rows = B, st.a = (int)h, st.b = (int)w, st.c = (int)cin, st.n = co;
+            st.g.epi = e;
             if (pooled_along) st.mask = words(L.flag_bits[l]), st.invert = inverted;
         } else if (l == 0 && first_direct) {
             st.kind = NetStep::kFirstConv;

@@ -25,7 +25,8 @@ constexpr int kMaxDigits = QNN_MAX_PLANES;
 enum SliceKind {
     kPm1 = 0,   // every digit is one +-1 plane, multiplied as +-1
     kPair = 1,  // every digit is one or two 0/1 planes, multiplied as a number 0 .. 3
-    kOne = 2    // every digit is one plane, multiplied as 0 / 1 (a +-1 plane too: 2 b - 1 = 2 (b - 1/2))
+    kOne = 2,   // every digit is one plane, multiplied as 0 / 1 (a +-1 plane too: 2 b - 1 = 2 (b - 1/2))
+    kMap = 3    // one plane "value is -1" of a +-1 map whose channels fill whole words, 0 outside the image (sliced kernel, left operand)
 };
 // The digit's value is 2^lg (u - offset2 / 2), u = the number made of its planes' bits (as inverted).
 struct SliceDigit {
@@ -104,7 +105,9 @@ __device__ __forceinline__ v4i make_operand(const u32x4 &z0, const u32x4 &z1, co
     v4i f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        if constexpr (kKind == kPair) {
+        if constexpr (kKind == kMap) {
+            f[i] = (int)(((z0[i] << (3 - ph)) & 0x88888888u) | z1[i]);  // (z1: 1.0 in every nibble, or nothing)
+        } else if constexpr (kKind == kPair) {
             const uint32_t z = (ph & 1) ? z1[i] : z0[i];
             f[i] = (int)(((ph & 2) ? (z >> 2) : z) & 0x33333333u);
         } else if constexpr (kKind == kOne) {
@@ -143,10 +146,13 @@ __device__ __forceinline__ u32x4 load_piece(const uint8_t *p, const SliceArgs &s
 struct Patch {
     uint32_t off, in;
 };
-__device__ __forceinline__ Patch patch_of(const GemmArgs &g, const SliceArgs &sc, const uint32_t m) {
+// quads: the rows come in fours of the pixels that 2 x 2 pooling makes one, and Ho, Wo and the quotients are the pooled map's.
+__device__ __forceinline__ Patch patch_of(const GemmArgs &g, const SliceArgs &sc, const uint32_t m, const bool quads = false) {
     const uint32_t per = (uint32_t)(g.A.Ho * g.A.Wo);
     uint32_t rem, xo;
-    const uint32_t img = quotient(m, per, sc.inv_hw, rem), yo = quotient(rem, (uint32_t)g.A.Wo, sc.inv_w, xo);
+    const uint32_t img = quotient(quads ? m >> 2 : m, per, sc.inv_hw, rem);
+    uint32_t yo = quotient(rem, (uint32_t)g.A.Wo, sc.inv_w, xo);
+    if (quads) yo = 2u * yo + ((m >> 1) & 1u), xo = 2u * xo + (m & 1u);
     const int y = (int)yo * g.A.stride - g.A.pad, x = (int)xo * g.A.stride - g.A.pad;
     auto inside = [](const int first, const int taps, const int size) {  // taps t with 0 <= first + t < size
         const int lo = first < 0 ? (-first < 16 ? -first : 16) : 0, end = size - first;

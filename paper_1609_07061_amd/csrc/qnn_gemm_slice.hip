@@ -33,6 +33,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, waves_per_simd(kA, kW, BMb)) void g
     constexpr bool kPixels = kRows != kMatrix;
     constexpr int BM = 32 * BMb, BN = 32 * BNb, kPitch = BN + 4;
     constexpr int NA = kA == kPair ? 2 : 1, NW = kW == kPair ? 2 : 1;  // planes of a digit
+    constexpr int ZA = kA == kPair || kA == kMap ? 2 : 1;             // fields of an operand
     // partial sums: a slot per wave; with 64 x 64 tiles half as many (see below), so that four workgroups fit on a compute unit and not two
     // (convolution of a 0/1 map 64 x 56 x 56, 16 -> 32 channels of 5 x 5: 79.3 -> 37.3 us, with the lone plane by itself)
     constexpr uint32_t kSlots = BMb == 2 ? kMaxWaves / 2 : kMaxWaves;
@@ -51,7 +52,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, waves_per_simd(kA, kW, BMb)) void g
         uint32_t m = m0 + 32 * b + r;
         m = m < (uint32_t)g.M ? m : (uint32_t)g.M - 1u;
         if constexpr (kPixels) {
-            const Patch p = patch_of(g, sc, m);
+            const Patch p = patch_of(g, sc, m, kA == kMap && g.pool_and != nullptr);
             a_off[b] = p.off, a_in[b] = p.in;
         } else {
             a_off[b] = m * (uint32_t)(g.A.ld * 4), a_in[b] = 0u;
@@ -119,8 +120,16 @@ __global__ __launch_bounds__(64 * kMaxWaves, waves_per_simd(kA, kW, BMb)) void g
     const bool corrected = (kA == kPair || kW == kPair) && sc.corrected != 0;
     // one chunk of one digit pair
     auto multiply = [&](const Chunk &x, const SliceDigit &da, const SliceDigit &dw, const bool clear) __attribute__((always_inline)) {
-        u32x4 za[NA][BMb], zw[NW][BNb];
+        u32x4 za[ZA][BMb], zw[NW][BNb];
         auto prepare = [&](auto kind_tag, const u32x4 p0, const u32x4 p1, const SliceDigit &d, const uint32_t skip, const bool clr, u32x4 &z0, u32x4 &z1) __attribute__((always_inline)) {
+            if constexpr (decltype(kind_tag)::value == kMap) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bool in = (uint32_t)i >= skip && (kRows != kNarrowPatches || (uint32_t)i < sc.row_words);
+                    z0[i] = in ? p0[i] : 0u, z1[i] = in ? 0x22222222u : 0u;
+                }
+                return 0;
+            }
             u32x4 w0 = p0, w1 = p1;
             if (clr) {
 #pragma unroll
@@ -137,19 +146,19 @@ __global__ __launch_bounds__(64 * kMaxWaves, waves_per_simd(kA, kW, BMb)) void g
         const int shift = da.lg + dw.lg;
 #pragma unroll
         for (int b = 0; b < BMb; ++b) {
-            const int sum = prepare(std::integral_constant<int, kA>{}, x.a[0][b], x.a[NA - 1][b], da, x.skip_a[b], clear || kPixels, za[0][b], za[NA - 1][b]);
+            const int sum = prepare(std::integral_constant<int, kA>{}, x.a[0][b], x.a[NA - 1][b], da, x.skip_a[b], clear || kPixels, za[0][b], za[ZA - 1][b]);
             if (corrected) corr_a[b] += ((sum * dw.offset2) << shift) >> 1;
         }
 #pragma unroll
         for (int b = 0; b < BNb; ++b) {
-            const int sum = prepare(std::integral_constant<int, kW>{}, x.w[0][b], x.w[NW - 1][b], dw, x.skip, clear || kPixels, zw[0][b], zw[NW - 1][b]);
+            const int sum = prepare(std::integral_constant<int, kW>{}, x.w[0][b], x.w[NW - 1][b], dw, x.skip, kA != kMap && (clear || kPixels), zw[0][b], zw[NW - 1][b]);
             if (corrected) corr_w[b] += ((sum * da.offset2) << shift) >> 1;
         }
         auto phase = [&](auto ph_tag) __attribute__((always_inline)) {
             constexpr int ph = decltype(ph_tag)::value;
             v4i fa[BMb], fw[BNb];
 #pragma unroll
-            for (int b = 0; b < BMb; ++b) fa[b] = make_operand<kA>(za[0][b], za[NA - 1][b], ph);
+            for (int b = 0; b < BMb; ++b) fa[b] = make_operand<kA>(za[0][b], za[ZA - 1][b], ph);
 #pragma unroll
             for (int b = 0; b < BNb; ++b) fw[b] = make_operand<kW>(zw[0][b], zw[NW - 1][b], ph);
 #pragma unroll
@@ -264,6 +273,25 @@ __global__ __launch_bounds__(64 * kMaxWaves, waves_per_simd(kA, kW, BMb)) void g
         const bool live = n < g.N;
         const int32_t T = threshold;
         const bool flip = live && flip_flag != 0u;
+        if constexpr (kA == kMap && BN == 32) {
+            // four rows are a pixel behind the pooling: OR, or AND where the filter's bits are flipped
+            if (g.pool_and) {
+                const uint32_t all = (g.pool_and[tn] ^ g.pool_invert);
+                for (uint32_t row0 = 4u * wave; row0 < rows; row0 += 4u * waves) {
+                    uint64_t bits[2];
+#pragma unroll
+                    for (uint32_t h = 0; h < 2; ++h) {
+                        const uint32_t row = row0 + 2u * h + kg;
+                        float s = part[0][row][col];
+                        for (uint32_t w = 1; w < slots; ++w) s += part[w][row][col];
+                        bits[h] = __ballot(live && (((int32_t)s >= T) != flip));
+                    }
+                    const uint32_t a = (uint32_t)bits[0], b = (uint32_t)(bits[0] >> 32), c = (uint32_t)bits[1], d = (uint32_t)(bits[1] >> 32);
+                    if (lane == 0u) g.epi.out_bits[(int64_t)((m0 + row0) >> 2) * g.epi.ldo + tn] = ((a | b | c | d) & ~all) | (a & b & c & d & all);
+                }
+                return;
+            }
+        }
         for (uint32_t row0 = wave * kRowsPerWave; row0 < rows; row0 += waves * kRowsPerWave) {
             const uint32_t row = row0 + lane / BN;  // (below BM: BM is a multiple of kRowsPerWave)
             float s = part[0][row][col];
@@ -525,5 +553,56 @@ int launch_gemm_slice(const GemmArgs &g, hipStream_t s) {
     const SliceFn fn = !pix ? slice_kernel<kMatrix>(ka, kw, large, four) : (g.A.Cw < 4 ? slice_kernel<kNarrowPatches>(ka, kw, large, four) : slice_kernel<kPatches>(ka, kw, large, four));
     return QNN_LAUNCH("gemm_slice", fn, dim3((unsigned)tiles), dim3(64u * waves), 0, s, g, sc, make_tiles(tiles_m, tiles_n));
 }
+
+// The same kernel on a +-1 map's plane "value is -1" (3 x 3 convolution, channels that fill whole words): half the loads and two thirds of the
+// instructions of the 2-bit code, no plane "inside the image" to fill, and 2 x 2 pooling in the epilogue.  Bound: latency.  Where 32 x 32 tiles are
+// taken.  App. A ConvNet of width 128, 4 images of 32 x 32, all layers: 53.5 -> 45.7 us with the last two convolutions here (12 -> 10 launches), 43.0
+// with all that have few tiles; 1 image of 16 x 16 46.4 -> 38.6.
+namespace slice {
+static bool map_args(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N, bool pooled, GemmArgs &g, SliceArgs &sc) {
+    std::memset(&g, 0, sizeof(g));
+    const int64_t Cw = words_for(C);
+    if (B < 1 || H < 1 || Wd < 1 || H > 32767 || Wd > 32767 || C % 32 != 0 || C > (1 << 24) || N < 1 || (pooled && (H < 2 || Wd < 2))) return false;
+    if (B > 0x7FFFFF00LL / (H * Wd)) return false;
+    g.A.rows_are_pixels = 1;
+    g.A.H = (int)H, g.A.Wd = (int)Wd, g.A.Ho = (int)H, g.A.Wo = (int)Wd, g.A.Cw = (int)Cw, g.A.KH = 3, g.A.KW = 3, g.A.pad = 1, g.A.stride = 1;
+    g.pa.count = 1, g.pa.mode = QNN_PLANE_SIGN, g.pa.coef[0] = 1;
+    g.pw.count = 1, g.pw.mode = QNN_PLANE_SIGN, g.pw.coef[0] = 1;
+    g.ldw = g.Kw = 9 * Cw;
+    g.M = B * H * Wd, g.N = N, g.K = 9 * C;
+    int ka, kw;
+    if (!slice_args(g, false, sc, ka, kw)) return false;
+    sc.c0 = 0;  // (elements beyond a row are zeros here)
+    if (pooled) {
+        g.A.Ho = (int)(H / 2), g.A.Wo = (int)(Wd / 2);
+        g.M = 4 * B * g.A.Ho * g.A.Wo;
+        sc.inv_hw = inverse_of((int64_t)g.A.Ho * g.A.Wo), sc.inv_w = inverse_of(g.A.Wo);
+    }
+    const int64_t tiles64 = ceil_div(B * H * Wd, 64) * ceil_div(N, 64);
+    return tiles64 < 160 || B * H * Wd <= 32 || N <= 32;
+}
+
+bool map_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N, bool pooled) {
+    GemmArgs g;
+    SliceArgs sc;
+    return map_args(B, H, Wd, C, N, pooled, g, sc);
+}
+
+int launch_map(const uint32_t *plane, int64_t B, int H, int Wd, int64_t C, const uint32_t *W, int64_t N, const int32_t *T, const uint8_t *flip, uint32_t *out,
+               int64_t ldo, const uint32_t *pool_and, bool pool_invert, hipStream_t s) {
+    GemmArgs g;
+    SliceArgs sc;
+    if (!map_args(B, H, Wd, C, N, pool_and != nullptr, g, sc)) return fail(QNN_ERR_UNSUPPORTED, "convolution of a +-1 map: shape not supported");
+    g.A.base = plane, g.W = W;
+    g.epi.T = T, g.epi.flip = flip, g.epi.out_bits = out, g.epi.ldo = ldo;
+    g.pool_and = pool_and, g.pool_invert = pool_invert ? 0xFFFFFFFFu : 0u;
+    const int64_t tiles_m = ceil_div(g.M, 32), tiles_n = ceil_div(N, 32), tiles = tiles_m * tiles_n, items = sc.chunks;
+    if (tiles > 0x7FFFFFFFLL) return fail(QNN_ERR_SHAPE, "gemm: too many tiles");
+    const bool four = four_waves(items, tiles), narrow = g.A.Cw < 4;
+    const SliceFn fn = narrow ? (four ? gemm_slice_kernel<kMap, kPm1, kNarrowPatches, 1, 1, 4> : gemm_slice_kernel<kMap, kPm1, kNarrowPatches, 1, 1, 16>)
+                              : (four ? gemm_slice_kernel<kMap, kPm1, kPatches, 1, 1, 4> : gemm_slice_kernel<kMap, kPm1, kPatches, 1, 1, 16>);
+    return QNN_LAUNCH("gemm_slice", fn, dim3((unsigned)tiles), dim3(64u * (four ? 4 : (items < 16 ? (int)items : 16))), 0, s, g, sc, make_tiles(tiles_m, tiles_n));
+}
+}  // namespace slice
 
 }  // namespace qnn

@@ -367,17 +367,19 @@ bool conv_map_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N) {
     return 9 * Cw * 32 < 8388608 && ceil_div(M, kTile) * ceil_div(N, kTile) <= 0x7FFFFFFFLL;
 }
 
-// Tiles of 128 x 128 from which on a map is read as its plane, against its 2-bit code on the sliced kernel (App. A ConvNets, width / images of
-// 16 x 16 to 32 x 32, us, every convolution on the code -> all of them on planes):
-//   Pixels that fit LDS (qnn_gemm_image.hip): from 16 tiles on (128 / 16 of 32 x 32 66 -> 52, 128 / 8 of 24 x 24 56 -> 51, and 53 from four on); and where
-//   channels and filters are whole words, of up to 128 channels always (32 / 1 51 -> 36, 64 / 1 51 -> 40), up to 256 where the pooling goes
-//   along (96 / 1 51 -> 45); beyond that the sliced kernel's sixteen waves a tile are the faster ones (200 / 1 of 16 x 16 55 -> 73, 256 / 1 54 -> 74).
+// Tiles of 128 x 128 from which on a map is read by the kernels of whole tiles, against the sliced kernel, on the plane too or (channels that are no
+// whole words, larger tiles) on the 2-bit code (App. A ConvNets, width / images of 16 x 16 to 32 x 32, us):
+//   Pixels that fit LDS (qnn_gemm_image.hip), against the plane: from 40 on, where its 32 x 32 tiles end (128 / 16 of 32 x 32 52.0 -> 48.0 with the last
+//   three layers sliced, 128 / 8 44.6 -> 43.0, 128 / 64 56.2 and 55.2; with the line at 64 and the 2-bit code between 96 / 32 50.7 -> 66.4); with whole
+//   words, of up to 64 channels, always (32 / 1 36.8 -> 35.0, 64 / 8 38.1 -> 37.5; 96 / 1 38.5 against 40.4).
+//   Against the 2-bit code: from 16 on (128 / 16 of 32 x 32 66 -> 52, 128 / 8 of 24 x 24 56 -> 51).
 //   Others: from 48 on (128 / 4, 16, 64, 256 of 32 x 32 57, 74, 83, 140 with the line there, 77, 78, 84, 143 with planes alone, 58, 86, 137, 209 with
-//   none, all before the kernel that holds the pixels in LDS).
+//   none, all before the kernels that hold the pixels in LDS or slice a plane).
 bool conv_map_preferred(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N, bool pooled) {
-    const int64_t tiles = ceil_div(B * H * Wd, kTile) * ceil_div(N, kTile), Cw = words_for(C);
+    const int64_t tiles = ceil_div(B * H * Wd, kTile) * ceil_div(N, kTile);
     if (!image::map_supports(B, H, Wd, C, N, pooled)) return tiles >= 48;
-    return tiles >= 16 || (C % 32 == 0 && N % 32 == 0 && Cw <= (pooled ? 8 : 4));
+    if (slice::map_supports(B, H, Wd, C, N, pooled)) return tiles >= 40 || (N % 32 == 0 && C <= 64);
+    return tiles >= 16;
 }
 
 int64_t conv_class_ld(int64_t N) { return ceil_div(N, kTile) * kTile; }

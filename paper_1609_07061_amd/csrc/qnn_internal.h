@@ -239,6 +239,12 @@ int launch_threshold_sign(const int32_t *C, int64_t ldc, int64_t M, int64_t N, c
 bool conv_map_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N);
 bool conv_map_preferred(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N, bool pooled);  // against the map's 2-bit code
 bool conv_map_pools(int64_t H, int64_t Wd);
+// The same convolution where tiles are few (qnn_gemm_slice.hip): thresholds as they are, flips not complemented.
+namespace slice {
+bool map_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N, bool pooled);
+int launch_map(const uint32_t *plane, int64_t B, int H, int Wd, int64_t C, const uint32_t *W, int64_t N, const int32_t *T, const uint8_t *flip, uint32_t *out,
+               int64_t ldo, const uint32_t *pool_and, bool pool_invert, hipStream_t s);
+}  // namespace slice
 int64_t conv_class_ld(int64_t N);
 int launch_conv_map(const uint32_t *plane, int64_t B, int H, int Wd, int64_t C, const uint32_t *W, int64_t N, const uint8_t *flip_complement,
                     uint32_t *out, int64_t ldo, const int32_t *class_thr, const uint32_t *pool_and, bool pool_invert, hipStream_t s);
