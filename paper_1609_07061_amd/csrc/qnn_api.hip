@@ -926,6 +926,7 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
         uint32_t *kept_bits = inverted ? kept + B * ho * wo * Cwo : kept;  // where the output bits go
         uint32_t *conv_dst = pool[l] ? words(L.tmp) : kept_bits;
         const uint8_t *fl = inverted ? reinterpret_cast<const uint8_t *>(ws + L.flag_inv[l]) : (flip ? flip[l] : nullptr);
+        if (l > 0 && (!aligned4(W[l]) || !aligned4(T[l]))) return fail(QNN_ERR_ALIGN, "convnet: W[%d] or T[%d] not 4-byte aligned", l, l);
         const int before = plan.n - 1;
         NetStep &st = push();
         st.kind = NetStep::kGemm;
