@@ -322,8 +322,9 @@ __device__ __forceinline__ void product(const GemmArgs &g, const ImageArgs &x, u
             load_next(kGroup);
             load_next(2u * kGroup);
         }
-        // (the first group has landed: the pixels were asked for behind it)
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        // The first group has landed, the two behind it may be on their way.  (Every wave waits for its own part of it: one without a pixel to stage has
+        // waited for no load so far.)
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(2 * BN / 64) : "memory");
         if (d == 0) {
 #pragma unroll
             for (int i = 0; i < NB; ++i)
