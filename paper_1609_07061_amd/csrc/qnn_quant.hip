@@ -527,30 +527,33 @@ extern "C" int qnn_binary_backward(const uint32_t *G, int Pg, const int32_t *coe
     const size_t need = qnn_binary_backward_workspace_bytes(M, N, K, Pg);
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) || workspace_bytes < need)
         return fail(QNN_ERR_WORKSPACE, "binary_backward: workspace NULL, misaligned or smaller than %zu bytes", need);
-    // the products check the int32 range themselves, but only at their launch: do it here so that nothing is enqueued
+    // the products check all this themselves, but only at their launch: do it here so that nothing is enqueued, and nothing read
+    if (modeG != QNN_PLANE_BIT && modeG != QNN_PLANE_SIGN) return fail(QNN_ERR_SHAPE, "binary_backward: unknown plane mode %d", modeG);
+    // Gradient planes in bit mode are zero beyond the matrix, so the reduction may run over whole groups of four words
+    // (the products' 16-byte load paths) whatever the other operand holds there; the transposes write that padding.
+    const bool pad = modeG == QNN_PLANE_BIT;
+    const int64_t ldn = padded_words(N), ldm = padded_words(M), red_m = pad ? ldm * 32 : M;  // red_m: what g_W is summed over
+    if (N > 0x7FFFFFFFLL || red_m > 0x7FFFFFFFLL) return fail(QNN_ERR_SHAPE, "binary_backward: M or N out of range");
+    if (Pg > 1 && strideG_words < 0) return fail(QNN_ERR_SHAPE, "binary_backward: negative plane stride");
+    if (!aligned4(G) || !aligned4(W) || !aligned4(A) || !aligned4(gA) || !aligned4(gW))
+        return fail(QNN_ERR_ALIGN, "binary_backward: pointer not 4-byte aligned");
     long double sg = 0;
     for (int p = 0; p < Pg; ++p) sg += coefG[p] < 0 ? -(long double)coefG[p] : coefG[p];
     if (sg * (long double)((M > N ? M : N) + 127) >= 2147483648.0L)
         return fail(QNN_ERR_OVERFLOW, "binary_backward: gradient sums may exceed int32");
     uint8_t *ws = static_cast<uint8_t *>(workspace);
-    const int64_t ldn = padded_words(N), ldm = padded_words(M);
     uint32_t *Wt = reinterpret_cast<uint32_t *>(ws);
     uint32_t *At = reinterpret_cast<uint32_t *>(ws + round_up_256((size_t)K * ldn * 4));
     uint32_t *Gt = reinterpret_cast<uint32_t *>(ws + round_up_256((size_t)K * ldn * 4) + round_up_256((size_t)K * ldm * 4));
     const int32_t one = 1;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // Gradient planes in bit mode are zero beyond the matrix, so the reduction may run over whole groups of four words
-    // (the products' 16-byte load paths) whatever the other operand holds there; the transposes write that padding.
-    const bool pad = modeG == QNN_PLANE_BIT;
     int rc;
     BackwardArgs b;
     b.pg.count = Pg, b.pg.mode = modeG;
     for (int p = 0; p < Pg; ++p) b.pg.coef[p] = coefG[p];
     b.G = G, b.W = W, b.A = A, b.ldg = ldg_words, b.strideG = Pg > 1 ? strideG_words : 0, b.ldw = ldw_words, b.lda = lda_words;
     b.gA = gA, b.gW = gW, b.ld_ga = ld_ga, b.ld_gw = ld_gw, b.M = M, b.N = N, b.K = K;
-    // (what the products refuse is left to them)
-    const bool valid = (modeG == QNN_PLANE_BIT || modeG == QNN_PLANE_SIGN) && b.strideG >= 0 && aligned4(G) && aligned4(gA) && aligned4(gW);
-    if (valid && backward_mixed_preferred(b)) {
+    if (backward_mixed_preferred(b)) {
         bool no_memory;
         rc = mixed::launch_backward(b, workspace, workspace_bytes, no_memory, st);
         if (rc == QNN_OK) note_engine(QNN_ENGINE_MFMA_LDS);
@@ -559,7 +562,6 @@ extern "C" int qnn_binary_backward(const uint32_t *G, int Pg, const int32_t *coe
     }
     // g_a = g W: the reduction runs over n, so W (N x K, packed along k) is needed packed along n; g_W = g^T a: over the samples m, so both
     // operands are needed packed along m
-    const int64_t red_m = pad ? ldm * 32 : M;
     const int64_t strideG = Pg > 1 ? strideG_words : 0, words_n = pad ? ldn : words_for(N), words_m = pad ? ldm : words_for(M);
     const TransposeJobs jobs = {{transpose_job(W, N, K, ldw_words, 0, 1, Wt, ldn, 0, words_n), transpose_job(G, M, N, ldg_words, strideG, Pg, Gt, ldm, N * ldm, words_m),
                                  transpose_job(A, M, K, lda_words, 0, 1, At, ldm, 0, words_m)}};
