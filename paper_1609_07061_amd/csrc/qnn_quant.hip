@@ -351,11 +351,16 @@ __global__ __launch_bounds__(kBlock) void transpose_bits_tile_kernel(const uint3
 bool aligned4(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 3u) == 0; }
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// large matrices whose rows are made of whole, aligned 16-byte groups: the tiled kernel
+bool takes_tiles(const uint32_t *in, int64_t rows, int64_t cols, int64_t ld_in, int64_t in_plane_stride, const uint32_t *out, int64_t ld_out,
+                 int64_t out_plane_stride) {
+    return rows >= 256 && cols >= 256 && ld_in % 4 == 0 && ld_out % 4 == 0 && in_plane_stride % 4 == 0 && out_plane_stride % 4 == 0 && aligned16(in) &&
+           aligned16(out);
+}
+
 int launch_transpose(const uint32_t *in, int64_t rows, int64_t cols, int64_t ld_in, int64_t in_plane_stride, int nplanes,
                      uint32_t *out, int64_t ld_out, int64_t out_plane_stride, int64_t out_words, hipStream_t s) {
-    // large matrices whose rows are made of whole, aligned 16-byte groups: the tiled kernel
-    if (rows >= 256 && cols >= 256 && ld_in % 4 == 0 && ld_out % 4 == 0 && in_plane_stride % 4 == 0 && out_plane_stride % 4 == 0 &&
-        aligned16(in) && aligned16(out)) {
+    if (takes_tiles(in, rows, cols, ld_in, in_plane_stride, out, ld_out, out_plane_stride)) {
         // (the tiles cover out_words words of every output row: what lies beyond the input's rows is written as zeros)
         const int64_t tiles_r = ceil_div(out_words * 32, (int64_t)kTrRows), tiles_c = ceil_div(words_for(cols), (int64_t)kTrWords);
         const int64_t tiles = tiles_r * tiles_c;
@@ -371,6 +376,9 @@ int launch_transpose(const uint32_t *in, int64_t rows, int64_t cols, int64_t ld_
 // The three transpositions of a backward step on bit planes in one launch (three launches of 3 to 4 us each depend on the one before, which is most of what
 // a small step takes: 73 x 384 x 640 29 -> 23 us, 303 x 2752 x 384 48 -> 31).  A thread takes 32 rows x one word, a workgroup 256 rows x 32 words, any layout; eight threads
 // write the eight words of an output row.
+// Not for gradients of more than 1.2e9 bits that the tiled kernel takes, launch by launch (whole step, K = 64, us, launches apart / joint: 8192 x 65536, 4 planes
+// 441 / 468, 1 plane 115 / 96; 16384 x 16384, 4 planes 203 / 183; K = 1024: 20480 x 20480, 8 planes 1893 / 1944, 4 planes 963 / 987; rows of no whole
+// groups, 30000 x 30000 x 96, 4 planes, 2822 / 873).
 struct TransposeJob {
     const uint32_t *in;
     uint32_t *out;
@@ -563,12 +571,18 @@ extern "C" int qnn_binary_backward(const uint32_t *G, int Pg, const int32_t *coe
     // g_a = g W: the reduction runs over n, so W (N x K, packed along k) is needed packed along n; g_W = g^T a: over the samples m, so both
     // operands are needed packed along m
     const int64_t strideG = Pg > 1 ? strideG_words : 0, words_n = pad ? ldn : words_for(N), words_m = pad ? ldm : words_for(M);
-    const TransposeJobs jobs = {{transpose_job(W, N, K, ldw_words, 0, 1, Wt, ldn, 0, words_n), transpose_job(G, M, N, ldg_words, strideG, Pg, Gt, ldm, N * ldm, words_m),
-                                 transpose_job(A, M, K, lda_words, 0, 1, At, ldm, 0, words_m)}};
-    uint64_t blocks = 0;
-    for (const TransposeJob &j : jobs.job) blocks += (uint64_t)j.across * j.down * (&j == &jobs.job[1] ? Pg : 1);
-    if (blocks > 0x7FFFFFFFULL) return fail(QNN_ERR_SHAPE, "binary_backward: too many elements");
-    if ((rc = QNN_LAUNCH("transpose_bits", transpose_jobs_kernel, dim3((unsigned)blocks), dim3(256), 0, st, jobs))) return rc;
+    if ((double)Pg * (double)M * (double)N > 1.2e9 && takes_tiles(G, M, N, ldg_words, strideG, Gt, ldm, N * ldm)) {
+        if ((rc = launch_transpose(W, N, K, ldw_words, 0, 1, Wt, ldn, 0, words_n, st))) return rc;
+        if ((rc = launch_transpose(G, M, N, ldg_words, strideG, Pg, Gt, ldm, N * ldm, words_m, st))) return rc;
+        if ((rc = launch_transpose(A, M, K, lda_words, 0, 1, At, ldm, 0, words_m, st))) return rc;
+    } else {
+        const TransposeJobs jobs = {{transpose_job(W, N, K, ldw_words, 0, 1, Wt, ldn, 0, words_n), transpose_job(G, M, N, ldg_words, strideG, Pg, Gt, ldm, N * ldm, words_m),
+                                     transpose_job(A, M, K, lda_words, 0, 1, At, ldm, 0, words_m)}};
+        uint64_t blocks = 0;
+        for (const TransposeJob &j : jobs.job) blocks += (uint64_t)j.across * j.down * (&j == &jobs.job[1] ? Pg : 1);
+        if (blocks > 0x7FFFFFFFULL) return fail(QNN_ERR_SHAPE, "binary_backward: too many elements");
+        if ((rc = QNN_LAUNCH("transpose_bits", transpose_jobs_kernel, dim3((unsigned)blocks), dim3(256), 0, st, jobs))) return rc;
+    }
     if ((rc = qnn_bitplane_gemm(G, Pg, coefG, modeG, ldg_words, strideG_words, Wt, 1, &one, QNN_PLANE_SIGN, ldn, 0, gA, ld_ga,
                                 M, K, N, stream)))
         return rc;
