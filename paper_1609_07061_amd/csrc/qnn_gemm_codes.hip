@@ -56,6 +56,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_codes_kernel(const GemmArgs 
     int32_t *const start_tab = thr_tab + 2 * kTable;
 #pragma unroll
     for (uint32_t h = 0; h < kTable; h += 64) flip_tab[h + lane] = 0u;  // flip flags default to "none"
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (before the loads that write the same words)
     auto opaque = [](uint32_t v) __attribute__((always_inline)) {  // keeps address arithmetic where it is used
         asm volatile("" : "+v"(v));
         return v;

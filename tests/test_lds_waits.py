@@ -1,5 +1,6 @@
-"""The convolution kernels that hold a tile's pixels in LDS: every wave waits for its own part of the filters before a barrier behind which others read
-it, also a wave that stages no pixel because the tile has few of them."""
+"""Waits that order LDS writes.  The convolution kernels that hold a tile's pixels in LDS: every wave waits for its own part of the filters before a
+barrier behind which others read it, also a wave that stages no pixel because the tile has few of them.  The kernel of uint8 codes: flip flags are
+cleared before the loads that bring them in are sent."""
 import os
 import re
 import subprocess
@@ -33,6 +34,15 @@ def test_barriers_count_loads(tmp_path):
     for name, code in kernels.items():
         waits = [code[i - 1] for i, instruction in enumerate(code) if instruction.startswith("s_barrier")]
         assert waits and all(re.match(r"s_waitcnt vmcnt\(\d+\) lgkmcnt\(0\)", w) for w in waits), (name, waits)
+
+
+def test_flags_are_cleared_before_they_arrive(tmp_path):
+    kernels = {name: code for name, code in _kernels("qnn_gemm_codes.hip", tmp_path).items() if "gemm_codes_kernel" in name}
+    assert len(kernels) == 2
+    for name, code in kernels.items():
+        cleared = min(i for i, instruction in enumerate(code) if instruction.startswith("ds_write"))
+        sent = min(i for i, instruction in enumerate(code) if instruction.startswith("global_load_lds_"))
+        assert cleared < sent and any(re.match(r"s_waitcnt.*lgkmcnt\(0\)", i) for i in code[cleared:sent] if "vmcnt" not in i), name
 
 
 @pytest.mark.gpu
