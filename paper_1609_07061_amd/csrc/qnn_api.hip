@@ -431,10 +431,10 @@ int plan_mlp(const uint8_t *x, int64_t batch, int64_t ldx, int in_bits, int n_la
         g.M = batch, g.N = dims[1], g.K = dims[0], g.Kw = words_for(dims[0]);
         if (int rc = check_range(g)) return rc;
         // The plane area of the workspace is free where codes are multiplied: if it holds them, the weights go there as bits in the order of the
-        // operands, with their row sums.  Otherwise few rows go to the kernel without an image, more to the one that expands bits per wave.
+        // operands, with their row sums.  Otherwise few tiles go to the kernel without an image, more to the one that expands bits per wave.
         const size_t ib = round256(codes::image_bytes(dims[1], dims[0]));
         const bool has_image = ib + round256((size_t)dims[1] * 4) <= off;
-        if (engine == QNN_ENGINE_AUTO && codes::small_preferred(g, mfma_preferred(g), has_image)) {
+        if (engine == QNN_ENGINE_AUTO && codes::small_preferred(g, mfma_preferred(g) && mfma_supports(g), has_image)) {
             if (!aligned4(W[0]) || !aligned4(T[0])) return fail(QNN_ERR_ALIGN, "mlp: pointer not 4-byte aligned");
             plan.engine[0] = QNN_ENGINE_MFMA;
             plan.pack_planes = false, plan.few_rows = true;

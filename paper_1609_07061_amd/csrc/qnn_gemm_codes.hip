@@ -381,11 +381,15 @@ bool supports(const GemmArgs &g) {
     return g.A.rows_are_bytes && g.w_image && g.rw_scaled && g.epi.T && g.K < 131072 && (long double)g.M * g.A.ld < 4294967296.0L && g.N < 0x7FFFFFF0;
 }
 
-// Forward step with a 10-neuron second layer, us, otherwise / this.  No room for the image, so that bits would be expanded per wave: always (4096 neurons,
-// 784 codes, 300 rows 37.3 / 23.4; 3072 codes, 500 rows 79 / 50; 32 codes, 512 neurons, 4000 rows 27.6 / 7.8).  Where bit planes would be packed: sums
-// beyond 2^24, for which only the VALU is left, always (65536 codes, 512 neurons, 200 rows 2530 / 122); otherwise up to 8192 codes and
-// 49152 steps of 32 codes (784 codes, 512 neurons: 32 rows 14.0 / 10.6, 3000 rows 27.3 / 19.1; 3072 codes, 512 neurons, 1000 rows 22.9 / 17.4; beyond that
-// 4096 neurons, 200 rows 27.0 / 28.7; 12288 codes, 512 neurons, 32 rows 26.6 / 27.1, 2000 rows 73 / 91).
+// Forward step with a 10-neuron second layer, us, otherwise / this.
+//   No room for the image, so that bits would be expanded per wave by tiles of 256 x 256: up to 3840 tiles of up to 1024 codes, 2816 of more, whatever the
+//   rows (784 codes: 300 rows, 4096 neurons 37.3 / 23.4, 500 rows, 7400 neurons 28.8 / 24.1, beyond it 500 rows, 32768 neurons 40.5 / 80.7; 3072 codes: 500
+//   rows, 5376 neurons 78 / 65, 7392 neurons 79 / 87; 8192 codes, 1000 rows, 65536 neurons 746 / 3565).
+//   Bit planes otherwise: sums beyond 2^24, for which only the VALU is left, always (65536 codes, 512 neurons, 200 rows 2530 / 122).  Otherwise up
+//   to 8192 codes and 49152 steps of 32 codes (784 codes, 512 neurons: 32 rows 14.0 / 10.6, 3000 rows 27.3 / 19.1; 3072 codes, 512 neurons, 1000 rows
+//   22.9 / 17.4; beyond that 4096 neurons, 200 rows 27.0 / 28.7; 12288 codes, 512 neurons, 32 rows 26.6 / 27.1, 2000 rows 73 / 91), and of up to 256 codes
+//   in rows of whole 128-byte lines up to 20480 (128 codes: 600 rows, 6720 neurons 21.3 / 19.4, 10944 neurons 22.5 / 27.0, but 112 codes 22.5 / 20.2, and 27.6 in
+//   rows of 128; 256 codes: 100 rows, 8192 neurons 15.6 / 12.2, 32768 neurons 25.9 / 29.6).
 bool small_preferred(const GemmArgs &g, bool large, bool has_image) {
     if (large && has_image) return false;
     if (!(g.A.rows_are_bytes && g.epi.T && g.K < 131072 && g.K % 16 == 0 && g.A.ld % 16 == 0 && reinterpret_cast<uintptr_t>(g.A.base) % 16 == 0 &&
@@ -393,7 +397,9 @@ bool small_preferred(const GemmArgs &g, bool large, bool has_image) {
         return false;
     const int64_t tiles = ceil_div(g.M, 32) * ceil_div(g.N, 32), steps = ceil_div(g.K, 32);
     if (tiles >= 1 << 24) return false;
-    return large || 255 * g.K > 1 << 24 || (steps <= 256 && tiles * steps <= 49152);
+    if (large) return tiles <= (steps <= 32 ? 3840 : 2816);
+    if (255 * g.K > 1 << 24) return true;
+    return steps <= 256 && tiles * steps <= (steps <= 8 && g.A.ld % 128 == 0 ? 20480 : 49152);
 }
 
 int launch_small(const GemmArgs &g, hipStream_t s) {
