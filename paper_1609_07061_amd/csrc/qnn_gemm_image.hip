@@ -566,13 +566,26 @@ bool conv_supports(const GemmArgs &g) {
     return blocks(B, g.A.H, g.A.Wd, 32 * (int64_t)g.A.Cw, g.N, false, (g.pa.count + 1) / 2) != 0;
 }
 
-// From 128 tiles of 128 x 128 on (150 convolutions of 1 to 256 images of 6 x 6 to 28 x 28, 64 to 384 channels and filters, 1, 2 and 4 bits: 1.0 to 2.0
-// times as fast there as on the tiled kernel but for five of them, 0.88 to 0.97; 37 x 28 x 28, 64 -> 192, 4 bits 23.3 -> 11.7 us, 202 x 15 x 15, 238 -> 128,
-// 2 bits 22.1 -> 13.8, 256 x 13 x 13, 384 -> 256, 2 bits 30.2 -> 26.8; below on the sliced kernel 0.3 to 1.1), and not where half of a tile's 128
-// filters are missing and the patches are long (255 x 21 x 21, 207 -> 64, 1 bit 17.5 against 21.2; 54 x 28 x 28, 128 -> 64, 2 bits 11.1 -> 9.1).
+// From 128 tiles of 128 x 128 on (1090 convolutions of 1 to 1000 images of 6 x 6 to 112 x 112, 3 to 384 channels, 8 to 701 filters, 1, 2 and 4 bits: 0.93
+// to 7 times as fast there as on the tiled kernel, us there / here: 37 x 28 x 28, 64 -> 192, 4 bits 23.3 / 11.7; 202 x 15 x 15, 238 -> 128, 2 bits 22.1 / 13.8; 256
+// x 13 x 13, 384 -> 256, 2 bits 30.2 / 23.8; below on the sliced kernel 0.3 to 1.1), but not
+//   * where half of a tile's 128 filters are missing and the patches are long (255 x 21 x 21, 207 -> 64, 1 bit 17.5 / 21.2; 54 x 28 x 28, 128 -> 64, 2 bits
+//     11.1 / 9.1);
+//   * for int32 sums where three quarters are missing (35 x 32 x 32, 128 -> 32, 2 bits 6.5 / 9.5, 32 -> 8, 1 bit 5.9 / 7.3), nor on one bit where the 64 are not
+//     full (66 x 56 x 56, 32 -> 48 21.5 / 28.1) or the patch has more than two words a tap (24 x 24, 128 -> 64 7.9 / 8.7, 64 -> 64 8.5 / 7.5), nor on two where they are
+//     not full and it has more than three (131 x 14 x 14, 128 -> 48 7.6 / 8.8);
+//   * for one or two bits and sums beyond the cache in rows of no whole lines that three tiles and more share: a line's parts reach memory apart there
+//     (79 x 64 x 64, 9 -> 331, 1 bit, 428 MB 154 / 209, 332 filters 157 / 167; 300 x 28 x 28, 311 MB 117 / 90).
 bool conv_preferred(const GemmArgs &g) {
     if (ceil_div(g.M, 128) * ceil_div(g.N, 128) < 128) return false;
-    return (g.N > 64 || (int64_t)g.A.Cw * ((g.pa.count + 1) / 2) <= 4) && conv_supports(g);
+    const int64_t words = (int64_t)g.A.Cw * ((g.pa.count + 1) / 2);
+    const bool sums = g.epi.T == nullptr;
+    if (g.N <= 64 && words > 4) return false;
+    if (sums && g.N <= 32) return false;
+    if (sums && g.N <= 64 && g.pa.count == 1 && (g.N < 64 || words > 2)) return false;
+    if (sums && g.N < 64 && g.pa.count == 2 && words > 3) return false;
+    if (sums && g.N > 256 && g.N % 32 != 0 && g.pa.count <= 2 && (g.N % 4 != 0 || words == 1) && 4.0 * (double)g.M * (double)g.N > 384e6) return false;
+    return conv_supports(g);
 }
 
 int launch_conv(const GemmArgs &given, hipStream_t s) {
