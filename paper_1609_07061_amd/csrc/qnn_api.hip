@@ -858,41 +858,41 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
         plan.flags.bits[l] = words(L.flag_bits[l]);
         plan.flags.inv[l] = ws + L.flag_inv[l];
     }
-    // whether a convolution (not the first) reads its map as the plane "value is -1" (tiled FP4 kernel) or as the 2-bit code
-    auto on_plane = [&](int64_t hh, int64_t ww, int64_t cc, int l) {
-        const int64_t co = cout[l];
-        return (engine == QNN_ENGINE_AUTO || engine == QNN_ENGINE_MFMA_FP4) && conv_map_supports(B, hh, ww, cc, co) &&
-               (engine != QNN_ENGINE_AUTO || conv_map_preferred(B, hh, ww, cc, co, pool[l] != 0));
-    };
-    // ... and whether that kernel finds room for its pixels in LDS, with the pooling that follows or without
-    auto in_lds = [&](int64_t hh, int64_t ww, int64_t cc, int64_t co, bool pooled) { return image::map_supports(B, hh, ww, cc, co, pooled); };
-    // ... or where tiles are few, on the sliced kernel; all of these need the one plane alone
-    auto on_slice = [&](int64_t hh, int64_t ww, int64_t cc, int l) {
-        return engine == QNN_ENGINE_AUTO && !on_plane(hh, ww, cc, l) && slice::map_supports(B, hh, ww, cc, cout[l], pool[l] != 0);
-    };
-    auto reads_plane = [&](int64_t hh, int64_t ww, int64_t cc, int l) { return on_plane(hh, ww, cc, l) || on_slice(hh, ww, cc, l); };
-    // whether a convolution's output is pooled along (without that kernel not where the next one reads a 2-bit code, whose other plane the pooling
-    // kernel writes)
-    auto pools_along = [&](int l, int64_t hh, int64_t ww, int64_t cc) {
-        if (!pool[l] || !reads_plane(hh, ww, cc, l)) return false;
-        if (on_plane(hh, ww, cc, l) && in_lds(hh, ww, cc, cout[l], true)) return true;
-        if (on_plane(hh, ww, cc, l) && !conv_map_pools(hh, ww)) return false;
-        return l + 1 >= n_conv || reads_plane(hh / 2, ww / 2, cout[l], l + 1);
-    };
-    // thresholds per border class of the convolutions on planes whose pixels do not fit there
-    plan.prep.count = 0;
+    // How each convolution (not the first) reads its map and what is done along, worked out once per call, last layer first.
+    struct Route {
+        bool on_map;    // as the plane "value is -1", on the kernels of whole tiles
+        bool on_slice;  // ... where tiles are few, on the sliced kernel (neither: the 2-bit code)
+        bool in_lds;    // on_map: the tile's pixels find room in LDS, pooled along or not as `pools` says
+        bool pools;     // the max-pooling is done along
+    } route[kMaxNetLayers + 1] = {};
+    int64_t hs[kMaxNetLayers], wds[kMaxNetLayers], cs[kMaxNetLayers];  // input maps
     {
         int64_t hh = H, ww = Wd, cc = C0;
         for (int l = 0; l < n_conv; ++l) {
-            if (l > 0 && on_plane(hh, ww, cc, l) && !in_lds(hh, ww, cc, cout[l], pools_along(l, hh, ww, cc))) {
-                const int j = plan.prep.count++;
-                plan.prep.W[j] = W[l], plan.prep.T[j] = T[l];
-                plan.prep.out[j] = reinterpret_cast<int32_t *>(ws + L.class_thr[l]);
-                plan.prep.N[j] = cout[l], plan.prep.ld[j] = conv_class_ld(cout[l]);
-                plan.prep.Cw[j] = (int)words_for(cc), plan.prep.C[j] = cc;
-            }
+            hs[l] = hh, wds[l] = ww, cs[l] = cc;
             if (pool[l]) hh /= 2, ww /= 2;
             cc = cout[l];
+        }
+    }
+    plan.prep.count = 0;
+    for (int l = n_conv - 1; l > 0 && (engine == QNN_ENGINE_AUTO || engine == QNN_ENGINE_MFMA_FP4); --l) {
+        const int64_t hh = hs[l], ww = wds[l], cc = cs[l], co = cout[l];
+        const bool pooled = pool[l] != 0, whole_tiles = conv_map_supports(B, hh, ww, cc, co);
+        const bool fits = whole_tiles && image::map_supports(B, hh, ww, cc, co, pooled);
+        const bool sliced = engine == QNN_ENGINE_AUTO && slice::map_supports(B, hh, ww, cc, co, pooled);
+        Route &r = route[l];
+        r.on_map = whole_tiles && (engine != QNN_ENGINE_AUTO || conv_map_preferred(B, hh, ww, cc, co, fits, sliced));
+        r.on_slice = sliced && !r.on_map;
+        // (without the kernel that holds pixels in LDS not where the next one reads a 2-bit code, whose other plane the pooling kernel writes)
+        if (pooled && (r.on_map || r.on_slice))
+            r.pools = (r.on_map && fits) || ((r.on_slice || conv_map_pools(hh, ww)) && (l + 1 >= n_conv || route[l + 1].on_map || route[l + 1].on_slice));
+        r.in_lds = r.on_map && (r.pools == pooled ? fits : image::map_supports(B, hh, ww, cc, co, false));
+        if (r.on_map && !r.in_lds) {  // thresholds per border class
+            const int j = plan.prep.count++;
+            plan.prep.W[j] = W[l], plan.prep.T[j] = T[l];
+            plan.prep.out[j] = reinterpret_cast<int32_t *>(ws + L.class_thr[l]);
+            plan.prep.N[j] = co, plan.prep.ld[j] = conv_class_ld(co);
+            plan.prep.Cw[j] = (int)words_for(cc), plan.prep.C[j] = cc;
         }
     }
     // The first convolution multiplies the 8-bit codes themselves when a pixel's patch fits one matrix-core operand
@@ -931,12 +931,11 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
         NetStep &st = push();
         st.kind = NetStep::kGemm;
         const Epilogue e{nullptr, 0, T[l], fl, conv_dst, Cwo};
-        const bool on_map = l > 0 && on_plane(h, w, cin, l);
+        const bool on_map = route[l].on_map, pooled_along = route[l].pools, map_in_lds = route[l].in_lds;
         // the next convolution reads this layer's output: as a plane it takes "value is -1" alone,
         // otherwise the 2-bit code, whose plane "inside the image" is then written too
-        const bool ones_needed = inverted && !reads_plane(ho, wo, co, l + 1);
-        const bool pooled_along = l > 0 && pools_along(l, h, w, cin);
-        const bool map_in_lds = on_map && in_lds(h, w, cin, co, pooled_along), ones_along = map_in_lds && ones_needed && pooled_along == (pool[l] != 0);
+        const bool ones_needed = inverted && !(route[l + 1].on_map || route[l + 1].on_slice);
+        const bool ones_along = map_in_lds && ones_needed && pooled_along == (pool[l] != 0);
         if (on_map) {
             st.kind = NetStep::kConvMap;
             st.src = a_planes + a_stride, st.w = W[l], st.dst = pooled_along ? kept_bits : conv_dst, st.dst2 = map_in_lds ? nullptr : ws + L.class_thr[l];
@@ -945,7 +944,7 @@ int qnn_binary_convnet_forward(const uint8_t *x, int64_t B, int64_t H, int64_t W
             st.g.epi = e;
             st.g.epi.flip = inverted ? (flip ? flip[l] : nullptr) : reinterpret_cast<const uint8_t *>(ws + L.flag_inv[l]);
             if (pooled_along) st.mask = words(L.flag_bits[l]), st.invert = inverted;
-        } else if (l > 0 && on_slice(h, w, cin, l)) {
+        } else if (route[l].on_slice) {
             st.kind = NetStep::kConvSlice;
             st.src = a_planes + a_stride, st.w = W[l], st.dst = pooled_along ? kept_bits : conv_dst;
             st.rows = B, st.a = (int)h, st.b = (int)w, st.c = (int)cin, st.n = co;

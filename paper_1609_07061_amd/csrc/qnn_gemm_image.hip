@@ -515,36 +515,43 @@ bool plan(int64_t B, int64_t H, int64_t W, int64_t C, int64_t N, bool pooled, in
 // instructions of all that share a compute unit (us; of App. A's layers on 256 images, 4 / 2: 32 x 32, 128 -> 128 channels, 1024 / 2048 tiles,
 // 19.7 / 22.7; 16 x 16, 128 -> 256, 512 / 1024, 11.1 / 12.8, 256 -> 256 18.3 / 19.6; 8 x 8, 256 -> 512, 256 / 512, 13.0 / 11.7).  0: the pixels
 // do not fit.
-static int blocks(int64_t B, int64_t H, int64_t W, int64_t C, int64_t N, bool pooled, int digits) {
-    int best = 0;
+struct Plan {
+    int PB;
+    ImageArgs x;
+    int64_t M, lds_bytes;
+};
+static int blocks(int64_t B, int64_t H, int64_t W, int64_t C, int64_t N, bool pooled, int digits, Plan &best) {
+    best.PB = 0;
     double least = 0.0;
     const int64_t cus = compute_units();
     for (int PB = 2; PB <= 4; PB += 2) {
-        ImageArgs x;
-        int64_t M, lds_bytes;
-        if (!plan(B, H, W, C, N, pooled, PB, M, x, lds_bytes)) continue;
-        const int64_t tiles = (int64_t)x.tiles_m * x.tiles_n, per = PB == 2 && 3 * lds_bytes <= 160 * 1024 ? 3 : 2, rest = tiles % (per * cus);
+        Plan p;
+        p.PB = PB;
+        if (!plan(B, H, W, C, N, pooled, PB, p.M, p.x, p.lds_bytes)) continue;
+        const int64_t tiles = (int64_t)p.x.tiles_m * p.x.tiles_n, per = PB == 2 && 3 * p.lds_bytes <= 160 * 1024 ? 3 : 2, rest = tiles % (per * cus);
         const double own = PB == 2 ? 3.0 : 3.6, products = 0.0134 * PB * 9.0 * (double)words_for(C) * digits;
         const double us = (double)(tiles / (per * cus)) * (own + (double)per * products) + (rest ? own + (double)ceil_div(rest, cus) * products : 0.0);
-        if (best == 0 || us < least) best = PB, least = us;
+        if (best.PB == 0 || us < least) best = p, least = us;
     }
-    return best;
+    return best.PB;
 }
 
-bool map_supports(int64_t B, int64_t H, int64_t W, int64_t C, int64_t N, bool pooled) { return 9 * C < (1 << 21) && blocks(B, H, W, C, N, pooled, 1) != 0; }
+bool map_supports(int64_t B, int64_t H, int64_t W, int64_t C, int64_t N, bool pooled) {
+    Plan p;
+    return 9 * C < (1 << 21) && blocks(B, H, W, C, N, pooled, 1, p) != 0;
+}
 
 int launch_map(const uint32_t *plane, int64_t B, int H, int W, int64_t C, const uint32_t *filters, int64_t N, const int32_t *T, const uint8_t *flip_complement,
                uint32_t *out, uint32_t *ones, int64_t ldo, const uint32_t *pool_and, bool pool_invert, hipStream_t s) {
-    ImageArgs x;
+    Plan p;
+    ImageArgs &x = p.x;
+    if (blocks(B, H, W, C, N, pool_and != nullptr, 1, p) == 0) return fail(QNN_ERR_UNSUPPORTED, "convolution of a +-1 map: shape not supported");
     GemmArgs g;
     std::memset(&g, 0, sizeof(g));
-    int64_t lds_bytes;
-    const int PB = blocks(B, H, W, C, N, pool_and != nullptr, 1);
-    if (PB == 0 || !plan(B, H, W, C, N, pool_and != nullptr, PB, g.M, x, lds_bytes)) return fail(QNN_ERR_UNSUPPORTED, "convolution of a +-1 map: shape not supported");
-    g.N = N, g.K = 9 * C, g.Kw = 9 * words_for(C), g.W = filters;
+    g.M = p.M, g.N = N, g.K = 9 * C, g.Kw = 9 * words_for(C), g.W = filters;
     g.epi.T = T, g.epi.flip = flip_complement, g.epi.out_bits = out, g.epi.ldo = ldo;
     x.planes = plane, x.count = 1, x.flip_bytes = flip_complement ? (uint32_t)N : 0u, x.pool_and = pool_and, x.pool_invert = pool_invert ? 0xFFFFFFFFu : 0u, x.ones = ones;
-    return QNN_LAUNCH("conv_map", (PB == 4 ? tall::gemm_map_kernel<2, 2> : square::gemm_map_kernel<2, 2>), dim3(x.tiles_m * x.tiles_n), dim3(kThreads), (unsigned)lds_bytes, s, g, x);
+    return QNN_LAUNCH("conv_map", (p.PB == 4 ? tall::gemm_map_kernel<2, 2> : square::gemm_map_kernel<2, 2>), dim3(x.tiles_m * x.tiles_n), dim3(kThreads), (unsigned)p.lds_bytes, s, g, x);
 }
 
 // A convolution's arguments: images of bit planes 1, 2, 4, ... times a factor (0: something else), +-1 filters.
@@ -563,7 +570,8 @@ bool conv_supports(const GemmArgs &g) {
     // thresholds start the sums in halves: below 2^21; int32 sums are whole numbers below 2^24
     if (f == 0 || (g.epi.T && f != 1) || most >= (g.epi.T ? 1 << 21 : 1 << 24)) return false;
     const int64_t B = g.M / ((int64_t)g.A.H * g.A.Wd);
-    return blocks(B, g.A.H, g.A.Wd, 32 * (int64_t)g.A.Cw, g.N, false, (g.pa.count + 1) / 2) != 0;
+    Plan p;
+    return blocks(B, g.A.H, g.A.Wd, 32 * (int64_t)g.A.Cw, g.N, false, (g.pa.count + 1) / 2, p) != 0;
 }
 
 // From 128 tiles of 128 x 128 on (1090 convolutions of 1 to 1000 images of 6 x 6 to 112 x 112, 3 to 384 channels, 8 to 701 filters, 1, 2 and 4 bits: 0.93
@@ -572,7 +580,7 @@ bool conv_supports(const GemmArgs &g) {
 //   * where half of a tile's 128 filters are missing and the patches are long (255 x 21 x 21, 207 -> 64, 1 bit 17.5 / 21.2; 54 x 28 x 28, 128 -> 64, 2 bits
 //     11.1 / 9.1);
 //   * for int32 sums where three quarters are missing (35 x 32 x 32, 128 -> 32, 2 bits 6.5 / 9.5, 32 -> 8, 1 bit 5.9 / 7.3), nor on one bit where the 64 are not
-//     full (66 x 56 x 56, 32 -> 48 21.5 / 28.1) or the patch has more than two words a tap (24 x 24, 128 -> 64 7.9 / 8.7, 64 -> 64 8.5 / 7.5), nor on two where they are
+//     full (66 x 56 x 56, 64 -> 48 23.7 / 28.1) or the patch has more than two words a tap (24 x 24, 128 -> 64 7.9 / 8.7, 64 -> 64 8.5 / 7.5), nor on two where they are
 //     not full and it has more than three (131 x 14 x 14, 128 -> 48 7.6 / 8.8);
 //   * for one or two bits and sums beyond the cache in rows of no whole lines that three tiles and more share: a line's parts reach memory apart there
 //     (79 x 64 x 64, 9 -> 331, 1 bit, 428 MB 154 / 209, 332 filters 157 / 167; 300 x 28 x 28, 311 MB 117 / 90).
@@ -589,18 +597,17 @@ bool conv_preferred(const GemmArgs &g) {
 }
 
 int launch_conv(const GemmArgs &given, hipStream_t s) {
-    ImageArgs x;
+    Plan p;
+    ImageArgs &x = p.x;
     GemmArgs g = given;
-    int64_t lds_bytes, M;
     const int64_t B = g.M / ((int64_t)g.A.H * g.A.Wd), C = 32 * (int64_t)g.A.Cw;  // (what lies beyond the channels is zero bits)
-    const int PB = blocks(B, g.A.H, g.A.Wd, C, g.N, false, (g.pa.count + 1) / 2);
-    if (PB == 0 || !plan(B, g.A.H, g.A.Wd, C, g.N, false, PB, M, x, lds_bytes)) return fail(QNN_ERR_UNSUPPORTED, "convolution: shape not supported");
+    if (blocks(B, g.A.H, g.A.Wd, C, g.N, false, (g.pa.count + 1) / 2, p) == 0) return fail(QNN_ERR_UNSUPPORTED, "convolution: shape not supported");
     x.planes = g.A.base, x.plane_stride = (uint64_t)g.A.plane_stride, x.count = g.pa.count;
     x.flip_bytes = g.epi.flip ? (uint32_t)g.N : 0u, x.invert = 0xFFFFFFFFu;
     g.pa.coef[0] = factor(given);
-    auto kernel = g.epi.T ? (PB == 4 ? gemm_image_kernel<4, 2, true> : gemm_image_kernel<2, 2, true>)
-                          : (PB == 4 ? gemm_image_kernel<4, 2, false> : gemm_image_kernel<2, 2, false>);
-    return QNN_LAUNCH("conv_image", kernel, dim3(x.tiles_m * x.tiles_n), dim3(kThreads), (unsigned)lds_bytes, s, g, x);
+    auto kernel = g.epi.T ? (p.PB == 4 ? gemm_image_kernel<4, 2, true> : gemm_image_kernel<2, 2, true>)
+                          : (p.PB == 4 ? gemm_image_kernel<4, 2, false> : gemm_image_kernel<2, 2, false>);
+    return QNN_LAUNCH("conv_image", kernel, dim3(x.tiles_m * x.tiles_n), dim3(kThreads), (unsigned)p.lds_bytes, s, g, x);
 }
 
 }  // namespace image

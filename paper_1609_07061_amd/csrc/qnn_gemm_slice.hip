@@ -560,10 +560,12 @@ int launch_gemm_slice(const GemmArgs &g, hipStream_t s) {
 // with all that have few tiles; 1 image of 16 x 16 46.4 -> 38.6.
 namespace slice {
 static bool map_args(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N, bool pooled, GemmArgs &g, SliceArgs &sc) {
-    std::memset(&g, 0, sizeof(g));
     const int64_t Cw = words_for(C);
     if (B < 1 || H < 1 || Wd < 1 || H > 32767 || Wd > 32767 || C % 32 != 0 || C > (1 << 24) || N < 1 || (pooled && (H < 2 || Wd < 2))) return false;
     if (B > 0x7FFFFF00LL / (H * Wd)) return false;
+    const int64_t tiles64 = ceil_div(B * H * Wd, 64) * ceil_div(N, 64);
+    if (tiles64 >= 160 && B * H * Wd > 32 && N > 32) return false;
+    std::memset(&g, 0, sizeof(g));
     g.A.rows_are_pixels = 1;
     g.A.H = (int)H, g.A.Wd = (int)Wd, g.A.Ho = (int)H, g.A.Wo = (int)Wd, g.A.Cw = (int)Cw, g.A.KH = 3, g.A.KW = 3, g.A.pad = 1, g.A.stride = 1;
     g.pa.count = 1, g.pa.mode = QNN_PLANE_SIGN, g.pa.coef[0] = 1;
@@ -578,8 +580,7 @@ static bool map_args(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N, boo
         g.M = 4 * B * g.A.Ho * g.A.Wo;
         sc.inv_hw = inverse_of((int64_t)g.A.Ho * g.A.Wo), sc.inv_w = inverse_of(g.A.Wo);
     }
-    const int64_t tiles64 = ceil_div(B * H * Wd, 64) * ceil_div(N, 64);
-    return tiles64 < 160 || B * H * Wd <= 32 || N <= 32;
+    return true;
 }
 
 bool map_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N, bool pooled) {

@@ -375,10 +375,10 @@ bool conv_map_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N) {
 //   Against the 2-bit code: from 16 on (128 / 16 of 32 x 32 66 -> 52, 128 / 8 of 24 x 24 56 -> 51).
 //   Others: from 48 on (128 / 4, 16, 64, 256 of 32 x 32 57, 74, 83, 140 with the line there, 77, 78, 84, 143 with planes alone, 58, 86, 137, 209 with
 //   none, all before the kernels that hold the pixels in LDS or slice a plane).
-bool conv_map_preferred(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N, bool pooled) {
+bool conv_map_preferred(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N, bool in_lds, bool sliced) {
     const int64_t tiles = ceil_div(B * H * Wd, kTile) * ceil_div(N, kTile);
-    if (!image::map_supports(B, H, Wd, C, N, pooled)) return tiles >= 48;
-    if (slice::map_supports(B, H, Wd, C, N, pooled)) return tiles >= 40 || (N % 32 == 0 && C <= 64);
+    if (!in_lds) return tiles >= 48;
+    if (sliced) return tiles >= 40 || (N % 32 == 0 && C <= 64);
     return tiles >= 16;
 }
 

@@ -237,7 +237,7 @@ int launch_threshold_sign(const int32_t *C, int64_t ldc, int64_t M, int64_t N, c
 // launch_conv_first or launch_conv_class_thr (for all convolutions of a network at once).  The 2 x 2 max-pooling that follows is done along if
 // conv_map_pools (pool_and = packed flip flags of the filters, pool_invert = the map holds inverted bits; null: no pooling).
 bool conv_map_supports(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N);
-bool conv_map_preferred(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N, bool pooled);  // against the map's 2-bit code
+bool conv_map_preferred(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N, bool in_lds, bool sliced);  // ... image::, slice::map_supports
 bool conv_map_pools(int64_t H, int64_t Wd);
 // The same convolution where tiles are few (qnn_gemm_slice.hip): thresholds as they are, flips not complemented.
 namespace slice {
