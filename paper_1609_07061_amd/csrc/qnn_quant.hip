@@ -475,7 +475,9 @@ extern "C" int qnn_log_quant_planes(const float *x, const float *gate, int64_t r
         return fail(QNN_ERR_SHAPE, "log_quant_planes: %lld magnitudes do not fit %d-bit two's complement %s",
                     (long long)levels, nbits, as_value ? "values" : "codes");
     if (rows == 0) return QNN_OK;
-    if (emin >= -125 && emax <= 128)
+    // (many short rows leave most of a wave's elements beyond the row, zeros, which the other form is done with at once: 15000 x 64 16.1 -> 17.0 us here, x 128
+    // 1 - 4 % slower, x 160 0 - 2 % faster; 1000 rows of any length 2 - 18 % faster)
+    if (emin >= -125 && emax <= 128 && (K > 128 || rows <= 2048))
         return launch_quant("log_quant_planes", x, gate, rows, K, ldx, ld_gate,
                             LogQNormal{(int32_t)((uint32_t)(0x800000 - 0x3504F4) - ((uint32_t)(emin + 126) << 23)), emax - emin + 1, as_value ? 1 : 0}, nbits, planes,
                             ld_words, plane_stride_words, static_cast<hipStream_t>(stream));
