@@ -99,32 +99,32 @@ __device__ __forceinline__ void product(const GemmArgs &g, const ImageArgs &x, u
     const uint32_t pixels = (row1 + 2u - row0) * (x.W + 1u) + 1u, pieces = (x.Cw + 3u) / 4u;
     // Pixels to LDS, four words of a pixel per thread and turn: asked for, and put there
     constexpr int kAhead = kMap ? 4 : 2;  // pieces whose loads are on their way together
-            struct Piece {
-                u32x4 v0, v1;
-                uint8_t *dst;
-                uint32_t sign, plus_one, first;  // first: channel
-            };
-            const uint32_t count = pixels * pieces;
+    struct Piece {
+        u32x4 v0, v1;
+        uint8_t *dst;
+        uint32_t sign, plus_one, first;  // first: channel
+    };
+    const uint32_t count = pixels * pieces;
     auto load4 = [&](const uint32_t *base, const uint32_t at) __attribute__((always_inline)) {
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(base), 0, (int)x.plane_bytes, 0x00027000);
         return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)at, 0, 0));
     };
     auto ask = [&](const uint32_t d, const uint32_t i, Piece &p) __attribute__((always_inline)) {
-                const bool second = !kMap && 2u * d + 1u < (uint32_t)x.count;
+        const bool second = !kMap && 2u * d + 1u < (uint32_t)x.count;
         uint32_t piece, c, yy;
-                const uint32_t pixel = quotient(i, pieces, x.inv_pieces, piece), pr = quotient(pixel, x.W + 1u, x.inv_w1, c);
-                const uint32_t b = quotient(row0 + pr, x.H + 1u, x.inv_h1, yy);
-                const bool inside = yy != 0u && c != 0u && b < x.images;
-                // (outside the image: beyond the plane, which reads as zeros; a ragged pixel's last piece reads the next pixel's words along)
+        const uint32_t pixel = quotient(i, pieces, x.inv_pieces, piece), pr = quotient(pixel, x.W + 1u, x.inv_w1, c);
+        const uint32_t b = quotient(row0 + pr, x.H + 1u, x.inv_h1, yy);
+        const bool inside = yy != 0u && c != 0u && b < x.images;
+        // (outside the image: beyond the plane, which reads as zeros; a ragged pixel's last piece reads the next pixel's words along)
         const uint32_t src = inside && i < count ? (((b * x.H + yy - 1u) * x.W + c - 1u) * x.Cw + 4u * piece) * 4u : 0xFFFFFFF0u;
         const uint32_t *const p0 = x.planes + (kMap ? 0u : 2u * d * x.plane_stride);
         p.v0 = load4(p0, src);
         if constexpr (!kMap) p.v1 = load4(p0 + (second ? x.plane_stride : 0u), second ? src : 0xFFFFFFF0u);
         p.dst = lds + pixel * x.pitch + 64u * piece;
-                p.sign = inside ? 0x88888888u : 0u, p.plus_one = inside ? 0x22222222u : 0u;
-                p.first = 128u * piece;
-            };
-            const bool whole = x.C % 128u == 0u;  // pixels of whole pieces
+        p.sign = inside ? 0x88888888u : 0u, p.plus_one = inside ? 0x22222222u : 0u;
+        p.first = 128u * piece;
+    };
+    const bool whole = x.C % 128u == 0u;  // pixels of whole pieces
     auto put = [&](const Piece &p) __attribute__((always_inline)) {
         auto expand = [&](const int e) __attribute__((always_inline)) {
             u32x4 o;
@@ -452,24 +452,12 @@ __device__ __forceinline__ void product(const GemmArgs &g, const ImageArgs &x, u
 
 constexpr int waves_per_simd(int PB) { return PB == 2 ? 3 : 2; }
 
-// +-1 maps, WM x WN waves of 64 x 64 ...
-namespace square {
-template <int WM, int WN>
-__global__ __launch_bounds__(kThreads, waves_per_simd(2)) void gemm_map_kernel(const GemmArgs g, const ImageArgs x) {
-    static_assert(WM == 2 && WN == 2, "how `product` deals the tile out");
+// +-1 maps, 2 x 2 waves of 32 PB x 64
+template <int PB>
+__global__ __launch_bounds__(kThreads, waves_per_simd(PB)) void gemm_map_image_kernel(const GemmArgs g, const ImageArgs x) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    product<2, 2, true, true>(g, x, lds);
+    product<PB, 2, true, true>(g, x, lds);
 }
-}  // namespace square
-// ... and of 128 x 64
-namespace tall {
-template <int WM, int WN>
-__global__ __launch_bounds__(kThreads, waves_per_simd(4)) void gemm_map_kernel(const GemmArgs g, const ImageArgs x) {
-    static_assert(WM == 2 && WN == 2, "how `product` deals the tile out");
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    product<4, 2, true, true>(g, x, lds);
-}
-}  // namespace tall
 // images of bit planes
 template <int PB, int NB, bool kSign>
 __global__ __launch_bounds__(kThreads, waves_per_simd(PB)) void gemm_image_kernel(const GemmArgs g, const ImageArgs x) {
@@ -551,7 +539,7 @@ int launch_map(const uint32_t *plane, int64_t B, int H, int W, int64_t C, const 
     g.M = p.M, g.N = N, g.K = 9 * C, g.Kw = 9 * words_for(C), g.W = filters;
     g.epi.T = T, g.epi.flip = flip_complement, g.epi.out_bits = out, g.epi.ldo = ldo;
     x.planes = plane, x.count = 1, x.flip_bytes = flip_complement ? (uint32_t)N : 0u, x.pool_and = pool_and, x.pool_invert = pool_invert ? 0xFFFFFFFFu : 0u, x.ones = ones;
-    return QNN_LAUNCH("conv_map", (p.PB == 4 ? tall::gemm_map_kernel<2, 2> : square::gemm_map_kernel<2, 2>), dim3(x.tiles_m * x.tiles_n), dim3(kThreads), (unsigned)p.lds_bytes, s, g, x);
+    return QNN_LAUNCH("conv_map", (p.PB == 4 ? gemm_map_image_kernel<4> : gemm_map_image_kernel<2>), dim3(x.tiles_m * x.tiles_n), dim3(kThreads), (unsigned)p.lds_bytes, s, g, x);
 }
 
 // A convolution's arguments: images of bit planes 1, 2, 4, ... times a factor (0: something else), +-1 filters.

@@ -70,7 +70,7 @@ def test_convnet_small(seed, B, H, Wd, C0, couts, pools, fcs, engine):
 
 
 # the kernels of a convolution behind the first layer: on the map's plane "value is -1", or as a product of any size on its 2-bit code
-MAP, SLICE = r"gemm_map_kernel<2, 2>", r"gemm_slice_kernel<.*"
+MAP, SLICE = r"gemm_map_image_kernel<[24]>", r"gemm_slice_kernel<.*"
 
 
 def _products(q, case, couts, fcs, engine=0):

@@ -49,15 +49,18 @@ def _bits(sums, T, flip):
     return torch.where((sums >= T) != (flip != 0), 1.0, -1.0)
 
 
-@pytest.mark.parametrize("B,H,Wd,cin,N,pool,tile", [
-    (13, 29, 31, 990, 1056, 0, "2, 4"),   # 128 x 256, pixels and filters ragged (32 filters in the last tile), 31 words of channels
-    (57, 12, 16, 990, 1056, 1, "2, 4"),   # ... pooled along
-    (26, 29, 31, 990, 800, 0, "4, 4"),    # 256 x 128
-    (123, 12, 16, 990, 800, 1, "4, 4"),
-    (37, 21, 30, 100, 96, 0, "2, 2"),
+@pytest.mark.parametrize("B,H,Wd,cin,N,pool,kernel", [
+    (13, 29, 31, 990, 1056, 0, "gemm_map_kernel<2, 4>"),   # 128 x 256, pixels and filters ragged (32 filters in the last tile), 31 words of channels
+    (57, 12, 16, 990, 1056, 1, "gemm_map_kernel<2, 4>"),   # ... pooled along
+    (26, 29, 31, 990, 800, 0, "gemm_map_kernel<4, 4>"),    # 256 x 128
+    (123, 12, 16, 990, 800, 1, "gemm_map_kernel<4, 4>"),
+    (37, 21, 30, 990, 96, 0, "gemm_map_kernel<2, 2>"),   # 128 x 128
+    (75, 12, 16, 990, 96, 1, "gemm_map_kernel<2, 2>"),
+    (37, 21, 30, 100, 96, 0, "gemm_map_image_kernel<2>"),   # pixels in LDS: 128 x 128
+    (256, 17, 15, 100, 160, 1, "gemm_map_image_kernel<4>"),  # 256 x 128, odd sizes pooled along
 ])
 @pytest.mark.parametrize("with_flip", [True, False])
-def test_tiles_of_wide_layers(seed, B, H, Wd, cin, N, pool, tile, with_flip):
+def test_tiles_of_wide_layers(seed, B, H, Wd, cin, N, pool, kernel, with_flip):
     import paper_1609_07061_amd as q
 
     couts, pools, fcs = [cin, N], [0, pool], [5]
@@ -68,9 +71,9 @@ def test_tiles_of_wide_layers(seed, B, H, Wd, cin, N, pool, tile, with_flip):
     h = _bits(_conv(dev(x), dev(conv_w[0])), dev(T[0]), flips[0])
     z = _conv(h, dev(conv_w[1]))
     if pool:
-        z = z.reshape(B, H // 2, 2, Wd // 2, 2, N).amax(dim=(2, 4))
+        z = z[:, :H // 2 * 2, :Wd // 2 * 2].reshape(B, H // 2, 2, Wd // 2, 2, N).amax(dim=(2, 4))
     h = _bits(z, dev(T[1]), flips[1]).reshape(B, -1)
     want = h.double() @ dev(fc_w[0]).double().t().contiguous()
     assert np.array_equal(got, host(want.to(torch.int32)))
     kernels = _products(q, case, couts, fcs)
-    assert kernels[1] == f"gemm_map_kernel<{tile}>", kernels
+    assert kernels[1] == kernel, kernels
