@@ -17,8 +17,8 @@
 //   * thresholds: the sums start from 1/2 - T, so that a finished sum's sign is its bit.
 // Workgroup: 2 x 2 waves of 32 PB pixels x 32 NB filters, several on a compute unit: one stages its pixels while others multiply.
 // What is left (App. A's layers on 256 images): the matrix cores' time, 0.9 of it in the loop, and 2 to 3 us at the start and end of every round of
-// tiles that nothing covers, since all of them start at once.  Five layers 93 -> 76 us, the whole forward pass 111.8 -> 96.0; on patches by tap, with a
-// pooling kernel behind small layers, 4 images 57 -> 51, one image of 32 x 32 and 32 filters 54 -> 36.
+// tiles that nothing covers, since all of them start at once.  Five layers 98 -> 75 us (under the profiler), the whole forward pass 111 -> 88.4; one image of 32 x 32
+// and 32 filters 54 -> 36.
 #include <cstring>
 
 #include "qnn_gemm_mfma_kernel.h"

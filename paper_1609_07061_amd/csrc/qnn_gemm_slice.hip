@@ -556,8 +556,8 @@ int launch_gemm_slice(const GemmArgs &g, hipStream_t s) {
 
 // The same kernel on a +-1 map's plane "value is -1" (3 x 3 convolution, channels that fill whole words): half the loads and two thirds of the
 // instructions of the 2-bit code, no plane "inside the image" to fill, and 2 x 2 pooling in the epilogue.  Bound: latency.  Where 32 x 32 tiles are
-// taken.  App. A ConvNet of width 128, 4 images of 32 x 32, all layers: 53.5 -> 45.7 us with the last two convolutions here (11 -> 9 launches), 43.0
-// with all that have few tiles; 1 image of 16 x 16 46.4 -> 38.6.
+// taken.  App. A ConvNet of width 128, 4 images of 32 x 32, all layers: 56 -> 45 us with all five convolutions here (12 -> 9
+// launches); 1 image of 16 x 16 46.4 -> 38.6.
 namespace slice {
 static bool map_args(int64_t B, int64_t H, int64_t Wd, int64_t C, int64_t N, bool pooled, GemmArgs &g, SliceArgs &sc) {
     const int64_t Cw = words_for(C);
