@@ -24,6 +24,7 @@ pytestmark = pytest.mark.gpu
     (160, 32769, 112, 112, True),
     (160, 32769, 112, 128, False),
     (160, 32769, 128, 144, True),
+    (130, 8193, 131056, 131056, True),  # longer than the kernels of large tiles take: VALU otherwise
 ])
 def test_both_sides(seed, M, N, K, ldx, small):
     import paper_1609_07061_amd as q
